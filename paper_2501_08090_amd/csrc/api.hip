@@ -105,7 +105,7 @@ int32_t chiron_model_destroy(chiron_model* m) {
         (void)hipEventDestroy(t.b);
     }
     linear_free(m->lm);
-    void* bufs[] = {m->attn_norm, m->ffn_norm, m->final_norm, m->embed, m->h, m->x, m->qkvb, m->qb, m->part, m->asplit, m->x_bt, m->x_lens, m->attn, m->gub,
+    void* bufs[] = {m->attn_norm, m->ffn_norm, m->final_norm, m->embed, m->h, m->x, m->qkvb, m->qb, m->part, m->asplit, m->attn, m->gub,
                     m->cos_t, m->sin_t, m->aws.plan, m->aws.part_o, m->aws.part_ml};
     for (void* b : bufs)
         if (b) (void)hipFree(b);
@@ -162,8 +162,6 @@ int32_t chiron_model_create(const chiron_model_config* cfg, chiron_model** out) 
         if (hipMemset(m->asplit, 0, bytes) != hipSuccess || hipDeviceSynchronize() != hipSuccess)
             TRY(fail(CHIRON_ERR_HIP, "clearing the activation workspace failed"));
     }
-    TRY(dev_alloc((void**)&m->x_bt, (size_t)B * cfg->max_blocks_per_seq * 4));
-    TRY(dev_alloc((void**)&m->x_lens, (size_t)B * 4));
     TRY(dev_alloc((void**)&m->attn, (size_t)B * qn * 4));
     TRY(dev_alloc((void**)&m->gub, (size_t)B * F * 4));  // silu(gate) * up, fp32 rows
     TRY(dev_alloc((void**)&m->cos_t, (size_t)B * (d / 2) * 4));
@@ -306,18 +304,16 @@ static int32_t check_step_args(const chiron_model* m, const chiron_kvpool* p, co
 // whether the feed-forward block's intermediate takes the tiled two-term form (needs the workspace for it)
 static bool ffn_packed(const Linear& down, int M, const uint16_t* asplit) { return asplit && M >= linear_big_min_rows(down); }
 
-// One pass of the model over B rows.  Row r carries token tokens[r] at position seq_lens[r] of the request whose
-// pages block_table row r lists.  With q_len == 1 a row is a request.  With q_len > 1 rows r = i*q_len + t are the
-// new tokens of request i (expanded index arrays), and attention runs per request over (req_bt, req_lens, B/q_len):
-// a pass over a request's pages serves as many of its q_len tokens as fit the attention kernel's operand columns.
+// One pass of the model over B = n_req * q_len rows: row r = i * q_len + t is the t-th new token of request i, fed at
+// position seq_lens[i] + t.  Attention runs per request: a pass over a request's pages serves as many of its q_len
+// tokens as fit the attention kernel's operand columns.
 static int32_t step_rows(chiron_model* m, chiron_kvpool* p, const int32_t* block_table, const int32_t* seq_lens,
-                         const int32_t* tokens, int32_t B, const int32_t* req_bt, const int32_t* req_lens, int32_t q_len,
-                         float* logits, hipStream_t st) {
+                         const int32_t* tokens, int32_t n_req, int32_t q_len, float* logits, hipStream_t st) {
     const AttnShape ash = attn_shape(m->cfg.n_q_heads / m->cfg.n_kv_heads, q_len, q_len);
     int32_t rc;
     const chiron_model_config& c = m->cfg;
     const int H = c.hidden, d = c.head_dim, F = c.ffn, qn = c.n_q_heads * d, kn = c.n_kv_heads * d;
-    const int n_req = B / q_len;
+    const int B = n_req * q_len;
     const int mb = c.max_blocks_per_seq;
     // while kernel timing is on, the kernels of each launch carry their own start/stop events (see launch())
     TimingScope scope;
@@ -335,17 +331,16 @@ static int32_t step_rows(chiron_model* m, chiron_kvpool* p, const int32_t* block
     } while (0)
     const int msplit = linear_max_split();
     int ks_res = 0, ks_qkv = 1;  // K-slices waiting in m->part for the residual stream / of the QKV projection
-    STEP(CHIRON_K_OTHER, launch_embed(m->embed, tokens, B, H, m->h, st));
-    STEP(CHIRON_K_OTHER, launch_rope_table(seq_lens, B, d, c.rope_base, m->cos_t, m->sin_t, st));
-    STEP(CHIRON_K_OTHER, launch_attn_plan(m->aws, req_lens, req_bt, mb, ash, n_req, c.n_kv_heads, st));
+    STEP(CHIRON_K_OTHER, launch_step_begin(m->aws, seq_lens, block_table, mb, ash, n_req, c.n_kv_heads, m->embed, tokens, H, m->h, d,
+                                           c.rope_base, m->cos_t, m->sin_t, st));
     for (int l = 0; l < c.n_layers; ++l) {
         // h += (slices of the previous down projection); x = norm(h)
         STEP(CHIRON_K_RMSNORM, launch_rmsnorm(m->h, m->part, ks_res, m->attn_norm + (size_t)l * H, B, H, c.rms_eps, m->x, st));
         STEP(CHIRON_K_QKV, launch_linear(m->qkv[l], m->x, H, B, m->qkvb, qn + 2 * kn, 0, PRO_NONE, m->part, msplit, &ks_qkv, m->asplit, st));
         STEP(CHIRON_K_ROPE_APPEND,
              launch_rope_append(p->d, l, ks_qkv > 1 ? m->part : m->qkvb, ks_qkv, c.n_q_heads, m->cos_t, m->sin_t, block_table,
-                                mb, seq_lens, B, m->qb, st));
-        STEP(CHIRON_K_ATTN, launch_attn_main(m->aws, p->d, l, m->qb, qn, c.n_q_heads, req_bt, mb, req_lens, ash, n_req, st));
+                                mb, seq_lens, q_len, B, m->qb, st));
+        STEP(CHIRON_K_ATTN, launch_attn_main(m->aws, p->d, l, m->qb, qn, c.n_q_heads, block_table, mb, seq_lens, ash, n_req, st));
         STEP(CHIRON_K_ATTN_MERGE, launch_attn_merge(m->aws, p->d, c.n_q_heads, ash, n_req, m->attn, qn, st));
         STEP(CHIRON_K_O, launch_linear(m->wo[l], m->attn, qn, B, m->h, H, 1, PRO_NONE, m->part, msplit, &ks_res, m->asplit, st));
         if (ks_res == 1) ks_res = 0;  // written straight into h
@@ -375,7 +370,7 @@ int32_t chiron_decode_step(chiron_model* m, chiron_kvpool* p, const int32_t* blo
     if (rc) return rc;
     if (batch == 0) return CHIRON_OK;
     if (!logits) return fail(CHIRON_ERR_INVALID_ARG, "logits is null");
-    return step_rows(m, p, block_table, seq_lens, tokens, batch, block_table, seq_lens, 1, logits, (hipStream_t)stream);
+    return step_rows(m, p, block_table, seq_lens, tokens, batch, 1, logits, (hipStream_t)stream);
 }
 
 int32_t chiron_decode_step_multi(chiron_model* m, chiron_kvpool* p, const int32_t* block_table, const int32_t* seq_lens,
@@ -392,11 +387,7 @@ int32_t chiron_decode_step_multi(chiron_model* m, chiron_kvpool* p, const int32_
     // rows (i, t) share request i's pages; row t sees the K/V that rows t' <= t append in the same layer, because
     // every layer appends all rows before its attention starts
     if (!logits) return fail(CHIRON_ERR_INVALID_ARG, "logits is null");
-    rc = launch_expand_rows(block_table, seq_lens, batch, q_len, m->cfg.max_blocks_per_seq, m->x_bt, m->x_lens,
-                            (hipStream_t)stream);
-    if (rc) return rc;
-    // attention runs per request: its pages are read once per group of as many tokens as fit the 16 operand columns
-    return step_rows(m, p, m->x_bt, m->x_lens, tokens, batch * q_len, block_table, seq_lens, q_len, logits, (hipStream_t)stream);
+    return step_rows(m, p, block_table, seq_lens, tokens, batch, q_len, logits, (hipStream_t)stream);
 }
 
 static int32_t check_inputs_host(const chiron_model_config* cfg, int32_t num_blocks, int32_t block_size,

@@ -22,25 +22,10 @@
 #include <cstdlib>
 #include <type_traits>
 
-#include "chiron_internal.h"
-#include "device_util.h"
+#include "attn_plan.h"
 
 namespace chiron {
 
-// plan buffer layout (int32): [0] n_items, [1] chunk_pages, [2..3] unused,
-// [4, 4+max_batch) first item of pass v, [.., +max_batch) number of items of pass v,
-// then item_seq[cap_items] (the pass), item_pg0[cap_items].  A pass v = request * ng + token group (AttnShape).
-// Last, 32-byte aligned, one record of 8 ints per item: {pass, first page, attended length, the ids of the item's
-// first four pages (past its end: its last page), 0}: everything a wave needs before its first tile load, in one
-// scalar load instead of a chain of four dependent ones (the block table does not differ between layers).
-// After the records, kTicketQueues ticket counters kTicketStride ints apart, all 0 between attention launches.
-__host__ __device__ inline int64_t plan_rec_offset(int max_batch, int cap_items) {
-    return (4 + 2 * (int64_t)max_batch + 2 * (int64_t)cap_items + 7) / 8 * 8;
-}
-constexpr int kTicketQueues = 8, kTicketStride = 64;
-__host__ __device__ inline int64_t plan_ticket_offset(int max_batch, int cap_items) {
-    return (plan_rec_offset(max_batch, cap_items) + 8 * (int64_t)cap_items + kTicketStride - 1) / kTicketStride * kTicketStride;
-}
 int64_t attn_plan_ints(int max_batch, int cap_items) { return plan_ticket_offset(max_batch, cap_items) + kTicketQueues * kTicketStride; }
 
 AttnShape attn_shape(int G, int q_len, int len_bias) {
@@ -52,123 +37,38 @@ AttnShape attn_shape(int G, int q_len, int len_bias) {
     return sh;
 }
 
-// positions attended by pass v (its last token's view)
-__device__ __forceinline__ int pass_len(const int32_t* __restrict__ seq_lens, const AttnShape& sh, int v) {
-    const int i = v / sh.ng, g = v - i * sh.ng;
-    return seq_lens[i] + sh.bias0 + g * sh.tg + min(sh.tg, sh.q_len - g * sh.tg);
-}
+__global__ __launch_bounds__(kPlanThreads) void attn_plan_kernel(PlanArgs a) { attn_plan_block(a); }
 
-constexpr int kPlanThreads = 1024;
-
-__global__ __launch_bounds__(kPlanThreads) void attn_plan_kernel(int32_t* __restrict__ plan, int max_batch, int cap_items,
-                                                                 const int32_t* __restrict__ seq_lens, AttnShape sh,
-                                                                 int batch, int n_kv, int slots, int target_waves, int force_cp, int item_limit,
-                                                                 const int32_t* __restrict__ bt, int max_blocks) {
-    batch *= sh.ng;  // passes
-    __shared__ int scan[kPlanThreads];
-    int32_t* seq_item0 = plan + 4;
-    int32_t* seq_nch = plan + 4 + max_batch;
-    int32_t* item_seq = plan + 4 + 2 * max_batch;
-    int32_t* item_pg0 = item_seq + cap_items;
-    const int tid = threadIdx.x;
-    if (tid < kTicketQueues) plan[plan_ticket_offset(max_batch, cap_items) + tid * kTicketStride] = 0;
-    const int per = (batch + kPlanThreads - 1) / kPlanThreads;  // requests per thread, contiguous
-    const int i0 = tid * per, i1 = min(batch, i0 + per);
-
-    // block-wide sums over the requests (every thread gets the total)
-    auto block_sum = [&](int v) {
-        __syncthreads();
-        scan[tid] = v;
-        __syncthreads();
-        for (int o = kPlanThreads / 2; o > 0; o >>= 1) {
-            if (tid < o) scan[tid] += scan[tid + o];
-            __syncthreads();
-        }
-        return scan[0];
-    };
-    auto count_items = [&](int cp) {
-        int n = 0;
-        for (int i = i0; i < i1; ++i) n += ((pass_len(seq_lens, sh, i) + kBlockSize - 1) / kBlockSize + cp - 1) / cp;
-        return block_sum(n);
-    };
-    int pages = 0;
-    for (int i = i0; i < i1; ++i) pages += (pass_len(seq_lens, sh, i) + kBlockSize - 1) / kBlockSize;
-    const int total = block_sum(pages);
-
-    // Pages per item.  A wave takes items w, w + slots, ...: if the list is only a little longer than the number of
-    // wave slots, a few waves run a second item alone, at latency-bound speed, after everyone else has finished.
-    // So: when one round can hold everything, take the smallest item size that fits one round (all items stream
-    // concurrently); otherwise make the items small enough for at least four rounds, where a ragged last round
-    // costs little, but not so small that the per-item partial result weighs against the bytes the item reads.
-    int cp;
-    if ((int64_t)count_items(64) * n_kv <= slots) {
-        int lo = 2, hi = 64;
-        while (lo < hi) {  // uniform over the workgroup: every thread sees the same counts
-            const int mid = (lo + hi) / 2;
-            if ((int64_t)count_items(mid) * n_kv <= slots) hi = mid;
-            else lo = mid + 1;
-        }
-        cp = lo;
-    } else {
-        cp = 64;
-        while (cp > 8 && (int64_t)(total / cp) * n_kv < target_waves) cp >>= 1;
-    }
-    while (cp < (1 << 24) && total / cp + batch > item_limit) cp <<= 1;  // the host has checked that batch < item_limit
-    if (force_cp > 0 && total / force_cp + batch <= item_limit) cp = force_cp;
-    __syncthreads();
-
-    // exclusive scan of items per request
-    int items = 0;
-    for (int i = i0; i < i1; ++i) {
-        int np = (pass_len(seq_lens, sh, i) + kBlockSize - 1) / kBlockSize;
-        items += (np + cp - 1) / cp;
-    }
-    scan[tid] = items;
-    __syncthreads();
-    for (int o = 1; o < kPlanThreads; o <<= 1) {
-        int v = tid >= o ? scan[tid - o] : 0;
-        __syncthreads();
-        scan[tid] += v;
-        __syncthreads();
-    }
-    int off = scan[tid] - items;
-    for (int i = i0; i < i1; ++i) {
-        int np = (pass_len(seq_lens, sh, i) + kBlockSize - 1) / kBlockSize;
-        int nch = (np + cp - 1) / cp;
-        seq_item0[i] = off;
-        seq_nch[i] = nch;
-        const int len = pass_len(seq_lens, sh, i);
-        const int32_t* btrow = bt + (size_t)(i / sh.ng) * max_blocks;
-        for (int ch = 0; ch < nch; ++ch) {
-            item_seq[off + ch] = i;
-            item_pg0[off + ch] = ch * cp;
-            int32_t* rec = plan + plan_rec_offset(max_batch, cap_items) + 8 * (int64_t)(off + ch);
-            const int pg1 = min(ch * cp + cp, np);
-            rec[0] = i;
-            rec[1] = ch * cp;
-            rec[2] = len;
-            for (int u = 0; u < 4; ++u) rec[3 + u] = btrow[min(ch * cp + u, pg1 - 1)];
-            rec[7] = 0;
-        }
-        off += nch;
-    }
-    if (tid == kPlanThreads - 1) {
-        plan[0] = scan[tid];
-        plan[1] = cp;
-    }
-}
-
-int32_t launch_attn_plan(const AttnWorkspace& ws, const int32_t* seq_lens, const int32_t* bt, int max_blocks, const AttnShape& sh,
-                         int batch, int n_kv, hipStream_t st) {
+int32_t attn_plan_args(const AttnWorkspace& ws, const int32_t* seq_lens, const int32_t* bt, int max_blocks, const AttnShape& sh,
+                       int batch, int n_kv, PlanArgs* out) {
     const Tuning& t = tuning();
     if ((int64_t)batch * sh.ng > ws.max_batch) return fail(CHIRON_ERR_BATCH_TOO_LARGE, "attention: %d requests x %d token groups exceed the workspace", batch, sh.ng);
     const int slots = 4 * (t.attn_grid > 0 ? t.attn_grid : kNumCU * 2);  // waves of the persistent attention grid
     if ((int64_t)batch * sh.ng >= ws.cap_items / sh.tg)
         return fail(CHIRON_ERR_BATCH_TOO_LARGE, "attention: %d passes do not fit a work list of %d items", batch * sh.ng, ws.cap_items / sh.tg);
-    launch(attn_plan_kernel, dim3(1), dim3(kPlanThreads), st, ws.plan, ws.max_batch, ws.cap_items, seq_lens, sh, batch, n_kv, slots,
-                                                  t.attn_target_waves > 0 ? t.attn_target_waves : 4 * slots, t.attn_chunk_pages,
-                                                  ws.cap_items / sh.tg,  // a partial result holds tg tokens' heads
-                                                  bt, max_blocks);
+    PlanArgs& a = *out;
+    a.plan = ws.plan;
+    a.seq_lens = seq_lens;
+    a.bt = bt;
+    a.sh = sh;
+    a.max_batch = ws.max_batch;
+    a.cap_items = ws.cap_items;
+    a.batch = batch;
+    a.n_kv = n_kv;
+    a.slots = slots;
+    a.target_waves = t.attn_target_waves > 0 ? t.attn_target_waves : 4 * slots;
+    a.force_cp = t.attn_chunk_pages;
+    a.item_limit = ws.cap_items / sh.tg;  // a partial result holds tg tokens' heads
+    a.max_blocks = max_blocks;
+    return CHIRON_OK;
+}
+
+int32_t launch_attn_plan(const AttnWorkspace& ws, const int32_t* seq_lens, const int32_t* bt, int max_blocks, const AttnShape& sh,
+                         int batch, int n_kv, hipStream_t st) {
+    PlanArgs a;
+    int32_t rc = attn_plan_args(ws, seq_lens, bt, max_blocks, sh, batch, n_kv, &a);
+    if (rc) return rc;
+    launch(attn_plan_kernel, dim3(1), dim3(kPlanThreads), st, a);
     CHIRON_HIP(hipGetLastError());
     return CHIRON_OK;
 }
@@ -201,7 +101,7 @@ __global__ __launch_bounds__(256, 2) void paged_attn_kernel(PoolDesc p, int laye
     // item metadata (pass, first page, length, first page ids) comes in one record, fetched one item ahead.  The first
     // record is read without waiting for the item count (any record of the list is readable memory; a wave past the
     // end of the list discards it).
-    const int32_t* recs = plan + plan_rec_offset(max_batch, cap_items);
+    const int32_t* recs = plan + plan_rec_offset(max_batch);
     int w = blockIdx.x * 4 + wave;
     int v_nx, pg0_nx, len_nx, b0_nx, b1_nx, b2_nx, b3_nx;
     auto fetch_rec = [&](int item) {

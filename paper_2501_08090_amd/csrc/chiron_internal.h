@@ -112,7 +112,6 @@ int32_t launch_pack_rows(const uint16_t* src, int rows, int K, size_t tstride, u
                          hipStream_t st, int interleave = 0);
 
 // ---- elementwise / indexing kernels ---------------------------------------------------------------
-int32_t launch_embed(const uint16_t* table, const int32_t* tokens, int batch, int H, float* h, hipStream_t st);
 // out = rmsnorm(h) * gain.  With ks > 0 the row first absorbs the K-slices of the projection that feeds the
 // residual stream: h += sum_s part[s] (h is rewritten), then the norm is taken.
 int32_t launch_rmsnorm(float* h, const float* part, int ks, const uint16_t* gain, int rows, int n, float eps, float* out,
@@ -133,21 +132,18 @@ int32_t launch_append_kv(const PoolDesc& p, int layer, const uint16_t* k, const 
                          int max_blocks, const int32_t* seq_idx, const int32_t* pos, int64_t n, hipStream_t st);
 int32_t launch_gather_kv(const PoolDesc& p, int layer, const int32_t* bt_row, int len, uint16_t* k_out, uint16_t* v_out,
                          hipStream_t st);
-// multi-token step: row (i,t) of the expanded batch gets request i's block-table row and length seq_lens[i] + t
-int32_t launch_expand_rows(const int32_t* bt, const int32_t* seq_lens, int batch, int q_len, int max_blocks, int32_t* bt_out,
-                           int32_t* lens_out, hipStream_t st);
 // page migration: image = [page j][layer][kv head][K tile | V tile]; to_image != 0 copies pool -> image
 int32_t launch_swap(const PoolDesc& p, const int32_t* bt_row, int n_pages, uint16_t* image, int to_image, hipStream_t st);
 // decode-step variant: the fused qkv row [rows, (nq+2nkv)*d] is the sum of ks slices qkv[s] (slice stride
 // rows*ld); q and k are rotated in fp32; q goes to q_out [rows, nq*d]; k, v are rounded to bf16 and written at
-// slot(i, seq_lens[i]).
+// slot(r / q_len, seq_lens[r / q_len] + r % q_len), r the row.
 int32_t launch_rope_append(const PoolDesc& p, int layer, const float* qkv, int ks, int n_q, const float* cos_t,
-                           const float* sin_t, const int32_t* bt, int max_blocks, const int32_t* seq_lens, int batch,
-                           float* q_out, hipStream_t st);
+                           const float* sin_t, const int32_t* bt, int max_blocks, const int32_t* seq_lens, int q_len,
+                           int rows, float* q_out, hipStream_t st);
 
 // ---- paged attention ------------------------------------------------------------------------------
 struct AttnWorkspace {
-    int32_t* plan = nullptr;     // [0]=n_items, [1]=chunk_pages; then per-seq and per-item tables, ticket counters (see attention.hip)
+    int32_t* plan = nullptr;     // [0]=n_items, [1]=chunk_pages; then per-seq and per-item tables, ticket counters (see attn_plan.h)
     float* part_o = nullptr;     // [items*n_kv][tg*G][d], items*tg <= cap_items
     float* part_ml = nullptr;    // [items*n_kv][tg*G][2]
     int cap_items = 0, max_batch = 0;
@@ -167,6 +163,15 @@ AttnShape attn_shape(int G, int q_len, int len_bias);
 // (bt: the block table the attention launches of this plan will use; the plan copies each item's first page ids)
 int32_t launch_attn_plan(const AttnWorkspace& ws, const int32_t* seq_lens, const int32_t* bt, int max_blocks, const AttnShape& sh,
                          int batch, int n_kv, hipStream_t st);
+struct PlanArgs;
+// the launch parameters of that work list, after the checks of its limits (attn_plan.h)
+int32_t attn_plan_args(const AttnWorkspace& ws, const int32_t* seq_lens, const int32_t* bt, int max_blocks, const AttnShape& sh,
+                       int batch, int n_kv, PlanArgs* out);
+// What begins a step, in one launch: the work list for n_req requests of sh.q_len new tokens each, h[r] = table[tokens[r]]
+// widened to fp32 and the rotary table of position seq_lens[r / q_len] + r % q_len, for the n_req * q_len rows r.
+int32_t launch_step_begin(const AttnWorkspace& ws, const int32_t* seq_lens, const int32_t* bt, int max_blocks, const AttnShape& sh,
+                          int n_req, int n_kv, const uint16_t* table, const int32_t* tokens, int H, float* h, int d, float base,
+                          float* cos_t, float* sin_t, hipStream_t st);
 // launch_attn_main leaves the plan's ticket counters used; launch_attn_merge, which must follow it on the same stream
 // before the next launch_attn_main, puts them back to 0.
 int32_t launch_attn_main(const AttnWorkspace& ws, const PoolDesc& p, int layer, const float* q, int ldq, int n_q,
@@ -197,7 +202,6 @@ struct chiron_model {
     uint16_t* embed = nullptr;
     // step workspace, sized for max_batch
     float *h = nullptr, *x = nullptr, *qkvb = nullptr, *qb = nullptr, *attn = nullptr, *gub = nullptr;
-    int32_t *x_bt = nullptr, *x_lens = nullptr;  // expanded index arrays of the multi-token step
     float* part = nullptr;  // K-slice workspace of the projections: [max_split][max_batch][max(qkv width, hidden)]
     uint16_t* asplit = nullptr;  // hi and lo bf16 terms of a projection's input in tile order (large batches only)
     float *cos_t = nullptr, *sin_t = nullptr;

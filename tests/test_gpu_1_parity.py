@@ -293,6 +293,21 @@ def test_paged_attention(d, nq, nkv, lens):
         assert np.abs(got - want).max() <= KERNEL_TOL * max(1.0, np.abs(want).max())
 
 
+@pytest.mark.parametrize("batch", [1023, 2048, 2051])
+def test_paged_attention_work_list_of_many_requests(batch):
+    """The work list keeps the page counts of the first 2048 requests in LDS and reads the others' again; from 1025
+    requests on a thread counts several."""
+    lens = (1 + (np.arange(batch) * 37) % 41).astype(np.int32)
+    c = make_case(m=dict(I.TINY, n_layers=1, vocab=64, ffn=16), seed=17, storage="bf16", seq_lens=lens)
+    g = gpu_setup(c)
+    opool = fresh_pool(c)
+    q = (np.random.default_rng(18).standard_normal((batch, 4 * 64)) * 1.3).astype(np.float32)
+    print("attention", batch, "requests", flush=True)
+    got = B().op_paged_attention(g.model, g.pool, 0, torch.from_numpy(q).cuda(), g.block_table, g.seq_lens).cpu().numpy()
+    want = np.stack([orc.paged_attention(opool, 0, c.block_table[i], int(lens[i]), q[i].reshape(4, 64)).reshape(-1) for i in range(batch)])
+    assert np.abs(got - want).max() <= KERNEL_TOL * max(1.0, np.abs(want).max())
+
+
 @pytest.mark.parametrize("grid,chunk", [(4, 0), (4, 3), (2, 1), (0, 5), (8, 2), (24, 1)])
 def test_paged_attention_work_list_over_several_rounds(grid, chunk):
     """A small persistent grid (grid workgroups = 4*grid wave slots) makes every wave walk several items of the work
