@@ -6,7 +6,7 @@ import sys
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libchiron.so")
-SOURCES = ["api.hip", "elementwise.hip", "linear.hip", "linear_big.hip", "attention.hip"]
+SOURCES = ["api.hip", "elementwise.hip", "linear.hip", "linear_big.hip", "linear_few.hip", "attention.hip"]
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-Wall", "-Wno-unused-function",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops"]
 

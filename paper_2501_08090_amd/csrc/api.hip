@@ -163,7 +163,7 @@ int32_t chiron_model_create(const chiron_model_config* cfg, chiron_model** out) 
             TRY(fail(CHIRON_ERR_HIP, "clearing the activation workspace failed"));
     }
     TRY(dev_alloc((void**)&m->attn, (size_t)B * qn * 4));
-    TRY(dev_alloc((void**)&m->gub, (size_t)B * F * 4));  // silu(gate) * up, fp32 rows
+    TRY(dev_alloc((void**)&m->gub, (size_t)B * m->down[0].Kpad * 4));  // silu(gate) * up: fp32 rows, or two bf16 terms
     TRY(dev_alloc((void**)&m->cos_t, (size_t)B * (d / 2) * 4));
     TRY(dev_alloc((void**)&m->sin_t, (size_t)B * (d / 2) * 4));
     // attention work list: room for a few items per wave slot plus one ragged tail per request
@@ -186,10 +186,10 @@ int32_t chiron_model_load_layer(chiron_model* m, int32_t layer, const chiron_lay
     const chiron_model_config& c = m->cfg;
     const int H = c.hidden, d = c.head_dim, F = c.ffn, qn = c.n_q_heads * d, kn = c.n_kv_heads * d;
     int32_t rc;
-    // fused QKV: rows [q | k | v]; fused gate/up: 16 gate and the 16 up columns of the same indices per 32-row tile
-    if ((rc = launch_pack_rows((const uint16_t*)w->wq, qn, H, m->qkv[layer].tstride, m->qkv[layer].w, 0, st))) return rc;
-    if ((rc = launch_pack_rows((const uint16_t*)w->wk, kn, H, m->qkv[layer].tstride, m->qkv[layer].w, qn, st))) return rc;
-    if ((rc = launch_pack_rows((const uint16_t*)w->wv, kn, H, m->qkv[layer].tstride, m->qkv[layer].w, qn + kn, st))) return rc;
+    // fused QKV: rows [q | k | v], each head in the order of qkv_packed_dim; fused gate/up: 16 gate and the 16 up columns of the same indices per 32-row tile
+    if ((rc = launch_pack_rows((const uint16_t*)w->wq, qn, H, m->qkv[layer].tstride, m->qkv[layer].w, 0, st, d))) return rc;
+    if ((rc = launch_pack_rows((const uint16_t*)w->wk, kn, H, m->qkv[layer].tstride, m->qkv[layer].w, qn, st, d))) return rc;
+    if ((rc = launch_pack_rows((const uint16_t*)w->wv, kn, H, m->qkv[layer].tstride, m->qkv[layer].w, qn + kn, st, d))) return rc;
     if ((rc = launch_pack_rows((const uint16_t*)w->wo, H, qn, m->wo[layer].tstride, m->wo[layer].w, 0, st))) return rc;
     if ((rc = launch_pack_rows((const uint16_t*)w->w_gate, F, H, m->gu[layer].tstride, m->gu[layer].w, 0, st, 1))) return rc;
     if ((rc = launch_pack_rows((const uint16_t*)w->w_up, F, H, m->gu[layer].tstride, m->gu[layer].w, 0, st, 2))) return rc;
@@ -333,6 +333,35 @@ static int32_t step_rows(chiron_model* m, chiron_kvpool* p, const int32_t* block
     int ks_res = 0, ks_qkv = 1;  // K-slices waiting in m->part for the residual stream / of the QKV projection
     STEP(CHIRON_K_OTHER, launch_step_begin(m->aws, seq_lens, block_table, mb, ash, n_req, c.n_kv_heads, m->embed, tokens, H, m->h, d,
                                            c.rope_base, m->cos_t, m->sin_t, st));
+    if (linear_few_rows(B)) {
+        // Up to 16 rows six launches a layer instead of nine: the projections into the residual stream complete it (no
+        // K-slices for anybody to add), so the norms move into the operand loads of the projections behind them, and the
+        // QKV projection rotates and appends by itself.
+        for (int l = 0; l < c.n_layers; ++l) {
+            const NormIn an{m->attn_norm + (size_t)l * H, c.rms_eps}, fn{m->ffn_norm + (size_t)l * H, c.rms_eps};
+            RopeOut ro;
+            ro.pool = p->d;
+            ro.cos_t = m->cos_t;
+            ro.sin_t = m->sin_t;
+            ro.bt = block_table;
+            ro.seq_lens = seq_lens;
+            ro.q_out = m->qb;
+            ro.layer = l;
+            ro.n_q = c.n_q_heads;
+            ro.q_len = q_len;
+            ro.max_blocks = mb;
+            STEP(CHIRON_K_QKV, launch_qkv_few(m->qkv[l], m->h, H, B, an, ro, st));
+            STEP(CHIRON_K_ATTN, launch_attn_main(m->aws, p->d, l, m->qb, qn, c.n_q_heads, block_table, mb, seq_lens, ash, n_req, st));
+            STEP(CHIRON_K_ATTN_MERGE, launch_attn_merge(m->aws, p->d, c.n_q_heads, ash, n_req, m->attn, qn, st));
+            STEP(CHIRON_K_O, launch_linear_few(m->wo[l], m->attn, qn, B, 0, m->h, H, 1, st));
+            STEP(CHIRON_K_GATEUP, launch_linear(m->gu[l], m->h, H, B, m->gub, m->down[l].Kpad, EPI_SWIGLU_FEW, PRO_NONE, nullptr, 1, nullptr,
+                                                nullptr, st, &fn));
+            STEP(CHIRON_K_DOWN, launch_linear_few(m->down[l], m->gub, (int64_t)B * (m->down[l].Kpad / 8), B, 1, m->h, H, 1, st));
+        }
+        const NormIn ln{m->final_norm, c.rms_eps};
+        STEP(CHIRON_K_LMHEAD, launch_linear(m->lm, m->h, H, B, logits, c.vocab, EPI_STORE, PRO_NONE, nullptr, 1, nullptr, nullptr, st, &ln));
+        return CHIRON_OK;
+    }
     for (int l = 0; l < c.n_layers; ++l) {
         // h += (slices of the previous down projection); x = norm(h)
         STEP(CHIRON_K_RMSNORM, launch_rmsnorm(m->h, m->part, ks_res, m->attn_norm + (size_t)l * H, B, H, c.rms_eps, m->x, st));
@@ -581,6 +610,8 @@ int32_t chiron_linear_destroy(chiron_linear* l) {
 // too small), followed by the plain sum of the slices that the step's consumers do on the fly
 static int32_t op_linear_common(const Linear& L, const float* x, int lda, int M, float* y, int accumulate, int prologue,
                                 hipStream_t st) {
+    // few rows: one launch that needs no workspace (very wide outputs have enough column tiles for the tiled kernel)
+    if (prologue == PRO_NONE && linear_few_rows(M) && L.N <= 16384) return launch_linear_few(L, x, lda, M, 0, y, L.N, accumulate, st);
     float* part = nullptr;
     const int msplit = linear_max_split();
     // wide outputs (LM head, gate/up) have enough column tiles on their own and are never sliced in the step
@@ -628,12 +659,16 @@ int32_t chiron_op_swiglu_ffn(const chiron_linear* gate_up, const chiron_linear* 
     if (D.K != F) return fail(CHIRON_ERR_SHAPE, "swiglu_ffn: gate/up has %d columns, the down projection %d inputs", F, D.K);
     hipStream_t st = (hipStream_t)stream;
     // the intermediate in the form the decode step gives it at this row count
-    const bool packed = M >= linear_big_min_rows(D);
-    const size_t bytes = packed ? 2 * linear_big_split_elems(M, D.Kpad) * 2 : (size_t)M * F * 4;
+    const bool few = linear_few_rows(M) && D.N <= 16384;
+    const bool packed = !few && M >= linear_big_min_rows(D);
+    const size_t bytes = packed ? 2 * linear_big_split_elems(M, D.Kpad) * 2 : (size_t)M * D.Kpad * 4;
     void* act = nullptr;
     CHIRON_HIP(hipMallocAsync(&act, bytes, st));
     int32_t rc = CHIRON_OK;
-    if (packed) {
+    if (few) {
+        rc = launch_linear(G, x, G.K, M, (float*)act, D.Kpad, EPI_SWIGLU_FEW, PRO_NONE, nullptr, 1, nullptr, nullptr, st);
+        if (!rc) rc = launch_linear_few(D, (const float*)act, (int64_t)M * (D.Kpad / 8), M, 1, y, D.N, accumulate, st);
+    } else if (packed) {
         if (hipMemsetAsync(act, 0, bytes, st) != hipSuccess) rc = fail(CHIRON_ERR_HIP, "clearing the activation workspace failed");
         if (!rc) rc = launch_linear(G, x, G.K, M, (float*)act, D.Kpad, EPI_SWIGLU_PACKED, PRO_NONE, nullptr, 1, nullptr, nullptr, st);
         if (!rc) rc = op_linear_common(D, (const float*)act, 0, M, y, accumulate, PRO_PACKED, st);

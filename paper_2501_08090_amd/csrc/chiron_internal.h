@@ -72,8 +72,22 @@ enum Prologue { PRO_NONE = 0, PRO_PACKED = 2 };
 // What a projection does with its result.  EPI_SLICES is chosen inside launch_linear when it slices K.  The SwiGLU
 // epilogues belong to a fused gate/up matrix packed with launch_pack_rows(..., interleave): the output has N/2 columns,
 // out[m][j] = silu(gate[m][j]) * up[m][j], as fp32 rows (EPI_SWIGLU) or as the two bf16 terms in the tile order that
-// PRO_PACKED reads (EPI_SWIGLU_PACKED: y is the base of the hi terms, ldy the padded K of the consuming projection).
-enum Epilogue { EPI_STORE = 0, EPI_ADD = 1, EPI_SLICES = 2, EPI_SWIGLU = 3, EPI_SWIGLU_PACKED = 4 };
+// PRO_PACKED reads (EPI_SWIGLU_PACKED: y is the base of the hi terms, ldy the padded K of the consuming projection), or as
+// the two terms in the order [k/8][M rows][8] that the few-row projection reads (EPI_SWIGLU_FEW, ldy likewise).
+enum Epilogue { EPI_STORE = 0, EPI_ADD = 1, EPI_SLICES = 2, EPI_SWIGLU = 3, EPI_SWIGLU_PACKED = 4, EPI_SWIGLU_FEW = 5 };
+
+// RMS norm taken in a projection's operand load: the input is A * gain / rms(A) row by row (gain: bf16 [K])
+struct NormIn {
+    const uint16_t* gain = nullptr;
+    float eps = 0.f;
+};
+
+// Column of dim e within its head in the fused QKV matrix: a 32-column tile holds the dims j0 .. j0+15 and their rotary
+// partners j0+d/2 .. j0+d/2+15, so one workgroup of the few-row projection has both of a pair.
+__host__ __device__ inline int qkv_packed_dim(int e, int d) {
+    const int half = d / 2, j = e % half;
+    return j / 16 * 32 + e / half * 16 + j % 16;
+}
 
 // Performance knobs (0 = built-in heuristic); see chiron_set_tuning.
 struct Tuning {
@@ -96,10 +110,12 @@ Tuning& tuning();
 // If the launch slices K (only when `part` is given; at most max_split slices), slice s stores its partial product
 // at part[s][M][N] and *ksplit_out = number of slices: the caller's consumer adds them up.  Otherwise the result
 // goes to y as `epilogue` (EPI_STORE, EPI_ADD, or a SwiGLU epilogue, which never slices) says and *ksplit_out = 1.
+// `norm` (unsliced launches of at most 16 rows only): the input is rmsnorm(A) * gain.
 // `asplit` (optional) is a workspace of 2 * linear_big_split_elems(M, L.Kpad) bf16 values: with it and the
 // linear_big_all knob, launches of many rows first store the two bf16 terms of A there (launch_linear_big).
 int32_t launch_linear(const Linear& L, const float* A, int lda, int M, float* y, int ldy, int epilogue, int prologue,
-                      float* part, int max_split, int* ksplit_out, uint16_t* asplit, hipStream_t st);
+                      float* part, int max_split, int* ksplit_out, uint16_t* asplit, hipStream_t st,
+                      const NormIn* norm = nullptr);
 int32_t launch_linear_big(const Linear& L, const float* A, int lda, int M, float* y, int ldy, int epilogue,
                           float* part, int max_split, int* ksplit_out, uint16_t* asplit, hipStream_t st);
 size_t linear_big_split_elems(int M, int Kpad);
@@ -107,9 +123,17 @@ int linear_big_min_rows(const Linear& L);
 int linear_max_split();
 int32_t launch_reduce_partials(const float* part, int ks, int64_t n, float* y, int accumulate, hipStream_t st);
 // interleave: 0 = source row r becomes packed row row_offset + r; 1 / 2 = the source is the gate / up half of a fused
-// gate/up matrix, whose 32-row tiles hold 16 gate and the 16 up columns of the same indices (rows % 16 == 0)
+// gate/up matrix, whose 32-row tiles hold 16 gate and the 16 up columns of the same indices (rows % 16 == 0);
+// 64 or more = the head dimension of a fused QKV matrix, whose heads are in the order of qkv_packed_dim
 int32_t launch_pack_rows(const uint16_t* src, int rows, int K, size_t tstride, uint16_t* dst_packed, int row_offset,
                          hipStream_t st, int interleave = 0);
+
+// ---- projections of up to 16 rows (linear_few.hip) -----------------------------------------------
+// whether M rows take that path (a forced launch shape keeps the tiled kernels)
+bool linear_few_rows(int M);
+// y (+)= A * W^T; one launch, no workspace.  A: fp32 rows of stride lda, or (packed) the two bf16 terms that
+// EPI_SWIGLU_FEW writes, with lda = distance from the hi to the lo terms in 16-byte units
+int32_t launch_linear_few(const Linear& L, const float* A, int64_t lda, int M, int packed, float* y, int ldy, int add, hipStream_t st);
 
 // ---- elementwise / indexing kernels ---------------------------------------------------------------
 // out = rmsnorm(h) * gain.  With ks > 0 the row first absorbs the K-slices of the projection that feeds the
@@ -127,7 +151,19 @@ struct PoolDesc {
     int64_t layer_stride = 0;  // elements
     int num_blocks = 0, n_kv = 0, d = 0, n_layers = 0;
 };
-// K tile of one (page, kv head): [d/8][16 tok][8];  V tile: [d/32][4 tok-groups][16][2][4 tok]  (see kernels)
+// K tile of one (page, kv head): [d/8][16 tok][8];  V tile: [d/32][4 tok-groups][16][2][4 tok]  (see kv_layout.h)
+
+// What the few-row QKV projection does with its result: q and k are rotated with the table's row (cos_t, sin_t
+// [rows, d/2]), q goes to q_out [rows, n_q*d], k and v are rounded to bf16 and written at their slots; row r is token
+// r % q_len of request r / q_len.
+struct RopeOut {
+    PoolDesc pool;
+    const float *cos_t = nullptr, *sin_t = nullptr;
+    const int32_t *bt = nullptr, *seq_lens = nullptr;
+    float* q_out = nullptr;
+    int layer = 0, n_q = 0, q_len = 1, max_blocks = 0;
+};
+int32_t launch_qkv_few(const Linear& L, const float* h, int lda, int M, const NormIn& norm, const RopeOut& ro, hipStream_t st);
 int32_t launch_append_kv(const PoolDesc& p, int layer, const uint16_t* k, const uint16_t* v, const int32_t* bt,
                          int max_blocks, const int32_t* seq_idx, const int32_t* pos, int64_t n, hipStream_t st);
 int32_t launch_gather_kv(const PoolDesc& p, int layer, const int32_t* bt_row, int len, uint16_t* k_out, uint16_t* v_out,

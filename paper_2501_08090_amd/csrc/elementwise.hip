@@ -1,6 +1,7 @@
 // Bandwidth-bound kernels of the decode step: what begins it (embedding gather, rotary table, attention work list), RMSNorm, rotary embedding,
 // KV append / gather (the slot contract), and small utilities.  gfx950, wave64.
 #include "attn_plan.h"
+#include "kv_layout.h"
 
 namespace chiron {
 
@@ -167,19 +168,7 @@ int32_t launch_rope(float* x, int ldx, int n_heads, int d, const float* cos_t, c
     return CHIRON_OK;
 }
 
-// ---- KV pool addressing -----------------------------------------------------------------------------------
-// Pool memory: [layer][block][kv head][K tile | V tile], each tile 16*d bf16.
-//   K tile: element (tok t, dim e) at ((e/8)*16 + t)*8 + e%8               -> rows of 8 dims, token-major groups
-//   V tile: element (tok t, dim e) at ((((e/32)*4 + t/4)*16 + e%16)*2 + (e%32)/16)*4 + t%4   -> token-minor
-// Both orders make every matrix-core operand fragment of the attention kernel a contiguous 1 KiB read.
-__device__ __forceinline__ size_t tile_base(const PoolDesc& p, int layer, int block, int kvh) {
-    return (size_t)layer * (size_t)p.layer_stride + ((size_t)block * p.n_kv + kvh) * (size_t)(2 * 16 * p.d);
-}
-__device__ __forceinline__ int k_off(int t, int e) { return ((e >> 3) * 16 + t) * 8 + (e & 7); }
-__device__ __forceinline__ int v_off(int t, int e) {
-    return (((((e >> 5) * 4 + (t >> 2)) * 16 + (e & 15)) * 2 + ((e & 31) >> 4)) * 4) + (t & 3);
-}
-
+// ---- KV append and gather (element order: kv_layout.h) -------------------------------------------------------
 __global__ __launch_bounds__(256) void append_kv_kernel(PoolDesc p, int layer, const uint16_t* __restrict__ k,
                                                         const uint16_t* __restrict__ v, const int32_t* __restrict__ bt,
                                                         int max_blocks, const int32_t* __restrict__ seq_idx,
@@ -252,7 +241,7 @@ int32_t launch_swap(const PoolDesc& p, const int32_t* bt_row, int n_pages, uint1
     return CHIRON_OK;
 }
 
-// ---- decode step: sum the K-slices of the QKV projection, rotate q and k, round k and v to bf16, write them
+// ---- decode step: sum the K-slices of the QKV projection (whose columns are in packed order), rotate q and k, round k and v to bf16, write them
 // at their slots.  One wave per (request, head): lane j owns dims j, j+64, ... of the head. ------------
 __global__ __launch_bounds__(64) void rope_append_kernel(PoolDesc p, int layer, const float* __restrict__ qkv, int ks,
                                                          size_t slice_stride, int n_q,
@@ -266,7 +255,7 @@ __global__ __launch_bounds__(64) void rope_append_kernel(PoolDesc p, int layer, 
     const float* row = qkv + (size_t)i * ld + (size_t)hd * d;
     // sum over the K-slices, four independent loads in flight at a time, slices added in ascending order
     auto val = [&](int e) {
-        const float* q = row + e;
+        const float* q = row + qkv_packed_dim(e, d);
         float v = 0.f;
         int s = 0;
         for (; s + 4 <= ks; s += 4) {

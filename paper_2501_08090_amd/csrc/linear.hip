@@ -33,14 +33,17 @@ __host__ __device__ inline int gate_up_packed_row(int j, int kind) {
     return 32 * (j / 16) + 8 * ((j % 16) / 4) + 4 * kind + j % 4;
 }
 
-// interleave: 0 = rows go to row_offset + r; 1 / 2 = r is a gate / up column of a fused gate/up matrix
+// interleave: 0 = rows go to row_offset + r; 1 / 2 = r is a gate / up column of a fused gate/up matrix; 64 or more = head dimension of a
+// fused QKV matrix
 __global__ __launch_bounds__(256) void pack_rows_kernel(const uint16_t* __restrict__ src, int rows, int K, size_t tstride,
                                                         uint16_t* __restrict__ dst, int row_offset, int interleave) {
     int kgroups = K / 8;
     int64_t total = (int64_t)rows * kgroups;
     for (int64_t t = (int64_t)blockIdx.x * 256 + threadIdx.x; t < total; t += (int64_t)gridDim.x * 256) {
         int r = (int)(t / kgroups), kg = (int)(t % kgroups);
-        int n = interleave ? gate_up_packed_row(r, interleave - 1) : r + row_offset;
+        int n = r + row_offset;
+        if (interleave >= 64) n = n / interleave * interleave + qkv_packed_dim(n % interleave, interleave);
+        else if (interleave) n = gate_up_packed_row(r, interleave - 1);
         uint4 v = *reinterpret_cast<const uint4*>(src + (size_t)r * K + (size_t)kg * 8);
         *reinterpret_cast<uint4*>(dst + (size_t)(n / 32) * tstride + (size_t)kg * 256 + (size_t)(n % 32) * 8) = v;
     }
@@ -49,7 +52,8 @@ __global__ __launch_bounds__(256) void pack_rows_kernel(const uint16_t* __restri
 int32_t launch_pack_rows(const uint16_t* src, int rows, int K, size_t tstride, uint16_t* dst_packed, int row_offset,
                          hipStream_t st, int interleave) {
     if (rows == 0) return CHIRON_OK;
-    if (interleave && rows % 16 != 0) return fail(CHIRON_ERR_SHAPE, "gate/up packing: %d columns are not a multiple of 16", rows);
+    if ((interleave == 1 || interleave == 2) && rows % 16 != 0) return fail(CHIRON_ERR_SHAPE, "gate/up packing: %d columns are not a multiple of 16", rows);
+    if (interleave >= 64 && (rows % interleave || row_offset % interleave)) return fail(CHIRON_ERR_SHAPE, "QKV packing: %d rows are not whole heads", rows);
     int64_t total = (int64_t)rows * (K / 8);
     int blocks = (int)((total + 255) / 256 < 8192 ? (total + 255) / 256 : 8192);
     launch(pack_rows_kernel, dim3(blocks), dim3(256), st, src, rows, K, tstride, dst_packed, row_offset, interleave);
@@ -66,22 +70,29 @@ int32_t launch_pack_rows(const uint16_t* src, int rows, int K, size_t tstride, u
 // WNT: weight loads carry the non-temporal hint (every weight is read once: a single M-tile).  With several M-tiles
 // the same weights are read once per M-tile through the L2, and the hint makes those re-reads slower (measured on the
 // 8B gate/up shape at 2048 rows: the weight stream alone 268 us with the hint, 194 us without).
-template <int MT, int NF, int KS, int PRO, bool WNT = true>
+// NORM: the input is rmsnorm(A) * gain.  A workgroup of an unsliced projection reads whole rows anyway: the gain is applied
+// while a chunk is staged, the sum of squares is taken from the same values, and the row's 1/rms multiplies the accumulators.
+template <int MT, int NF, int KS, int PRO, bool WNT = true, bool NORM = false>
 __global__ __launch_bounds__(256, (MT * NF <= 8 && !(MT == 4 && PRO != PRO_NONE) ? 2 : 1)) void linear_kernel(const uint16_t* __restrict__ Wp, size_t tstride, int Npad, int Nreal, int K, int Kpad,
                                                      const float* __restrict__ A, int lda, int M,
                                                      float* __restrict__ Y, int ldy, int chunks_per_split,
-                                                     int mode, size_t part_stride, int gx, int gy, int gz, int remap) {
+                                                     int mode, size_t part_stride, int gx, int gy, int gz, int remap,
+                                                     const uint16_t* __restrict__ gain, float eps) {
     constexpr int MROWS = 32 * MT;
     constexpr int RS = MROWS + 1;      // LDS row stride in 16-byte units (+1 breaks the power-of-two stride)
     constexpr int KG = 2 * KS;         // 8-wide k-groups per chunk
     constexpr int KC = 16 * KS;        // k per chunk
-    constexpr int TASKS = MROWS * KG;  // 8-float staging tasks per chunk
+    // (with NORM there are at most 16 rows: the upper half of the tile is not staged where that saves whole passes, and the
+    // columns of the product that it would give are never stored)
+    constexpr int SROWS = NORM && MT == 1 && 16 * KG % 256 == 0 ? 16 : MROWS;
+    constexpr int TASKS = SROWS * KG;  // 8-float staging tasks per chunk
     static_assert(TASKS % 256 == 0, "staging assumes whole passes of the workgroup");
     constexpr int TPT = TASKS / 256;
     // activation loads and staging spread over the k-steps of a chunk (see below; measured on one device against the
     // bunched form: gate/up at 64 rows 50.3 against 53.6 us, at 192 rows 101 against 109 us).  The widest tile keeps
     // them bunched: it has no registers left for the first chunk's separate staging set.
     constexpr bool SPREAD = PRO != PRO_PACKED && MT * NF <= 8 && TPT <= KS;
+    static_assert(!NORM || SPREAD, "the norm is built into the spread staging only");
 
     __shared__ uint4 lds_hi[2][KG * RS];
     __shared__ uint4 lds_lo[2][KG * RS];
@@ -135,22 +146,36 @@ __global__ __launch_bounds__(256, (MT * NF <= 8 && !(MT == 4 && PRO != PRO_NONE)
         for (int f = 0; f < NF; ++f)
             w[s][f] = WNT ? load_stream_16(wp[f] + off) : *reinterpret_cast<const uint4*>(wp[f] + off);
     };
-    // staging task i of a chunk: 8 consecutive k of one row, thread tid + 256*i
-    auto load_task = [&](int c, int i, float4 (&ar)[2]) {
+    // staging task i of a chunk: 8 consecutive k of one row, thread tid + 256*i.  A thread's tasks share their k, so the
+    // gains of a chunk are one load, with the last task: by then the previous chunk's gains have been used.
+    uint4 g0 = make_uint4(0, 0, 0, 0), greg = g0;  // gains of the first chunk and of the one being staged
+    float ss[TPT];                                 // this thread's part of its rows' sums of squares
+#pragma unroll
+    for (int i = 0; i < TPT; ++i) ss[i] = 0.f;
+    auto load_task = [&](int c, int i, float4 (&ar)[2], uint4& gr) {
         int task = tid + i * 256;
         int kg = task % KG, m = task / KG;
         int k = c * KC + kg * 8;
         const float* p = A + (size_t)min(m0 + m, M - 1) * lda + min(k, K - 8);
         ar[0] = *reinterpret_cast<const float4*>(p);
         ar[1] = *reinterpret_cast<const float4*>(p + 4);
+        if (NORM && i == TPT - 1) gr = *reinterpret_cast<const uint4*>(gain + min(k, K - 8));
     };
-    auto stage_task = [&](int c, int i, int buf, const float4 (&ar)[2]) {
+    auto stage_task = [&](int c, int i, int buf, const float4 (&ar)[2], const uint4& gr) {
         int task = tid + i * 256;
         int kg = task % KG, m = task / KG;
         const bool ok = (m0 + m < M) && (c * KC + kg * 8 < K);
         float v[8] = {ar[0].x, ar[0].y, ar[0].z, ar[0].w, ar[1].x, ar[1].y, ar[1].z, ar[1].w};
 #pragma unroll
         for (int e = 0; e < 8; ++e) v[e] = ok ? v[e] : 0.f;
+        if (NORM) {
+            const uint32_t gw[4] = {gr.x, gr.y, gr.z, gr.w};
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+                ss[i] = fmaf(v[e], v[e], ss[i]);
+                v[e] *= (e & 1) ? bf16_hi(gw[e / 2]) : bf16_lo(gw[e / 2]);
+            }
+        }
         uint4 hi, lo;
         split2(v[0], v[1], hi.x, lo.x);
         split2(v[2], v[3], hi.y, lo.y);
@@ -161,11 +186,11 @@ __global__ __launch_bounds__(256, (MT * NF <= 8 && !(MT == 4 && PRO != PRO_NONE)
     };
     auto load_a = [&](int c) {
 #pragma unroll
-        for (int i = 0; i < TPT; ++i) load_task(c, i, areg[i]);
+        for (int i = 0; i < TPT; ++i) load_task(c, i, areg[i], greg);
     };
     auto stage_a = [&](int c, int buf) {
 #pragma unroll
-        for (int i = 0; i < TPT; ++i) stage_task(c, i, buf, areg[i]);
+        for (int i = 0; i < TPT; ++i) stage_task(c, i, buf, areg[i], greg);
     };
     // PRO_PACKED: chunk c of the pre-split activations goes HBM/L2 -> LDS directly (16 bytes per lane, a wave
     // fills 64 consecutive rows of one k-group), no registers and no LDS store instructions in between
@@ -284,7 +309,7 @@ __global__ __launch_bounds__(256, (MT * NF <= 8 && !(MT == 4 && PRO != PRO_NONE)
             // loads, which only the loop uses, behind the barrier and out of that order.)
             float4 a0[TPT][2];
 #pragma unroll
-            for (int i = 0; i < TPT; ++i) load_task(c_begin, i, a0[i]);
+            for (int i = 0; i < TPT; ++i) load_task(c_begin, i, a0[i], g0);
             __builtin_amdgcn_sched_barrier(0);
             if (c_begin < c_last) {
 #pragma unroll
@@ -294,12 +319,12 @@ __global__ __launch_bounds__(256, (MT * NF <= 8 && !(MT == 4 && PRO != PRO_NONE)
 #pragma unroll
                     for (int i = 0; i < TPT; ++i)
                         if (i * KS / TPT == s) {
-                            load_task(c_begin + 1, i, areg[i]);
+                            load_task(c_begin + 1, i, areg[i], greg);
                             __builtin_amdgcn_sched_barrier(0);
                         }
                 }
 #pragma unroll
-                for (int i = 0; i < TPT; ++i) stage_task(c_begin, i, 0, a0[i]);
+                for (int i = 0; i < TPT; ++i) stage_task(c_begin, i, 0, a0[i], g0);
                 lds_barrier();
                 int buf = 0, c = c_begin;
                 do {
@@ -311,9 +336,9 @@ __global__ __launch_bounds__(256, (MT * NF <= 8 && !(MT == 4 && PRO != PRO_NONE)
 #pragma unroll
                         for (int i = 0; i < TPT; ++i)
                             if (i * KS / TPT == s) {
-                                stage_task(c + 1, i, buf ^ 1, areg[i]);
+                                stage_task(c + 1, i, buf ^ 1, areg[i], greg);
                                 __builtin_amdgcn_sched_barrier(0);
-                                load_task(min(c + 2, c_last), i, areg[i]);
+                                load_task(min(c + 2, c_last), i, areg[i], greg);
                                 __builtin_amdgcn_sched_barrier(0);
                             }
                     }
@@ -326,7 +351,7 @@ __global__ __launch_bounds__(256, (MT * NF <= 8 && !(MT == 4 && PRO != PRO_NONE)
 #pragma unroll
                 for (int s = 0; s < KS; ++s) load_w(c_begin, s);
 #pragma unroll
-                for (int i = 0; i < TPT; ++i) stage_task(c_begin, i, 0, a0[i]);
+                for (int i = 0; i < TPT; ++i) stage_task(c_begin, i, 0, a0[i], g0);
                 lds_barrier();
 #pragma unroll
                 for (int s = 0; s < KS; ++s) mma_step(0, s);
@@ -363,6 +388,27 @@ __global__ __launch_bounds__(256, (MT * NF <= 8 && !(MT == 4 && PRO != PRO_NONE)
         for (int s = 0; s < KS; ++s) mma_step(buf, s);
     }
 
+    if constexpr (NORM) {
+        __shared__ float s_inv[MROWS];
+        // the KG threads that staged a row sit side by side in one wave
+#pragma unroll
+        for (int i = 0; i < TPT; ++i) {
+            float s = ss[i];
+#pragma unroll
+            for (int o = 1; o < KG; o <<= 1) s += __shfl_xor(s, o);
+            if (tid % KG == 0) s_inv[(tid + i * 256) / KG] = 1.0f / sqrtf(s / (float)K + eps);
+        }
+        lds_barrier();
+#pragma unroll
+        for (int t = 0; t < MT; ++t) {
+            const float inv = s_inv[t * 32 + (lane & 31)];
+#pragma unroll
+            for (int f = 0; f < NF; ++f)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) acc[f][t][r] *= inv;
+        }
+    }
+
     // D[i][j]: lane holds column j = lane%32 (an activation row m) and rows i = 8*(r/4) + 4*(lane/32) + r%4
     // (output columns n) for r = 0..15.
     if (mode >= EPI_SWIGLU) {
@@ -390,13 +436,14 @@ __global__ __launch_bounds__(256, (MT * NF <= 8 && !(MT == 4 && PRO != PRO_NONE)
                     *reinterpret_cast<float4*>(dst + 4) = make_float4(v[4], v[5], v[6], v[7]);
                 } else {
                     // the two bf16 terms in 32-row x 8-k tile order (ldy = k-groups of the consumer, part_stride = distance
-                    // from the hi to the lo terms in 16-byte units)
+                    // from the hi to the lo terms in 16-byte units), or with the M rows of a k-group side by side
                     uint4 hi, lo;
                     split2(v[0], v[1], hi.x, lo.x);
                     split2(v[2], v[3], hi.y, lo.y);
                     split2(v[4], v[5], hi.z, lo.z);
                     split2(v[6], v[7], hi.w, lo.w);
-                    uint4* dst = reinterpret_cast<uint4*>(Y) + ((size_t)(m / 32) * ldy + (size_t)(2 * tile + half)) * 32 + (m & 31);
+                    uint4* dst = reinterpret_cast<uint4*>(Y) + (mode == EPI_SWIGLU_FEW ? (size_t)(2 * tile + half) * M + m
+                                     : ((size_t)(m / 32) * ldy + (size_t)(2 * tile + half)) * 32 + (m & 31));
                     dst[0] = hi;
                     dst[part_stride] = lo;
                 }
@@ -460,11 +507,11 @@ Tuning& tuning() {
     return t;
 }
 
-template <int MT, int NF, int PRO, int KS = 4, bool WNT = true>
+template <int MT, int NF, int PRO, int KS = 4, bool WNT = true, bool NORM = false>
 static void launch_cfg(int nblocks, hipStream_t st, const Linear& L, const float* A, int lda, int M, float* y, int ldy,
-                       int cps, int mode, size_t part_stride, int gx, int gy, int gz) {
-    launch(linear_kernel<MT, NF, KS, PRO, WNT>, dim3(nblocks), dim3(256), st, L.w, L.tstride, L.Npad, L.N, L.K, L.Kpad, A, lda, M, y, ldy, cps, mode,
-                                                           part_stride, gx, gy, gz, tuning().linear_xcd_remap);
+                       int cps, int mode, size_t part_stride, int gx, int gy, int gz, const NormIn& norm = NormIn()) {
+    launch(linear_kernel<MT, NF, KS, PRO, WNT, NORM>, dim3(nblocks), dim3(256), st, L.w, L.tstride, L.Npad, L.N, L.K, L.Kpad, A, lda, M, y, ldy, cps, mode,
+                                                           part_stride, gx, gy, gz, tuning().linear_xcd_remap, norm.gain, norm.eps);
 }
 
 int linear_max_split() { return 16; }
@@ -482,10 +529,12 @@ int linear_big_min_rows(const Linear& L) {
 }
 
 int32_t launch_linear(const Linear& L, const float* A, int lda, int M, float* y, int ldy, int epilogue, int prologue,
-                      float* part, int max_split, int* ksplit_out, uint16_t* asplit, hipStream_t st) {
+                      float* part, int max_split, int* ksplit_out, uint16_t* asplit, hipStream_t st, const NormIn* norm) {
     if (ksplit_out) *ksplit_out = 1;
     if (M == 0) return CHIRON_OK;
-    if (epilogue != EPI_STORE && epilogue != EPI_ADD && epilogue != EPI_SWIGLU && epilogue != EPI_SWIGLU_PACKED)
+    if (norm && (part || prologue != PRO_NONE || !linear_few_rows(M)))
+        return fail(CHIRON_ERR_INVALID_ARG, "linear: a norm in the operand load needs an unsliced launch of few rows");
+    if (epilogue != EPI_STORE && epilogue != EPI_ADD && epilogue != EPI_SWIGLU && epilogue != EPI_SWIGLU_PACKED && epilogue != EPI_SWIGLU_FEW)
         return fail(CHIRON_ERR_INVALID_ARG, "linear: unknown epilogue %d", epilogue);
     if (epilogue >= EPI_SWIGLU) {
         // gate and up of one column must meet in one workgroup with the whole sum over K
@@ -602,10 +651,17 @@ int32_t launch_linear(const Linear& L, const float* A, int lda, int M, float* y,
     if (epilogue == EPI_SWIGLU_PACKED) {  // ldy: the consumer's padded K
         ldd = ldy / 8;
         part_stride = linear_big_split_elems(M, ldy) / 8;
+    } else if (epilogue == EPI_SWIGLU_FEW) {
+        part_stride = (size_t)M * (ldy / 8);
     }
     int nblocks = (gx * ksplit * gz + 7) / 8 * 8;
 #define CHIRON_LAUNCH(MT_, NF_) launch_cfg<MT_, NF_, PRO_NONE>(nblocks, st, L, A, lda, M, dst, ldd, cps, mode, part_stride, gx, ksplit, gz)
-    if (ks16) {
+    if (norm) {  // at most 16 rows, unsliced: one of these three
+        if (ks16) launch_cfg<1, 1, PRO_NONE, 16, true, true>(nblocks, st, L, A, lda, M, dst, ldd, cps, mode, part_stride, gx, ksplit, gz, *norm);
+        else if (mt == 1 && nf == 2) launch_cfg<1, 2, PRO_NONE, 4, true, true>(nblocks, st, L, A, lda, M, dst, ldd, cps, mode, part_stride, gx, ksplit, gz, *norm);
+        else if (mt == 2 && nf == 4) launch_cfg<1, 4, PRO_NONE, 4, true, true>(nblocks, st, L, A, lda, M, dst, ldd, cps, mode, part_stride, gx, ksplit, gz, *norm);
+        else return fail(CHIRON_ERR_INVALID_ARG, "linear: no shape with the norm for %d rows of %d columns", M, L.N);
+    } else if (ks16) {
         launch_cfg<1, 1, PRO_NONE, 16>(nblocks, st, L, A, lda, M, dst, ldd, cps, mode, part_stride, gx, ksplit, gz);
     } else if (ks8 && mt == 3) {
         launch_cfg<3, 1, PRO_NONE, 8>(nblocks, st, L, A, lda, M, dst, ldd, cps, mode, part_stride, gx, ksplit, gz);

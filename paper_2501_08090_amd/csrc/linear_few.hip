@@ -1,0 +1,248 @@
+// Projections of a few rows (up to 16).  There the weight stream is everything, and what the tiled kernel of linear.hip
+// spends around it is launches: K-slices that a kernel of their own has to add up, the norm before, the rotary embedding
+// behind.  Here a workgroup owns 16 or 32 output columns over the WHOLE of K: its 8 waves take an eighth of K each, add
+// their accumulators through LDS, and the result is final.  So the residual stream is complete when the kernel ends, the
+// next projection can take the RMS norm in its own operand load (gain on the way in, the row's 1/rms, which it learns from
+// the same loads, on the way out), and the QKV projection can rotate and write the cache itself.
+//
+// The waves share nothing until the end: each loads its weights and its activations (fp32, from L2) straight into operand
+// registers (v_mfma_f32_16x16x32_bf16, weights as A, 16 activation rows as B, two bf16 terms each), 8 k-steps of 32 ahead;
+// no LDS and no barrier in the loop.  Every workgroup reads all rows of its input, which is what ends the range: at 16 rows
+// the activations of a 4096-wide input are as many bytes per workgroup (256 KiB) as the weights of its 32 columns.
+//
+// Measured per layer at the 8B widths and one row, against the tiled kernels with the norms and the rotary embedding as
+// launches of their own: QKV 12.2 us (11.4 + 4.8 + 4.7), O 7.4 (8.2; 4.5 TB/s with the launch), gate/up with its norm 38.8
+// (37.7 + 4.8), down 20.6 (19.6; 5.7 TB/s); four layers and the head 575 -> 522 us, 664 -> 623 at 11 rows.  A single
+// projection of 4096 x 4096 with its K-slices summed 27 -> 7.7 us.  At 16 rows down is level with the tiled kernel and the
+// norm it saves (26 against 20 + 5 us) and the others gain; beyond, the activation loads outweigh the launches.
+// Rings of 12 or 16 k-steps were slower (8.4 .. 9.0 against 7.7 us at 4096 x 4096), as bytes in flight are not what is short.
+#include "chiron_internal.h"
+#include "device_util.h"
+#include "kv_layout.h"
+
+namespace chiron {
+
+constexpr int kFewWaves = 8;
+
+// CT: 16-column tiles per workgroup.
+// FEW_ROWS: A is fp32 rows.
+// FEW_PACKED: A holds the two bf16 terms, [k/8][M rows][8], hi terms first (lda = distance to the lo terms in 16-byte
+//   units): no conversion, and a wave's loads are contiguous pieces of 16*M bytes instead of 32 bytes of each row.
+// FEW_QKV: the fused QKV projection of a decode step, whose input is rmsnorm(A) * gain, A fp32 rows, and which ends in the
+//   rotary embedding and the append to the cache.
+enum FewMode { FEW_ROWS, FEW_PACKED, FEW_QKV };
+template <int CT, int MODE>
+__global__ __launch_bounds__(64 * kFewWaves) void linear_few_kernel(const uint16_t* __restrict__ Wp, size_t tstride, int N, int K, int Kpad,
+                                                                   const float* __restrict__ A, int64_t lda, int M,
+                                                                   const uint16_t* __restrict__ gain, float eps,
+                                                                   float* __restrict__ Y, int ldy, int add, RopeOut ro) {
+    constexpr bool QKV = MODE == FEW_QKV;
+    constexpr int D = 8;        // k-steps in flight per wave (CT KiB of weights each)
+    constexpr int WS = 72;      // float4 units between the 16x16 tiles in LDS, 18 between a tile's row groups: no two
+    constexpr int QS = 18;      // threads of the final sum that read at once share a bank
+    __shared__ float4 s_acc[kFewWaves * CT * WS];
+    __shared__ float s_ss[kFewWaves][16];
+    static_assert(!QKV || CT == 2, "a rotary pair sits in the two halves of a 32-column tile");
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int row = lane & 15, kq = lane >> 4;
+    const int ct0 = blockIdx.x * CT;  // first 16-column tile
+
+    // this thread's output: row om, column oc of the workgroup's columns.  What the epilogue needs for it (the old value of
+    // the residual stream, or a chain of dependent loads for the rotation and the slot) is fetched first and is there long
+    // before the weights are.
+    const int om = tid / (16 * CT), oc = tid % (16 * CT);
+    const bool live = om < M;
+    float cs = 0.f, sn = 0.f;
+    int block = 0, slot = 0;
+    const int half = QKV ? ro.pool.d / 2 : 1;
+    const int hd = QKV ? (int)blockIdx.x / (ro.pool.d / 32) : 0;                          // head
+    const int j = QKV ? ((int)blockIdx.x % (ro.pool.d / 32)) * 16 + (oc & 15) : 0;        // first dim of this thread's pair
+    if (QKV && live) {
+        const int req = om / ro.q_len;
+        const int ps = ro.seq_lens[req] + om % ro.q_len;
+        cs = ro.cos_t[(size_t)om * half + j];
+        sn = ro.sin_t[(size_t)om * half + j];
+        block = ro.bt[(size_t)req * ro.max_blocks + ps / kBlockSize];
+        slot = ps % kBlockSize;
+    }
+
+    const int n_out = ct0 * 16 + oc;
+    float y_old = 0.f;
+    if (!QKV && add && live && n_out < N && tid < 256 * CT) y_old = Y[(size_t)om * ldy + n_out];
+
+    const int S = Kpad / (32 * kFewWaves);  // k-steps of this wave (the packed weights are zero past K)
+    const int st0 = wave * S;
+    // A wave walks its eighth of K from a start that differs between workgroups: with K a power of two the weight streams of
+    // all workgroups would stay in step on the same memory channels (8192 x 8192, 256 workgroups: 24.1 against 21.3 us).
+    const int rot = (int)(blockIdx.x / 8 * 3) % S;
+    auto k_step = [&](int step) {
+        const int sr = step + rot;
+        return st0 + (sr >= S ? sr - S : sr);
+    };
+    const uint16_t* wp = Wp + (size_t)(ct0 / 2) * tstride + (size_t)((ct0 & 1) * 128) + kq * 256 + row * 8;
+    const float* arow = A + (size_t)min(row, M - 1) * lda;                    // fp32 rows
+    const uint4* apack = reinterpret_cast<const uint4*>(A) + kq * M + min(row, M - 1);  // packed terms
+    floatx4 acc[CT];
+#pragma unroll
+    for (int t = 0; t < CT; ++t) acc[t] = floatx4{0.f, 0.f, 0.f, 0.f};
+    float ss = 0.f;
+    uint4 w[D][CT], g[QKV ? D : 1];
+    float4 a[D][2];                           // fp32 rows
+    uint4 p[MODE == FEW_PACKED ? D : 1][2];   // packed terms: hi, lo
+
+    auto load = [&](int step, int s) {
+        const int st = k_step(min(step, S - 1));
+        const uint16_t* wk = wp + (size_t)st * 1024;
+#pragma unroll
+        for (int t = 0; t < CT; ++t) w[s][t] = load_stream_16(wk + t * 128);
+        if (MODE == FEW_PACKED) {
+            p[s][0] = apack[(size_t)st * (4 * M)];
+            p[s][1] = apack[(size_t)st * (4 * M) + lda];
+            return;
+        }
+        const int k = min(st * 32 + kq * 8, K - 8);
+        a[s][0] = *reinterpret_cast<const float4*>(arow + k);
+        a[s][1] = *reinterpret_cast<const float4*>(arow + k + 4);
+        if (QKV) g[s] = *reinterpret_cast<const uint4*>(gain + k);
+    };
+    auto compute = [&](int step, int s) {
+        const int k0 = k_step(step) * 32;
+        uint4 hi, lo;
+        if (MODE == FEW_PACKED) {
+            hi = p[s][0];
+            lo = p[s][1];
+            if (k0 + 32 > K && k0 + kq * 8 >= K) hi = lo = make_uint4(0, 0, 0, 0);  // the padding of K may hold any bits
+        } else {
+            float v[8] = {a[s][0].x, a[s][0].y, a[s][0].z, a[s][0].w, a[s][1].x, a[s][1].y, a[s][1].z, a[s][1].w};
+            if (k0 + 32 > K) {  // uniform: a step that reaches past K
+                const bool ok = k0 + kq * 8 < K;
+#pragma unroll
+                for (int e = 0; e < 8; ++e) v[e] = ok ? v[e] : 0.f;
+            }
+            if (QKV) {
+                const uint32_t gw[4] = {g[s].x, g[s].y, g[s].z, g[s].w};
+#pragma unroll
+                for (int e = 0; e < 8; ++e) {
+                    ss = fmaf(v[e], v[e], ss);
+                    v[e] *= (e & 1) ? bf16_hi(gw[e / 2]) : bf16_lo(gw[e / 2]);
+                }
+            }
+            split2(v[0], v[1], hi.x, lo.x);
+            split2(v[2], v[3], hi.y, lo.y);
+            split2(v[4], v[5], hi.z, lo.z);
+            split2(v[6], v[7], hi.w, lo.w);
+        }
+#pragma unroll
+        for (int t = 0; t < CT; ++t)
+            acc[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(*reinterpret_cast<bf16x8*>(&w[s][t]), *reinterpret_cast<bf16x8*>(&hi), acc[t], 0, 0, 0);
+#pragma unroll
+        for (int t = 0; t < CT; ++t)
+            acc[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(*reinterpret_cast<bf16x8*>(&w[s][t]), *reinterpret_cast<bf16x8*>(&lo), acc[t], 0, 0, 0);
+    };
+
+    if (S >= D) {
+        // whole rings: a slot is reloaded as soon as it has been multiplied.  Loads are unconditional (past the wave's
+        // last k-step they repeat it), so the number in flight is the same on every path and no wait drains the queue.
+#pragma unroll
+        for (int s = 0; s < D; ++s) {
+            load(s, s);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        int step = 0;
+        for (; step + D < S; step += D) {
+#pragma unroll
+            for (int s = 0; s < D; ++s) {
+                compute(step + s, s);
+                load(step + D + s, s);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        }
+#pragma unroll
+        for (int s = 0; s < D; ++s)
+            if (step + s < S) compute(step + s, s);  // uniform
+    } else {
+#pragma unroll
+        for (int s = 0; s < D; ++s)
+            if (s < S) load(s, s);
+#pragma unroll
+        for (int s = 0; s < D; ++s)
+            if (s < S) compute(s, s);
+    }
+
+    // D[i][j]: lane holds column j = lane % 16 (an activation row) and rows i = 4 * (lane / 16) + r (output columns)
+#pragma unroll
+    for (int t = 0; t < CT; ++t)
+        s_acc[(wave * CT + t) * WS + row + kq * QS] = make_float4(acc[t][0], acc[t][1], acc[t][2], acc[t][3]);
+    if (QKV) {
+        ss += __shfl_xor(ss, 16);
+        ss += __shfl_xor(ss, 32);
+        if (lane < 16) s_ss[wave][lane] = ss;
+    }
+    __syncthreads();
+    if (CT == 1 && tid >= 256) return;
+    const float* sp = reinterpret_cast<const float*>(s_acc) + (size_t)((oc / 16) * WS + om + ((oc & 15) / 4) * QS) * 4 + (oc & 3);
+    float v = 0.f;
+#pragma unroll
+    for (int k = 0; k < kFewWaves; ++k) v += sp[k * CT * WS * 4];
+    if (QKV) {
+        float tot = 0.f;
+#pragma unroll
+        for (int k = 0; k < kFewWaves; ++k) tot += s_ss[k][om];
+        v *= 1.0f / sqrtf(tot / (float)K + eps);
+    }
+    if (QKV) {
+        const float other = __shfl_xor(v, 16);  // the other half of the rotary pair (dims j and j + d/2)
+        if (!live) return;
+        const int hi = oc / 16, e = j + hi * half;
+        if (hd < ro.n_q + ro.pool.n_kv) v = hi ? v * cs + other * sn : v * cs - other * sn;
+        if (hd < ro.n_q) {
+            ro.q_out[(size_t)om * ro.n_q * 2 * half + (size_t)hd * 2 * half + e] = v;
+        } else {
+            const int kv = hd - ro.n_q;  // K heads, then V heads
+            const bool is_v = kv >= ro.pool.n_kv;
+            uint16_t* tile = ro.pool.base + tile_base(ro.pool, ro.layer, block, is_v ? kv - ro.pool.n_kv : kv);
+            tile[is_v ? 32 * half + v_off(slot, e) : k_off(slot, e)] = f32_to_bf16_rne(v);
+        }
+    } else {
+        if (live && n_out < N) Y[(size_t)om * ldy + n_out] = y_old + v;
+    }
+}
+
+bool linear_few_rows(int M) {
+    const Tuning& t = tuning();
+    return M <= 16 && !t.linear_mt && !t.linear_nf && !t.linear_ksplit && !t.linear_ks && !t.linear_big_all;
+}
+
+int32_t launch_linear_few(const Linear& L, const float* A, int64_t lda, int M, int packed, float* y, int ldy, int add, hipStream_t st) {
+    if (M == 0) return CHIRON_OK;
+    if (M > 16) return fail(CHIRON_ERR_INVALID_ARG, "linear: %d rows on the few-row path", M);
+    if (L.K % 16 != 0 || L.K < 16) return fail(CHIRON_ERR_SHAPE, "linear: K=%d must be a positive multiple of 16", L.K);
+    if ((!packed && lda % 4 != 0) || ((uintptr_t)A & 15)) return fail(CHIRON_ERR_INVALID_ARG, "linear: input rows must be 16-byte aligned");
+    // 32 columns per workgroup (half as many loads of the same activations) where that still gives every CU one:
+    // 8192 outputs of 28672 inputs 68 against 75 us at one row, 72 against 89 us at 8; 4096 outputs of 14336 inputs 25 against 20 us
+    const int ct = (L.N + 31) / 32 >= kNumCU ? 2 : 1;
+    const dim3 grid((L.N + 16 * ct - 1) / (16 * ct)), block(64 * kFewWaves);
+#define CHIRON_FEW(CT_, MODE_) \
+    launch(linear_few_kernel<CT_, MODE_>, grid, block, st, L.w, L.tstride, L.N, L.K, L.Kpad, A, lda, M, (const uint16_t*)nullptr, 0.f, y, ldy, add, RopeOut())
+    if (ct == 1 && packed) CHIRON_FEW(1, FEW_PACKED);
+    else if (ct == 1) CHIRON_FEW(1, FEW_ROWS);
+    else if (packed) CHIRON_FEW(2, FEW_PACKED);
+    else CHIRON_FEW(2, FEW_ROWS);
+#undef CHIRON_FEW
+    CHIRON_HIP(hipGetLastError());
+    return CHIRON_OK;
+}
+
+int32_t launch_qkv_few(const Linear& L, const float* h, int lda, int M, const NormIn& norm, const RopeOut& ro, hipStream_t st) {
+    if (M == 0) return CHIRON_OK;
+    if (M > 16) return fail(CHIRON_ERR_INVALID_ARG, "linear: %d rows on the few-row path", M);
+    if (L.N != (ro.n_q + 2 * ro.pool.n_kv) * ro.pool.d || ro.pool.d % 32 != 0)
+        return fail(CHIRON_ERR_SHAPE, "linear: %d columns are not the heads of a fused QKV projection", L.N);
+    launch(linear_few_kernel<2, FEW_QKV>, dim3(L.N / 32), dim3(64 * kFewWaves), st, L.w, L.tstride, L.N, L.K, L.Kpad, h, (int64_t)lda, M, norm.gain,
+           norm.eps, (float*)nullptr, 0, 0, ro);
+    CHIRON_HIP(hipGetLastError());
+    return CHIRON_OK;
+}
+
+}  // namespace chiron

@@ -150,6 +150,33 @@ def test_linear(M, N, K):
     lin.close()
 
 
+@pytest.mark.parametrize("M,N,K", [(3, 1, 16), (1, 17, 16), (16, 17, 256), (15, 33, 2032), (7, 48, 2304), (16, 64, 4112), (2, 8192, 272), (16, 8209, 48), (3, 100, 2048)])
+def test_linear_few_rows(M, N, K):
+    """Up to 16 rows: 16 or (from 8192 columns) 32 columns per workgroup, 8 waves with an eighth of K each (fewer k-steps
+    than the ring holds, whole rings, a remainder behind them, a last step past K), columns past the last tile."""
+    rng = np.random.default_rng(M + 3 * N + 5 * K)
+    x = rng.standard_normal((M, K)).astype(np.float32)
+    W = I.normal((N, K), 0.05, 5, "wf", N, K)
+    print("linear few", M, N, K, flush=True)
+    lin = B().Linear(W.cuda())
+    want = orc.linear(x, I.to_numpy_storage(W))
+    y0 = rng.standard_normal((M, N)).astype(np.float32)
+    assert rel_err(lin(torch.from_numpy(x).cuda()).cpu().numpy(), want) <= KERNEL_TOL
+    assert rel_err(lin(torch.from_numpy(x).cuda(), torch.from_numpy(y0).cuda(), accumulate=True).cpu().numpy(), want + y0) <= KERNEL_TOL
+    lin.close()
+
+
+@pytest.mark.parametrize("M,K,F,N", [(1, 64, 16, 40), (16, 256, 688, 256), (5, 1040, 2064, 8208), (11, 256, 4096, 512)])
+def test_swiglu_ffn_few_rows(M, K, F, N):
+    """the feed-forward block whose intermediate is handed over as packed terms of M rows"""
+    x, Wg, Wu, Wd, _, want = ffn_case(M, K, F, N, M + K + F)
+    b = B()
+    gu, down = b.GateUp(Wg.cuda(), Wu.cuda()), b.Linear(Wd.cuda())
+    print("ffn few", M, K, F, N, flush=True)
+    assert rel_err(gu.ffn(down, torch.from_numpy(x).cuda()).cpu().numpy(), want) <= KERNEL_TOL
+    gu.close(); down.close()
+
+
 def ffn_case(M, K, F, N, seed, scale=2.0):
     """x [M,K] fp32, Wg, Wu [F,K], Wd [N,F] bf16 and the oracle's act = silu(x Wg^T) * (x Wu^T), y = act Wd^T"""
     rng = np.random.default_rng(seed)
@@ -456,6 +483,39 @@ def test_decode_step_over_seeded_random_geometries():
 
 G4_D128 = dict(I.TINY, head_dim=128, n_kv_heads=2, n_q_heads=8)
 G8_D128 = dict(I.TINY, head_dim=128, n_kv_heads=1, n_q_heads=8)
+
+
+@pytest.mark.parametrize("m,batch,T", [(I.TINY, 1, 1), (I.TINY, 16, 1), (G4_D128, 5, 3), (dict(I.TINY, hidden=2320, ffn=272, vocab=8400), 16, 1),
+                                       (dict(G4_D128, n_q_heads=2, n_kv_heads=2, hidden=272, vocab=33000), 3, 5)])
+def test_step_of_few_rows_equals_the_general_path(m, batch, T):
+    """Up to 16 rows the step takes the few-row projections (norms and rotary embedding fused); a forced tile height of
+    the general kernels (any knob of theirs) keeps the general path.  Same logits to fp32 rounding; new K and V
+    are fp32 sums within KERNEL_TOL of their scale (what two correct kernels may be apart), rounded to bf16: few values
+    differ, by one neighbour (2^-7 of the value) or, near zero, by that distance.  Past the first layer the distance is
+    that of the logits: a value that fell on the other neighbour there moves an attention output by up to 2^-8 / 16 of
+    the values' scale (16 positions in the shortest context), and the norm and the projections behind it by a few times that."""
+    c = make_case(m=m, batch=batch, seed=41, storage="bf16", gain_jitter=0.2)
+    g = gpu_setup(c, max_batch=batch * T)
+    b = B()
+    lens = c.seq_lens - T  # room for T new tokens in the pages that are there
+    sl = torch.from_numpy(lens.astype(np.int32)).cuda()
+    tok = torch.from_numpy(np.random.default_rng(3).integers(0, m["vocab"], (batch, T)).astype(np.int32)).cuda()
+    out = []
+    for mt in (0, 1):
+        print("few rows", m["name"], batch, T, "mt", mt, flush=True)
+        b.set_tuning("linear_mt", mt)
+        try:
+            lg = b.decode_step_multi(g.model, g.pool, g.block_table, sl, tok)
+        finally:
+            b.set_tuning("linear_mt", 0)
+        kv = [g.pool.gather(l, g.block_table[i], int(lens[i]) + T) for l in range(m["n_layers"]) for i in range(batch)]
+        out.append((lg.cpu().numpy().reshape(batch * T, -1), [x.float().cpu().numpy() for p in kv for x in p]))
+    (lg0, kv0), (lg1, kv1) = out
+    assert np.abs(lg0 - lg1).max() <= 2e-3 * lg1.std()
+    for j, (x, y) in enumerate(zip(kv0, kv1)):
+        tol = KERNEL_TOL if j < 2 * batch else 2e-3
+        assert np.all(np.abs(x - y) <= 2.0 ** -7 * np.abs(y) + tol * y.std())
+        assert np.mean(x != y) <= 0.02
 
 
 @pytest.mark.parametrize("m,T", [(I.TINY, 2), (I.TINY, 4), (I.TINY, 8), (I.TINY, 9), (I.TINY, 17), (G4_D128, 4), (G4_D128, 3),
