@@ -53,6 +53,43 @@ def test_append_gather_bit_exact(m, kind, batch):
         o += L
 
 
+@pytest.mark.parametrize("d,nkv", [(64, 1), (128, 8), (64, 3)])
+@pytest.mark.parametrize("order", ["in order", "offset runs", "shuffled", "unaligned"])
+def test_append_gather_any_order_and_alignment(d, nkv, order):
+    """Runs of four positions that start anywhere in the input, tokens without such a run, tokens in any order, and
+    rows that are not 16-byte aligned (element-wise kernels): every value lands in its slot and nowhere else."""
+    lens = [1, 7, 16, 35]
+    c = make_case(m=dict(I.TINY, n_layers=1, head_dim=d, n_kv_heads=nkv, n_q_heads=nkv, vocab=64, ffn=16), seed=15, storage="bf16", seq_lens=lens)
+    g = gpu_setup(c)
+    g.pool.memory.view(torch.int16).fill_(0x7FC0)
+    idx = np.arange(sum(lens))
+    if order == "offset runs":
+        idx = np.concatenate([idx[1:], idx[:1]])[:-2]  # two positions stay unwritten
+    elif order == "shuffled":
+        idx = np.random.default_rng(5).permutation(idx)
+    k, v = c.kv_t[0]
+    at = torch.from_numpy(idx)
+    kk, vv = k[at].cuda().contiguous(), v[at].cuda().contiguous()
+    if order == "unaligned":
+        kk, vv = (torch.cat([x.new_zeros(1), x.reshape(-1)])[1:].view(x.shape) for x in (kk, vv))
+        assert kk.data_ptr() % 16 and kk.is_contiguous()
+    print("append", d, nkv, order, flush=True)
+    g.pool.append(0, kk, vv, g.block_table, torch.from_numpy(c.seq_idx[idx]).cuda(), torch.from_numpy(c.pos[idx]).cuda())
+    wk, wv = np.full(k.shape, 0x7FC0, np.uint16), np.full(k.shape, 0x7FC0, np.uint16)
+    wk[idx], wv[idx] = bits(k)[idx], bits(v)[idx]
+    o = 0
+    for i, L in enumerate(lens):
+        n = int(I.pages_needed([L])[0]) * 16
+        gk, gv = g.pool.gather(0, g.block_table[i].contiguous(), n)
+        assert np.array_equal(bits(gk)[:L], wk[o:o + L]) and np.array_equal(bits(gv)[:L], wv[o:o + L])
+        assert np.all(bits(gk)[L:] == 0x7FC0) and np.all(bits(gv)[L:] == 0x7FC0)
+        b = B()
+        uk, uv = (torch.zeros(L * nkv * d + 3, dtype=torch.bfloat16, device="cuda")[1:1 + L * nkv * d] for _ in range(2))
+        b._check(b.load().chiron_gather_kv(g.pool._h, 0, b._ptr(g.block_table[i].contiguous()), L, b._ptr(uk), b._ptr(uv), b._stream()))
+        assert np.array_equal(bits(uk).reshape(L, nkv, d), wk[o:o + L]) and np.array_equal(bits(uv).reshape(L, nkv, d), wv[o:o + L])
+        o += L
+
+
 def test_append_overwrites_only_its_slot():
     c = make_case(batch=3, seed=12, storage="bf16")
     g = gpu_setup(c)
