@@ -56,7 +56,7 @@ int32_t attn_plan_args(const AttnWorkspace& ws, const int32_t* seq_lens, const i
     a.batch = batch;
     a.n_kv = n_kv;
     a.slots = slots;
-    a.target_waves = t.attn_target_waves > 0 ? t.attn_target_waves : 4 * slots;
+    a.target_waves = t.attn_target_waves > 0 ? t.attn_target_waves : slots;
     a.force_cp = t.attn_chunk_pages;
     a.item_limit = ws.cap_items / sh.tg;  // a partial result holds tg tokens' heads
     a.max_blocks = max_blocks;
@@ -103,7 +103,7 @@ __global__ __launch_bounds__(256, 2) void paged_attn_kernel(PoolDesc p, int laye
     // end of the list discards it).
     const int32_t* recs = plan + plan_rec_offset(max_batch);
     int w = blockIdx.x * 4 + wave;
-    int v_nx, pg0_nx, len_nx, b0_nx, b1_nx, b2_nx, b3_nx;
+    int v_nx, pg0_nx, len_nx, b0_nx, b1_nx, b2_nx, b3_nx, part_nx;
     auto fetch_rec = [&](int item) {
         const int32_t* r = recs + 8 * (size_t)min(item, cap_items - 1);
         v_nx = __builtin_amdgcn_readfirstlane(r[0]);
@@ -113,6 +113,7 @@ __global__ __launch_bounds__(256, 2) void paged_attn_kernel(PoolDesc p, int laye
         b1_nx = __builtin_amdgcn_readfirstlane(r[4]);
         b2_nx = __builtin_amdgcn_readfirstlane(r[5]);
         b3_nx = __builtin_amdgcn_readfirstlane(r[6]);
+        part_nx = __builtin_amdgcn_readfirstlane(r[7]);
     };
     fetch_rec(w / n_kv);
     const bool draw = n_work > n_waves;  // one round holds everything: no second item for anybody
@@ -120,8 +121,8 @@ __global__ __launch_bounds__(256, 2) void paged_attn_kernel(PoolDesc p, int laye
     const int nq = gridDim.x >= kTicketQueues ? kTicketQueues : 1, qj = blockIdx.x % nq;
     int32_t* ticket = tickets + qj * kTicketStride;
     while (w < n_work) {
-        const int it = w / n_kv, c = w - it * n_kv;
-        const int pg0 = pg0_nx, len = len_nx;
+        const int c = w % n_kv;
+        const int pg0 = pg0_nx, len = len_nx, part = part_nx;
         const int first_ids[4] = {b0_nx, b1_nx, b2_nx, b3_nx};
         const int i = MULTI ? v_nx / sh.ng : v_nx, g = MULTI ? v_nx - i * sh.ng : 0;
         const int tv = MULTI ? min(sh.tg, sh.q_len - g * sh.tg) : 1;  // tokens of this pass
@@ -273,7 +274,7 @@ __global__ __launch_bounds__(256, 2) void paged_attn_kernel(PoolDesc p, int laye
         l_run += __shfl_xor(l_run, 16);
         l_run += __shfl_xor(l_run, 32);
         if (head < cols) {
-            const size_t slot = (size_t)w * pcols + head;
+            const size_t slot = ((size_t)part * n_kv + c) * pcols + head;
             if (lg == 0) {
                 part_ml[slot * 2] = MULTI ? fmaxf(m_run, -1e30f) : m_run;
                 part_ml[slot * 2 + 1] = l_run;

@@ -8,19 +8,22 @@
 namespace chiron {
 
 // plan buffer layout (int32): [0] n_items, [1] chunk_pages, [2..3] unused,
-// [4, 4+max_batch) first item of pass v, [.., +max_batch) number of items of pass v.
-// A pass v = request * ng + token group (AttnShape).
-// Then, 32-byte aligned, one record of 8 ints per item: {pass, first page, attended length, the ids of the item's
-// first four pages (past its end: its last page), 0}: everything a wave needs before its first tile load, in one
-// scalar load instead of a chain of four dependent ones (the block table does not differ between layers).
+// [4, 4+max_batch) first partial result of pass v, [.., +max_batch) number of partial results of pass v (one per item, in
+// page order), [.., +max_batch) items placed before v's first, [.., +max_batch) place of v's last piece in the list if
+// that is no whole item.  A pass v = request * ng + token group (AttnShape).
+// Then, 32-byte aligned, one record of 8 ints per item, in the order in which items are taken: {pass, first
+// page, attended length, the ids of the item's first four pages (past its end: its last page), partial result}: everything a
+// wave needs before its first tile load, in one scalar load instead of a chain of four dependent ones (the block table does
+// not differ between layers).
 // After the records, kTicketQueues ticket counters kTicketStride ints apart, all 0 between attention launches.
-__host__ __device__ inline int64_t plan_rec_offset(int max_batch) { return (4 + 2 * (int64_t)max_batch + 7) / 8 * 8; }
+__host__ __device__ inline int64_t plan_rec_offset(int max_batch) { return (4 + 4 * (int64_t)max_batch + 7) / 8 * 8; }
 constexpr int kTicketQueues = 8, kTicketStride = 64;
 __host__ __device__ inline int64_t plan_ticket_offset(int max_batch, int cap_items) {
     return (plan_rec_offset(max_batch) + 8 * (int64_t)cap_items + kTicketStride - 1) / kTicketStride * kTicketStride;
 }
 
 constexpr int kPlanThreads = 1024;  // threads of the workgroup that runs attn_plan_block
+constexpr int kPlanMaxRound = 4096; // largest item, in pages, of a list that one round of the grid holds
 constexpr int kPlanCached = 2048;   // passes whose page counts and offsets are kept in LDS
 
 struct PlanArgs {
@@ -42,14 +45,16 @@ __device__ __forceinline__ int pass_len(const int32_t* __restrict__ seq_lens, co
 // item's request is found by bisection), not request by request: one long request is no serial loop of one thread.
 // Measured on the attention entry point: 664 -> 646 us at 32 requests of 28k tokens, where the serial loop took 28 us.
 __device__ __forceinline__ void attn_plan_block(const PlanArgs& a) {
-    __shared__ int s_np[kPlanCached], s_off[kPlanCached];
-    __shared__ int s_sum[2][kPlanThreads / 64];
+    __shared__ int s_np[kPlanCached], s_whole[kPlanCached], s_last[kPlanCached];
+    __shared__ int s_sum[2][kPlanThreads / 64], s_scan[4][kPlanThreads / 64];
     const AttnShape sh = a.sh;
     const int batch = a.batch * sh.ng;  // passes
     const int max_batch = a.max_batch, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     int32_t* plan = a.plan;
     int32_t* seq_item0 = plan + 4;
     int32_t* seq_nch = plan + 4 + max_batch;
+    int32_t* seq_whole = plan + 4 + 2 * max_batch;
+    int32_t* seq_last = plan + 4 + 3 * max_batch;
     if (tid < kTicketQueues) plan[plan_ticket_offset(max_batch, a.cap_items) + tid * kTicketStride] = 0;
     for (int v = tid; v < min(batch, kPlanCached); v += kPlanThreads) s_np[v] = (pass_len(a.seq_lens, sh, v) + kBlockSize - 1) / kBlockSize;
     __syncthreads();
@@ -77,72 +82,119 @@ __device__ __forceinline__ void attn_plan_block(const PlanArgs& a) {
     };
     const int total = count_items(1);
 
-    // Pages per item.  A wave takes items w, w + slots, ...: if the list is only a little longer than the number of
-    // wave slots, a few waves run a second item alone, at latency-bound speed, after everyone else has finished.
-    // So: when one round can hold everything, take the smallest item size that fits one round (all items stream
-    // concurrently); otherwise make the items small enough for at least four rounds, where a ragged last round
-    // costs little, but not so small that the per-item partial result weighs against the bytes the item reads.
-    int cp;
-    if ((int64_t)count_items(64) * a.n_kv <= a.slots) {
-        int lo = 2, hi = 64;
-        while (lo < hi) {  // uniform over the workgroup: every thread sees the same counts
+    // Pages per item.  Starting an item costs a wave a load latency or two, and an item that is left when the others have
+    // run out streams alone, at a fraction of the rate (about 15 GB/s a wave).  So: when one round of the grid can hold
+    // everything, take the smallest item size for which it does (all items stream concurrently, nothing is drawn), whatever
+    // that size is as long as it leaves no more than a quarter of the round empty (32 requests of 24k .. 32k tokens: 227
+    // pages 571 us, 32 pages in seven rounds 648 us; 96 requests of 2k tokens 187 against 214 us).  Otherwise items of
+    // 64 pages (with 128 / 250 requests of both classes 193 / 382 us, with 16 pages 206 / 392), fewer pages only while
+    // that does not fill one round.
+    int cp = 0;
+    bool drawn = true;  // whether waves draw further items after their first
+    const auto fits = [&](int c) { return (int64_t)count_items(c) * a.n_kv <= a.slots; };  // uniform: every thread sees the same counts
+    // the largest item that leaves no more than a quarter of the round's page slots empty
+    const int full = (int)min((int64_t)kPlanMaxRound, (int64_t)total * a.n_kv * 4 / ((int64_t)a.slots * 3));
+    const bool small = fits(64);
+    if (small || (full > 64 && fits(full))) {
+        int lo = small ? 2 : (int)max((int64_t)65, (int64_t)total * a.n_kv / a.slots), hi = small ? 64 : full;
+        while (lo < hi) {
             const int mid = (lo + hi) / 2;
-            if ((int64_t)count_items(mid) * a.n_kv <= a.slots) hi = mid;
+            if (fits(mid)) hi = mid;
             else lo = mid + 1;
         }
         cp = lo;
+        drawn = false;
     } else {
         cp = 64;
         while (cp > 8 && (int64_t)(total / cp) * a.n_kv < a.target_waves) cp >>= 1;
     }
+    const int cp_rule = cp;
     while (cp < (1 << 24) && total / cp + batch > a.item_limit) cp <<= 1;  // the host has checked that batch < item_limit
     if (a.force_cp > 0 && total / a.force_cp + batch <= a.item_limit) cp = a.force_cp;
+    drawn = drawn || cp != cp_rule;
 
-    // exclusive scan of items per request
-    int items = 0;
-    for (int i = i0; i < i1; ++i) items += (pages_of(i) + cp - 1) / cp;
-    int scan = items;
-#pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-        const int v = __shfl_up(scan, o);
-        if (lane >= o) scan += v;
-    }
-    if (lane == 63) s_sum[turn][wave] = scan;
-    __syncthreads();
-    int off = scan - items, n_items = 0;
-#pragma unroll
-    for (int k = 0; k < kPlanThreads / 64; ++k) {
-        if (k < wave) off += s_sum[turn][k];
-        n_items += s_sum[turn][k];
-    }
+    // The items in the order in which waves draw them: whole ones (cp pages) first, then the requests' last pieces of at
+    // least half that, then the rest, so that what is drawn last is short (512 / 300 / 250 requests of both classes:
+    // 744 -> 727, 464 -> 442, 379 -> 358 us).  In a single round nothing is drawn, and request order, which mixes long and
+    // short items on a CU, is 2 us faster at 64 requests.
+    // Exclusive scans over the requests of the numbers of items and, if drawn, of whole items, long and short last pieces.
+    auto last_piece = [&](int np) { return np % cp; };
+    int cnt[4] = {0, 0, 0, 0}, off[4], total4[4] = {0, 0, 0, 0};
     for (int i = i0; i < i1; ++i) {
-        const int nch = (pages_of(i) + cp - 1) / cp;
-        if (i < kPlanCached) s_off[i] = off;
-        seq_item0[i] = off;
+        const int np = pages_of(i), r = last_piece(np);
+        cnt[0] += (np + cp - 1) / cp;
+        if (!drawn) continue;
+        cnt[1] += np / cp;
+        cnt[2] += r > 0 && 2 * r >= cp;
+        cnt[3] += r > 0 && 2 * r < cp;
+    }
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+        if (c > 0 && !drawn) break;
+        int scan = cnt[c];
+#pragma unroll
+        for (int o = 1; o < 64; o <<= 1) {
+            const int v = __shfl_up(scan, o);
+            if (lane >= o) scan += v;
+        }
+        if (lane == 63) s_scan[c][wave] = scan;
+        off[c] = scan - cnt[c];
+    }
+    __syncthreads();
+#pragma unroll
+    for (int c = 0; c < 4; ++c)
+#pragma unroll
+        for (int k = 0; k < kPlanThreads / 64; ++k) {
+            if (c > 0 && !drawn) break;
+            if (k < wave) off[c] += s_scan[c][k];
+            total4[c] += s_scan[c][k];
+        }
+    const int n_whole = drawn ? total4[1] : total4[0];  // items placed by bisection: whole ones, or all in request order
+    int4* recs = reinterpret_cast<int4*>(plan + plan_rec_offset(max_batch));
+    auto put = [&](int it, int v, int ch, int partial) {  // the record of chunk ch of pass v
+        const int pg0 = ch * cp, last = min(pg0 + cp, pages_of(v)) - 1;
+        const int32_t* btrow = a.bt + (size_t)(v / sh.ng) * a.max_blocks;
+        const int b0 = btrow[pg0], b1 = btrow[min(pg0 + 1, last)], b2 = btrow[min(pg0 + 2, last)], b3 = btrow[min(pg0 + 3, last)];
+        recs[2 * it] = make_int4(v, pg0, pass_len(a.seq_lens, sh, v), b0);
+        recs[2 * it + 1] = make_int4(b1, b2, b3, partial);
+    };
+    off[2] += n_whole;
+    off[3] += n_whole + total4[2];
+    for (int i = i0; i < i1; ++i) {
+        const int np = pages_of(i), nch = (np + cp - 1) / cp, r = last_piece(np), before = drawn ? off[1] : off[0];
+        if (i < kPlanCached) s_whole[i] = before;
+        seq_whole[i] = before;
+        seq_item0[i] = off[0];
         seq_nch[i] = nch;
-        off += nch;
+        if (drawn) {
+            const int place = r == 0 ? -1 : (2 * r >= cp ? off[2]++ : off[3]++);
+            if (i < kPlanCached) s_last[i] = place;
+            seq_last[i] = place;
+        }
+        off[0] += nch;
+        if (drawn) off[1] += np / cp;
     }
     if (tid == 0) {
-        plan[0] = n_items;
+        plan[0] = total4[0];
         plan[1] = cp;
     }
-    __syncthreads();  // (also orders the offsets past kPlanCached, which this workgroup reads back from global memory)
-
-    int4* recs = reinterpret_cast<int4*>(plan + plan_rec_offset(max_batch));
-    for (int it = tid; it < n_items; it += kPlanThreads) {
-        int lo = 0, hi = batch - 1;  // the last pass whose first item is not past `it`
+    __syncthreads();  // (also orders what this workgroup reads back from global memory)
+    for (int u = tid; u < n_whole + (drawn ? batch : 0); u += kPlanThreads) {
+        if (u >= n_whole) {  // a last piece
+            const int v = u - n_whole, place = v < kPlanCached ? s_last[v] : seq_last[v];
+            if (place >= 0) put(place, v, pages_of(v) / cp, seq_item0[v] + pages_of(v) / cp);
+            continue;
+        }
+        const int it = u;
+        int lo = 0, hi = batch - 1;  // the last pass with no more than `it` of these items before it
         while (lo < hi) {
             const int mid = (lo + hi + 1) / 2;
-            const int first = mid < kPlanCached ? s_off[mid] : seq_item0[mid];
-            if (first <= it) lo = mid;
+            const int before = mid < kPlanCached ? s_whole[mid] : seq_whole[mid];
+            if (before <= it) lo = mid;
             else hi = mid - 1;
         }
-        const int pg0 = (it - (lo < kPlanCached ? s_off[lo] : seq_item0[lo])) * cp;
-        const int last = min(pg0 + cp, pages_of(lo)) - 1;
-        const int32_t* btrow = a.bt + (size_t)(lo / sh.ng) * a.max_blocks;
-        const int b0 = btrow[pg0], b1 = btrow[min(pg0 + 1, last)], b2 = btrow[min(pg0 + 2, last)], b3 = btrow[min(pg0 + 3, last)];
-        recs[2 * it] = make_int4(lo, pg0, pass_len(a.seq_lens, sh, lo), b0);
-        recs[2 * it + 1] = make_int4(b1, b2, b3, 0);
+        const int ch = it - (lo < kPlanCached ? s_whole[lo] : seq_whole[lo]);
+        put(it, lo, ch, drawn ? seq_item0[lo] + ch : it);
     }
 }
 

@@ -100,7 +100,7 @@ struct Tuning {
     int linear_ks = 0;              // k-steps of 16 per chunk (depth of the weight ring): 4, 8 or 16
     int linear_big_all = 0;         // 1: pre-split every projection's input from that row count on, not only the down projection's
     int attn_grid = 0;              // workgroups of the persistent attention grid
-    int attn_target_waves = 0;      // work items aimed for when one round of the grid cannot hold the list (0 = 4 rounds)
+    int attn_target_waves = 0;      // work items aimed for when one round of the grid cannot hold the list (0 = one per wave)
     int attn_chunk_pages = 0;       // forced pages per item
 };
 Tuning& tuning();
