@@ -560,6 +560,62 @@ int32_t chiron_op_rmsnorm(const float* h, const void* gain, int32_t rows, int32_
     return launch_rmsnorm(const_cast<float*>(h), nullptr, 0, (const uint16_t*)gain, rows, n, eps, out, (hipStream_t)stream);
 }
 
+// Scratch memory of the single-projection entry points.  From the default pool every call after a synchronisation
+// pays for fresh memory (0.1 .. 0.7 ms), because that pool gives everything back at once.  This one, per device, keeps
+// up to kScratchKeep bytes while a chiron_linear of the device exists; the last one's destruction gives them back.  The runtime
+// orders reuse by stream, so threads and streams need nothing more.
+static constexpr uint64_t kScratchKeep = (uint64_t)1 << 30;
+static constexpr int kScratchDevices = 64;
+static struct {
+    hipMemPool_t pool;
+    int users;
+} g_scratch_pool[kScratchDevices];
+static std::mutex g_scratch_pool_mutex;
+
+// the device whose pool a new chiron_linear keeps, or -1 if there is none (its calls then use the default pool)
+static int scratch_pool_enter() {
+    int dev = -1;
+    if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= kScratchDevices) return -1;
+    std::lock_guard<std::mutex> lock(g_scratch_pool_mutex);
+    auto& g = g_scratch_pool[dev];
+    if (!g.pool) {
+        hipMemPoolProps props = {};
+        props.allocType = hipMemAllocationTypePinned;
+        props.location.type = hipMemLocationTypeDevice;
+        props.location.id = dev;
+        hipMemPool_t pool = nullptr;
+        uint64_t keep = kScratchKeep;
+        if (hipMemPoolCreate(&pool, &props) != hipSuccess || hipMemPoolSetAttribute(pool, hipMemPoolAttrReleaseThreshold, &keep) != hipSuccess) {
+            (void)hipGetLastError();
+            if (pool) (void)hipMemPoolDestroy(pool);
+            return -1;
+        }
+        g.pool = pool;
+    }
+    ++g.users;
+    return dev;
+}
+
+static void scratch_pool_leave(int dev) {
+    if (dev < 0) return;
+    std::lock_guard<std::mutex> lock(g_scratch_pool_mutex);
+    auto& g = g_scratch_pool[dev];
+    if (--g.users == 0) (void)hipMemPoolTrimTo(g.pool, 0);
+}
+
+static int32_t scratch_alloc(int dev, void** out, size_t bytes, hipStream_t st) {
+    *out = nullptr;
+    if (bytes == 0) return CHIRON_OK;
+    // (a stream that is being captured, or one of another device, takes the default pool as any allocation does)
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusActive;
+    int cur = -1;
+    if (dev >= 0 && hipGetDevice(&cur) == hipSuccess && cur == dev && hipStreamIsCapturing(st, &cap) == hipSuccess && cap == hipStreamCaptureStatusNone)
+        CHIRON_HIP(hipMallocFromPoolAsync(out, bytes, g_scratch_pool[dev].pool, st));
+    else
+        CHIRON_HIP(hipMallocAsync(out, bytes, st));
+    return CHIRON_OK;
+}
+
 int32_t chiron_linear_create(const void* w, int32_t N, int32_t K, void* stream, chiron_linear** out) {
     if (!out) return fail(CHIRON_ERR_INVALID_ARG, "out is null");
     *out = nullptr;
@@ -574,6 +630,7 @@ int32_t chiron_linear_create(const void* w, int32_t N, int32_t K, void* stream, 
         delete l;
         return rc;
     }
+    l->device = scratch_pool_enter();
     *out = l;
     return CHIRON_OK;
 }
@@ -594,6 +651,7 @@ int32_t chiron_linear_create_gate_up(const void* w_gate, const void* w_up, int32
         delete l;
         return rc;
     }
+    l->device = scratch_pool_enter();
     *out = l;
     return CHIRON_OK;
 }
@@ -601,30 +659,43 @@ int32_t chiron_linear_create_gate_up(const void* w_gate, const void* w_up, int32
 int32_t chiron_linear_destroy(chiron_linear* l) {
     if (l) {
         linear_free(l->L);
+        scratch_pool_leave(l->device);
         delete l;
     }
     return CHIRON_OK;
 }
 
 // the projection as the decode step launches it (K sliced into a workspace when the grid would otherwise be
-// too small), followed by the plain sum of the slices that the step's consumers do on the fly
-static int32_t op_linear_common(const Linear& L, const float* x, int lda, int M, float* y, int accumulate, int prologue,
-                                hipStream_t st) {
-    // few rows: one launch that needs no workspace (very wide outputs have enough column tiles for the tiled kernel)
-    if (prologue == PRO_NONE && linear_few_rows(M) && L.N <= 16384) return launch_linear_few(L, x, lda, M, 0, y, L.N, accumulate, st);
-    float* part = nullptr;
-    const int msplit = linear_max_split();
+// too small), followed by the plain sum of the slices that the step's consumers do on the fly.
+// part: op_linear_scratch() bytes (16-byte aligned) of it hold the slices and, behind them, the split input.
+struct OpScratch {
+    size_t part_bytes = 0, split_bytes = 0;
+    int max_split = 1;
+    size_t bytes() const { return part_bytes + split_bytes; }
+};
+static OpScratch op_linear_scratch(const Linear& L, int M, int prologue) {
+    OpScratch sc;
+    if (prologue == PRO_NONE && linear_few_rows(M) && L.N <= 16384) return sc;  // the few-row path needs none
+    const bool split = prologue == PRO_NONE && tuning().linear_big_all && M >= linear_big_min_rows(L);
+    if (split) sc.split_bytes = 2 * linear_big_split_elems(M, L.Kpad) * 2;
     // wide outputs (LM head, gate/up) have enough column tiles on their own and are never sliced in the step
-    const bool may_split = L.N <= 16384;
-    if (may_split) CHIRON_HIP(hipMallocAsync((void**)&part, (size_t)msplit * M * L.N * sizeof(float), st));
-    uint16_t* asplit = nullptr;
-    if (prologue == PRO_NONE && tuning().linear_big_all && M >= linear_big_min_rows(L))
-        CHIRON_HIP(hipMallocAsync((void**)&asplit, 2 * linear_big_split_elems(M, L.Kpad) * 2, st));
+    if (L.N <= 16384) {
+        sc.max_split = linear_max_split();
+        const int ks = linear_slices(L, M, split ? PRO_PACKED : prologue, sc.max_split);
+        if (ks > 1) sc.part_bytes = ((size_t)ks * M * L.N * sizeof(float) + 255) / 256 * 256;
+    }
+    return sc;
+}
+
+static int32_t op_linear_common(const Linear& L, const float* x, int lda, int M, float* y, int accumulate, int prologue,
+                                const OpScratch& sc, void* scratch, hipStream_t st) {
+    // few rows: one launch (very wide outputs have enough column tiles for the tiled kernel)
+    if (prologue == PRO_NONE && linear_few_rows(M) && L.N <= 16384) return launch_linear_few(L, x, lda, M, 0, y, L.N, accumulate, st);
+    float* part = sc.part_bytes ? (float*)scratch : nullptr;
+    uint16_t* asplit = sc.split_bytes ? (uint16_t*)((char*)scratch + sc.part_bytes) : nullptr;
     int ks = 1;
-    int32_t rc = launch_linear(L, x, lda, M, y, L.N, accumulate ? EPI_ADD : EPI_STORE, prologue, part, msplit, &ks, asplit, st);
-    if (asplit) (void)hipFreeAsync(asplit, st);
+    int32_t rc = launch_linear(L, x, lda, M, y, L.N, accumulate ? EPI_ADD : EPI_STORE, prologue, part, sc.max_split, &ks, asplit, st);
     if (!rc && ks > 1) rc = launch_reduce_partials(part, ks, (int64_t)M * L.N, y, accumulate, st);
-    if (part) (void)hipFreeAsync(part, st);
     return rc;
 }
 
@@ -634,7 +705,14 @@ int32_t chiron_op_linear(const chiron_linear* l, const float* x, int32_t M, floa
     if (M == 0) return CHIRON_OK;
     if (!x || !y) return fail(CHIRON_ERR_INVALID_ARG, "linear: a pointer is null");
     if (l->gate_up) return fail(CHIRON_ERR_INVALID_ARG, "linear: a fused gate/up matrix goes with the SwiGLU entry points only");
-    return op_linear_common(l->L, x, l->L.K, M, y, accumulate, PRO_NONE, (hipStream_t)stream);
+    hipStream_t st = (hipStream_t)stream;
+    const OpScratch sc = op_linear_scratch(l->L, M, PRO_NONE);
+    void* scratch = nullptr;
+    int32_t rc = scratch_alloc(l->device, &scratch, sc.bytes(), st);
+    if (rc) return rc;
+    rc = op_linear_common(l->L, x, l->L.K, M, y, accumulate, PRO_NONE, sc, scratch, st);
+    if (scratch) (void)hipFreeAsync(scratch, st);
+    return rc;
 }
 
 int32_t chiron_op_gate_up_swiglu(const chiron_linear* gate_up, const float* x, int32_t M, float* act, void* stream) {
@@ -661,20 +739,23 @@ int32_t chiron_op_swiglu_ffn(const chiron_linear* gate_up, const chiron_linear* 
     // the intermediate in the form the decode step gives it at this row count
     const bool few = linear_few_rows(M) && D.N <= 16384;
     const bool packed = !few && M >= linear_big_min_rows(D);
-    const size_t bytes = packed ? 2 * linear_big_split_elems(M, D.Kpad) * 2 : (size_t)M * D.Kpad * 4;
-    void* act = nullptr;
-    CHIRON_HIP(hipMallocAsync(&act, bytes, st));
-    int32_t rc = CHIRON_OK;
+    const size_t bytes = ((packed ? 2 * linear_big_split_elems(M, D.Kpad) * 2 : (size_t)M * D.Kpad * 4) + 255) / 256 * 256;
+    const OpScratch sc = few ? OpScratch() : op_linear_scratch(D, M, packed ? PRO_PACKED : PRO_NONE);
+    void* act = nullptr;  // the intermediate, then the down projection's scratch
+    int32_t rc = scratch_alloc(gate_up->device, &act, bytes + sc.bytes(), st);
+    if (rc) return rc;
+    void* scratch = (char*)act + bytes;
     if (few) {
         rc = launch_linear(G, x, G.K, M, (float*)act, D.Kpad, EPI_SWIGLU_FEW, PRO_NONE, nullptr, 1, nullptr, nullptr, st);
         if (!rc) rc = launch_linear_few(D, (const float*)act, (int64_t)M * (D.Kpad / 8), M, 1, y, D.N, accumulate, st);
     } else if (packed) {
-        if (hipMemsetAsync(act, 0, bytes, st) != hipSuccess) rc = fail(CHIRON_ERR_HIP, "clearing the activation workspace failed");
+        // the epilogue writes the columns below F only: the padding of K must not hold NaN bits when the down projection reads it
+        if (D.Kpad != F && hipMemsetAsync(act, 0, bytes, st) != hipSuccess) rc = fail(CHIRON_ERR_HIP, "clearing the activation workspace failed");
         if (!rc) rc = launch_linear(G, x, G.K, M, (float*)act, D.Kpad, EPI_SWIGLU_PACKED, PRO_NONE, nullptr, 1, nullptr, nullptr, st);
-        if (!rc) rc = op_linear_common(D, (const float*)act, 0, M, y, accumulate, PRO_PACKED, st);
+        if (!rc) rc = op_linear_common(D, (const float*)act, 0, M, y, accumulate, PRO_PACKED, sc, scratch, st);
     } else {
         rc = launch_linear(G, x, G.K, M, (float*)act, F, EPI_SWIGLU, PRO_NONE, nullptr, 1, nullptr, nullptr, st);
-        if (!rc) rc = op_linear_common(D, (const float*)act, F, M, y, accumulate, PRO_NONE, st);
+        if (!rc) rc = op_linear_common(D, (const float*)act, F, M, y, accumulate, PRO_NONE, sc, scratch, st);
     }
     (void)hipFreeAsync(act, st);
     return rc;

@@ -107,7 +107,7 @@ Tuning& tuning();
 
 // C[M,N] = A[M,K] * W^T.  A is fp32 with row stride lda (PRO_NONE), or the tiled bf16 terms of it (PRO_PACKED: hi terms
 // at A, lo terms linear_big_split_elems(M, L.Kpad) bf16 values further).
-// If the launch slices K (only when `part` is given; at most max_split slices), slice s stores its partial product
+// If the launch slices K (only if max_split > 1, and at most that many slices; `part` may be null if linear_slices says 1), slice s stores its partial product
 // at part[s][M][N] and *ksplit_out = number of slices: the caller's consumer adds them up.  Otherwise the result
 // goes to y as `epilogue` (EPI_STORE, EPI_ADD, or a SwiGLU epilogue, which never slices) says and *ksplit_out = 1.
 // `norm` (unsliced launches of at most 16 rows only): the input is rmsnorm(A) * gain.
@@ -121,6 +121,8 @@ int32_t launch_linear_big(const Linear& L, const float* A, int lda, int M, float
 size_t linear_big_split_elems(int M, int Kpad);
 int linear_big_min_rows(const Linear& L);
 int linear_max_split();
+// number of K-slices launch_linear takes for M rows when it is given a workspace of max_split slices
+int linear_slices(const Linear& L, int M, int prologue, int max_split);
 int32_t launch_reduce_partials(const float* part, int ks, int64_t n, float* y, int accumulate, hipStream_t st);
 // interleave: 0 = source row r becomes packed row row_offset + r; 1 / 2 = the source is the gate / up half of a fused
 // gate/up matrix, whose 32-row tiles hold 16 gate and the 16 up columns of the same indices (rows % 16 == 0);
@@ -220,6 +222,7 @@ int32_t launch_attn_merge(const AttnWorkspace& ws, const PoolDesc& p, int n_q, c
 
 struct chiron_linear {
     chiron::Linear L;
+    int device = -1;       // whose scratch pool it keeps alive (see api.hip), -1: none
     bool gate_up = false;  // rows are the interleaved [gate | up] of a feed-forward block
 };
 

@@ -495,7 +495,34 @@ __global__ __launch_bounds__(256) void reduce_partials_kernel(const float* __res
     }
 }
 
+// the same, 16 bytes a thread and four slices' loads in flight (100 x 8192 from 8 slices 12.8 -> 9.5 us, bounded by memory)
+__global__ __launch_bounds__(256) void reduce_partials_vec_kernel(const float4* __restrict__ part, int ks, size_t stride4,
+                                                                  int64_t n4, float4* __restrict__ y, int accumulate) {
+    for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n4; i += (int64_t)gridDim.x * 256) {
+        float4 v = accumulate ? y[i] : make_float4(0.f, 0.f, 0.f, 0.f);
+        auto add = [&](const float4& t) { v.x += t.x; v.y += t.y; v.z += t.z; v.w += t.w; };
+        int s = 0;
+        for (; s + 4 <= ks; s += 4) {
+            float4 t[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) t[u] = part[(size_t)(s + u) * stride4 + i];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) add(t[u]);
+        }
+        for (; s < ks; ++s) add(part[(size_t)s * stride4 + i]);
+        y[i] = v;
+    }
+}
+
 int32_t launch_reduce_partials(const float* part, int ks, int64_t n, float* y, int accumulate, hipStream_t st) {
+    if (n % 4 == 0 && (((uintptr_t)part | (uintptr_t)y) & 15) == 0) {
+        const int64_t n4 = n / 4;
+        const int blocks = (int)((n4 + 255) / 256 < 8192 ? (n4 + 255) / 256 : 8192);
+        launch(reduce_partials_vec_kernel, dim3(blocks), dim3(256), st, reinterpret_cast<const float4*>(part), ks, (size_t)n4, n4,
+               reinterpret_cast<float4*>(y), accumulate);
+        CHIRON_HIP(hipGetLastError());
+        return CHIRON_OK;
+    }
     int blocks = (int)((n + 255) / 256 < 4096 ? (n + 255) / 256 : 4096);
     launch(reduce_partials_kernel, dim3(blocks), dim3(256), st, part, ks, (size_t)n, n, y, accumulate);
     CHIRON_HIP(hipGetLastError());
@@ -528,26 +555,12 @@ int linear_big_min_rows(const Linear& L) {
     return v == 0 ? big_min_rows_default(L) : (v < 0 ? INT32_MAX : v);
 }
 
-int32_t launch_linear(const Linear& L, const float* A, int lda, int M, float* y, int ldy, int epilogue, int prologue,
-                      float* part, int max_split, int* ksplit_out, uint16_t* asplit, hipStream_t st, const NormIn* norm) {
-    if (ksplit_out) *ksplit_out = 1;
-    if (M == 0) return CHIRON_OK;
-    if (norm && (part || prologue != PRO_NONE || !linear_few_rows(M)))
-        return fail(CHIRON_ERR_INVALID_ARG, "linear: a norm in the operand load needs an unsliced launch of few rows");
-    if (epilogue != EPI_STORE && epilogue != EPI_ADD && epilogue != EPI_SWIGLU && epilogue != EPI_SWIGLU_PACKED && epilogue != EPI_SWIGLU_FEW)
-        return fail(CHIRON_ERR_INVALID_ARG, "linear: unknown epilogue %d", epilogue);
-    if (epilogue >= EPI_SWIGLU) {
-        // gate and up of one column must meet in one workgroup with the whole sum over K
-        if (part) return fail(CHIRON_ERR_INVALID_ARG, "linear: the SwiGLU epilogue cannot slice K");
-        if (L.N % 32 != 0) return fail(CHIRON_ERR_SHAPE, "linear: a fused gate/up matrix has a multiple of 32 rows (got %d)", L.N);
-        if (ldy % (epilogue == EPI_SWIGLU ? 4 : 8) != 0 || ((uintptr_t)y & 15))
-            return fail(CHIRON_ERR_INVALID_ARG, "linear: SwiGLU output rows must be 16-byte aligned");
-    }
-    if (asplit && prologue != PRO_PACKED && M >= linear_big_min_rows(L) && tuning().linear_big_all)
-        return launch_linear_big(L, A, lda, M, y, ldy, epilogue, part, max_split, ksplit_out, asplit, st);
-    if (L.K % 16 != 0 || L.K < 16) return fail(CHIRON_ERR_SHAPE, "linear: K=%d must be a positive multiple of 16", L.K);
-    if (prologue != PRO_PACKED && (lda % 4 != 0 || ((uintptr_t)A & 15)))
-        return fail(CHIRON_ERR_INVALID_ARG, "linear: input rows must be 16-byte aligned");
+// the launch shape of a tiled projection: rows / 32 and column tiles per wave, k-steps per chunk, workgroups along N and M, K-slices and
+// chunks per slice
+struct LinearShape {
+    int mt, nf, ks, gx, gz, ksplit, cps;
+};
+static LinearShape linear_shape(const Linear& L, int M, bool sliceable, int prologue, int max_split) {
     const Tuning& tn = tuning();
     // Tile shape.  Up to 64 rows the kernel is HBM-bound: 32- or 64-row tiles; one column tile per wave when K can
     // be sliced (twice the workgroups along N, so half the K-slices for the consumer to add up) or when that is
@@ -578,7 +591,7 @@ int32_t launch_linear(const Linear& L, const float* A, int lda, int M, float* y,
     if (tn.linear_nf) nf = tn.linear_nf;
     else if (big && tiles >= 256) nf = 4;
     else if (tiles < 64) nf = 1;
-    else if (!part) {
+    else if (!sliceable) {
         const int max_nf = mt == 3 ? 2 : 4;
         nf = 1;
         while (nf < max_nf && ((tiles + 4 * nf - 1) / (4 * nf)) * gz > kNumCU) nf *= 2;
@@ -601,7 +614,7 @@ int32_t launch_linear(const Linear& L, const float* A, int lda, int M, float* y,
         // four column tiles per wave unless K-slicing cannot make up for the smaller grid (one 128-row tile of a
         // 4096-wide output: 8 workgroup columns x 16 slices = half the chip; 58 against 45 us)
         const int gx4 = (tiles + 15) / 16, gz4 = (M + 127) / 128;
-        const bool fills = !part || (int64_t)gx4 * gz4 * max_split >= 200;
+        const bool fills = !sliceable || (int64_t)gx4 * gz4 * max_split >= 200;
         nf = tn.linear_nf ? (tn.linear_nf == 4 ? 4 : 2) : (tiles >= 128 && fills ? 4 : 2);
     }
     if (nf == 4 && mt == 1) mt = 2;
@@ -610,7 +623,7 @@ int32_t launch_linear(const Linear& L, const float* A, int lda, int M, float* y,
     int gx = (tiles + 4 * nf - 1) / (4 * nf);
     // an unsliced projection whose 64-row tiles give a few workgroups more than two per CU takes 96-row tiles if those
     // fit (gate/up at 289..320 rows: 560 workgroups 190 us, 448 workgroups 167 us)
-    if (!tn.linear_mt && !part && mt == 2 && prologue == PRO_NONE && nf <= 2 && gx * gz > 2 * kNumCU && gx * gz <= 3 * kNumCU &&
+    if (!tn.linear_mt && !sliceable && mt == 2 && prologue == PRO_NONE && nf <= 2 && gx * gz > 2 * kNumCU && gx * gz <= 3 * kNumCU &&
         gx * ((M + 95) / 96) <= 2 * kNumCU) {
         mt = 3;
         gz = (M + 95) / 96;
@@ -618,12 +631,12 @@ int32_t launch_linear(const Linear& L, const float* A, int lda, int M, float* y,
     // A projection that cannot slice K (no workspace) runs one workgroup per CU; a ring of 8 k-steps then keeps twice
     // the weight bytes in flight per wave, which measured 9 % faster on the gate/up shape at 64 rows.
     const bool ks8 = (mt == 2 || (mt == 3 && nf == 1)) && nf <= 2 && prologue != PRO_PACKED &&
-                     (tn.linear_ks == 8 || (tn.linear_ks == 0 && nf == 1 && !part && prologue == PRO_NONE));
+                     (tn.linear_ks == 8 || (tn.linear_ks == 0 && nf == 1 && !sliceable && prologue == PRO_NONE));
     // Up to 32 rows a wave has two MFMAs per k-step and its weight stream is bound by the bytes it keeps in flight over
     // the load latency: the unsliced one-tile-per-wave shape takes a ring of 16 k-steps (16 KiB per wave; measured on the
     // 8B gate/up shape: 37.3 against 40.0 us at one row, 39.8 against 41.4 us at 32 rows; no gain at 64 rows)
     const bool ks16 = mt == 1 && nf == 1 && prologue == PRO_NONE && L.Kpad % 256 == 0 &&
-                      (tn.linear_ks == 16 || (tn.linear_ks == 0 && !part));
+                      (tn.linear_ks == 16 || (tn.linear_ks == 0 && !sliceable));
     const int KC = ks16 ? 256 : (ks8 ? 128 : 64);
     int chunks = (L.K + KC - 1) / KC;
     int ksplit = tn.linear_ksplit ? tn.linear_ksplit : (tn.linear_target_blocks + gx * gz - 1) / (gx * gz);
@@ -640,10 +653,39 @@ int32_t launch_linear(const Linear& L, const float* A, int lda, int M, float* y,
     }
     if (ksplit > chunks / 2) ksplit = chunks / 2;
     if (ksplit > max_split) ksplit = max_split;
-    if (!part) ksplit = 1;
+    if (!sliceable) ksplit = 1;
     if (ksplit < 1) ksplit = 1;
     int cps = (chunks + ksplit - 1) / ksplit;
     ksplit = (chunks + cps - 1) / cps;  // no empty slices
+    return LinearShape{mt, nf, ks16 ? 16 : (ks8 ? 8 : 4), gx, gz, ksplit, cps};
+}
+
+int linear_slices(const Linear& L, int M, int prologue, int max_split) { return M > 0 ? linear_shape(L, M, true, prologue, max_split).ksplit : 1; }
+
+int32_t launch_linear(const Linear& L, const float* A, int lda, int M, float* y, int ldy, int epilogue, int prologue,
+                      float* part, int max_split, int* ksplit_out, uint16_t* asplit, hipStream_t st, const NormIn* norm) {
+    if (ksplit_out) *ksplit_out = 1;
+    if (M == 0) return CHIRON_OK;
+    if (norm && (max_split > 1 || prologue != PRO_NONE || !linear_few_rows(M)))
+        return fail(CHIRON_ERR_INVALID_ARG, "linear: a norm in the operand load needs an unsliced launch of few rows");
+    if (epilogue != EPI_STORE && epilogue != EPI_ADD && epilogue != EPI_SWIGLU && epilogue != EPI_SWIGLU_PACKED && epilogue != EPI_SWIGLU_FEW)
+        return fail(CHIRON_ERR_INVALID_ARG, "linear: unknown epilogue %d", epilogue);
+    if (epilogue >= EPI_SWIGLU) {
+        // gate and up of one column must meet in one workgroup with the whole sum over K
+        if (max_split > 1) return fail(CHIRON_ERR_INVALID_ARG, "linear: the SwiGLU epilogue cannot slice K");
+        if (L.N % 32 != 0) return fail(CHIRON_ERR_SHAPE, "linear: a fused gate/up matrix has a multiple of 32 rows (got %d)", L.N);
+        if (ldy % (epilogue == EPI_SWIGLU ? 4 : 8) != 0 || ((uintptr_t)y & 15))
+            return fail(CHIRON_ERR_INVALID_ARG, "linear: SwiGLU output rows must be 16-byte aligned");
+    }
+    if (asplit && prologue != PRO_PACKED && M >= linear_big_min_rows(L) && tuning().linear_big_all)
+        return launch_linear_big(L, A, lda, M, y, ldy, epilogue, part, max_split, ksplit_out, asplit, st);
+    if (L.K % 16 != 0 || L.K < 16) return fail(CHIRON_ERR_SHAPE, "linear: K=%d must be a positive multiple of 16", L.K);
+    if (prologue != PRO_PACKED && (lda % 4 != 0 || ((uintptr_t)A & 15)))
+        return fail(CHIRON_ERR_INVALID_ARG, "linear: input rows must be 16-byte aligned");
+    const LinearShape shape = linear_shape(L, M, max_split > 1, prologue, max_split);
+    const int mt = shape.mt, nf = shape.nf, gx = shape.gx, gz = shape.gz, ksplit = shape.ksplit, cps = shape.cps;
+    const bool ks8 = shape.ks == 8, ks16 = shape.ks == 16;
+    if (ksplit > 1 && !part) return fail(CHIRON_ERR_INVALID_ARG, "linear: no workspace for %d K-slices", ksplit);
     int mode = ksplit > 1 ? EPI_SLICES : epilogue;
     float* dst = ksplit > 1 ? part : y;
     int ldd = ksplit > 1 ? L.N : ldy;

@@ -357,6 +357,55 @@ def test_paged_attention(d, nq, nkv, lens):
         assert np.abs(got - want).max() <= KERNEL_TOL * max(1.0, np.abs(want).max())
 
 
+@pytest.mark.parametrize("d,nq,nkv,batch", [(64, 4, 2, 514), (128, 12, 3, 350), (128, 16, 1, 1030)])
+def test_paged_attention_merge_of_many_rows(d, nq, nkv, batch):
+    """With passes x KV heads above half a round of the grid a lane group per head folds all items of a row, four at a
+    time: one to ten items of one page, and head counts that leave the last workgroup of a row partly empty."""
+    lens = (1 + (np.arange(batch) * 37) % 157).astype(np.int32)
+    c = make_case(m=dict(I.TINY, n_layers=1, head_dim=d, n_q_heads=nq, n_kv_heads=nkv, vocab=64, ffn=16), seed=19, storage="bf16", seq_lens=lens)
+    g = gpu_setup(c)
+    opool = fresh_pool(c)
+    q = (np.random.default_rng(20).standard_normal((batch, nq * d)) * 1.3).astype(np.float32)
+    b = B()
+    print("attention merge", d, nq, nkv, batch, flush=True)
+    b.set_tuning("attn_chunk_pages", 1)
+    try:
+        got = b.op_paged_attention(g.model, g.pool, 0, torch.from_numpy(q).cuda(), g.block_table, g.seq_lens).cpu().numpy()
+    finally:
+        b.set_tuning("attn_chunk_pages", 0)
+    for i in range(0, batch, 7):
+        want = orc.paged_attention(opool, 0, c.block_table[i], int(lens[i]), q[i].reshape(nq, d)).reshape(-1)
+        assert np.abs(got[i] - want).max() <= KERNEL_TOL * max(1.0, np.abs(want).max()), i
+
+
+def test_projections_on_two_streams_share_the_scratch_pool():
+    """K-sliced projections and feed-forward blocks take scratch from one pool per device: calls in flight on two
+    streams, after a synchronisation, and after other handles of the device have gone."""
+    b = B()
+    rng = np.random.default_rng(33)
+    x = torch.from_numpy(rng.standard_normal((70, 1024)).astype(np.float32)).cuda()
+    W = [I.normal((768, 1024), 0.05, 8, "ws", i) for i in range(2)]
+    Wg, Wu, Wd = (I.normal(sh, 0.05, 8, "wsf", i) for i, sh in enumerate(((512, 1024), (512, 1024), (768, 512))))
+    lin = [b.Linear(w.cuda()) for w in W]
+    gu, down = b.GateUp(Wg.cuda(), Wu.cuda()), b.Linear(Wd.cuda())
+    torch.cuda.synchronize()
+    want = [l(x).clone() for l in lin] + [gu.ffn(down, x).clone()]
+    torch.cuda.synchronize()
+    streams = [torch.cuda.Stream() for _ in range(2)]
+    got = [[], []]
+    for r in range(20):
+        for k, st in enumerate(streams):
+            with torch.cuda.stream(st):
+                got[k].append([lin[k](x), gu.ffn(down, x)])
+    torch.cuda.synchronize()
+    for k in range(2):
+        for y, f in got[k]:
+            assert torch.equal(y, want[k]) and torch.equal(f, want[2])
+    lin[1].close(); gu.close(); down.close()
+    assert torch.equal(lin[0](x), want[0])
+    lin[0].close()
+
+
 @pytest.mark.parametrize("batch", [1023, 2048, 2051])
 def test_paged_attention_work_list_of_many_requests(batch):
     """The work list keeps the page counts of the first 2048 requests in LDS and reads the others' again; from 1025
