@@ -2,9 +2,9 @@
 // straight into matrix-core operand registers, and fp32 activations staged through LDS as two
 // bf16 terms (hi + lo).  gfx950, wave64, v_mfma_f32_32x32x16_bf16.
 //
-// Work split: a workgroup of 4 waves owns 4*NF tiles of 32 output columns (one wave = NF tiles),
+// Work split: a workgroup of NW = 4 (or 8) waves owns NW*NF tiles of 32 output columns (one wave = NF tiles),
 // one M-tile of 32*MT rows and one slice of K.  Weights are read exactly once per M-tile; the
-// activation chunk of the current K-slice is shared by the 4 waves through LDS.  With more than
+// activation chunk of the current K-slice is shared by the waves through LDS.  With more than
 // one K-slice each slice stores its partial product in a workspace [slice][M][N]; the kernel that
 // consumes the projection (residual add + RMSNorm, or RoPE) sums the slices while it reads them,
 // in a fixed order, so results are reproducible run to run.
@@ -72,8 +72,8 @@ int32_t launch_pack_rows(const uint16_t* src, int rows, int K, size_t tstride, u
 // 8B gate/up shape at 2048 rows: the weight stream alone 268 us with the hint, 194 us without).
 // NORM: the input is rmsnorm(A) * gain.  A workgroup of an unsliced projection reads whole rows anyway: the gain is applied
 // while a chunk is staged, the sum of squares is taken from the same values, and the row's 1/rms multiplies the accumulators.
-template <int MT, int NF, int KS, int PRO, bool WNT = true, bool NORM = false>
-__global__ __launch_bounds__(256, (MT * NF <= 8 && !(MT == 4 && PRO != PRO_NONE) ? 2 : 1)) void linear_kernel(const uint16_t* __restrict__ Wp, size_t tstride, int Npad, int Nreal, int K, int Kpad,
+template <int MT, int NF, int KS, int PRO, bool WNT = true, bool NORM = false, int NW = 4>
+__global__ __launch_bounds__(64 * NW, (NW == 8 || (MT * NF <= 8 && !(MT == 4 && PRO != PRO_NONE)) ? 2 : 1)) void linear_kernel(const uint16_t* __restrict__ Wp, size_t tstride, int Npad, int Nreal, int K, int Kpad,
                                                      const float* __restrict__ A, int lda, int M,
                                                      float* __restrict__ Y, int ldy, int chunks_per_split,
                                                      int mode, size_t part_stride, int gx, int gy, int gz, int remap,
@@ -84,10 +84,11 @@ __global__ __launch_bounds__(256, (MT * NF <= 8 && !(MT == 4 && PRO != PRO_NONE)
     constexpr int KC = 16 * KS;        // k per chunk
     // (with NORM there are at most 16 rows: the upper half of the tile is not staged where that saves whole passes, and the
     // columns of the product that it would give are never stored)
-    constexpr int SROWS = NORM && MT == 1 && 16 * KG % 256 == 0 ? 16 : MROWS;
+    constexpr int T = 64 * NW;  // threads
+    constexpr int SROWS = NORM && MT == 1 && 16 * KG % T == 0 ? 16 : MROWS;
     constexpr int TASKS = SROWS * KG;  // 8-float staging tasks per chunk
-    static_assert(TASKS % 256 == 0, "staging assumes whole passes of the workgroup");
-    constexpr int TPT = TASKS / 256;
+    static_assert(TASKS % T == 0, "staging assumes whole passes of the workgroup");
+    constexpr int TPT = TASKS / T;
     // activation loads and staging spread over the k-steps of a chunk (see below; measured on one device against the
     // bunched form: gate/up at 64 rows 50.3 against 53.6 us, at 192 rows 101 against 109 us).  The widest tile keeps
     // them bunched: it has no registers left for the first chunk's separate staging set.
@@ -107,7 +108,7 @@ __global__ __launch_bounds__(256, (MT * NF <= 8 && !(MT == 4 && PRO != PRO_NONE)
     if (logical >= total) return;  // grid is padded to a multiple of 8 (uniform over the workgroup)
     const int bz = logical % gz, bx = (logical / gz) % gx, by = logical / (gz * gx);
     const int m0 = bz * MROWS;
-    const int tile0 = (bx * 4 + wave) * NF;  // first 32-column tile of this wave
+    const int tile0 = (bx * NW + wave) * NF;  // first 32-column tile of this wave
     const int chunks_total = (K + KC - 1) / KC;
     const int c_begin = by * chunks_per_split;
     int c_end = c_begin + chunks_per_split;
@@ -146,14 +147,14 @@ __global__ __launch_bounds__(256, (MT * NF <= 8 && !(MT == 4 && PRO != PRO_NONE)
         for (int f = 0; f < NF; ++f)
             w[s][f] = WNT ? load_stream_16(wp[f] + off) : *reinterpret_cast<const uint4*>(wp[f] + off);
     };
-    // staging task i of a chunk: 8 consecutive k of one row, thread tid + 256*i.  A thread's tasks share their k, so the
+    // staging task i of a chunk: 8 consecutive k of one row, thread tid + T*i.  A thread's tasks share their k, so the
     // gains of a chunk are one load, with the last task: by then the previous chunk's gains have been used.
     uint4 g0 = make_uint4(0, 0, 0, 0), greg = g0;  // gains of the first chunk and of the one being staged
     float ss[TPT];                                 // this thread's part of its rows' sums of squares
 #pragma unroll
     for (int i = 0; i < TPT; ++i) ss[i] = 0.f;
     auto load_task = [&](int c, int i, float4 (&ar)[2], uint4& gr) {
-        int task = tid + i * 256;
+        int task = tid + i * T;
         int kg = task % KG, m = task / KG;
         int k = c * KC + kg * 8;
         const float* p = A + (size_t)min(m0 + m, M - 1) * lda + min(k, K - 8);
@@ -162,7 +163,7 @@ __global__ __launch_bounds__(256, (MT * NF <= 8 && !(MT == 4 && PRO != PRO_NONE)
         if (NORM && i == TPT - 1) gr = *reinterpret_cast<const uint4*>(gain + min(k, K - 8));
     };
     auto stage_task = [&](int c, int i, int buf, const float4 (&ar)[2], const uint4& gr) {
-        int task = tid + i * 256;
+        int task = tid + i * T;
         int kg = task % KG, m = task / KG;
         const bool ok = (m0 + m < M) && (c * KC + kg * 8 < K);
         float v[8] = {ar[0].x, ar[0].y, ar[0].z, ar[0].w, ar[1].x, ar[1].y, ar[1].z, ar[1].w};
@@ -194,9 +195,9 @@ __global__ __launch_bounds__(256, (MT * NF <= 8 && !(MT == 4 && PRO != PRO_NONE)
     };
     // PRO_PACKED: chunk c of the pre-split activations goes HBM/L2 -> LDS directly (16 bytes per lane, a wave
     // fills 64 consecutive rows of one k-group), no registers and no LDS store instructions in between
-    constexpr int JOBS = KG * (MROWS / 64) * 2;  // (k-group, 64-row half, hi|lo) per chunk, dealt to the 4 waves
-    static_assert(PRO != PRO_PACKED || (MROWS % 64 == 0 && JOBS % 4 == 0), "packed input needs 64-row halves");
-    constexpr int WJOBS = PRO == PRO_PACKED ? JOBS / 4 : 1;
+    constexpr int JOBS = KG * (MROWS / 64) * 2;  // (k-group, 64-row half, hi|lo) per chunk, dealt to the waves
+    static_assert(PRO != PRO_PACKED || (MROWS % 64 == 0 && JOBS % NW == 0), "packed input needs 64-row halves");
+    constexpr int WJOBS = PRO == PRO_PACKED ? JOBS / NW : 1;
     // per job: this lane's source at chunk 0 (it advances by one chunk of k-groups per chunk) and the wave-uniform
     // LDS byte address of the job's destination in either buffer
     const float4* dma_src[WJOBS];
@@ -204,7 +205,7 @@ __global__ __launch_bounds__(256, (MT * NF <= 8 && !(MT == 4 && PRO != PRO_NONE)
     if (PRO == PRO_PACKED) {
 #pragma unroll
         for (int j = 0; j < WJOBS; ++j) {
-            const int job = wave + 4 * j;
+            const int job = wave + NW * j;
             const int lo = job & 1, half = (job >> 1) % (MROWS / 64), kg = (job >> 1) / (MROWS / 64);
             const int m = half * 64 + lane;
             const size_t idx = ((size_t)min(bz * MT + m / 32, mtiles_all - 1) * kgroups + kg) * 32 + (m & 31);
@@ -396,7 +397,7 @@ __global__ __launch_bounds__(256, (MT * NF <= 8 && !(MT == 4 && PRO != PRO_NONE)
             float s = ss[i];
 #pragma unroll
             for (int o = 1; o < KG; o <<= 1) s += __shfl_xor(s, o);
-            if (tid % KG == 0) s_inv[(tid + i * 256) / KG] = 1.0f / sqrtf(s / (float)K + eps);
+            if (tid % KG == 0) s_inv[(tid + i * T) / KG] = 1.0f / sqrtf(s / (float)K + eps);
         }
         lds_barrier();
 #pragma unroll
@@ -534,10 +535,10 @@ Tuning& tuning() {
     return t;
 }
 
-template <int MT, int NF, int PRO, int KS = 4, bool WNT = true, bool NORM = false>
+template <int MT, int NF, int PRO, int KS = 4, bool WNT = true, bool NORM = false, int NW = 4>
 static void launch_cfg(int nblocks, hipStream_t st, const Linear& L, const float* A, int lda, int M, float* y, int ldy,
                        int cps, int mode, size_t part_stride, int gx, int gy, int gz, const NormIn& norm = NormIn()) {
-    launch(linear_kernel<MT, NF, KS, PRO, WNT, NORM>, dim3(nblocks), dim3(256), st, L.w, L.tstride, L.Npad, L.N, L.K, L.Kpad, A, lda, M, y, ldy, cps, mode,
+    launch(linear_kernel<MT, NF, KS, PRO, WNT, NORM, NW>, dim3(nblocks), dim3(64 * NW), st, L.w, L.tstride, L.Npad, L.N, L.K, L.Kpad, A, lda, M, y, ldy, cps, mode,
                                                            part_stride, gx, gy, gz, tuning().linear_xcd_remap, norm.gain, norm.eps);
 }
 
@@ -555,10 +556,10 @@ int linear_big_min_rows(const Linear& L) {
     return v == 0 ? big_min_rows_default(L) : (v < 0 ? INT32_MAX : v);
 }
 
-// the launch shape of a tiled projection: rows / 32 and column tiles per wave, k-steps per chunk, workgroups along N and M, K-slices and
-// chunks per slice
+// the launch shape of a tiled projection: rows / 32 and column tiles per wave, waves per workgroup, k-steps per chunk,
+// workgroups along N and M, K-slices and chunks per slice
 struct LinearShape {
-    int mt, nf, ks, gx, gz, ksplit, cps;
+    int mt, nf, nw, ks, gx, gz, ksplit, cps;
 };
 static LinearShape linear_shape(const Linear& L, int M, bool sliceable, int prologue, int max_split) {
     const Tuning& tn = tuning();
@@ -657,7 +658,32 @@ static LinearShape linear_shape(const Linear& L, int M, bool sliceable, int prol
     if (ksplit < 1) ksplit = 1;
     int cps = (chunks + ksplit - 1) / ksplit;
     ksplit = (chunks + cps - 1) / cps;  // no empty slices
-    return LinearShape{mt, nf, ks16 ? 16 : (ks8 ? 8 : 4), gx, gz, ksplit, cps};
+    // Eight waves instead of four over the same columns where that pays: two waves per SIMD, of which one multiplies while
+    // the other converts activations or waits.  Measured (whole calls, one device):
+    //   128 rows x 512 columns: the 8B-wide feed-forward block of 2048 rows 1160 -> 1144 us, two layers and the head at 500
+    //     requests 3114 -> 3088 us (and no accumulator spills);
+    //   64 x 256 with several M-tiles: four layers of 128 rows 1110 -> 1096 us; with one M-tile 64 rows get 0.3 % slower, the
+    //     workgroup then being short of bytes in flight and not of issue slots;
+    //   97..128 rows, K sliced: one 128 x 256 tile for two of 64 x 512 (a fifth less traffic per workgroup): 1081 -> 1067 us;
+    //     unsliced (70B-wide gate/up) it is matrix-core bound and 3 % slower.
+    // 64 x 512 shows no difference, pre-split input 1 % less.
+    int nw = 4;
+    if (prologue == PRO_NONE) {
+        if (mt == 4 && nf == 4) {
+            nw = 8;
+            nf = 2;
+        } else if (mt == 2 && nf == 2 && gz > 1 && !ks8) {
+            nw = 8;
+            nf = 1;
+        } else if (!tn.linear_mt && !tn.linear_nf && mt == 2 && nf == 4 && gz == 2 && M > 96 && ksplit > 1) {
+            nw = 8;
+            mt = 4;
+            nf = 1;
+            gz = 1;
+            gx = (tiles + 7) / 8;
+        }
+    }
+    return LinearShape{mt, nf, nw, ks16 ? 16 : (ks8 ? 8 : 4), gx, gz, ksplit, cps};
 }
 
 int linear_slices(const Linear& L, int M, int prologue, int max_split) { return M > 0 ? linear_shape(L, M, true, prologue, max_split).ksplit : 1; }
@@ -683,7 +709,7 @@ int32_t launch_linear(const Linear& L, const float* A, int lda, int M, float* y,
     if (prologue != PRO_PACKED && (lda % 4 != 0 || ((uintptr_t)A & 15)))
         return fail(CHIRON_ERR_INVALID_ARG, "linear: input rows must be 16-byte aligned");
     const LinearShape shape = linear_shape(L, M, max_split > 1, prologue, max_split);
-    const int mt = shape.mt, nf = shape.nf, gx = shape.gx, gz = shape.gz, ksplit = shape.ksplit, cps = shape.cps;
+    const int mt = shape.mt, nf = shape.nf, nw = shape.nw, gx = shape.gx, gz = shape.gz, ksplit = shape.ksplit, cps = shape.cps;
     const bool ks8 = shape.ks == 8, ks16 = shape.ks == 16;
     if (ksplit > 1 && !part) return fail(CHIRON_ERR_INVALID_ARG, "linear: no workspace for %d K-slices", ksplit);
     int mode = ksplit > 1 ? EPI_SLICES : epilogue;
@@ -716,10 +742,13 @@ int32_t launch_linear(const Linear& L, const float* A, int lda, int M, float* y,
         else if (nf == 4) launch_cfg<4, 4, PRO_PACKED>(nblocks, st, L, A, lda, M, dst, ldd, cps, mode, part_stride, gx, ksplit, gz);
         else if (gz > 1) launch_cfg<4, 2, PRO_PACKED, 4, false>(nblocks, st, L, A, lda, M, dst, ldd, cps, mode, part_stride, gx, ksplit, gz);
         else launch_cfg<4, 2, PRO_PACKED>(nblocks, st, L, A, lda, M, dst, ldd, cps, mode, part_stride, gx, ksplit, gz);
+    } else if (nw == 8) {
+        if (mt == 4 && nf == 2 && gz > 1) launch_cfg<4, 2, PRO_NONE, 4, false, false, 8>(nblocks, st, L, A, lda, M, dst, ldd, cps, mode, part_stride, gx, ksplit, gz);
+        else if (mt == 4 && nf == 2) launch_cfg<4, 2, PRO_NONE, 4, true, false, 8>(nblocks, st, L, A, lda, M, dst, ldd, cps, mode, part_stride, gx, ksplit, gz);
+        else if (mt == 4) launch_cfg<4, 1, PRO_NONE, 4, true, false, 8>(nblocks, st, L, A, lda, M, dst, ldd, cps, mode, part_stride, gx, ksplit, gz);
+        else launch_cfg<2, 1, PRO_NONE, 4, true, false, 8>(nblocks, st, L, A, lda, M, dst, ldd, cps, mode, part_stride, gx, ksplit, gz);
     } else if (nf == 4) {
-        if (mt == 4 && gz > 1) launch_cfg<4, 4, PRO_NONE, 4, false>(nblocks, st, L, A, lda, M, dst, ldd, cps, mode, part_stride, gx, ksplit, gz);
-        else if (mt == 4) launch_cfg<4, 4, PRO_NONE>(nblocks, st, L, A, lda, M, dst, ldd, cps, mode, part_stride, gx, ksplit, gz);
-        else launch_cfg<2, 4, PRO_NONE>(nblocks, st, L, A, lda, M, dst, ldd, cps, mode, part_stride, gx, ksplit, gz);
+        launch_cfg<2, 4, PRO_NONE>(nblocks, st, L, A, lda, M, dst, ldd, cps, mode, part_stride, gx, ksplit, gz);
     } else if (mt == 1 && nf == 1) CHIRON_LAUNCH(1, 1);
     else if (mt == 1) CHIRON_LAUNCH(1, 2);
     else if (mt == 2 && nf == 1) CHIRON_LAUNCH(2, 1);

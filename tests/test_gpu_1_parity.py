@@ -261,6 +261,23 @@ def test_swiglu_ffn(M, K, F, N):
     gu.close(); down.close()
 
 
+@pytest.mark.parametrize("M,N,K", [(97, 8200, 2064), (128, 4096, 1024), (100, 2080, 512), (129, 2080, 272), (250, 2144, 528), (384, 8224, 64),
+                                   (500, 8192, 192), (387, 16400, 48)])
+def test_linear_eight_waves(M, N, K):
+    """the eight-wave shapes: 128 x 512 (from 384 rows, wide outputs), 64 x 256 with several M-tiles, one 128 x 256 tile
+    for 97..128 rows with K sliced; ragged rows, columns past the last tile, K below and past whole chunks"""
+    rng = np.random.default_rng(M + 3 * N + 5 * K)
+    x = rng.standard_normal((M, K)).astype(np.float32)
+    W = I.normal((N, K), 0.05, 6, "w8", N, K)
+    print("linear eight waves", M, N, K, flush=True)
+    lin = B().Linear(W.cuda())
+    want = orc.linear(x, I.to_numpy_storage(W))
+    y0 = rng.standard_normal((M, N)).astype(np.float32)
+    assert rel_err(lin(torch.from_numpy(x).cuda()).cpu().numpy(), want) <= KERNEL_TOL
+    assert rel_err(lin(torch.from_numpy(x).cuda(), torch.from_numpy(y0).cuda(), accumulate=True).cpu().numpy(), want + y0) <= KERNEL_TOL
+    lin.close()
+
+
 def test_linear_over_seeded_random_shapes():
     """The launch shape (rows per tile, column tiles per wave, K-slices, pre-split input) is chosen from M, N and K by
     several rules: 48 seeded random shapes, widths from a few columns to more than two workgroups per CU and rows
