@@ -278,6 +278,25 @@ def test_linear_eight_waves(M, N, K):
     lin.close()
 
 
+@pytest.mark.parametrize("M,F", [(129, 16400), (200, 24576), (256, 8192)])
+def test_gate_up_wide_input_row_tiles(M, F):
+    """K >= 8192, unsliced: 128-row tiles past one of them where they give three quarters of the CUs a workgroup (F = 24576),
+    64- and 96-row tiles otherwise"""
+    K = 8192
+    x = torch.from_numpy(np.random.default_rng(M + F).standard_normal((M, K)).astype(np.float32))
+    Wg, Wu = I.normal((F, K), 0.01, 6, "wgw", F), I.normal((F, K), 0.01, 6, "wuw", F)
+    b = B()
+    print("gate/up wide", M, F, flush=True)
+    gu = b.GateUp(Wg.cuda(), Wu.cuda())
+    got = gu.swiglu(x.cuda()).cpu()
+    gu.close()
+    rows = torch.arange(0, M, 9)  # sampled rows against fp64 sums
+    xg = x[rows].cuda().double()
+    g, u = xg @ Wg.cuda().double().t(), xg @ Wu.cuda().double().t()
+    want = (torch.nn.functional.silu(g) * u).cpu().float().numpy()
+    assert rel_err(got[rows].numpy(), want) <= KERNEL_TOL
+
+
 def test_linear_over_seeded_random_shapes():
     """The launch shape (rows per tile, column tiles per wave, K-slices, pre-split input) is chosen from M, N and K by
     several rules: 48 seeded random shapes, widths from a few columns to more than two workgroups per CU and rows
