@@ -28,11 +28,11 @@ MFMA_BF16_PEAK_TFLOPS = 2500.0
 # `sha` is the sha256 of the kernel's source file at that time; with any other source the figure is reported null.
 TRAFFIC = {
     # (workload, kernel class): (source file, sha256, fetch bytes, write bytes)
-    ("llama8b-b64-lognormal800", "attn"): ("attention.hip", "02217a164f11f306204df37f6e2b724792ba1bdb546d81105e6be8e84d6e4635", 275697032, 4259904),
-    ("llama8b-b64-lognormal800", "gateup"): ("linear.hip", "05a738cc438354e18a9eb186fdc7e1c7d3925e12a706b569264088025053acdc", 243439145, 3670016),
-    ("llama8b-b64-lognormal800", "down"): ("linear.hip", "05a738cc438354e18a9eb186fdc7e1c7d3925e12a706b569264088025053acdc", 121329453, 16777219),
-    ("llama8b-mixed-sweep512", "attn"): ("attention.hip", "02217a164f11f306204df37f6e2b724792ba1bdb546d81105e6be8e84d6e4635", 4197918185, 37881916),
-    ("llama8b-b32-long32k", "attn"): ("attention.hip", "02217a164f11f306204df37f6e2b724792ba1bdb546d81105e6be8e84d6e4635", 3723503215, 30211101),
+    ("llama8b-b64-lognormal800", "attn"): ("attention.hip", "0ce537b9d8896e4bbd896f7009353995d581f7a3b2b558858f66f6781245dec8", 275691824, 4259911),
+    ("llama8b-b64-lognormal800", "gateup"): ("linear.hip", "cbaa3ab9ad5e49ac9c7cea4200cf981c402d61f78b91d2d922f4b6411c8368dd", 243436004, 3670016),
+    ("llama8b-b64-lognormal800", "down"): ("linear.hip", "cbaa3ab9ad5e49ac9c7cea4200cf981c402d61f78b91d2d922f4b6411c8368dd", 121338096, 16777226),
+    ("llama8b-mixed-sweep512", "attn"): ("attention.hip", "0ce537b9d8896e4bbd896f7009353995d581f7a3b2b558858f66f6781245dec8", 4196831402, 21763317),
+    ("llama8b-b32-long32k", "attn"): ("attention.hip", "0ce537b9d8896e4bbd896f7009353995d581f7a3b2b558858f66f6781245dec8", 3721428398, 4260218),
 }
 
 

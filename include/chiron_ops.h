@@ -79,7 +79,9 @@ int32_t chiron_op_paged_attention(chiron_model *m, const chiron_kvpool *p, int32
  *   linear_big_all (1: from that row count on every other projection's input is split into such terms first),
  *   linear_ks (4|8|16: k-steps per chunk, the depth of the weight ring),
  *   attn_grid, attn_target_waves, attn_chunk_pages.
- * They change launch shapes only, never results beyond summation order. Unknown keys are an error. */
+ * They change launch shapes only, never results beyond summation order (up to 16 rows a forced linear_nf, linear_mt,
+ * linear_ksplit, linear_ks or linear_big_all also keeps the tiled kernels instead of the few-row ones). Unknown keys are
+ * an error. */
 int32_t chiron_set_tuning(const char *key, int32_t value);
 
 #ifdef __cplusplus
