@@ -607,9 +607,14 @@ static int32_t scratch_alloc(int dev, void** out, size_t bytes, hipStream_t st) 
     *out = nullptr;
     if (bytes == 0) return CHIRON_OK;
     // (a stream that is being captured, or one of another device, takes the default pool as any allocation does)
-    hipStreamCaptureStatus cap = hipStreamCaptureStatusActive;
+    bool own = false;
     int cur = -1;
-    if (dev >= 0 && hipGetDevice(&cur) == hipSuccess && cur == dev && hipStreamIsCapturing(st, &cap) == hipSuccess && cap == hipStreamCaptureStatusNone)
+    if (dev >= 0 && hipGetDevice(&cur) == hipSuccess && cur == dev) {
+        hipStreamCaptureStatus cap = hipStreamCaptureStatusActive;
+        own = hipStreamIsCapturing(st, &cap) == hipSuccess && cap == hipStreamCaptureStatusNone;
+        if (!own) (void)hipGetLastError();
+    }
+    if (own)
         CHIRON_HIP(hipMallocFromPoolAsync(out, bytes, g_scratch_pool[dev].pool, st));
     else
         CHIRON_HIP(hipMallocAsync(out, bytes, st));
