@@ -29,7 +29,8 @@ int32_t chiron_linear_create(const void *w, int32_t N, int32_t K, void *stream, 
 int32_t chiron_linear_destroy(chiron_linear *l);
 
 /* y[M,N] = x[M,K] * W^T (accumulate == 0) or y += x * W^T (accumulate != 0, the residual add).
- * x, y dev fp32 row-major.  x is split into two bf16 terms, products accumulate in fp32. */
+ * x, y dev fp32 row-major; they may overlap (a square matrix applied in place), which costs a pass over the result.
+ * x is split into two bf16 terms, products accumulate in fp32. */
 int32_t chiron_op_linear(const chiron_linear *l, const float *x, int32_t M, float *y, int32_t accumulate,
                          void *stream);
 

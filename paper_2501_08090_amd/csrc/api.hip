@@ -678,29 +678,33 @@ struct OpScratch {
     int max_split = 1;
     size_t bytes() const { return part_bytes + split_bytes; }
 };
-static OpScratch op_linear_scratch(const Linear& L, int M, int prologue) {
+static OpScratch op_linear_scratch(const Linear& L, int M, int prologue, bool in_place = false) {
     OpScratch sc;
-    if (prologue == PRO_NONE && linear_few_rows(M) && L.N <= 16384) return sc;  // the few-row path needs none
+    if (prologue == PRO_NONE && linear_few_rows(M) && L.N <= 16384 && !in_place) return sc;  // the few-row path needs none
     const bool split = prologue == PRO_NONE && tuning().linear_big_all && M >= linear_big_min_rows(L);
     if (split) sc.split_bytes = 2 * linear_big_split_elems(M, L.Kpad) * 2;
     // wide outputs (LM head, gate/up) have enough column tiles on their own and are never sliced in the step
+    int ks = 1;
     if (L.N <= 16384) {
         sc.max_split = linear_max_split();
-        const int ks = linear_slices(L, M, split ? PRO_PACKED : prologue, sc.max_split);
-        if (ks > 1) sc.part_bytes = ((size_t)ks * M * L.N * sizeof(float) + 255) / 256 * 256;
+        ks = linear_slices(L, M, split ? PRO_PACKED : prologue, sc.max_split);
     }
+    if (ks > 1 || in_place) sc.part_bytes = ((size_t)ks * M * L.N * sizeof(float) + 255) / 256 * 256;
     return sc;
 }
 
+// in_place: y shares memory with x.  Workgroups that are still reading x must not meet another's output there, so the
+// product goes to the scratch memory whole, sliced or not, and the sum of the slices brings it to y.
 static int32_t op_linear_common(const Linear& L, const float* x, int lda, int M, float* y, int accumulate, int prologue,
-                                const OpScratch& sc, void* scratch, hipStream_t st) {
+                                const OpScratch& sc, void* scratch, hipStream_t st, bool in_place = false) {
     // few rows: one launch (very wide outputs have enough column tiles for the tiled kernel)
-    if (prologue == PRO_NONE && linear_few_rows(M) && L.N <= 16384) return launch_linear_few(L, x, lda, M, 0, y, L.N, accumulate, st);
+    if (prologue == PRO_NONE && linear_few_rows(M) && L.N <= 16384 && !in_place) return launch_linear_few(L, x, lda, M, 0, y, L.N, accumulate, st);
     float* part = sc.part_bytes ? (float*)scratch : nullptr;
     uint16_t* asplit = sc.split_bytes ? (uint16_t*)((char*)scratch + sc.part_bytes) : nullptr;
     int ks = 1;
-    int32_t rc = launch_linear(L, x, lda, M, y, L.N, accumulate ? EPI_ADD : EPI_STORE, prologue, part, sc.max_split, &ks, asplit, st);
-    if (!rc && ks > 1) rc = launch_reduce_partials(part, ks, (int64_t)M * L.N, y, accumulate, st);
+    int32_t rc = launch_linear(L, x, lda, M, in_place ? part : y, L.N, accumulate && !in_place ? EPI_ADD : EPI_STORE, prologue, part, sc.max_split,
+                               &ks, asplit, st);
+    if (!rc && (ks > 1 || in_place)) rc = launch_reduce_partials(part, ks, (int64_t)M * L.N, y, accumulate, st);
     return rc;
 }
 
@@ -711,11 +715,12 @@ int32_t chiron_op_linear(const chiron_linear* l, const float* x, int32_t M, floa
     if (!x || !y) return fail(CHIRON_ERR_INVALID_ARG, "linear: a pointer is null");
     if (l->gate_up) return fail(CHIRON_ERR_INVALID_ARG, "linear: a fused gate/up matrix goes with the SwiGLU entry points only");
     hipStream_t st = (hipStream_t)stream;
-    const OpScratch sc = op_linear_scratch(l->L, M, PRO_NONE);
+    const bool in_place = x < y + (size_t)M * l->L.N && y < x + (size_t)M * l->L.K;
+    const OpScratch sc = op_linear_scratch(l->L, M, PRO_NONE, in_place);
     void* scratch = nullptr;
     int32_t rc = scratch_alloc(l->device, &scratch, sc.bytes(), st);
     if (rc) return rc;
-    rc = op_linear_common(l->L, x, l->L.K, M, y, accumulate, PRO_NONE, sc, scratch, st);
+    rc = op_linear_common(l->L, x, l->L.K, M, y, accumulate, PRO_NONE, sc, scratch, st, in_place);
     if (scratch) (void)hipFreeAsync(scratch, st);
     return rc;
 }

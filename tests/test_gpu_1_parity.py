@@ -203,6 +203,23 @@ def test_linear_few_rows(M, N, K):
     lin.close()
 
 
+@pytest.mark.parametrize("M,N", [(1, 64), (5, 1024), (16, 2048), (16, 4096), (17, 48), (40, 1024), (130, 256)])
+def test_linear_in_place(M, N):
+    """A square matrix whose result overwrites (or is added to) its own input: no workgroup may read what another has
+    already written.  Few rows, K sliced, K too short to be sliced."""
+    rng = np.random.default_rng(M + 7 * N)
+    x = rng.standard_normal((M, N)).astype(np.float32)
+    W = I.normal((N, N), 0.05, 5, "wip", N)
+    lin = B().Linear(W.cuda())
+    want = orc.linear(x, I.to_numpy_storage(W))
+    for accumulate in (False, True):
+        print("linear in place", M, N, accumulate, flush=True)
+        h = torch.from_numpy(x).cuda()
+        lin(h, h, accumulate=accumulate)
+        assert rel_err(h.cpu().numpy(), want + x if accumulate else want) <= KERNEL_TOL
+    lin.close()
+
+
 @pytest.mark.parametrize("M,K,F,N", [(1, 64, 16, 40), (16, 256, 688, 256), (5, 1040, 2064, 8208), (11, 256, 4096, 512)])
 def test_swiglu_ffn_few_rows(M, K, F, N):
     """the feed-forward block whose intermediate is handed over as packed terms of M rows"""
