@@ -760,7 +760,7 @@ int32_t chiron_op_swiglu_ffn(const chiron_linear* gate_up, const chiron_linear* 
         if (!rc) rc = launch_linear_few(D, (const float*)act, (int64_t)M * (D.Kpad / 8), M, 1, y, D.N, accumulate, st);
     } else if (packed) {
         // the epilogue writes the columns below F only: the padding of K must not hold NaN bits when the down projection reads it
-        if (D.Kpad != F && hipMemsetAsync(act, 0, bytes, st) != hipSuccess) rc = fail(CHIRON_ERR_HIP, "clearing the activation workspace failed");
+        rc = launch_clear_k_padding((uint16_t*)act, M, F, D.Kpad, st);
         if (!rc) rc = launch_linear(G, x, G.K, M, (float*)act, D.Kpad, EPI_SWIGLU_PACKED, PRO_NONE, nullptr, 1, nullptr, nullptr, st);
         if (!rc) rc = op_linear_common(D, (const float*)act, 0, M, y, accumulate, PRO_PACKED, sc, scratch, st);
     } else {

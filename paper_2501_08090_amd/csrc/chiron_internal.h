@@ -119,6 +119,8 @@ int32_t launch_linear(const Linear& L, const float* A, int lda, int M, float* y,
 int32_t launch_linear_big(const Linear& L, const float* A, int lda, int M, float* y, int ldy, int epilogue,
                           float* part, int max_split, int* ksplit_out, uint16_t* asplit, hipStream_t st);
 size_t linear_big_split_elems(int M, int Kpad);
+// zeroes the columns K .. Kpad-1 of both terms of such an input (none if K == Kpad)
+int32_t launch_clear_k_padding(uint16_t* asplit, int M, int K, int Kpad, hipStream_t st);
 int linear_big_min_rows(const Linear& L);
 int linear_max_split();
 // number of K-slices launch_linear takes for M rows when it is given a workspace of max_split slices

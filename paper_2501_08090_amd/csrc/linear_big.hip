@@ -34,6 +34,24 @@ __global__ __launch_bounds__(256) void split_pack_kernel(const float* __restrict
     }
 }
 
+// The k-groups of the padding, 512 contiguous bytes each (32 rows of 16), hi and lo terms: at most 30 groups of 32 rows, where
+// clearing the whole input wrote M * Kpad * 4 bytes (blocks of 2048 rows, 14320 columns: 1171 -> 1165 us, 5504 of 2048:
+// 290 -> 286).  A kernel and not a memset: callers record these calls into graphs.
+__global__ __launch_bounds__(256) void clear_k_padding_kernel(uint4* __restrict__ a, int kg0, int kgroups, int64_t pieces) {
+    const int64_t t = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    if (t >= pieces) return;
+    const int pad = (kgroups - kg0) * 32;  // pieces per 32-row tile; tiles of the lo terms follow those of the hi terms
+    a[(t / pad) * ((int64_t)kgroups * 32) + (int64_t)kg0 * 32 + t % pad] = make_uint4(0, 0, 0, 0);
+}
+
+int32_t launch_clear_k_padding(uint16_t* asplit, int M, int K, int Kpad, hipStream_t st) {
+    if (K >= Kpad || M <= 0) return CHIRON_OK;
+    const int64_t pieces = (int64_t)((M + 31) / 32) * 2 * ((Kpad - K) / 8) * 32;
+    launch(clear_k_padding_kernel, dim3((unsigned)((pieces + 255) / 256)), dim3(256), st, reinterpret_cast<uint4*>(asplit), K / 8, Kpad / 8, pieces);
+    CHIRON_HIP(hipGetLastError());
+    return CHIRON_OK;
+}
+
 size_t linear_big_split_elems(int M, int Kpad) { return (size_t)((M + 31) / 32) * 32 * Kpad; }
 
 int32_t launch_linear_big(const Linear& L, const float* A, int lda, int M, float* y, int ldy, int epilogue,

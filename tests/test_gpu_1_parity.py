@@ -278,6 +278,48 @@ def test_swiglu_ffn(M, K, F, N):
     gu.close(); down.close()
 
 
+@pytest.mark.parametrize("M,F", [(40, 688), (1, 16), (600, 272)])
+def test_swiglu_ffn_records_no_memset_into_a_graph(M, F):
+    """Memset nodes have replayed wrongly here: a feed-forward block whose width is no multiple of 256 (so that the padding of
+    the tiled intermediate has to be cleared) is recorded as kernels and memory nodes only.  The graph is not launched."""
+    import ctypes as C
+    x, Wg, Wu, Wd, _, want = ffn_case(M, 256, F, 512, M + F)
+    b = B()
+    gu, down = b.GateUp(Wg.cuda(), Wu.cuda()), b.Linear(Wd.cuda())
+    xd, y = torch.from_numpy(x).cuda(), torch.empty((M, 512), device="cuda")
+    b.set_tuning("linear_big_min_m", 1)  # the tiled form at any row count
+    b.set_tuning("linear_ks", 4)         # (no few-row path)
+    try:
+        # memory full of NaN bits where the call's scratch will be
+        junk = torch.full((1 << 22,), float("nan"), device="cuda")
+        del junk
+        gu.ffn(down, xd, y)
+        torch.cuda.synchronize()
+        assert rel_err(y.cpu().numpy(), want) <= KERNEL_TOL
+        lib, st = b.load(), torch.cuda.Stream()
+        graph, n = C.c_void_p(), C.c_size_t()
+        with torch.cuda.stream(st):
+            assert lib.hipStreamBeginCapture(C.c_void_p(st.cuda_stream), C.c_int(2)) == 0  # relaxed
+            try:
+                gu.ffn(down, xd, y)
+            finally:
+                assert lib.hipStreamEndCapture(C.c_void_p(st.cuda_stream), C.byref(graph)) == 0
+    finally:
+        b.set_tuning("linear_big_min_m", 0)
+        b.set_tuning("linear_ks", 0)
+    assert lib.hipGraphGetNodes(graph, None, C.byref(n)) == 0
+    nodes = (C.c_void_p * n.value)()
+    assert lib.hipGraphGetNodes(graph, nodes, C.byref(n)) == 0
+    kinds = []
+    for node in nodes:
+        k = C.c_int()
+        assert lib.hipGraphNodeGetType(C.c_void_p(node), C.byref(k)) == 0
+        kinds.append(k.value)
+    assert lib.hipGraphDestroy(graph) == 0
+    assert kinds.count(0) >= 2 and 2 not in kinds  # kernel nodes, no memset node
+    gu.close(); down.close()
+
+
 @pytest.mark.parametrize("M,N,K", [(97, 8200, 2064), (128, 4096, 1024), (100, 2080, 512), (129, 2080, 272), (250, 2144, 528), (384, 8224, 64),
                                    (500, 8192, 192), (387, 16400, 48)])
 def test_linear_eight_waves(M, N, K):
