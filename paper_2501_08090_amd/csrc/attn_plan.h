@@ -7,16 +7,16 @@
 
 namespace chiron {
 
-// plan buffer layout (int32): [0] n_items, [1] chunk_pages, [2..3] unused,
+// plan buffer layout (int32): [0] n_items, [1] chunk_pages, [2] number of long passes (more than kMergeLong items), [3] unused,
 // [4, 4+max_batch) first partial result of pass v, [.., +max_batch) number of partial results of pass v (one per item, in
 // page order), [.., +max_batch) items placed before v's first, [.., +max_batch) place of v's last piece in the list if
-// that is no whole item.  A pass v = request * ng + token group (AttnShape).
+// that is no whole item, [.., +max_batch) the long passes in any order.  A pass v = request * ng + token group (AttnShape).
 // Then, 32-byte aligned, one record of 8 ints per item, in the order in which items are taken: {pass, first
 // page, attended length, the ids of the item's first four pages (past its end: its last page), partial result}: everything a
 // wave needs before its first tile load, in one scalar load instead of a chain of four dependent ones (the block table does
 // not differ between layers).
 // After the records, kTicketQueues ticket counters kTicketStride ints apart, all 0 between attention launches.
-__host__ __device__ inline int64_t plan_rec_offset(int max_batch) { return (4 + 4 * (int64_t)max_batch + 7) / 8 * 8; }
+__host__ __device__ inline int64_t plan_rec_offset(int max_batch) { return (4 + 5 * (int64_t)max_batch + 7) / 8 * 8; }
 constexpr int kTicketQueues = 8, kTicketStride = 64;
 __host__ __device__ inline int64_t plan_ticket_offset(int max_batch, int cap_items) {
     return (plan_rec_offset(max_batch) + 8 * (int64_t)cap_items + kTicketStride - 1) / kTicketStride * kTicketStride;
@@ -24,6 +24,7 @@ __host__ __device__ inline int64_t plan_ticket_offset(int max_batch, int cap_ite
 
 constexpr int kPlanThreads = 1024;  // threads of the workgroup that runs attn_plan_block
 constexpr int kPlanMaxRound = 4096; // largest item, in pages, of a list that one round of the grid holds
+constexpr int kMergeLong = 16;      // a pass of more items is long for the merge
 constexpr int kPlanCached = 2048;   // passes whose page counts and offsets are kept in LDS
 
 struct PlanArgs {
@@ -46,7 +47,7 @@ __device__ __forceinline__ int pass_len(const int32_t* __restrict__ seq_lens, co
 // Measured on the attention entry point: 664 -> 646 us at 32 requests of 28k tokens, where the serial loop took 28 us.
 __device__ __forceinline__ void attn_plan_block(const PlanArgs& a) {
     __shared__ int s_np[kPlanCached], s_whole[kPlanCached], s_last[kPlanCached];
-    __shared__ int s_sum[2][kPlanThreads / 64], s_scan[4][kPlanThreads / 64];
+    __shared__ int s_sum[2][kPlanThreads / 64], s_scan[4][kPlanThreads / 64], s_long;
     const AttnShape sh = a.sh;
     const int batch = a.batch * sh.ng;  // passes
     const int max_batch = a.max_batch, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -55,6 +56,8 @@ __device__ __forceinline__ void attn_plan_block(const PlanArgs& a) {
     int32_t* seq_nch = plan + 4 + max_batch;
     int32_t* seq_whole = plan + 4 + 2 * max_batch;
     int32_t* seq_last = plan + 4 + 3 * max_batch;
+    int32_t* long_passes = plan + 4 + 4 * max_batch;
+    if (tid == 0) s_long = 0;
     if (tid < kTicketQueues) plan[plan_ticket_offset(max_batch, a.cap_items) + tid * kTicketStride] = 0;
     for (int v = tid; v < min(batch, kPlanCached); v += kPlanThreads) s_np[v] = (pass_len(a.seq_lens, sh, v) + kBlockSize - 1) / kBlockSize;
     __syncthreads();
@@ -166,6 +169,7 @@ __device__ __forceinline__ void attn_plan_block(const PlanArgs& a) {
         seq_whole[i] = before;
         seq_item0[i] = off[0];
         seq_nch[i] = nch;
+        if (nch > kMergeLong) long_passes[atomicAdd(&s_long, 1)] = i;
         if (drawn) {
             const int place = r == 0 ? -1 : (2 * r >= cp ? off[2]++ : off[3]++);
             if (i < kPlanCached) s_last[i] = place;
@@ -179,6 +183,7 @@ __device__ __forceinline__ void attn_plan_block(const PlanArgs& a) {
         plan[1] = cp;
     }
     __syncthreads();  // (also orders what this workgroup reads back from global memory)
+    if (tid == 0) plan[2] = s_long;
     for (int u = tid; u < n_whole + (drawn ? batch : 0); u += kPlanThreads) {
         if (u >= n_whole) {  // a last piece
             const int v = u - n_whole, place = v < kPlanCached ? s_last[v] : seq_last[v];

@@ -473,6 +473,52 @@ def test_paged_attention_merge_of_many_rows(d, nq, nkv, batch):
         assert np.abs(got[i] - want).max() <= KERNEL_TOL * max(1.0, np.abs(want).max()), i
 
 
+@pytest.mark.parametrize("d,nq,nkv,batch,every", [(64, 4, 2, 514, 171), (128, 12, 3, 350, 349), (128, 16, 1, 1030, 100), (64, 4, 2, 520, 1)])
+def test_paged_attention_merge_of_skewed_batches(d, nq, nkv, batch, every):
+    """Many rows of one or two items and a few (every n-th request) of 17 to 70: those are dealt over the grid, a workgroup per
+    row and head; if all are that long (every = 1) they are folded like the short ones."""
+    rng = np.random.default_rng(23)
+    lens = rng.integers(1, 30, batch)
+    at = np.arange(0, batch, every)
+    lens[at] = 16 * np.where(at % 2, 17, rng.integers(17, 71, len(at)))  # (pages of one item each)
+    c = make_case(m=dict(I.TINY, n_layers=1, head_dim=d, n_q_heads=nq, n_kv_heads=nkv, vocab=64, ffn=16), seed=24, storage="bf16",
+                  seq_lens=lens.astype(np.int32))
+    g = gpu_setup(c)
+    opool = fresh_pool(c)
+    q = (rng.standard_normal((batch, nq * d)) * 1.3).astype(np.float32)
+    b = B()
+    print("attention merge, skewed", d, nq, nkv, batch, every, flush=True)
+    b.set_tuning("attn_chunk_pages", 1)
+    try:
+        got = b.op_paged_attention(g.model, g.pool, 0, torch.from_numpy(q).cuda(), g.block_table, g.seq_lens).cpu().numpy()
+    finally:
+        b.set_tuning("attn_chunk_pages", 0)
+    for i in sorted(set(range(0, batch, 13)) | set(at[:40].tolist())):
+        want = orc.paged_attention(opool, 0, c.block_table[i], int(lens[i]), q[i].reshape(nq, d)).reshape(-1)
+        assert np.abs(got[i] - want).max() <= KERNEL_TOL * max(1.0, np.abs(want).max()), i
+
+
+def test_multi_token_step_of_a_skewed_batch():
+    """The same with 11 new tokens per request (two token groups, the second not full): the long requests' logits in a batch of
+    260 against those of a batch of their own, which merges with a workgroup per row and head."""
+    T, lens = 11, np.random.default_rng(25).integers(12, 40, 260)
+    long = [0, 130, 259]
+    lens[long] = [700, 1100, 430]
+    c = make_case(m=dict(I.TINY, vocab=64), seed=26, storage="bf16", seq_lens=lens.astype(np.int32))
+    g = gpu_setup(c, max_batch=260 * T)
+    b = B()
+    sl = torch.from_numpy((lens - T).astype(np.int32)).cuda()
+    tok = torch.from_numpy(np.random.default_rng(27).integers(0, 64, (260, T)).astype(np.int32)).cuda()
+    print("multi-token step, skewed", flush=True)
+    b.set_tuning("attn_chunk_pages", 1)
+    try:
+        got = b.decode_step_multi(g.model, g.pool, g.block_table, sl, tok)[long].cpu().numpy()
+        alone = b.decode_step_multi(g.model, g.pool, g.block_table[long].contiguous(), sl[long].contiguous(), tok[long].contiguous()).cpu().numpy()
+    finally:
+        b.set_tuning("attn_chunk_pages", 0)
+    assert np.abs(got - alone).max() <= 2e-3 * alone.std()  # other tile shapes; new K and V may round to the other bf16 neighbour
+
+
 def test_projections_on_two_streams_share_the_scratch_pool():
     """K-sliced projections and feed-forward blocks take scratch from one pool per device: calls in flight on two
     streams, after a synchronisation, and after other handles of the device have gone."""
