@@ -666,10 +666,11 @@ static LinearShape linear_shape(const Linear& L, int M, bool sliceable, int prol
     // the other converts activations or waits.  Measured (whole calls, one device):
     //   128 rows x 512 columns: the 8B-wide feed-forward block of 2048 rows 1160 -> 1144 us, two layers and the head at 500
     //     requests 3114 -> 3088 us (and no accumulator spills);
-    //   64 x 256 with several M-tiles: four layers of 128 rows 1110 -> 1096 us; with one M-tile 64 rows get 0.3 % slower, the
-    //     workgroup then being short of bytes in flight and not of issue slots;
-    //   97..128 rows, K sliced: one 128 x 256 tile for two of 64 x 512 (a fifth less traffic per workgroup): 1081 -> 1067 us;
-    //     unsliced (70B-wide gate/up) it is matrix-core bound and 3 % slower.
+    //   64 x 256 with several M-tiles: four layers of 128 rows 1110 -> 1096 us; 200 rows of 5632 gate/up columns at K = 2048
+    //     33.6 -> 30.4; with one M-tile 64 rows get 0.3 % slower, the workgroup then being short of bytes in flight and not of
+    //     issue slots.
+    // One 128 x 256 tile for two of 64 x 512 (97..128 rows, K sliced) was tried: level within a step, but 3..10 % slower as a
+    // projection by itself (128 rows, 8192 x 28672: 144 against 130 us), so wide outputs keep 64-row tiles there.
     // 64 x 512 shows no difference, pre-split input 1 % less.
     int nw = 4;
     if (prologue == PRO_NONE) {
@@ -679,12 +680,6 @@ static LinearShape linear_shape(const Linear& L, int M, bool sliceable, int prol
         } else if (mt == 2 && nf == 2 && gz > 1 && !ks8) {
             nw = 8;
             nf = 1;
-        } else if (!tn.linear_mt && !tn.linear_nf && mt == 2 && nf == 4 && gz == 2 && M > 96 && ksplit > 1) {
-            nw = 8;
-            mt = 4;
-            nf = 1;
-            gz = 1;
-            gx = (tiles + 7) / 8;
         }
     }
     return LinearShape{mt, nf, nw, ks16 ? 16 : (ks8 ? 8 : 4), gx, gz, ksplit, cps};
@@ -749,7 +744,6 @@ int32_t launch_linear(const Linear& L, const float* A, int lda, int M, float* y,
     } else if (nw == 8) {
         if (mt == 4 && nf == 2 && gz > 1) launch_cfg<4, 2, PRO_NONE, 4, false, false, 8>(nblocks, st, L, A, lda, M, dst, ldd, cps, mode, part_stride, gx, ksplit, gz);
         else if (mt == 4 && nf == 2) launch_cfg<4, 2, PRO_NONE, 4, true, false, 8>(nblocks, st, L, A, lda, M, dst, ldd, cps, mode, part_stride, gx, ksplit, gz);
-        else if (mt == 4) launch_cfg<4, 1, PRO_NONE, 4, true, false, 8>(nblocks, st, L, A, lda, M, dst, ldd, cps, mode, part_stride, gx, ksplit, gz);
         else launch_cfg<2, 1, PRO_NONE, 4, true, false, 8>(nblocks, st, L, A, lda, M, dst, ldd, cps, mode, part_stride, gx, ksplit, gz);
     } else if (nf == 4) {
         launch_cfg<2, 4, PRO_NONE>(nblocks, st, L, A, lda, M, dst, ldd, cps, mode, part_stride, gx, ksplit, gz);
