@@ -570,13 +570,16 @@ static LinearShape linear_shape(const Linear& L, int M, bool sliceable, int prol
     // 384 rows, and earlier when 128-row tiles pad the rows no further than 64-row tiles do, from 96 rows for a
     // very wide output (the LM head), at K >= 8192 past one such tile, or from 224 rows if K is sliced (70B-wide gate/up at
     // 200 rows 594 us with 64-row tiles, 345 with 128-row ones), and below 384 rows only if that gives three quarters of the
-    // CUs a workgroup (32000 columns at K = 8192, 256 rows: 126 workgroups 328 us, 252 of 64 rows 200).  Measured on the 8B
-    // and 70B shapes.
+    // CUs a workgroup (32000 columns at K = 8192, 256 rows: 126 workgroups 328 us, 252 of 64 rows 200).  97..128 rows of a very
+    // wide output take one 128-row tile also where two of 64 x 512 would need more than a round of the chip (80000 columns
+    // at K = 4096, 97 rows: 200 against 232 us; 65536 columns, where they just fit, 190 against 131).  Measured on the 8B and
+    // 70B shapes.
     const int tiles_n = L.Npad / 32;
     const int pad64 = (M + 63) / 64 * 64, pad128 = (M + 127) / 128 * 128;
     const int thr128 = tiles_n >= 2048 ? 96 : (L.K >= 8192 ? (sliceable ? 224 : 129) : 384);
     // (outputs narrower than 256 column tiles keep the 64-row shape at any row count: measured 8-12 % faster)
-    const bool fills128 = sliceable || (tiles_n + 15) / 16 * (pad128 / 128) >= kNumCU * 3 / 4;
+    const int cols512 = (tiles_n + 15) / 16;
+    const bool fills128 = sliceable || cols512 * (pad128 / 128) >= kNumCU * 3 / 4 || (M > 96 && pad128 == 128 && cols512 * 2 > kNumCU);
     const bool big = tiles_n >= 256 && (M >= 384 || (pad128 == pad64 && M >= thr128 && fills128));
     // 65..96 rows take one 96-row tile: with 64-row tiles the second M-tile would stream every weight again for a
     // handful of rows (a step of 17 % in the whole decode step's latency between batch 64 and 65).  Likewise above

@@ -321,11 +321,12 @@ def test_swiglu_ffn_records_no_memset_into_a_graph(M, F):
 
 
 @pytest.mark.parametrize("M,N,K", [(97, 8200, 2064), (128, 4096, 1024), (100, 2080, 512), (129, 2080, 272), (250, 2144, 528), (384, 8224, 64),
-                                   (500, 8192, 192), (387, 16400, 48), (97, 16352, 3088), (127, 8200, 6160), (100, 4096, 12304)])
+                                   (500, 8192, 192), (387, 16400, 48), (97, 16352, 3088), (127, 8200, 6160), (100, 4096, 12304),
+                                   (97, 65600, 64), (96, 65600, 64), (128, 65536, 48)])
 def test_linear_eight_waves(M, N, K):
-    """the eight-wave shapes: 128 x 512 (from 384 rows, wide outputs) and 64 x 256 with several M-tiles; ragged rows, columns past
+    """the eight-wave shapes: 128 x 512 (from 384 rows, wide outputs; 97 of 65600 columns) and 64 x 256 with several M-tiles; ragged rows, columns past
     the last tile, K below and past whole chunks.  Beside them the four-wave ones they border on: one 96-row tile of 129 rows,
-    and 64 x 512 for 97..128 rows where slices of at least twelve chunks fill the chip (the last three)."""
+    and 64 x 512 for 97..128 rows where slices of at least twelve chunks fill the chip, or 65536 columns one round of it unsliced."""
     rng = np.random.default_rng(M + 3 * N + 5 * K)
     x = rng.standard_normal((M, K)).astype(np.float32)
     W = I.normal((N, K), 0.05, 6, "w8", N, K)
