@@ -232,8 +232,9 @@ int32_t chiron_local_autoscale_step(double itl, double itl_slo, double tput_prev
  * to the stream between kernels.  _end synchronises `stream` and returns, per kernel class, the summed kernel
  * time and the number of launches since _begin.  (The QKV, O, gate/up, down and LM-head projections are
  * instances of one kernel; a projection of many rows that first splits its input counts as one launch and its
- * time is the sum of its two kernels.  Up to 16 rows the norms are part of the projections behind them and the rotary
- * embedding and the append part of the QKV projection: those classes then have no launches of their own.) */
+ * time is the sum of its two kernels.  With few rows (at most 16, fewer the wider the model) the norms are part of the
+ * projections behind them and the rotary embedding and the append part of the QKV projection: those classes then
+ * have no launches of their own.) */
 enum {
     CHIRON_K_QKV = 0, CHIRON_K_O, CHIRON_K_GATEUP, CHIRON_K_DOWN, CHIRON_K_LMHEAD, CHIRON_K_ATTN, CHIRON_K_ATTN_MERGE,
     CHIRON_K_RMSNORM, CHIRON_K_ROPE_APPEND, CHIRON_K_OTHER, CHIRON_K_COUNT

@@ -333,8 +333,8 @@ static int32_t step_rows(chiron_model* m, chiron_kvpool* p, const int32_t* block
     int ks_res = 0, ks_qkv = 1;  // K-slices waiting in m->part for the residual stream / of the QKV projection
     STEP(CHIRON_K_OTHER, launch_step_begin(m->aws, seq_lens, block_table, mb, ash, n_req, c.n_kv_heads, m->embed, tokens, H, m->h, d,
                                            c.rope_base, m->cos_t, m->sin_t, st));
-    if (linear_few_rows(B)) {
-        // Up to 16 rows six launches a layer instead of nine: the projections into the residual stream complete it (no
+    if (step_few_rows(m->qkv[0], m->wo[0], m->down[0], B)) {
+        // With few rows six launches a layer instead of nine: the projections into the residual stream complete it (no
         // K-slices for anybody to add), so the norms move into the operand loads of the projections behind them, and the
         // QKV projection rotates and appends by itself.
         for (int l = 0; l < c.n_layers; ++l) {
@@ -680,7 +680,7 @@ struct OpScratch {
 };
 static OpScratch op_linear_scratch(const Linear& L, int M, int prologue, bool in_place = false) {
     OpScratch sc;
-    if (prologue == PRO_NONE && linear_few_rows(M) && L.N <= 16384 && !in_place) return sc;  // the few-row path needs none
+    if (prologue == PRO_NONE && !in_place && linear_few_pays(L, M)) return sc;  // the few-row path needs none
     const bool split = prologue == PRO_NONE && tuning().linear_big_all && M >= linear_big_min_rows(L);
     if (split) sc.split_bytes = 2 * linear_big_split_elems(M, L.Kpad) * 2;
     // wide outputs (LM head, gate/up) have enough column tiles on their own and are never sliced in the step
@@ -697,8 +697,7 @@ static OpScratch op_linear_scratch(const Linear& L, int M, int prologue, bool in
 // product goes to the scratch memory whole, sliced or not, and the sum of the slices brings it to y.
 static int32_t op_linear_common(const Linear& L, const float* x, int lda, int M, float* y, int accumulate, int prologue,
                                 const OpScratch& sc, void* scratch, hipStream_t st, bool in_place = false) {
-    // few rows: one launch (very wide outputs have enough column tiles for the tiled kernel)
-    if (prologue == PRO_NONE && linear_few_rows(M) && L.N <= 16384 && !in_place) return launch_linear_few(L, x, lda, M, 0, y, L.N, accumulate, st);
+    if (prologue == PRO_NONE && !in_place && linear_few_pays(L, M)) return launch_linear_few(L, x, lda, M, 0, y, L.N, accumulate, st);
     float* part = sc.part_bytes ? (float*)scratch : nullptr;
     uint16_t* asplit = sc.split_bytes ? (uint16_t*)((char*)scratch + sc.part_bytes) : nullptr;
     int ks = 1;
@@ -747,7 +746,7 @@ int32_t chiron_op_swiglu_ffn(const chiron_linear* gate_up, const chiron_linear* 
     if (D.K != F) return fail(CHIRON_ERR_SHAPE, "swiglu_ffn: gate/up has %d columns, the down projection %d inputs", F, D.K);
     hipStream_t st = (hipStream_t)stream;
     // the intermediate in the form the decode step gives it at this row count
-    const bool few = linear_few_rows(M) && D.N <= 16384;
+    const bool few = linear_few_pays_packed(D, M);
     const bool packed = !few && M >= linear_big_min_rows(D);
     const size_t bytes = ((packed ? 2 * linear_big_split_elems(M, D.Kpad) * 2 : (size_t)M * D.Kpad * 4) + 255) / 256 * 256;
     const OpScratch sc = few ? OpScratch() : op_linear_scratch(D, M, packed ? PRO_PACKED : PRO_NONE);

@@ -8,13 +8,13 @@
 // The waves share nothing until the end: each loads its weights and its activations (fp32, from L2) straight into operand
 // registers (v_mfma_f32_16x16x32_bf16, weights as A, 16 activation rows as B, two bf16 terms each), 8 k-steps of 32 ahead;
 // no LDS and no barrier in the loop.  Every workgroup reads all rows of its input, which is what ends the range: at 16 rows
-// the activations of a 4096-wide input are as many bytes per workgroup (256 KiB) as the weights of its 32 columns.
+// the activations of a 4096-wide input are as many bytes per workgroup (256 KiB) as the weights of its 32 columns.  Where
+// that is depends on the widths: see "which rows take this path" below.
 //
 // Measured per layer at the 8B widths and one row, against the tiled kernels with the norms and the rotary embedding as
 // launches of their own: QKV 12.2 us (11.4 + 4.8 + 4.7), O 7.4 (8.2; 4.5 TB/s with the launch), gate/up with its norm 38.8
 // (37.7 + 4.8), down 20.6 (19.6; 5.7 TB/s); four layers and the head 575 -> 522 us, 664 -> 623 at 11 rows.  A single
-// projection of 4096 x 4096 with its K-slices summed 27 -> 7.7 us.  At 16 rows down is level with the tiled kernel and the
-// norm it saves (26 against 20 + 5 us) and the others gain; beyond, the activation loads outweigh the launches.
+// projection of 4096 x 4096 with its K-slices summed 27 -> 7.7 us.
 // Rings of 12 or 16 k-steps were slower (8.4 .. 9.0 against 7.7 us at 4096 x 4096), as bytes in flight are not what is short.
 #include "chiron_internal.h"
 #include "device_util.h"
@@ -209,9 +209,65 @@ __global__ __launch_bounds__(64 * kFewWaves) void linear_few_kernel(const uint16
     }
 }
 
+// ---- which rows take this path -------------------------------------------------------------------------------
 bool linear_few_rows(int M) {
     const Tuning& t = tuning();
     return M <= 16 && !t.linear_mt && !t.linear_nf && !t.linear_ksplit && !t.linear_ks && !t.linear_big_all;
+}
+
+// 16-column tiles per workgroup.  Two (half as many loads of the same activations) where that still gives every CU a workgroup:
+// 8192 outputs of 28672 inputs 68 against 75 us at one row, 72 against 89 us at 8; 4096 outputs of 14336 inputs 25 against 20 us
+static int few_col_tiles(const Linear& L) { return (L.N + 31) / 32 >= kNumCU ? 2 : 1; }
+
+// Time of the kernel above at M rows, in microseconds: a launch's start and end, and the longest of
+//   the weight stream at 7.2 TB/s;
+//   what one CU takes in, weights and activations of its workgroups: 50 GB/s (fp32 rows; 45 with the rotation behind them,
+//     70 for packed terms), and 27 (one column tile) or 31 GB/s of weights for workgroups that share a CU while others idle;
+//   what all CUs together take in: 12 TB/s, of fp32 rows less the longer K is (10.4 at 28672).
+// The rates are fitted to single projections of 256 .. 16384 columns, K = 1024 .. 32768, and to the layers of 15 decoders of
+// 256 .. 16384 hidden columns, at 1 .. 16 rows; it is within 10 % of most of them (8B widths at 16 rows: 61 against 60 us for
+// QKV, O and down; 5120 wide with 40 KV heads: 119 against 126).
+static double few_us(const Linear& L, int M, FewMode mode) {
+    const int ct = mode == FEW_QKV ? 2 : few_col_tiles(L);
+    const int wgs = (L.N + 16 * ct - 1) / (16 * ct), rounds = (wgs + kNumCU - 1) / kNumCU;
+    const double w = 32e-6 * ct * L.K, a = 4e-6 * M * L.K;  // MB of weights and activations per workgroup
+    const double cu = mode == FEW_QKV ? 0.045 : (mode == FEW_PACKED ? 0.070 : 0.050);  // MB/us
+    const double chip = mode == FEW_PACKED ? 12.0 : 12.2 - L.K / 16000.0;
+    double t = wgs * w / 7.2;
+    const auto at_least = [&](double v) { t = v > t ? v : t; };
+    at_least(rounds * (w + a) / cu);
+    at_least((rounds > 1 ? rounds * kNumCU : wgs) * (w + a) / chip);
+    if (rounds > 1) at_least(rounds * w / (ct == 1 ? 0.027 : 0.031));
+    return 4.0 + t;
+}
+// the tiled kernel's, whose K-slices fill the chip evenly; it hardly depends on the rows there
+static double tiled_us(const Linear& L) { return 3.5 + 2e-6 * L.N * L.K / 6.6; }
+
+// A whole layer: what the few-row QKV, O and down projections take longer than the tiled ones must stay below the two norms and
+// the rotation that become part of them (13.6 us up to 4096 columns, 20 at 8192, 25 at 16384, less what the norm costs where it
+// goes).  Measured end to end, us per layer gained by this path at 1 / 8 / 12 / 16 rows: 8B widths 9 / 6 / 1 / -4, 70B widths
+// 8 / 7 / 2 / -9, 6144 wide (384 workgroups) 0 / -9 / -22 / -36, 12288 wide 6 / -12 / -23 / -51, 5120 wide with 40 KV heads (320 and
+// 480 workgroups) -8 / -17 / -31 / -43.  On one set of weights, whole steps by this rule are within 1 % of the better path.
+bool step_few_rows(const Linear& qkv, const Linear& o, const Linear& down, int M) {
+    if (!linear_few_rows(M)) return false;
+    const double saved = 5.9 + 1.3 / 1024 * qkv.K;
+    return few_us(qkv, M, FEW_QKV) + few_us(o, M, FEW_ROWS) + few_us(down, M, FEW_PACKED) <=
+           tiled_us(qkv) + tiled_us(o) + tiled_us(down) + (saved > 13.0 ? saved : 13.0);
+}
+
+// A projection by itself: against the tiled kernel, the sum of its slices (5 us), and no less than the 27 us that the host takes to
+// enqueue the two with their scratch memory.  A long K without a workgroup for every CU is a serial chain that nothing hides
+// (2048 x 28672, one row: 33 against 29 us).  4096 x 14336: 24 against 28 us at 8 rows, 33 against 30 at 16; 10240 x 28672 (320
+// workgroups): 112 against 98 at one row.  Very wide outputs have enough column tiles for the tiled kernel unsliced.
+bool linear_few_pays(const Linear& L, int M) {
+    if (!linear_few_rows(M) || L.N > 16384 || (L.K > 16384 && L.N < 4096)) return false;
+    const double tiled = 5.0 + tiled_us(L);
+    return few_us(L, M, FEW_ROWS) <= (tiled > 27.0 ? tiled : 27.0);
+}
+
+// the same for the down projection of a feed-forward block, whose scratch memory is there anyway
+bool linear_few_pays_packed(const Linear& L, int M) {
+    return linear_few_rows(M) && L.N <= 16384 && few_us(L, M, FEW_PACKED) <= 5.0 + tiled_us(L);
 }
 
 int32_t launch_linear_few(const Linear& L, const float* A, int64_t lda, int M, int packed, float* y, int ldy, int add, hipStream_t st) {
@@ -219,9 +275,7 @@ int32_t launch_linear_few(const Linear& L, const float* A, int64_t lda, int M, i
     if (M > 16) return fail(CHIRON_ERR_INVALID_ARG, "linear: %d rows on the few-row path", M);
     if (L.K % 16 != 0 || L.K < 16) return fail(CHIRON_ERR_SHAPE, "linear: K=%d must be a positive multiple of 16", L.K);
     if ((!packed && lda % 4 != 0) || ((uintptr_t)A & 15)) return fail(CHIRON_ERR_INVALID_ARG, "linear: input rows must be 16-byte aligned");
-    // 32 columns per workgroup (half as many loads of the same activations) where that still gives every CU one:
-    // 8192 outputs of 28672 inputs 68 against 75 us at one row, 72 against 89 us at 8; 4096 outputs of 14336 inputs 25 against 20 us
-    const int ct = (L.N + 31) / 32 >= kNumCU ? 2 : 1;
+    const int ct = few_col_tiles(L);
     const dim3 grid((L.N + 16 * ct - 1) / (16 * ct)), block(64 * kFewWaves);
 #define CHIRON_FEW(CT_, MODE_) \
     launch(linear_few_kernel<CT_, MODE_>, grid, block, st, L.w, L.tstride, L.N, L.K, L.Kpad, A, lda, M, (const uint16_t*)nullptr, 0.f, y, ldy, add, RopeOut())

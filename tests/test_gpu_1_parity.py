@@ -714,6 +714,16 @@ G4_D128 = dict(I.TINY, head_dim=128, n_kv_heads=2, n_q_heads=8)
 G8_D128 = dict(I.TINY, head_dim=128, n_kv_heads=1, n_q_heads=8)
 
 
+def norm_launches(g, step):
+    """(result, launches of the norm by itself: none on the few-row path)"""
+    B().kernel_timing_begin(g.model)
+    try:
+        out = step()
+    finally:
+        kt = B().kernel_timing_end(g.model)
+    return out, kt["rmsnorm"][1]
+
+
 @pytest.mark.parametrize("m,batch,T", [(I.TINY, 1, 1), (I.TINY, 16, 1), (G4_D128, 5, 3), (dict(I.TINY, hidden=2320, ffn=272, vocab=8400), 16, 1),
                                        (dict(G4_D128, n_q_heads=2, n_kv_heads=2, hidden=272, vocab=33000), 3, 5)])
 def test_step_of_few_rows_equals_the_general_path(m, batch, T):
@@ -734,9 +744,10 @@ def test_step_of_few_rows_equals_the_general_path(m, batch, T):
         print("few rows", m["name"], batch, T, "mt", mt, flush=True)
         b.set_tuning("linear_mt", mt)
         try:
-            lg = b.decode_step_multi(g.model, g.pool, g.block_table, sl, tok)
+            lg, norms = norm_launches(g, lambda: b.decode_step_multi(g.model, g.pool, g.block_table, sl, tok))
         finally:
             b.set_tuning("linear_mt", 0)
+        assert norms == (2 * m["n_layers"] + 1 if mt else 0)  # which path ran
         kv = [g.pool.gather(l, g.block_table[i], int(lens[i]) + T) for l in range(m["n_layers"]) for i in range(batch)]
         out.append((lg.cpu().numpy().reshape(batch * T, -1), [x.float().cpu().numpy() for p in kv for x in p]))
     (lg0, kv0), (lg1, kv1) = out
@@ -745,6 +756,29 @@ def test_step_of_few_rows_equals_the_general_path(m, batch, T):
         tol = KERNEL_TOL if j < 2 * batch else 2e-3
         assert np.all(np.abs(x - y) <= 2.0 ** -7 * np.abs(y) + tol * y.std())
         assert np.mean(x != y) <= 0.02
+
+
+def test_the_few_row_path_ends_where_its_activations_outweigh_it():
+    """480 and 320 workgroups of 5120 inputs each on 256 CUs: one row takes the few-row path, 16 rows do not.  The same holds for a
+    projection by itself, which shows in nothing but time: both sides of its range against the oracle."""
+    m = dict(I.TINY, name="wide", n_layers=1, hidden=5120, n_q_heads=40, n_kv_heads=40, head_dim=128, ffn=16, vocab=64)
+    c = make_case(m=m, seed=43, storage="bf16", seq_lens=np.arange(20, 36, dtype=np.int32))
+    g = gpu_setup(c)
+    b = B()
+    out = []
+    for n in (16, 1):
+        print("range of the few-row path", n, flush=True)
+        lg, norms = norm_launches(g, lambda: b.decode_step(g.model, g.pool, g.block_table, g.seq_lens, g.tokens, batch=n))
+        assert norms == (3 if n == 16 else 0)
+        out.append(lg[0].cpu().numpy())
+    assert np.abs(out[0] - out[1]).max() <= 2e-3 * out[0].std()
+    for M, N, K in ((8, 4096, 14336), (16, 4096, 14336), (1, 256, 28672), (16, 10240, 4096)):
+        x = np.random.default_rng(M + N).standard_normal((M, K)).astype(np.float32)
+        W = I.normal((N, K), 0.02, 5, "wr", N, K)
+        lin = b.Linear(W.cuda())
+        want = orc.linear(x[:2], I.to_numpy_storage(W))
+        assert rel_err(lin(torch.from_numpy(x).cuda()).cpu().numpy()[:2], want) <= KERNEL_TOL
+        lin.close()
 
 
 @pytest.mark.parametrize("m,T", [(I.TINY, 2), (I.TINY, 4), (I.TINY, 8), (I.TINY, 9), (I.TINY, 17), (G4_D128, 4), (G4_D128, 3),
