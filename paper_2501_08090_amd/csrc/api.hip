@@ -1,12 +1,14 @@
 // Host side of the C ABI (include/chiron.h, include/chiron_ops.h): handles, argument checks,
 // weight loading, and the sequence of kernel launches that makes one decode step.
 #include <algorithm>
+#include <chrono>
 #include <cmath>
 #include <cstdarg>
 #include <cstdio>
 #include <cstring>
 #include <mutex>
 #include <new>
+#include <thread>
 #include <unordered_set>
 #include <vector>
 
@@ -32,9 +34,36 @@ int32_t fail(int32_t code, const char* fmt, ...) {
 // smallest max_batch for which the model carries the workspace of the large-batch projection kernel
 static constexpr int kBigWorkspaceMinBatch = 96;
 
+// Scratch memory of the single-projection entry points.  From the default pool every call after a synchronisation
+// pays for fresh memory (0.1 .. 0.7 ms), because that pool gives everything back at once.  This one, per device, keeps
+// up to kScratchKeep bytes while a chiron_linear of the device exists; the last one's destruction gives them back, and so does
+// an allocation of this library that finds the device full.  The runtime orders reuse by stream, so threads and streams need
+// nothing more.
+static constexpr uint64_t kScratchKeep = (uint64_t)1 << 30;
+static constexpr int kScratchDevices = 64;
+static struct {
+    hipMemPool_t pool;
+    int users;
+} g_scratch_pool[kScratchDevices];
+static std::mutex g_scratch_pool_mutex;
+
+// gives back what the device's pool keeps and nobody uses; false if there is no pool
+static bool scratch_pool_trim(int dev) {
+    if (dev < 0 || dev >= kScratchDevices) return false;
+    std::lock_guard<std::mutex> lock(g_scratch_pool_mutex);
+    return g_scratch_pool[dev].pool && hipMemPoolTrimTo(g_scratch_pool[dev].pool, 0) == hipSuccess;
+}
+
 static int32_t dev_alloc(void** p, size_t bytes) {
     *p = nullptr;
     hipError_t e = hipMalloc(p, bytes ? bytes : 256);
+    int dev = -1;
+    if (e == hipErrorOutOfMemory && hipGetDevice(&dev) == hipSuccess && scratch_pool_trim(dev))
+        for (int i = 0; i < 10 && e == hipErrorOutOfMemory; ++i) {  // the driver takes some milliseconds to free what was given back
+            (void)hipGetLastError();
+            std::this_thread::sleep_for(std::chrono::milliseconds(10));
+            e = hipMalloc(p, bytes ? bytes : 256);
+        }
     if (e != hipSuccess) {
         *p = nullptr;
         (void)hipGetLastError();
@@ -560,18 +589,6 @@ int32_t chiron_op_rmsnorm(const float* h, const void* gain, int32_t rows, int32_
     return launch_rmsnorm(const_cast<float*>(h), nullptr, 0, (const uint16_t*)gain, rows, n, eps, out, (hipStream_t)stream);
 }
 
-// Scratch memory of the single-projection entry points.  From the default pool every call after a synchronisation
-// pays for fresh memory (0.1 .. 0.7 ms), because that pool gives everything back at once.  This one, per device, keeps
-// up to kScratchKeep bytes while a chiron_linear of the device exists; the last one's destruction gives them back.  The runtime
-// orders reuse by stream, so threads and streams need nothing more.
-static constexpr uint64_t kScratchKeep = (uint64_t)1 << 30;
-static constexpr int kScratchDevices = 64;
-static struct {
-    hipMemPool_t pool;
-    int users;
-} g_scratch_pool[kScratchDevices];
-static std::mutex g_scratch_pool_mutex;
-
 // the device whose pool a new chiron_linear keeps, or -1 if there is none (its calls then use the default pool)
 static int scratch_pool_enter() {
     int dev = -1;
@@ -607,17 +624,20 @@ static int32_t scratch_alloc(int dev, void** out, size_t bytes, hipStream_t st) 
     *out = nullptr;
     if (bytes == 0) return CHIRON_OK;
     // (a stream that is being captured, or one of another device, takes the default pool as any allocation does)
-    bool own = false;
-    int cur = -1;
-    if (dev >= 0 && hipGetDevice(&cur) == hipSuccess && cur == dev) {
+    if (dev >= 0) {
         hipStreamCaptureStatus cap = hipStreamCaptureStatusActive;
-        own = hipStreamIsCapturing(st, &cap) == hipSuccess && cap == hipStreamCaptureStatusNone;
-        if (!own) (void)hipGetLastError();
+        int of_stream = -1;
+        hipError_t e = hipStreamIsCapturing(st, &cap);
+        if (e == hipSuccess && cap == hipStreamCaptureStatusNone) e = st ? hipStreamGetDevice(st, &of_stream) : hipGetDevice(&of_stream);
+        if (e == hipSuccess && of_stream == dev) {
+            e = hipMallocFromPoolAsync(out, bytes, g_scratch_pool[dev].pool, st);
+            if (e == hipSuccess) return CHIRON_OK;
+            (void)scratch_pool_trim(dev);  // the default pool may then find the memory
+            *out = nullptr;
+        }
+        if (e != hipSuccess) (void)hipGetLastError();
     }
-    if (own)
-        CHIRON_HIP(hipMallocFromPoolAsync(out, bytes, g_scratch_pool[dev].pool, st));
-    else
-        CHIRON_HIP(hipMallocAsync(out, bytes, st));
+    CHIRON_HIP(hipMallocAsync(out, bytes, st));
     return CHIRON_OK;
 }
 

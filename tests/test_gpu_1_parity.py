@@ -2,6 +2,7 @@
 seeded inputs.  Index work (slots, gathers) must be bit-exact; floating point within the
 stated tolerances.  Needs a real MI355X: run with -m gpu."""
 import math
+import time
 
 import numpy as np
 import pytest
@@ -547,6 +548,32 @@ def test_projections_on_two_streams_share_the_scratch_pool():
     lin[1].close(); gu.close(); down.close()
     assert torch.equal(lin[0](x), want[0])
     lin[0].close()
+
+
+def test_a_full_device_gets_the_scratch_pool_back():
+    """The pool keeps what a feed-forward block of 4096 rows used (235 MB); an allocation of the library that fails (2^47 bytes: on
+    any device) gives that back before it is reported, and the block runs again."""
+    import ctypes as C
+    b = B()
+    x, Wg, Wu, Wd, _, want = ffn_case(8, 64, 14336, 64, 3)
+    gu, down = b.GateUp(Wg.cuda(), Wu.cuda()), b.Linear(Wd.cuda())
+    xd = torch.from_numpy(np.tile(x, (512, 1))).cuda()
+    y = torch.empty((4096, 64), device="cuda")
+    gu.ffn(down, xd, y)
+    torch.cuda.synchronize()
+    kept = torch.cuda.mem_get_info()[0]
+    h = C.c_void_p()
+    rc = b.load().chiron_linear_create(b._ptr(Wd.cuda()), C.c_int32(1 << 30), C.c_int32(1 << 16), b._stream(), C.byref(h))
+    assert rc == -5 and not h.value  # CHIRON_ERR_OOM
+    for _ in range(40):  # the driver frees with some delay
+        if torch.cuda.mem_get_info()[0] - kept >= 200 << 20:
+            break
+        time.sleep(0.05)
+    else:
+        pytest.fail("the pool kept its memory")
+    gu.ffn(down, xd, y)
+    assert rel_err(y[:8].cpu().numpy(), want) <= KERNEL_TOL and torch.equal(y[:8], y[8:16])
+    gu.close(); down.close()
 
 
 @pytest.mark.parametrize("batch", [1023, 2048, 2051])
