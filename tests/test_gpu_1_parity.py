@@ -626,6 +626,16 @@ def test_paged_attention_work_list_over_several_rounds(grid, chunk):
 
 # ---- the whole step ---------------------------------------------------------------------------------
 
+def norm_launches(g, step):
+    """(result, launches of the norm by itself: none on the few-row path)"""
+    B().kernel_timing_begin(g.model)
+    try:
+        out = step()
+    finally:
+        kt = B().kernel_timing_end(g.model)
+    return out, kt["rmsnorm"][1]
+
+
 def run_both(c, g=None, poison=False):
     g = g or gpu_setup(c, poison=poison)
     logits = B().decode_step(g.model, g.pool, g.block_table, g.seq_lens, g.tokens)
@@ -644,6 +654,118 @@ def check_logits(got, want, min_agree=0.99):
     assert err <= STEP_TOL
     assert agree >= min_agree
     return err
+
+
+# pages per request of lists that 32 wave slots (16 items of either KV head) hold in one round with items of more than 64 pages:
+# mixed lengths, a search that ends at its lower bound (one request in 16 items of 128) and at its upper one (158), and one
+# list that misses by a single item, which takes items of 64 pages drawn from the ticket counters
+@pytest.mark.parametrize("pages", [[563, 75, 2063], [2048], [316, 433, 336, 5, 793, 21], [783, 65, 262, 121, 508, 780, 461]])
+def test_paged_attention_one_round_of_long_items(pages):
+    d, nq, nkv = 64, 4, 2
+    lens = (16 * np.asarray(pages) - np.arange(len(pages)) % 16).astype(np.int32)
+    c = make_case(m=dict(I.TINY, n_layers=1, head_dim=d, n_q_heads=nq, n_kv_heads=nkv, vocab=64, ffn=16), seed=29, storage="bf16", seq_lens=lens,
+                  poison_unused=True)
+    g = gpu_setup(c, poison=True)
+    opool = fresh_pool(c)
+    q = (np.random.default_rng(30).standard_normal((len(lens), nq * d)) * 1.3).astype(np.float32)
+    b = B()
+    b.set_tuning("attn_grid", 8)
+    try:
+        print("attention, one round", pages, flush=True)
+        got = b.op_paged_attention(g.model, g.pool, 0, torch.from_numpy(q).cuda(), g.block_table, g.seq_lens).cpu().numpy()
+    finally:
+        b.set_tuning("attn_grid", 0)
+    for i in range(len(lens)):
+        want = orc.paged_attention(opool, 0, c.block_table[i], int(lens[i]), q[i].reshape(nq, d)).reshape(-1)
+        assert np.abs(got[i] - want).max() <= KERNEL_TOL * max(1.0, np.abs(want).max()), i
+
+
+def test_multi_token_step_with_long_items():
+    """The same with 11 new tokens per request, two passes each (token groups of 8 and 3): items of 94 pages in one round
+    of 64 slots against items of 16 pages."""
+    T, lens = 11, np.array([9000, 700, 12000], np.int32)
+    c = make_case(m=dict(I.TINY, vocab=64), seed=31, storage="bf16", seq_lens=lens)
+    g = gpu_setup(c, max_batch=3 * T)
+    b = B()
+    sl = torch.from_numpy(lens - T).cuda()
+    tok = torch.from_numpy(np.random.default_rng(32).integers(0, 64, (3, T)).astype(np.int32)).cuda()
+    out = []
+    b.set_tuning("attn_grid", 16)
+    try:
+        for chunk in (0, 16):
+            print("multi-token step, long items, chunk", chunk, flush=True)
+            b.set_tuning("attn_chunk_pages", chunk)
+            out.append(b.decode_step_multi(g.model, g.pool, g.block_table, sl, tok).cpu().numpy())
+    finally:
+        b.set_tuning("attn_grid", 0)
+        b.set_tuning("attn_chunk_pages", 0)
+    assert np.all(np.isfinite(out[0]))
+    assert np.abs(out[0] - out[1]).max() <= 2e-3 * out[1].std()
+
+
+def step_64(c, tok, newkv):
+    """(logits, k, v) of a step in 64 bits, tok [batch, T]; the attention of layer l sees the K and V that the library wrote for
+    the new tokens, newkv[l] = (k, v) [batch, T, heads, d], so that a value that rounds to the other bf16 neighbour is not
+    carried on; k, v [layer] are the unrounded ones"""
+    m = c.m
+    d, nkv, G, T = m["head_dim"], m["n_kv_heads"], m["n_q_heads"] // m["n_kv_heads"], tok.shape[1]
+    t64 = lambda a: torch.from_numpy(as_f64(a))
+    W = {k: ([t64(a) for a in v] if isinstance(v, list) else t64(v)) for k, v in c.w.items()}
+    norm = lambda h, gain: h / torch.sqrt((h * h).mean(-1, keepdim=True) + m["rms_eps"]) * gain
+    pos = torch.from_numpy(c.seq_lens.astype(np.int64))[:, None] + torch.arange(T)
+    ang = pos[..., None] * m["rope_base"] ** (-2.0 * torch.arange(d // 2, dtype=torch.float64) / d)
+    cs, sn = ang.cos()[:, :, None], ang.sin()[:, :, None]
+    rope = lambda x: torch.cat([x[..., :d // 2] * cs - x[..., d // 2:] * sn, x[..., d // 2:] * cs + x[..., :d // 2] * sn], -1)
+    ends = np.cumsum(c.seq_lens)
+    h, kvs = W["embed"][torch.from_numpy(tok).long()], []
+    for l in range(m["n_layers"]):
+        x = norm(h, W["attn_norm"][l])
+        q, k, v = ((x @ W[n][l].T).view(c.batch, T, -1, d) for n in ("wq", "wk", "wv"))
+        q, k = rope(q), rope(k)
+        kvs.append((k, v))
+        a = torch.empty(c.batch, T, m["n_q_heads"] * d, dtype=torch.float64)
+        for i, (e, n) in enumerate(zip(ends, c.seq_lens)):
+            K, V = (torch.cat([t64(c.kv[l][j][e - n:e]), newkv[l][j][i].double()]) for j in (0, 1))
+            for t in range(T):
+                s = torch.einsum("khd,nkd->khn", q[i, t].view(nkv, G, d), K[:n + t + 1]) / math.sqrt(d)
+                a[i, t] = torch.einsum("khn,nkd->khd", torch.softmax(s, -1), V[:n + t + 1]).reshape(-1)
+        h = h + a @ W["wo"][l].T
+        x = norm(h, W["ffn_norm"][l])
+        h = h + (torch.nn.functional.silu(x @ W["w_gate"][l].T) * (x @ W["w_up"][l].T)) @ W["w_down"][l].T
+    return norm(h, W["final_norm"]) @ W["lm_head"].T, kvs
+
+
+@pytest.mark.parametrize("batch,T,mt", [(1, 1, 0), (11, 1, 0), (3, 5, 0), (11, 1, 1), (20, 1, 0)])
+def test_step_against_64_bits(batch, T, mt):
+    """Few-row path, the general path on the same rows (mt = 1), and more rows: logits and new K and V.  An activation enters
+    the matrix cores with a relative error of at most 2^-17, once in each of a layer's five products and in p V, and in the
+    head's: 13 of them here, 1e-4 in all (measured 1e-5).  A new K or V is that far from the 64-bit value, plus its rounding to
+    bf16.  The step repeats itself bit by bit."""
+    m = dict(I.TINY, n_layers=2, hidden=1040, n_q_heads=16, n_kv_heads=4, ffn=2064, vocab=1009)
+    lens = np.random.default_rng(batch + T).integers(0, 200, batch).astype(np.int32)
+    c = make_case(m=m, seed=44, storage="bf16", gain_jitter=0.2, seq_lens=lens)
+    c.block_table, c.num_blocks = I.make_block_table(lens + T - 1, seed=44, pool_factor=2.0)
+    g = gpu_setup(c, max_batch=batch * T)
+    tok = I.token_ids(batch * T, m["vocab"], 7).reshape(batch, T)
+    b = B()
+    b.set_tuning("linear_mt", mt)
+    try:
+        print("64 bits", batch, T, mt, flush=True)
+        step = lambda: b.decode_step_multi(g.model, g.pool, g.block_table, g.seq_lens, torch.from_numpy(tok).cuda())
+        got, norms = norm_launches(g, step)
+        assert (norms == 0) == (batch * T <= 16 and not mt)
+        assert torch.equal(step(), got)
+    finally:
+        b.set_tuning("linear_mt", 0)
+    kv = [[g.pool.gather(l, g.block_table[i].contiguous(), int(lens[i]) + T) for i in range(batch)] for l in range(2)]
+    kv = [tuple(torch.stack([x[j][-T:] for x in row]).cpu() for j in (0, 1)) for row in kv]
+    want, kvs = step_64(c, tok, kv)
+    err = float((got.cpu().double() - want).norm() / want.norm())
+    print("relative error of the logits %.2e" % err, flush=True)
+    assert err <= 1e-4
+    for have, exact in zip(kv, kvs):
+        for x, y in zip(have, exact):
+            assert bool(((x.double() - y).abs() <= 2.0 ** -8 * y.abs() + 1e-4 * y.std()).all())
 
 
 @pytest.mark.parametrize("seed,jitter", [(0, 0.0), (1, 0.2)])
@@ -739,16 +861,6 @@ def test_decode_step_over_seeded_random_geometries():
 
 G4_D128 = dict(I.TINY, head_dim=128, n_kv_heads=2, n_q_heads=8)
 G8_D128 = dict(I.TINY, head_dim=128, n_kv_heads=1, n_q_heads=8)
-
-
-def norm_launches(g, step):
-    """(result, launches of the norm by itself: none on the few-row path)"""
-    B().kernel_timing_begin(g.model)
-    try:
-        out = step()
-    finally:
-        kt = B().kernel_timing_end(g.model)
-    return out, kt["rmsnorm"][1]
 
 
 @pytest.mark.parametrize("m,batch,T", [(I.TINY, 1, 1), (I.TINY, 16, 1), (G4_D128, 5, 3), (dict(I.TINY, hidden=2320, ffn=272, vocab=8400), 16, 1),
