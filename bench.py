@@ -25,9 +25,9 @@ MFMA_BF16_PEAK_TFLOPS = 2500.0
 
 # HBM bytes per launch from rocprofv3 --pmc FETCH_SIZE / WRITE_SIZE runs (profiles/*_hbm_traffic.md), already scaled
 # by what the same counters read for a plain 1 GiB copy.  Valid only for the kernel sources they were taken on:
-# `sha` is the sha256 of the kernel's source file at that time; with any other source the figure is reported null.
+# `sha` is source_hash() of the kernel's file at that time; with any other source the figure is reported null.
 TRAFFIC = {
-    # (workload, kernel class): (source file, sha256, fetch bytes, write bytes)
+    # (workload, kernel class): (source file, source_hash, fetch bytes, write bytes)
     ("llama8b-b64-lognormal800", "attn"): ("attention.hip", "0ce537b9d8896e4bbd896f7009353995d581f7a3b2b558858f66f6781245dec8", 275691824, 4259911),
     ("llama8b-b64-lognormal800", "gateup"): ("linear.hip", "cbaa3ab9ad5e49ac9c7cea4200cf981c402d61f78b91d2d922f4b6411c8368dd", 243436004, 3670016),
     ("llama8b-b64-lognormal800", "down"): ("linear.hip", "cbaa3ab9ad5e49ac9c7cea4200cf981c402d61f78b91d2d922f4b6411c8368dd", 121338096, 16777226),
@@ -36,18 +36,34 @@ TRAFFIC = {
 }
 
 
-def measured_traffic(workload, kclass):
+def source_hash(src, csrc=os.path.join(ROOT, "paper_2501_08090_amd", "csrc")):
+    """sha256 over a kernel's source file and the headers beside it that it includes, directly or through another (what an
+    item of attention holds, for one, is decided in a header); None if a file is missing"""
     import hashlib
+    import re
+    todo, texts = [src], {}
+    while todo:
+        name = todo.pop()
+        if name in texts:
+            continue
+        try:
+            with open(os.path.join(csrc, name), "rb") as f:
+                texts[name] = f.read()
+        except OSError:
+            return None
+        todo += [inc for inc in re.findall(r'^#include "([^"/]+)"', texts[name].decode(), re.M)]
+    h = hashlib.sha256()
+    for name in sorted(texts):
+        h.update(name.encode() + b"\0" + texts[name] + b"\0")
+    return h.hexdigest()
+
+
+def measured_traffic(workload, kclass):
     ent = TRAFFIC.get((workload, kclass))
     if not ent:
         return None
     src, sha, fetch, write = ent
-    path = os.path.join(ROOT, "paper_2501_08090_amd", "csrc", src)
-    try:
-        cur = hashlib.sha256(open(path, "rb").read()).hexdigest()
-    except OSError:
-        return None
-    return dict(fetch_bytes=fetch, write_bytes=write, total_bytes=fetch + write) if cur == sha else None
+    return dict(fetch_bytes=fetch, write_bytes=write, total_bytes=fetch + write) if source_hash(src) == sha else None
 
 
 def cpu_model():
