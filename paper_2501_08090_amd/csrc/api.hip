@@ -359,6 +359,9 @@ static int32_t step_rows(chiron_model* m, chiron_kvpool* p, const int32_t* block
         if ((rc = (expr))) return rc; \
     } while (0)
     const int msplit = linear_max_split();
+    // m->asplit holds zeros where the down projection reads the padding of its input, from the model's creation on; only the other
+    // projections' split inputs (a knob) can leave anything else there, NaN of one request included
+    const bool dirty = m->asplit && tuning().linear_big_all;
     int ks_res = 0, ks_qkv = 1;  // K-slices waiting in m->part for the residual stream / of the QKV projection
     STEP(CHIRON_K_OTHER, launch_step_begin(m->aws, seq_lens, block_table, mb, ash, n_req, c.n_kv_heads, m->embed, tokens, H, m->h, d,
                                            c.rope_base, m->cos_t, m->sin_t, st));
@@ -406,6 +409,7 @@ static int32_t step_rows(chiron_model* m, chiron_kvpool* p, const int32_t* block
         // a = silu(x Wg) * (x Wu) leaves the gate/up projection as fp32 rows, or, with many rows, as the tiled bf16 terms
         // that the down projection copies straight into LDS
         if (ffn_packed(m->down[l], B, m->asplit)) {
+            if (dirty) STEP(CHIRON_K_OTHER, launch_clear_k_padding(m->asplit, B, F, m->down[l].Kpad, st));
             STEP(CHIRON_K_GATEUP, launch_linear(m->gu[l], m->x, H, B, reinterpret_cast<float*>(m->asplit), m->down[l].Kpad, EPI_SWIGLU_PACKED,
                                                 PRO_NONE, nullptr, 1, nullptr, nullptr, st));
             STEP(CHIRON_K_DOWN, launch_linear(m->down[l], reinterpret_cast<const float*>(m->asplit), 0, B, m->h, H, EPI_ADD, PRO_PACKED,
@@ -418,6 +422,7 @@ static int32_t step_rows(chiron_model* m, chiron_kvpool* p, const int32_t* block
     }
     STEP(CHIRON_K_RMSNORM, launch_rmsnorm(m->h, m->part, ks_res, m->final_norm, B, H, c.rms_eps, m->x, st));
     STEP(CHIRON_K_LMHEAD, launch_linear(m->lm, m->x, H, B, logits, c.vocab, 0, PRO_NONE, nullptr, 1, nullptr, m->asplit, st));
+    if (dirty) STEP(CHIRON_K_OTHER, launch_clear_k_padding(m->asplit, c.max_batch, F, m->down[0].Kpad, st));
 #undef STEP
     return CHIRON_OK;
 }

@@ -954,6 +954,38 @@ def test_multi_token_step(m, T):
     assert e.value.code == -3
 
 
+def test_a_request_of_nan_leaves_nothing_behind_in_the_split_input():
+    """With every projection's input split into tiled terms, the workspace that holds them also holds the feed-forward
+    intermediate, whose padding (width 688 of 768) the down projection multiplies by zero: what another projection left there must
+    not be NaN.  A request whose embedding is NaN spoils its own logits and no others, in that step and in the next."""
+    c = make_case(m=dict(I.TINY, vocab=64), batch=100, kind="tiny", seed=45, storage="bf16")
+    bad = 70  # its terms lie where the padding of the first 32 rows is read
+    c.w_t["embed"][63] = float("nan")
+    c.tokens = np.where(c.tokens == 63, 0, c.tokens).astype(np.int32)
+    g = gpu_setup(c)
+    b = B()
+    spoiled = g.tokens.clone()
+    spoiled[bad] = 63
+    b.set_tuning("linear_big_all", 1)
+    b.set_tuning("linear_big_min_m", 1)
+    try:
+        print("nan in the split input", flush=True)
+        first = b.decode_step(g.model, g.pool, g.block_table, g.seq_lens, g.tokens).cpu()
+        nan = b.decode_step(g.model, g.pool, g.block_table, g.seq_lens, spoiled).cpu()
+        again = b.decode_step(g.model, g.pool, g.block_table, g.seq_lens, g.tokens).cpu()
+        b.decode_step(g.model, g.pool, g.block_table, g.seq_lens, spoiled)
+        b.set_tuning("linear_big_all", 0)  # only the intermediate is split from here on
+        plain = b.decode_step(g.model, g.pool, g.block_table, g.seq_lens, g.tokens).cpu()
+    finally:
+        b.set_tuning("linear_big_all", 0)
+        b.set_tuning("linear_big_min_m", 0)
+    others = [i for i in range(100) if i != bad]
+    assert torch.isfinite(first).all() and torch.isnan(nan[bad]).all()
+    assert torch.equal(nan[others], first[others])
+    assert torch.equal(again, first)
+    assert (plain - first).abs().max() <= 2e-3 * first.std()  # other tile shapes
+
+
 def test_continuous_batching_over_several_iterations():
     """The calls in the use the paper describes (Continuous Batching: requests join and leave the running batch between
     iterations; the queue and its lengths are the caller's): eight requests start, every iteration feeds each running
