@@ -176,6 +176,13 @@ int32_t launch_rope(float* x, int ldx, int n_heads, int d, const float* cos_t, c
 // transposes them in registers.  Copies, bounded by memory: on 8133 tokens of 8 x 128 (33 MB) the append takes
 // 21.5 us (3.1 TB/s read and written; 32 us element by element, where the 2-byte accesses were the bound), the gather of a
 // third of them 7.8 us (12.7), the append with three gathers 84 -> 46 us.
+// A wave of these kernels does the work of eight and more of the element kernels, one dependent load after the other: few
+// tokens take longer (8 x 128: append of 71 tokens 8.4 against 3.6 us, of 517, 2.1 MB of K and V, 6.2 against 5.1; gather of 517
+// tokens 4.5 against 3.8).  From about 3 MB on they win (2711 tokens of 8 x 64, 5.6 MB: append 7.0 against 8.0, gather 4.8 against 6.0).
+constexpr int64_t kVecAppendBytes = 4 << 20, kVecGatherBytes = 3 << 20;  // K and V
+static bool by_pieces(const PoolDesc& p, const void* k, const void* v, int64_t n, int64_t from_bytes) {
+    return (((uintptr_t)k | (uintptr_t)v) & 15) == 0 && n * p.n_kv * p.d * 4 >= from_bytes;
+}
 struct VPieces {
     uint4 u[8];  // piece of dim e0 + i: {e0+i: tokens 0,1 | 2,3; e0+16+i: tokens 0,1 | 2,3}
 };
@@ -276,7 +283,7 @@ __global__ __launch_bounds__(256) void append_kv_vec_kernel(PoolDesc p, int laye
     }
 }
 
-// input rows that are not 16-byte aligned
+// few tokens, and input rows that are not 16-byte aligned
 __global__ __launch_bounds__(256) void append_kv_kernel(PoolDesc p, int layer, const uint16_t* __restrict__ k,
                                                         const uint16_t* __restrict__ v, const int32_t* __restrict__ bt,
                                                         int max_blocks, const int32_t* __restrict__ seq_idx,
@@ -298,7 +305,7 @@ __global__ __launch_bounds__(256) void append_kv_kernel(PoolDesc p, int layer, c
 int32_t launch_append_kv(const PoolDesc& p, int layer, const uint16_t* k, const uint16_t* v, const int32_t* bt,
                          int max_blocks, const int32_t* seq_idx, const int32_t* pos, int64_t n, hipStream_t st) {
     if (n == 0) return CHIRON_OK;
-    if ((((uintptr_t)k | (uintptr_t)v) & 15) == 0) {
+    if (by_pieces(p, k, v, n, kVecAppendBytes)) {
         const int64_t wgs = (n + 15) / 16;
         launch(append_kv_vec_kernel, dim3((int)(wgs < 65536 ? wgs : 65536), 2), dim3(256), st, p, layer, k, v, bt, max_blocks, seq_idx, pos, n);
         CHIRON_HIP(hipGetLastError());
@@ -346,7 +353,7 @@ __global__ __launch_bounds__(256) void gather_kv_vec_kernel(PoolDesc p, int laye
     }
 }
 
-// outputs that are not 16-byte aligned
+// few tokens, and outputs that are not 16-byte aligned
 __global__ __launch_bounds__(256) void gather_kv_kernel(PoolDesc p, int layer, const int32_t* __restrict__ bt_row,
                                                         int len, uint16_t* __restrict__ k_out,
                                                         uint16_t* __restrict__ v_out) {
@@ -366,7 +373,7 @@ __global__ __launch_bounds__(256) void gather_kv_kernel(PoolDesc p, int layer, c
 int32_t launch_gather_kv(const PoolDesc& p, int layer, const int32_t* bt_row, int len, uint16_t* k_out, uint16_t* v_out,
                          hipStream_t st) {
     if (len == 0) return CHIRON_OK;
-    if ((((uintptr_t)k_out | (uintptr_t)v_out) & 15) == 0) {
+    if (by_pieces(p, k_out, v_out, len, kVecGatherBytes)) {
         const int wgs = (len + 15) / 16;
         launch(gather_kv_vec_kernel, dim3(wgs < 65536 ? wgs : 65536, 2), dim3(256), st, p, layer, bt_row, len, k_out, v_out);
         CHIRON_HIP(hipGetLastError());

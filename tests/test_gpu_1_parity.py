@@ -54,12 +54,14 @@ def test_append_gather_bit_exact(m, kind, batch):
         o += L
 
 
+@pytest.mark.parametrize("mb", [0, 4.5])
 @pytest.mark.parametrize("d,nkv", [(64, 1), (128, 8), (64, 3)])
 @pytest.mark.parametrize("order", ["in order", "offset runs", "shuffled", "unaligned"])
-def test_append_gather_any_order_and_alignment(d, nkv, order):
+def test_append_gather_any_order_and_alignment(d, nkv, order, mb):
     """Runs of four positions that start anywhere in the input, tokens without such a run, tokens in any order, and
-    rows that are not 16-byte aligned (element-wise kernels): every value lands in its slot and nowhere else."""
-    lens = [1, 7, 16, 35]
+    rows that are not 16-byte aligned: every value lands in its slot and nowhere else.  A few tokens (element-wise kernels), and
+    with a request of 4.5 MB beside them (16 bytes a lane where rows are aligned)."""
+    lens = [1, 7, 16, 35] + ([int(mb * 2 ** 20) // (4 * nkv * d) + 3] if mb else [])
     c = make_case(m=dict(I.TINY, n_layers=1, head_dim=d, n_kv_heads=nkv, n_q_heads=nkv, vocab=64, ffn=16), seed=15, storage="bf16", seq_lens=lens)
     g = gpu_setup(c)
     g.pool.memory.view(torch.int16).fill_(0x7FC0)
