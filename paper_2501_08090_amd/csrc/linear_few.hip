@@ -223,7 +223,8 @@ static int few_col_tiles(const Linear& L) { return (L.N + 31) / 32 >= kNumCU ? 2
 //   the weight stream at 7.2 TB/s;
 //   what one CU takes in, weights and activations of its workgroups: 50 GB/s (fp32 rows; 45 with the rotation behind them,
 //     70 for packed terms), and 27 (one column tile) or 31 GB/s of weights for workgroups that share a CU while others idle;
-//   what all CUs together take in: 12 TB/s, of fp32 rows less the longer K is (10.4 at 28672).
+//   what all CUs together take in: 12 TB/s, of fp32 rows less the longer K is (10.4 at 28672), and a sixth less with two
+//     column tiles if K is no multiple of 256 (16384 x 5808 and 14000 x 5008 at 16 rows: 10.0 and 9.4, 16384 x 6144: 11.5).
 // The rates are fitted to single projections of 256 .. 16384 columns, K = 1024 .. 32768, and to the layers of 15 decoders of
 // 256 .. 16384 hidden columns, at 1 .. 16 rows; it is within 10 % of most of them (8B widths at 16 rows: 61 against 60 us for
 // QKV, O and down; 5120 wide with 40 KV heads: 119 against 126).
@@ -232,7 +233,7 @@ static double few_us(const Linear& L, int M, FewMode mode) {
     const int wgs = (L.N + 16 * ct - 1) / (16 * ct), rounds = (wgs + kNumCU - 1) / kNumCU;
     const double w = 32e-6 * ct * L.K, a = 4e-6 * M * L.K;  // MB of weights and activations per workgroup
     const double cu = mode == FEW_QKV ? 0.045 : (mode == FEW_PACKED ? 0.070 : 0.050);  // MB/us
-    const double chip = mode == FEW_PACKED ? 12.0 : 12.2 - L.K / 16000.0;
+    const double chip = mode == FEW_PACKED ? 12.0 : (12.2 - L.K / 16000.0) * (ct == 2 && L.K % 256 ? 0.84 : 1.0);
     double t = wgs * w / 7.2;
     const auto at_least = [&](double v) { t = v > t ? v : t; };
     at_least(rounds * (w + a) / cu);
@@ -255,14 +256,14 @@ bool step_few_rows(const Linear& qkv, const Linear& o, const Linear& down, int M
            tiled_us(qkv) + tiled_us(o) + tiled_us(down) + (saved > 13.0 ? saved : 13.0);
 }
 
-// A projection by itself: against the tiled kernel, the sum of its slices (5 us), and no less than the 27 us that the host takes to
+// A projection by itself: against the tiled kernel, the sum of its slices (5 us), and no less than the 25 us that the host takes to
 // enqueue the two with their scratch memory.  A long K without a workgroup for every CU is a serial chain that nothing hides
 // (2048 x 28672, one row: 33 against 29 us).  4096 x 14336: 24 against 28 us at 8 rows, 33 against 30 at 16; 10240 x 28672 (320
 // workgroups): 112 against 98 at one row.  Very wide outputs have enough column tiles for the tiled kernel unsliced.
 bool linear_few_pays(const Linear& L, int M) {
     if (!linear_few_rows(M) || L.N > 16384 || (L.K > 16384 && L.N < 4096)) return false;
     const double tiled = 5.0 + tiled_us(L);
-    return few_us(L, M, FEW_ROWS) <= (tiled > 27.0 ? tiled : 27.0);
+    return few_us(L, M, FEW_ROWS) <= (tiled > 25.5 ? tiled : 25.5);
 }
 
 // the same for the down projection of a feed-forward block, whose scratch memory is there anyway
