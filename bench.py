@@ -28,11 +28,11 @@ MFMA_BF16_PEAK_TFLOPS = 2500.0
 # `sha` is source_hash() of the kernel's file at that time; with any other source the figure is reported null.
 TRAFFIC = {
     # (workload, kernel class): (source file, source_hash, fetch bytes, write bytes)
-    ("llama8b-b64-lognormal800", "attn"): ("attention.hip", "0ce537b9d8896e4bbd896f7009353995d581f7a3b2b558858f66f6781245dec8", 275691824, 4259911),
-    ("llama8b-b64-lognormal800", "gateup"): ("linear.hip", "cbaa3ab9ad5e49ac9c7cea4200cf981c402d61f78b91d2d922f4b6411c8368dd", 243436004, 3670016),
-    ("llama8b-b64-lognormal800", "down"): ("linear.hip", "cbaa3ab9ad5e49ac9c7cea4200cf981c402d61f78b91d2d922f4b6411c8368dd", 121338096, 16777226),
-    ("llama8b-mixed-sweep512", "attn"): ("attention.hip", "0ce537b9d8896e4bbd896f7009353995d581f7a3b2b558858f66f6781245dec8", 4196831402, 21763317),
-    ("llama8b-b32-long32k", "attn"): ("attention.hip", "0ce537b9d8896e4bbd896f7009353995d581f7a3b2b558858f66f6781245dec8", 3721428398, 4260218),
+    ("llama8b-b64-lognormal800", "attn"): ("attention.hip", "38998306df6ba30dfa44670975037f8b0df01cfbb21ab47bd044601eac1a6018", 275718491, 4259911),
+    ("llama8b-b64-lognormal800", "gateup"): ("linear.hip", "f70f49659a0166fa4db558e6975177f24afa34fcbcdfe65f1249f77f7474f6f7", 243437914, 3670016),
+    ("llama8b-b64-lognormal800", "down"): ("linear.hip", "f70f49659a0166fa4db558e6975177f24afa34fcbcdfe65f1249f77f7474f6f7", 121337987, 16777216),
+    ("llama8b-mixed-sweep512", "attn"): ("attention.hip", "38998306df6ba30dfa44670975037f8b0df01cfbb21ab47bd044601eac1a6018", 4196881681, 21763215),
+    ("llama8b-b32-long32k", "attn"): ("attention.hip", "38998306df6ba30dfa44670975037f8b0df01cfbb21ab47bd044601eac1a6018", 3721430412, 4260167),
 }
 
 
