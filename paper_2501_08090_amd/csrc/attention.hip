@@ -289,27 +289,21 @@ __global__ __launch_bounds__(256, 2) void paged_attn_kernel(PoolDesc p, int laye
 
 // Where the merge finds the partial results: row = request * q_len + token; the token's pass v = request * ng + token / tg; a
 // partial result holds G*tg columns per (item, kv head), column = (token % tg) * G + head.
-struct MergeArgs {
-    const int32_t* plan;
-    int max_batch, n_kv, G;
-    AttnShape sh;
-    const float *part_o, *part_ml;
-    float* out;
-    int ldo;
-};
 
 // merge the items of one (row, query head) by a workgroup: out = sum_j 2^(m_j - M) o_j / sum_j 2^(m_j - M) l_j.
 // 256 threads = 8 item slices x 32 lanes of float4 (D = 128) or 16 slices x 16 lanes (D = 64); slice k takes
 // items k, k+S, ...; the slices are combined through LDS in a fixed order.
 template <int D>
-__device__ __forceinline__ void merge_by_workgroup(const MergeArgs& g, int row, int a) {
+__device__ __forceinline__ void merge_by_workgroup(const int32_t* __restrict__ plan, int max_batch, int n_kv, int G, const AttnShape& sh,
+                                                   const float* __restrict__ part_o, const float* __restrict__ part_ml,
+                                                   float* __restrict__ out, int ldo, int row, int a) {
     constexpr int LANES = D / 4, S = 256 / LANES;
     __shared__ float4 s_num[S][LANES];
     __shared__ float s_den[S], s_max[S];
-    const int t = row % g.sh.q_len, v = row / g.sh.q_len * g.sh.ng + t / g.sh.tg;
-    const int c = a / g.G, j = (t % g.sh.tg) * g.G + a % g.G, GT = g.G * g.sh.tg, n_kv = g.n_kv;
+    const int t = row % sh.q_len, v = row / sh.q_len * sh.ng + t / sh.tg;
+    const int c = a / G, j = (t % sh.tg) * G + a % G, GT = G * sh.tg;
     const int sl = threadIdx.x / LANES, ln = threadIdx.x % LANES;
-    const int item0 = g.plan[4 + v], nch = g.plan[4 + g.max_batch + v];
+    const int item0 = plan[4 + v], nch = plan[4 + max_batch + v];
     // each slice folds its items with a running maximum, two items' loads in flight at a time
     float M = -INFINITY, den = 0.f;
     float4 num = make_float4(0.f, 0.f, 0.f, 0.f);
@@ -324,16 +318,16 @@ __device__ __forceinline__ void merge_by_workgroup(const MergeArgs& g, int row, 
     int ch = sl;
     for (; ch + S < nch; ch += 2 * S) {
         size_t s0 = ((size_t)(item0 + ch) * n_kv + c) * GT + j, s1 = ((size_t)(item0 + ch + S) * n_kv + c) * GT + j;
-        float2 ml0 = *reinterpret_cast<const float2*>(g.part_ml + s0 * 2), ml1 = *reinterpret_cast<const float2*>(g.part_ml + s1 * 2);
-        float4 o0 = *reinterpret_cast<const float4*>(g.part_o + s0 * D + ln * 4);
-        float4 o1 = *reinterpret_cast<const float4*>(g.part_o + s1 * D + ln * 4);
+        float2 ml0 = *reinterpret_cast<const float2*>(part_ml + s0 * 2), ml1 = *reinterpret_cast<const float2*>(part_ml + s1 * 2);
+        float4 o0 = *reinterpret_cast<const float4*>(part_o + s0 * D + ln * 4);
+        float4 o1 = *reinterpret_cast<const float4*>(part_o + s1 * D + ln * 4);
         fold(ml0.x, ml0.y, o0);
         fold(ml1.x, ml1.y, o1);
     }
     if (ch < nch) {
         size_t s0 = ((size_t)(item0 + ch) * n_kv + c) * GT + j;
-        float2 ml0 = *reinterpret_cast<const float2*>(g.part_ml + s0 * 2);
-        fold(ml0.x, ml0.y, *reinterpret_cast<const float4*>(g.part_o + s0 * D + ln * 4));
+        float2 ml0 = *reinterpret_cast<const float2*>(part_ml + s0 * 2);
+        fold(ml0.x, ml0.y, *reinterpret_cast<const float4*>(part_o + s0 * D + ln * 4));
     }
     s_num[sl][ln] = num;
     if (ln == 0) {
@@ -353,17 +347,21 @@ __device__ __forceinline__ void merge_by_workgroup(const MergeArgs& g, int row, 
             n4.x += wk * t4.x; n4.y += wk * t4.y; n4.z += wk * t4.z; n4.w += wk * t4.w;
         }
         float inv = 1.0f / dsum;
-        *reinterpret_cast<float4*>(g.out + (size_t)row * g.ldo + (size_t)a * D + ln * 4) =
+        *reinterpret_cast<float4*>(out + (size_t)row * ldo + (size_t)a * D + ln * 4) =
             make_float4(n4.x * inv, n4.y * inv, n4.z * inv, n4.w * inv);
     }
 }
 
 // a workgroup per (row, query head)
 template <int D>
-__global__ __launch_bounds__(256) void attn_reduce_kernel(MergeArgs g, int32_t* __restrict__ tickets) {
+__global__ __launch_bounds__(256) void attn_reduce_kernel(const int32_t* __restrict__ plan, int32_t* __restrict__ tickets,
+                                                          int max_batch, int n_kv, int G, AttnShape sh,
+                                                          const float* __restrict__ part_o,
+                                                          const float* __restrict__ part_ml, float* __restrict__ out,
+                                                          int ldo) {
     // the attention kernel before this one has drained: its ticket counters go back to 0 for the next one
     if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x < kTicketQueues) tickets[threadIdx.x * kTicketStride] = 0;
-    merge_by_workgroup<D>(g, blockIdx.x, blockIdx.y);
+    merge_by_workgroup<D>(plan, max_batch, n_kv, G, sh, part_o, part_ml, out, ldo, blockIdx.x, blockIdx.y);
 }
 
 // For many rows: a group of D/4 lanes per (row, query head) folds all its items, four at a time.  Most lists are short there
@@ -376,15 +374,19 @@ __global__ __launch_bounds__(256) void attn_reduce_kernel(MergeArgs g, int32_t* 
 // A workgroup folds four times as many items at a time as a lane group, so beyond that the lane groups are as fast.
 constexpr int kMergeDeal = 3;
 template <int D>
-__global__ __launch_bounds__(256) void attn_reduce_rows_kernel(MergeArgs g, int32_t* __restrict__ tickets) {
+__global__ __launch_bounds__(256) void attn_reduce_rows_kernel(const int32_t* __restrict__ plan, int32_t* __restrict__ tickets,
+                                                               int max_batch, int n_kv, int G, AttnShape sh,
+                                                               const float* __restrict__ part_o,
+                                                               const float* __restrict__ part_ml, float* __restrict__ out,
+                                                               int ldo) {
     constexpr int LANES = D / 4, HEADS = 256 / LANES, U = 4;
-    const int n_long = g.plan[2], nq = g.n_kv * g.G;
-    const int row = blockIdx.x, t = row % g.sh.q_len, v = row / g.sh.q_len * g.sh.ng + t / g.sh.tg;
+    const int n_long = plan[2], nq = n_kv * G;
+    const int row = blockIdx.x, t = row % sh.q_len, v = row / sh.q_len * sh.ng + t / sh.tg;
     const int a = blockIdx.y * HEADS + threadIdx.x / LANES, ln = threadIdx.x % LANES;
     if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x < kTicketQueues) tickets[threadIdx.x * kTicketStride] = 0;
-    const int c = a / g.G, j = (t % g.sh.tg) * g.G + a % g.G, GT = g.G * g.sh.tg;
-    const int item0 = g.plan[4 + v], nch = g.plan[4 + g.max_batch + v];
-    const int64_t jobs = (int64_t)n_long * g.sh.tg * nq, blocks = (int64_t)gridDim.x * gridDim.y;
+    const int c = a / G, j = (t % sh.tg) * G + a % G, GT = G * sh.tg;
+    const int item0 = plan[4 + v], nch = plan[4 + max_batch + v];
+    const int64_t jobs = (int64_t)n_long * sh.tg * nq, blocks = (int64_t)gridDim.x * gridDim.y;
     const bool deal = jobs <= kMergeDeal * blocks;
     if (a < nq && !(deal && nch > kMergeLong)) {
         float M = -INFINITY, den = 0.f;
@@ -394,9 +396,9 @@ __global__ __launch_bounds__(256) void attn_reduce_rows_kernel(MergeArgs g, int3
             float4 o[U];
 #pragma unroll
             for (int u = 0; u < U; ++u) {  // past the end: the last item once more, not used
-                const size_t s = ((size_t)(item0 + min(ch + u, nch - 1)) * g.n_kv + c) * GT + j;
-                ml[u] = *reinterpret_cast<const float2*>(g.part_ml + s * 2);
-                o[u] = *reinterpret_cast<const float4*>(g.part_o + s * D + ln * 4);
+                const size_t s = ((size_t)(item0 + min(ch + u, nch - 1)) * n_kv + c) * GT + j;
+                ml[u] = *reinterpret_cast<const float2*>(part_ml + s * 2);
+                o[u] = *reinterpret_cast<const float4*>(part_o + s * D + ln * 4);
             }
 #pragma unroll
             for (int u = 0; u < U; ++u) {
@@ -410,14 +412,14 @@ __global__ __launch_bounds__(256) void attn_reduce_rows_kernel(MergeArgs g, int3
             }
         }
         const float inv = 1.0f / den;
-        *reinterpret_cast<float4*>(g.out + (size_t)row * g.ldo + (size_t)a * D + ln * 4) = make_float4(num.x * inv, num.y * inv, num.z * inv, num.w * inv);
+        *reinterpret_cast<float4*>(out + (size_t)row * ldo + (size_t)a * D + ln * 4) = make_float4(num.x * inv, num.y * inv, num.z * inv, num.w * inv);
     }
     if (!deal) return;
     for (int64_t k = blockIdx.x + (int64_t)blockIdx.y * gridDim.x; k < jobs; k += blocks) {  // uniform over the workgroup
-        const int p = (int)(k / (g.sh.tg * nq)), r = (int)(k - (int64_t)p * (g.sh.tg * nq));
-        const int lv = g.plan[4 + 4 * g.max_batch + p], req = lv / g.sh.ng, token = (lv - req * g.sh.ng) * g.sh.tg + r / nq;
-        if (token >= g.sh.q_len) continue;  // the pass's last group is not full
-        merge_by_workgroup<D>(g, req * g.sh.q_len + token, r % nq);
+        const int p = (int)(k / (sh.tg * nq)), r = (int)(k - (int64_t)p * (sh.tg * nq));
+        const int lv = plan[4 + 4 * max_batch + p], req = lv / sh.ng, token = (lv - req * sh.ng) * sh.tg + r / nq;
+        if (token >= sh.q_len) continue;  // the pass's last group is not full
+        merge_by_workgroup<D>(plan, max_batch, n_kv, G, sh, part_o, part_ml, out, ldo, req * sh.q_len + token, r % nq);
         __syncthreads();  // before the next job's results take the place of this one's in LDS
     }
 }
@@ -479,16 +481,15 @@ int32_t launch_attn_merge(const AttnWorkspace& ws, const PoolDesc& p, int n_q, c
     // A workgroup per row and head folds a list of items in parallel; where the passes alone fill half a round of the attention
     // grid, lists are short on average and its dispatch costs more than that saves (the other kernel sees to the long ones).
     // (32 requests of 4 tokens, 8 items each: 7.1 us, and 3 % of the whole step more with the kernel for many rows.)
-    const MergeArgs args{ws.plan, ws.max_batch, p.n_kv, G, sh, ws.part_o, ws.part_ml, out, ldo};
     if ((int64_t)batch * sh.ng * p.n_kv * 2 <= 8 * kNumCU) {
         const dim3 g(rows, n_q);
-        if (p.d == 128) launch(attn_reduce_kernel<128>, g, dim3(256), st, args, tickets);
-        else launch(attn_reduce_kernel<64>, g, dim3(256), st, args, tickets);
+        if (p.d == 128) launch(attn_reduce_kernel<128>, g, dim3(256), st, ws.plan, tickets, ws.max_batch, p.n_kv, G, sh, ws.part_o, ws.part_ml, out, ldo);
+        else launch(attn_reduce_kernel<64>, g, dim3(256), st, ws.plan, tickets, ws.max_batch, p.n_kv, G, sh, ws.part_o, ws.part_ml, out, ldo);
     } else {
         const int heads = 256 / (p.d / 4);
         const dim3 g(rows, (n_q + heads - 1) / heads);
-        if (p.d == 128) launch(attn_reduce_rows_kernel<128>, g, dim3(256), st, args, tickets);
-        else launch(attn_reduce_rows_kernel<64>, g, dim3(256), st, args, tickets);
+        if (p.d == 128) launch(attn_reduce_rows_kernel<128>, g, dim3(256), st, ws.plan, tickets, ws.max_batch, p.n_kv, G, sh, ws.part_o, ws.part_ml, out, ldo);
+        else launch(attn_reduce_rows_kernel<64>, g, dim3(256), st, ws.plan, tickets, ws.max_batch, p.n_kv, G, sh, ws.part_o, ws.part_ml, out, ldo);
     }
     CHIRON_HIP(hipGetLastError());
     return CHIRON_OK;
