@@ -28,11 +28,11 @@ MFMA_BF16_PEAK_TFLOPS = 2500.0
 # `sha` is source_hash() of the kernel's file at that time; with any other source the figure is reported null.
 TRAFFIC = {
     # (workload, kernel class): (source file, source_hash, fetch bytes, write bytes)
-    ("llama8b-b64-lognormal800", "attn"): ("attention.hip", "38998306df6ba30dfa44670975037f8b0df01cfbb21ab47bd044601eac1a6018", 275718491, 4259911),
-    ("llama8b-b64-lognormal800", "gateup"): ("linear.hip", "f70f49659a0166fa4db558e6975177f24afa34fcbcdfe65f1249f77f7474f6f7", 243437914, 3670016),
-    ("llama8b-b64-lognormal800", "down"): ("linear.hip", "f70f49659a0166fa4db558e6975177f24afa34fcbcdfe65f1249f77f7474f6f7", 121337987, 16777216),
-    ("llama8b-mixed-sweep512", "attn"): ("attention.hip", "38998306df6ba30dfa44670975037f8b0df01cfbb21ab47bd044601eac1a6018", 4196881681, 21763215),
-    ("llama8b-b32-long32k", "attn"): ("attention.hip", "38998306df6ba30dfa44670975037f8b0df01cfbb21ab47bd044601eac1a6018", 3721430412, 4260167),
+    ("llama8b-b64-lognormal800", "attn"): ("attention.hip", "1c0e4644f4c54475cf59316009738234d2c27603c27ad556ae580eb81f239f23", 275681758, 4259901),
+    ("llama8b-b64-lognormal800", "gateup"): ("linear.hip", "f70f49659a0166fa4db558e6975177f24afa34fcbcdfe65f1249f77f7474f6f7", 243437734, 3670016),
+    ("llama8b-b64-lognormal800", "down"): ("linear.hip", "f70f49659a0166fa4db558e6975177f24afa34fcbcdfe65f1249f77f7474f6f7", 121337938, 16777226),
+    ("llama8b-mixed-sweep512", "attn"): ("attention.hip", "1c0e4644f4c54475cf59316009738234d2c27603c27ad556ae580eb81f239f23", 4196770145, 21763276),
+    ("llama8b-b32-long32k", "attn"): ("attention.hip", "1c0e4644f4c54475cf59316009738234d2c27603c27ad556ae580eb81f239f23", 3721447830, 4260188),
 }
 
 
