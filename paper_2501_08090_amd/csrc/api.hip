@@ -59,7 +59,7 @@ static int32_t dev_alloc(void** p, size_t bytes) {
     hipError_t e = hipMalloc(p, bytes ? bytes : 256);
     int dev = -1;
     if (e == hipErrorOutOfMemory && hipGetDevice(&dev) == hipSuccess && scratch_pool_trim(dev))
-        for (int i = 0; i < 10 && e == hipErrorOutOfMemory; ++i) {  // the driver takes some milliseconds to free what was given back
+        for (int i = 0; i < 10 && e == hipErrorOutOfMemory; ++i) {  // the GPU driver takes some milliseconds to free what was given back
             (void)hipGetLastError();
             std::this_thread::sleep_for(std::chrono::milliseconds(10));
             e = hipMalloc(p, bytes ? bytes : 256);

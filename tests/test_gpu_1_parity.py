@@ -567,7 +567,7 @@ def test_a_full_device_gets_the_scratch_pool_back():
     h = C.c_void_p()
     rc = b.load().chiron_linear_create(b._ptr(Wd.cuda()), C.c_int32(1 << 30), C.c_int32(1 << 16), b._stream(), C.byref(h))
     assert rc == -5 and not h.value  # CHIRON_ERR_OOM
-    for _ in range(40):  # the driver frees with some delay
+    for _ in range(40):  # the GPU driver frees with some delay
         if torch.cuda.mem_get_info()[0] - kept >= 200 << 20:
             break
         time.sleep(0.05)
