@@ -701,10 +701,12 @@ int32_t chiron_linear_destroy(chiron_linear* l) {
 struct OpScratch {
     size_t part_bytes = 0, split_bytes = 0;
     int max_split = 1;
+    SliceCost slices = SLICES_ALONE;
     size_t bytes() const { return part_bytes + split_bytes; }
 };
-static OpScratch op_linear_scratch(const Linear& L, int M, int prologue, bool in_place = false) {
+static OpScratch op_linear_scratch(const Linear& L, int M, int prologue, SliceCost slices, bool in_place = false) {
     OpScratch sc;
+    sc.slices = slices;
     if (prologue == PRO_NONE && !in_place && linear_few_pays(L, M)) return sc;  // the few-row path needs none
     const bool split = prologue == PRO_NONE && tuning().linear_big_all && M >= linear_big_min_rows(L);
     if (split) sc.split_bytes = 2 * linear_big_split_elems(M, L.Kpad) * 2;
@@ -712,7 +714,7 @@ static OpScratch op_linear_scratch(const Linear& L, int M, int prologue, bool in
     int ks = 1;
     if (L.N <= 16384) {
         sc.max_split = linear_max_split();
-        ks = linear_slices(L, M, split ? PRO_PACKED : prologue, sc.max_split);
+        ks = linear_slices(L, M, split ? PRO_PACKED : prologue, sc.max_split, slices);
     }
     if (ks > 1 || in_place) sc.part_bytes = ((size_t)ks * M * L.N * sizeof(float) + 255) / 256 * 256;
     return sc;
@@ -727,7 +729,7 @@ static int32_t op_linear_common(const Linear& L, const float* x, int lda, int M,
     uint16_t* asplit = sc.split_bytes ? (uint16_t*)((char*)scratch + sc.part_bytes) : nullptr;
     int ks = 1;
     int32_t rc = launch_linear(L, x, lda, M, in_place ? part : y, L.N, accumulate && !in_place ? EPI_ADD : EPI_STORE, prologue, part, sc.max_split,
-                               &ks, asplit, st);
+                               &ks, asplit, st, nullptr, sc.slices);
     if (!rc && (ks > 1 || in_place)) rc = launch_reduce_partials(part, ks, (int64_t)M * L.N, y, accumulate, st);
     return rc;
 }
@@ -740,7 +742,7 @@ int32_t chiron_op_linear(const chiron_linear* l, const float* x, int32_t M, floa
     if (l->gate_up) return fail(CHIRON_ERR_INVALID_ARG, "linear: a fused gate/up matrix goes with the SwiGLU entry points only");
     hipStream_t st = (hipStream_t)stream;
     const bool in_place = x < y + (size_t)M * l->L.N && y < x + (size_t)M * l->L.K;
-    const OpScratch sc = op_linear_scratch(l->L, M, PRO_NONE, in_place);
+    const OpScratch sc = op_linear_scratch(l->L, M, PRO_NONE, in_place ? SLICES_BLOCK : SLICES_ALONE, in_place);
     void* scratch = nullptr;
     int32_t rc = scratch_alloc(l->device, &scratch, sc.bytes(), st);
     if (rc) return rc;
@@ -774,7 +776,7 @@ int32_t chiron_op_swiglu_ffn(const chiron_linear* gate_up, const chiron_linear* 
     const bool few = linear_few_pays_packed(D, M);
     const bool packed = !few && M >= linear_big_min_rows(D);
     const size_t bytes = ((packed ? 2 * linear_big_split_elems(M, D.Kpad) * 2 : (size_t)M * D.Kpad * 4) + 255) / 256 * 256;
-    const OpScratch sc = few ? OpScratch() : op_linear_scratch(D, M, packed ? PRO_PACKED : PRO_NONE);
+    const OpScratch sc = few ? OpScratch() : op_linear_scratch(D, M, packed ? PRO_PACKED : PRO_NONE, SLICES_BLOCK);
     void* act = nullptr;  // the intermediate, then the down projection's scratch
     int32_t rc = scratch_alloc(gate_up->device, &act, bytes + sc.bytes(), st);
     if (rc) return rc;

@@ -105,6 +105,9 @@ struct Tuning {
 };
 Tuning& tuning();
 
+// What K-slices cost the caller besides their traffic: in a step a kernel that is there anyway adds them up; a feed-forward block
+// launches one for it; a projection by itself also allocates them.
+enum SliceCost { SLICES_STEP, SLICES_BLOCK, SLICES_ALONE };
 // C[M,N] = A[M,K] * W^T.  A is fp32 with row stride lda (PRO_NONE), or the tiled bf16 terms of it (PRO_PACKED: hi terms
 // at A, lo terms linear_big_split_elems(M, L.Kpad) bf16 values further).
 // If the launch slices K (only if max_split > 1, and at most that many slices; `part` may be null if linear_slices says 1), slice s stores its partial product
@@ -115,7 +118,7 @@ Tuning& tuning();
 // linear_big_all knob, launches of many rows first store the two bf16 terms of A there (launch_linear_big).
 int32_t launch_linear(const Linear& L, const float* A, int lda, int M, float* y, int ldy, int epilogue, int prologue,
                       float* part, int max_split, int* ksplit_out, uint16_t* asplit, hipStream_t st,
-                      const NormIn* norm = nullptr);
+                      const NormIn* norm = nullptr, SliceCost slices = SLICES_STEP);
 int32_t launch_linear_big(const Linear& L, const float* A, int lda, int M, float* y, int ldy, int epilogue,
                           float* part, int max_split, int* ksplit_out, uint16_t* asplit, hipStream_t st);
 size_t linear_big_split_elems(int M, int Kpad);
@@ -124,7 +127,7 @@ int32_t launch_clear_k_padding(uint16_t* asplit, int M, int K, int Kpad, hipStre
 int linear_big_min_rows(const Linear& L);
 int linear_max_split();
 // number of K-slices launch_linear takes for M rows when it is given a workspace of max_split slices
-int linear_slices(const Linear& L, int M, int prologue, int max_split);
+int linear_slices(const Linear& L, int M, int prologue, int max_split, SliceCost slices);
 int32_t launch_reduce_partials(const float* part, int ks, int64_t n, float* y, int accumulate, hipStream_t st);
 // interleave: 0 = source row r becomes packed row row_offset + r; 1 / 2 = the source is the gate / up half of a fused
 // gate/up matrix, whose 32-row tiles hold 16 gate and the 16 up columns of the same indices (rows % 16 == 0);

@@ -556,12 +556,58 @@ int linear_big_min_rows(const Linear& L) {
     return v == 0 ? big_min_rows_default(L) : (v < 0 ? INT32_MAX : v);
 }
 
+// ---- what a launch shape costs ------------------------------------------------------------------------------------
+// A CU's time per k of the K range, in ns, by tile: with up to one workgroup per CU (what an almost empty grid takes, and how much
+// more a full one does), and with several, per workgroup.  Measured with every tile forced in turn on fused gate/up matrices of
+// 688 .. 14336 columns, K = 512 .. 4096, 40 .. 2048 rows, and checked on others (2048, 28672 and 64128 columns, K up to 8192; K sliced,
+// 512 .. 8192 columns, K = 512 .. 14336, 20 .. 2048 rows): the median is within 5 % of the measured time, nine in ten within 18 %.
+struct TileCost {
+    int mt, nf;
+    double one, fill, many;
+};
+static constexpr TileCost kTileCost[] = {{1, 1, 6.5, 1.2, 6.7},    {1, 2, 9.9, 1.8, 11.3},   {2, 1, 8.8, 2.5, 9.5},   {2, 2, 13.4, 2.9, 15.4}, {2, 4, 22.5, 6.0, 27.4},
+                                         {3, 1, 12.3, 2.8, 15.0},  {3, 2, 20.0, 3.9, 21.5},  {4, 1, 19.2, 2.6, 17.5}, {4, 2, 25.2, 4.8, 26.5}, {4, 4, 37.3, 11.8, 48.7}};
+// A launch, its slowest CU or the weights at 6.4 TB/s, the result at 4.5 TB/s; K-slices (of M x N fp32) are written and read again by
+// whoever adds them: 0.4 us per MB, and 4 us for a launch of its own.  The host takes about as long for a call as for 15 us of a
+// block's second half or, where it has to allocate the slices, 26 us: a shape that is faster than that gains nothing by slicing.
+static double shape_us(const Linear& L, int M, const TileCost& t, int ksplit, int64_t k_per_slice, SliceCost slices) {
+    const int64_t wgs = (int64_t)((L.Npad / 32 + 4 * t.nf - 1) / (4 * t.nf)) * ((M + 32 * t.mt - 1) / (32 * t.mt)) * ksplit;
+    const double per_k = wgs <= kNumCU ? t.one + t.fill * wgs / kNumCU : t.many * ((wgs + kNumCU - 1) / kNumCU);
+    const double run = 1e-3 * k_per_slice * per_k, stream = 2e-6 * L.N * L.K / 6.4;
+    double us = 4.0 + (run > stream ? run : stream);
+    if (ksplit == 1) return us + 4e-6 * M * L.N / 4.5;
+    us += 0.4e-6 * 4.0 * ksplit * M * L.N + (slices == SLICES_STEP ? 1.0 : 4.0);
+    const double host = slices == SLICES_ALONE ? 26.0 : slices == SLICES_BLOCK ? 15.0 : 0.0;
+    return us > host ? us : host;
+}
+
+// Puts the shape with the least estimate in the place of the one given (tile, slices and chunks of kc per slice) if it is 5 % below
+// that one's; `most` slices at most.
+static void by_estimate(const Linear& L, int M, int kc, int most, SliceCost slices, int& mt, int& nf, int& ksplit, int& cps) {
+    double best = 1e30;
+    for (const TileCost& t : kTileCost)
+        if (t.mt == mt && t.nf == nf) best = 0.95 * shape_us(L, M, t, ksplit, (int64_t)cps * kc, slices);
+    const int chunks = (L.K + 63) / 64, rule_cps = cps;
+    for (const TileCost& t : kTileCost)
+        for (int want = 1; want <= most && (want == 1 || want <= chunks / 2); ++want) {
+            const int c = (chunks + want - 1) / want;
+            if ((chunks + c - 1) / c != want || (most > 1 && c > 16 && c > rule_cps)) continue;  // an empty slice; too long a one
+            const double us = shape_us(L, M, t, want, (int64_t)c * 64, slices);
+            if (us >= best) continue;
+            best = us;
+            mt = t.mt;
+            nf = t.nf;
+            ksplit = want;
+            cps = c;
+        }
+}
+
 // the launch shape of a tiled projection: rows / 32 and column tiles per wave, waves per workgroup, k-steps per chunk,
 // workgroups along N and M, K-slices and chunks per slice
 struct LinearShape {
     int mt, nf, nw, ks, gx, gz, ksplit, cps;
 };
-static LinearShape linear_shape(const Linear& L, int M, bool sliceable, int prologue, int max_split) {
+static LinearShape linear_shape(const Linear& L, int M, bool sliceable, int prologue, int max_split, SliceCost slices) {
     const Tuning& tn = tuning();
     // Tile shape.  Up to 64 rows the kernel is HBM-bound: 32- or 64-row tiles; one column tile per wave when K can
     // be sliced (twice the workgroups along N, so half the K-slices for the consumer to add up) or when that is
@@ -638,13 +684,14 @@ static LinearShape linear_shape(const Linear& L, int M, bool sliceable, int prol
     }
     // A projection that cannot slice K (no workspace) runs one workgroup per CU; a ring of 8 k-steps then keeps twice
     // the weight bytes in flight per wave, which measured 9 % faster on the gate/up shape at 64 rows.
-    const bool ks8 = (mt == 2 || (mt == 3 && nf == 1)) && nf <= 2 && prologue != PRO_PACKED &&
-                     (tn.linear_ks == 8 || (tn.linear_ks == 0 && nf == 1 && !sliceable && prologue == PRO_NONE));
+    const auto ring8 = [&] { return (mt == 2 || (mt == 3 && nf == 1)) && nf <= 2 && prologue != PRO_PACKED &&
+                     (tn.linear_ks == 8 || (tn.linear_ks == 0 && nf == 1 && !sliceable && prologue == PRO_NONE)); };
     // Up to 32 rows a wave has two MFMAs per k-step and its weight stream is bound by the bytes it keeps in flight over
     // the load latency: the unsliced one-tile-per-wave shape takes a ring of 16 k-steps (16 KiB per wave; measured on the
     // 8B gate/up shape: 37.3 against 40.0 us at one row, 39.8 against 41.4 us at 32 rows; no gain at 64 rows)
-    const bool ks16 = mt == 1 && nf == 1 && prologue == PRO_NONE && L.Kpad % 256 == 0 &&
-                      (tn.linear_ks == 16 || (tn.linear_ks == 0 && !sliceable));
+    const auto ring16 = [&] { return mt == 1 && nf == 1 && prologue == PRO_NONE && L.Kpad % 256 == 0 &&
+                                     (tn.linear_ks == 16 || (tn.linear_ks == 0 && !sliceable)); };
+    bool ks8 = ring8(), ks16 = ring16();
     const int KC = ks16 ? 256 : (ks8 ? 128 : 64);
     int chunks = (L.K + KC - 1) / KC;
     int ksplit = tn.linear_ksplit ? tn.linear_ksplit : (tn.linear_target_blocks + gx * gz - 1) / (gx * gz);
@@ -665,6 +712,36 @@ static LinearShape linear_shape(const Linear& L, int M, bool sliceable, int prol
     if (ksplit < 1) ksplit = 1;
     int cps = (chunks + ksplit - 1) / ksplit;
     ksplit = (chunks + cps - 1) / cps;  // no empty slices
+    // The rules above come from sweeps at the 8B and 70B widths.  Elsewhere they can leave most of the chip idle (128-row tiles of 512
+    // columns from 384 rows on: 48 workgroups for a gate/up of 4096 columns) or double the rounds of the grid, and a short K is
+    // sliced into ramps.  So any other shape whose estimate is 5 % below theirs takes their place; at their own widths up to 256
+    // rows none does.  Slices stay at most 1024 long (or as long as theirs): longer sums would round a little more.
+    //   gate/up, us: 4096 columns, K = 4096, 384 rows 162 -> 63; 5632, K = 2048, 512 rows 85 -> 56; 1376, K = 4096, 160 rows 55 -> 33;
+    //   512 shapes of the sweep 0.88 of the time on average, none over 1.01.
+    //   sliced, with the sum of the slices: 8192 x 512, 512 rows 36 -> 14; 6144 x 4096, 384 rows 58 -> 53; 2048 x 2048, 100 rows
+    //   16 -> 12; 462 shapes 0.88, none over 1.04.  (Up to 32 rows their choice is within 3 % of the best everywhere.)
+    if (prologue == PRO_NONE && M > 32 && !tn.linear_mt && !tn.linear_nf && !tn.linear_ksplit && !tn.linear_ks && tn.linear_target_blocks == kNumCU) {
+        // (a pure function of these sizes, about 3 us of the host's time: its last answers are kept, per thread)
+        struct Answer {
+            int N, K, M, most, slices, mt, nf, ksplit, cps;
+        };
+        static thread_local Answer answers[64];
+        const int most = sliceable ? max_split : 1;
+        Answer& a = answers[((unsigned)L.N * 31u + (unsigned)L.K * 17u + (unsigned)M * 5u + (unsigned)most + (unsigned)slices) % 64u];
+        if (a.M != M || a.N != L.N || a.K != L.K || a.most != most || a.slices != slices) {
+            a = Answer{L.N, L.K, M, most, slices, mt, nf, ksplit, cps};
+            by_estimate(L, M, KC, most, slices, a.mt, a.nf, a.ksplit, a.cps);
+        }
+        mt = a.mt;
+        nf = a.nf;
+        ksplit = a.ksplit;
+        cps = a.cps;
+        gx = (tiles + 4 * nf - 1) / (4 * nf);
+        gz = (M + 32 * mt - 1) / (32 * mt);
+        ks8 = ring8();
+        ks16 = ring16();
+        if (!sliceable) cps = (L.K + (ks16 ? 256 : (ks8 ? 128 : 64)) - 1) / (ks16 ? 256 : (ks8 ? 128 : 64));
+    }
     // Eight waves instead of four over the same columns where that pays: two waves per SIMD, of which one multiplies while
     // the other converts activations or waits.  Measured (whole calls, one device):
     //   128 rows x 512 columns: the 8B-wide feed-forward block of 2048 rows 1160 -> 1144 us, two layers and the head at 500
@@ -688,10 +765,12 @@ static LinearShape linear_shape(const Linear& L, int M, bool sliceable, int prol
     return LinearShape{mt, nf, nw, ks16 ? 16 : (ks8 ? 8 : 4), gx, gz, ksplit, cps};
 }
 
-int linear_slices(const Linear& L, int M, int prologue, int max_split) { return M > 0 ? linear_shape(L, M, true, prologue, max_split).ksplit : 1; }
+int linear_slices(const Linear& L, int M, int prologue, int max_split, SliceCost slices) {
+    return M > 0 ? linear_shape(L, M, true, prologue, max_split, slices).ksplit : 1;
+}
 
 int32_t launch_linear(const Linear& L, const float* A, int lda, int M, float* y, int ldy, int epilogue, int prologue,
-                      float* part, int max_split, int* ksplit_out, uint16_t* asplit, hipStream_t st, const NormIn* norm) {
+                      float* part, int max_split, int* ksplit_out, uint16_t* asplit, hipStream_t st, const NormIn* norm, SliceCost slices) {
     if (ksplit_out) *ksplit_out = 1;
     if (M == 0) return CHIRON_OK;
     if (norm && (max_split > 1 || prologue != PRO_NONE || !linear_few_rows(M)))
@@ -710,7 +789,7 @@ int32_t launch_linear(const Linear& L, const float* A, int lda, int M, float* y,
     if (L.K % 16 != 0 || L.K < 16) return fail(CHIRON_ERR_SHAPE, "linear: K=%d must be a positive multiple of 16", L.K);
     if (prologue != PRO_PACKED && (lda % 4 != 0 || ((uintptr_t)A & 15)))
         return fail(CHIRON_ERR_INVALID_ARG, "linear: input rows must be 16-byte aligned");
-    const LinearShape shape = linear_shape(L, M, max_split > 1, prologue, max_split);
+    const LinearShape shape = linear_shape(L, M, max_split > 1, prologue, max_split, slices);
     const int mt = shape.mt, nf = shape.nf, nw = shape.nw, gx = shape.gx, gz = shape.gz, ksplit = shape.ksplit, cps = shape.cps;
     const bool ks8 = shape.ks == 8, ks16 = shape.ks == 16;
     if (ksplit > 1 && !part) return fail(CHIRON_ERR_INVALID_ARG, "linear: no workspace for %d K-slices", ksplit);

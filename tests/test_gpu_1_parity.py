@@ -1122,3 +1122,26 @@ def test_error_paths_on_device():
     assert gu.ffn(plain, x).shape == (3, 32) and float(gu.ffn(plain, x).abs().max()) == 0.0        # silu(0) * 0 = 0
     for l in (gu, plain, narrow):
         l.close()
+
+
+@pytest.mark.parametrize("M,N,K", [(33, 512, 512), (384, 4096, 2048), (500, 2722, 464), (1455, 448, 1040), (160, 3000, 4096), (97, 6144, 512), (385, 6144, 4112),
+                                   (640, 8224, 1040), (1025, 3072, 2064), (512, 8192, 48), (40, 2048, 2048), (686, 1955, 1136), (2000, 96, 6160)])
+def test_linear_shapes_by_estimate(M, N, K):
+    """widths and row counts between those that the launch shapes were swept at, where the estimated time decides: every tile that is
+    built (32 to 128 rows, 128 to 512 columns), slices or none, ragged rows and columns; alone, added to y, and as the two halves of
+    a feed-forward block (K of which is the narrow side)"""
+    rng = np.random.default_rng(M + 3 * N + 7 * K)
+    x = rng.standard_normal((M, K)).astype(np.float32)
+    W = I.normal((N, K), 0.05, 12, "wse", N, K)
+    print("linear by estimate", M, N, K, flush=True)
+    lin = B().Linear(W.cuda())
+    want = orc.linear(x, I.to_numpy_storage(W))
+    y0 = rng.standard_normal((M, N)).astype(np.float32)
+    assert rel_err(lin(torch.from_numpy(x).cuda()).cpu().numpy(), want) <= KERNEL_TOL
+    assert rel_err(lin(torch.from_numpy(x).cuda(), torch.from_numpy(y0).cuda(), accumulate=True).cpu().numpy(), want + y0) <= KERNEL_TOL
+    lin.close()
+    F, H = N // 16 * 16, min(K, 528)
+    xs, Wg, Wu, Wd, _, want = ffn_case(M, H, F, 272, M + N)
+    gu, down = B().GateUp(Wg.cuda(), Wu.cuda()), B().Linear(Wd.cuda())
+    assert rel_err(gu.ffn(down, torch.from_numpy(xs).cuda()).cpu().numpy(), want) <= KERNEL_TOL
+    gu.close(); down.close()
