@@ -72,12 +72,11 @@ int32_t launch_pack_rows(const uint16_t* src, int rows, int K, size_t tstride, u
 // 8B gate/up shape at 2048 rows: the weight stream alone 268 us with the hint, 194 us without).
 // NORM: the input is rmsnorm(A) * gain.  A workgroup of an unsliced projection reads whole rows anyway: the gain is applied
 // while a chunk is staged, the sum of squares is taken from the same values, and the row's 1/rms multiplies the accumulators.
+// The workgroup's columns, K-slice and M-tile are bx, by, bz.
 template <int MT, int NF, int KS, int PRO, bool WNT = true, bool NORM = false, int NW = 4>
-__global__ __launch_bounds__(64 * NW, (NW == 8 || (MT * NF <= 8 && !(MT == 4 && PRO != PRO_NONE)) ? 2 : 1)) void linear_kernel(const uint16_t* __restrict__ Wp, size_t tstride, int Npad, int Nreal, int K, int Kpad,
-                                                     const float* __restrict__ A, int lda, int M,
-                                                     float* __restrict__ Y, int ldy, int chunks_per_split,
-                                                     int mode, size_t part_stride, int gx, int gy, int gz, int remap,
-                                                     const uint16_t* __restrict__ gain, float eps) {
+__device__ __forceinline__ void linear_tile(const uint16_t* __restrict__ Wp, size_t tstride, int Npad, int Nreal, int K, int Kpad,
+                                            const float* __restrict__ A, int lda, int M, float* __restrict__ Y, int ldy, int chunks_per_split,
+                                            int mode, size_t part_stride, int bx, int by, int bz, const uint16_t* __restrict__ gain, float eps) {
     constexpr int MROWS = 32 * MT;
     constexpr int RS = MROWS + 1;      // LDS row stride in 16-byte units (+1 breaks the power-of-two stride)
     constexpr int KG = 2 * KS;         // 8-wide k-groups per chunk
@@ -99,14 +98,6 @@ __global__ __launch_bounds__(64 * NW, (NW == 8 || (MT * NF <= 8 && !(MT == 4 && 
     __shared__ uint4 lds_lo[2][KG * RS];
 
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    // Workgroups are dealt to the 8 XCDs round-robin.  The 1-D grid is re-read so that consecutive logical ids
-    // sit on ONE XCD, and the M-tile index varies fastest: the workgroups that stream the same weight tiles for
-    // different rows then share that XCD's L2 instead of each pulling the tile from HBM.
-    const int total = gx * gy * gz;
-    const int per_xcd = (total + 7) / 8;
-    const int logical = remap ? (blockIdx.x % 8) * per_xcd + blockIdx.x / 8 : blockIdx.x;
-    if (logical >= total) return;  // grid is padded to a multiple of 8 (uniform over the workgroup)
-    const int bz = logical % gz, bx = (logical / gz) % gx, by = logical / (gz * gx);
     const int m0 = bz * MROWS;
     const int tile0 = (bx * NW + wave) * NF;  // first 32-column tile of this wave
     const int chunks_total = (K + KC - 1) / KC;
@@ -485,6 +476,45 @@ __global__ __launch_bounds__(64 * NW, (NW == 8 || (MT * NF <= 8 && !(MT == 4 && 
     }
 }
 
+// Workgroups are dealt to the 8 XCDs round-robin.  The 1-D grid (of a multiple of 8) is re-read so that consecutive logical ids
+// sit on ONE XCD, and the M-tile index varies fastest: the workgroups that stream the same weight tiles for
+// different rows then share that XCD's L2 instead of each pulling the tile from HBM.
+__device__ __forceinline__ int logical_block(int block, int total, int remap) { return remap ? (block % 8) * ((total + 7) / 8) + block / 8 : block; }
+
+template <int MT, int NF, int KS, int PRO, bool WNT = true, bool NORM = false, int NW = 4>
+__global__ __launch_bounds__(64 * NW, (NW == 8 || (MT * NF <= 8 && !(MT == 4 && PRO != PRO_NONE)) ? 2 : 1)) void linear_kernel(const uint16_t* __restrict__ Wp, size_t tstride, int Npad, int Nreal, int K, int Kpad,
+                                                     const float* __restrict__ A, int lda, int M,
+                                                     float* __restrict__ Y, int ldy, int chunks_per_split,
+                                                     int mode, size_t part_stride, int gx, int gy, int gz, int remap,
+                                                     const uint16_t* __restrict__ gain, float eps) {
+    const int logical = logical_block(blockIdx.x, gx * gy * gz, remap);
+    if (logical >= gx * gy * gz) return;  // uniform over the workgroup
+    linear_tile<MT, NF, KS, PRO, WNT, NORM, NW>(Wp, tstride, Npad, Nreal, K, Kpad, A, lda, M, Y, ldy, chunks_per_split, mode, part_stride,
+                                                (logical / gz) % gx, logical / (gz * gx), logical % gz, gain, eps);
+}
+
+// 128 rows x 512 columns by eight waves, K whole.  The tiles of whole rounds of the chip as they are (`whole` of them, a multiple of
+// 256), those of a last round that would be at most half full as two of 128 x 256, which then fill it: 2048 rows of 28672
+// columns at K = 4096 are 3.5 rounds.  Whole feed-forward blocks, us: 640 rows of 4096 -> 14336 -> 4096 455 -> 438, 1280 rows
+// 795 -> 763, 1500 rows of 2048 -> 11008 -> 2048 415 -> 395, 2048 rows of the first 1158 -> 1147 (there the card's power is short: the
+// clock falls as more of its matrix cores work).
+__global__ __launch_bounds__(512, 2) void linear_wide_kernel(const uint16_t* __restrict__ Wp, size_t tstride, int Npad, int Nreal, int K, int Kpad,
+                                                             const float* __restrict__ A, int lda, int M, float* __restrict__ Y, int ldy, int mode,
+                                                             size_t part_stride, int gx, int gz, int whole, int remap) {
+    const int chunks = (K + 63) / 64;
+    if ((int)blockIdx.x < whole) {
+        const int logical = logical_block(blockIdx.x, whole, remap);
+        linear_tile<4, 2, 4, PRO_NONE, false, false, 8>(Wp, tstride, Npad, Nreal, K, Kpad, A, lda, M, Y, ldy, chunks, mode, part_stride, logical / gz, 0,
+                                                        logical % gz, nullptr, 0.f);
+    } else {
+        const int rest = gx * gz - whole, logical = logical_block(blockIdx.x - whole, 2 * rest, remap);
+        if (logical >= 2 * rest) return;  // uniform over the workgroup
+        const int tile = whole + logical % rest;
+        linear_tile<4, 1, 4, PRO_NONE, false, false, 8>(Wp, tstride, Npad, Nreal, K, Kpad, A, lda, M, Y, ldy, chunks, mode, part_stride,
+                                                        2 * (tile / gz) + logical / rest, 0, tile % gz, nullptr, 0.f);
+    }
+}
+
 // sum of K-slices: y (+)= sum_s part[s]  (used by the single-kernel entry points; inside the decode step the
 // consumers of a projection do this sum themselves)
 __global__ __launch_bounds__(256) void reduce_partials_kernel(const float* __restrict__ part, int ks, size_t stride,
@@ -570,9 +600,12 @@ static constexpr TileCost kTileCost[] = {{1, 1, 6.5, 1.2, 6.7},    {1, 2, 9.9, 1
 // A launch, its slowest CU or the weights at 6.4 TB/s, the result at 4.5 TB/s; K-slices (of M x N fp32) are written and read again by
 // whoever adds them: 0.4 us per MB, and 4 us for a launch of its own.  The host takes about as long for a call as for 15 us of a
 // block's second half or, where it has to allocate the slices, 26 us: a shape that is faster than that gains nothing by slicing.
+// (128 x 512 tiles: a last round that is at most half full is taken as tiles of 256 columns, see linear_wide_kernel)
+static bool halved_last_round(int64_t wgs) { return wgs > kNumCU && wgs % kNumCU != 0 && wgs % kNumCU <= kNumCU / 2; }
 static double shape_us(const Linear& L, int M, const TileCost& t, int ksplit, int64_t k_per_slice, SliceCost slices) {
     const int64_t wgs = (int64_t)((L.Npad / 32 + 4 * t.nf - 1) / (4 * t.nf)) * ((M + 32 * t.mt - 1) / (32 * t.mt)) * ksplit;
-    const double per_k = wgs <= kNumCU ? t.one + t.fill * wgs / kNumCU : t.many * ((wgs + kNumCU - 1) / kNumCU);
+    double per_k = wgs <= kNumCU ? t.one + t.fill * wgs / kNumCU : t.many * ((wgs + kNumCU - 1) / kNumCU);
+    if (t.mt * t.nf == 16 && ksplit == 1 && halved_last_round(wgs)) per_k = t.many * (wgs / kNumCU) + 28.0;
     const double run = 1e-3 * k_per_slice * per_k, stream = 2e-6 * L.N * L.K / 6.4;
     double us = 4.0 + (run > stream ? run : stream);
     if (ksplit == 1) return us + 4e-6 * M * L.N / 4.5;
@@ -824,7 +857,12 @@ int32_t launch_linear(const Linear& L, const float* A, int lda, int M, float* y,
         else if (gz > 1) launch_cfg<4, 2, PRO_PACKED, 4, false>(nblocks, st, L, A, lda, M, dst, ldd, cps, mode, part_stride, gx, ksplit, gz);
         else launch_cfg<4, 2, PRO_PACKED>(nblocks, st, L, A, lda, M, dst, ldd, cps, mode, part_stride, gx, ksplit, gz);
     } else if (nw == 8) {
-        if (mt == 4 && nf == 2 && gz > 1) launch_cfg<4, 2, PRO_NONE, 4, false, false, 8>(nblocks, st, L, A, lda, M, dst, ldd, cps, mode, part_stride, gx, ksplit, gz);
+        const int tiles = gx * gz;
+        if (mt == 4 && nf == 2 && gz > 1 && ksplit == 1 && halved_last_round(tiles)) {
+            const int whole = tiles / kNumCU * kNumCU, blocks = whole + (2 * (tiles - whole) + 7) / 8 * 8;
+            launch(linear_wide_kernel, dim3(blocks), dim3(512), st, L.w, L.tstride, L.Npad, L.N, L.K, L.Kpad, A, lda, M, dst, ldd, mode, part_stride, gx, gz,
+                   whole, tuning().linear_xcd_remap);
+        } else if (mt == 4 && nf == 2 && gz > 1) launch_cfg<4, 2, PRO_NONE, 4, false, false, 8>(nblocks, st, L, A, lda, M, dst, ldd, cps, mode, part_stride, gx, ksplit, gz);
         else if (mt == 4 && nf == 2) launch_cfg<4, 2, PRO_NONE, 4, true, false, 8>(nblocks, st, L, A, lda, M, dst, ldd, cps, mode, part_stride, gx, ksplit, gz);
         else launch_cfg<2, 1, PRO_NONE, 4, true, false, 8>(nblocks, st, L, A, lda, M, dst, ldd, cps, mode, part_stride, gx, ksplit, gz);
     } else if (nf == 4) {

@@ -1125,7 +1125,8 @@ def test_error_paths_on_device():
 
 
 @pytest.mark.parametrize("M,N,K", [(33, 512, 512), (384, 4096, 2048), (500, 2722, 464), (1455, 448, 1040), (160, 3000, 4096), (97, 6144, 512), (385, 6144, 4112),
-                                   (640, 8224, 1040), (1025, 3072, 2064), (512, 8192, 48), (40, 2048, 2048), (686, 1955, 1136), (2000, 96, 6160)])
+                                   (640, 8224, 1040), (1025, 3072, 2064), (512, 8192, 48), (40, 2048, 2048), (686, 1955, 1136), (2000, 96, 6160),
+                                   (600, 28640, 80), (1290, 12300, 48)])  # 128 x 512 tiles with the last round in halves
 def test_linear_shapes_by_estimate(M, N, K):
     """widths and row counts between those that the launch shapes were swept at, where the estimated time decides: every tile that is
     built (32 to 128 rows, 128 to 512 columns), slices or none, ragged rows and columns; alone, added to y, and as the two halves of
