@@ -365,10 +365,11 @@ static int32_t step_rows(chiron_model* m, chiron_kvpool* p, const int32_t* block
     int ks_res = 0, ks_qkv = 1;  // K-slices waiting in m->part for the residual stream / of the QKV projection
     STEP(CHIRON_K_OTHER, launch_step_begin(m->aws, seq_lens, block_table, mb, ash, n_req, c.n_kv_heads, m->embed, tokens, H, m->h, d,
                                            c.rope_base, m->cos_t, m->sin_t, st));
-    if (step_few_rows(m->qkv[0], m->wo[0], m->down[0], B)) {
+    if (step_few_rows(m->qkv[0], m->wo[0], m->gu[0], m->down[0], B)) {
         // With few rows six launches a layer instead of nine: the projections into the residual stream complete it (no
         // K-slices for anybody to add), so the norms move into the operand loads of the projections behind them, and the
         // QKV projection rotates and appends by itself.
+        const bool few_gu = norm_few_pays(m->gu[0], B);
         for (int l = 0; l < c.n_layers; ++l) {
             const NormIn an{m->attn_norm + (size_t)l * H, c.rms_eps}, fn{m->ffn_norm + (size_t)l * H, c.rms_eps};
             RopeOut ro;
@@ -386,12 +387,14 @@ static int32_t step_rows(chiron_model* m, chiron_kvpool* p, const int32_t* block
             STEP(CHIRON_K_ATTN, launch_attn_main(m->aws, p->d, l, m->qb, qn, c.n_q_heads, block_table, mb, seq_lens, ash, n_req, st));
             STEP(CHIRON_K_ATTN_MERGE, launch_attn_merge(m->aws, p->d, c.n_q_heads, ash, n_req, m->attn, qn, st));
             STEP(CHIRON_K_O, launch_linear_few(m->wo[l], m->attn, qn, B, 0, m->h, H, 1, st));
-            STEP(CHIRON_K_GATEUP, launch_linear(m->gu[l], m->h, H, B, m->gub, m->down[l].Kpad, EPI_SWIGLU_FEW, PRO_NONE, nullptr, 1, nullptr,
-                                                nullptr, st, &fn));
+            if (few_gu) STEP(CHIRON_K_GATEUP, launch_norm_few(m->gu[l], m->h, H, B, &fn, 1, m->gub, m->down[l].Kpad, st));
+            else STEP(CHIRON_K_GATEUP, launch_linear(m->gu[l], m->h, H, B, m->gub, m->down[l].Kpad, EPI_SWIGLU_FEW, PRO_NONE, nullptr, 1, nullptr,
+                                                     nullptr, st, &fn));
             STEP(CHIRON_K_DOWN, launch_linear_few(m->down[l], m->gub, (int64_t)B * (m->down[l].Kpad / 8), B, 1, m->h, H, 1, st));
         }
         const NormIn ln{m->final_norm, c.rms_eps};
-        STEP(CHIRON_K_LMHEAD, launch_linear(m->lm, m->h, H, B, logits, c.vocab, EPI_STORE, PRO_NONE, nullptr, 1, nullptr, nullptr, st, &ln));
+        if (norm_few_pays(m->lm, B)) STEP(CHIRON_K_LMHEAD, launch_norm_few(m->lm, m->h, H, B, &ln, 0, logits, c.vocab, st));
+        else STEP(CHIRON_K_LMHEAD, launch_linear(m->lm, m->h, H, B, logits, c.vocab, EPI_STORE, PRO_NONE, nullptr, 1, nullptr, nullptr, st, &ln));
         return CHIRON_OK;
     }
     for (int l = 0; l < c.n_layers; ++l) {
@@ -782,7 +785,8 @@ int32_t chiron_op_swiglu_ffn(const chiron_linear* gate_up, const chiron_linear* 
     if (rc) return rc;
     void* scratch = (char*)act + bytes;
     if (few) {
-        rc = launch_linear(G, x, G.K, M, (float*)act, D.Kpad, EPI_SWIGLU_FEW, PRO_NONE, nullptr, 1, nullptr, nullptr, st);
+        rc = norm_few_pays(G, M) ? launch_norm_few(G, x, G.K, M, nullptr, 1, (float*)act, D.Kpad, st)
+                                 : launch_linear(G, x, G.K, M, (float*)act, D.Kpad, EPI_SWIGLU_FEW, PRO_NONE, nullptr, 1, nullptr, nullptr, st);
         if (!rc) rc = launch_linear_few(D, (const float*)act, (int64_t)M * (D.Kpad / 8), M, 1, y, D.N, accumulate, st);
     } else if (packed) {
         // the epilogue writes the columns below F only: the padding of K must not hold NaN bits when the down projection reads it

@@ -139,7 +139,8 @@ int32_t launch_pack_rows(const uint16_t* src, int rows, int K, size_t tstride, u
 // whether M rows can take that path (a forced launch shape keeps the tiled kernels)
 bool linear_few_rows(int M);
 // whether they should: the layers of a decode step, a projection by itself, the down projection of a feed-forward block
-bool step_few_rows(const Linear& qkv, const Linear& o, const Linear& down, int M);
+bool step_few_rows(const Linear& qkv, const Linear& o, const Linear& gu, const Linear& down, int M);
+bool norm_few_pays(const Linear& L, int M);
 bool linear_few_pays(const Linear& L, int M);
 bool linear_few_pays_packed(const Linear& L, int M);
 // y (+)= A * W^T; one launch, no workspace.  A: fp32 rows of stride lda, or (packed) the two bf16 terms that
@@ -174,6 +175,8 @@ struct RopeOut {
     float* q_out = nullptr;
     int layer = 0, n_q = 0, q_len = 1, max_blocks = 0;
 };
+// the products that are never sliced: gate/up (swiglu; norm may be null), with the result in the form of EPI_SWIGLU_FEW, and the head
+int32_t launch_norm_few(const Linear& L, const float* h, int lda, int M, const NormIn* norm, int swiglu, float* y, int ldy, hipStream_t st);
 int32_t launch_qkv_few(const Linear& L, const float* h, int lda, int M, const NormIn& norm, const RopeOut& ro, hipStream_t st);
 int32_t launch_append_kv(const PoolDesc& p, int layer, const uint16_t* k, const uint16_t* v, const int32_t* bt,
                          int max_blocks, const int32_t* seq_idx, const int32_t* pos, int64_t n, hipStream_t st);

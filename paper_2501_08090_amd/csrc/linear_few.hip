@@ -28,21 +28,24 @@ constexpr int kFewWaves = 8;
 // FEW_ROWS: A is fp32 rows.
 // FEW_PACKED: A holds the two bf16 terms, [k/8][M rows][8], hi terms first (lda = distance to the lo terms in 16-byte
 //   units): no conversion, and a wave's loads are contiguous pieces of 16*M bytes instead of 32 bytes of each row.
-// FEW_QKV: the fused QKV projection of a decode step, whose input is rmsnorm(A) * gain, A fp32 rows, and which ends in the
-//   rotary embedding and the append to the cache.
-enum FewMode { FEW_ROWS, FEW_PACKED, FEW_QKV };
+// FEW_SWIGLU: fp32 rows times a fused gate/up matrix; the result is the two terms of silu(gate) * up as FEW_PACKED reads them
+//   (ldy = distance to the lo terms in 16-byte units).
+// The other modes take rmsnorm(A) * gain of fp32 rows A:
+// FEW_NORM: a plain projection of it.  FEW_SWIGLU_NORM: FEW_SWIGLU of it.
+// FEW_QKV: the fused QKV projection of a decode step, which ends in the rotary embedding and the append to the cache.
+enum FewMode { FEW_ROWS, FEW_PACKED, FEW_SWIGLU, FEW_NORM, FEW_SWIGLU_NORM, FEW_QKV };
 template <int CT, int MODE>
 __global__ __launch_bounds__(64 * kFewWaves) void linear_few_kernel(const uint16_t* __restrict__ Wp, size_t tstride, int N, int K, int Kpad,
                                                                    const float* __restrict__ A, int64_t lda, int M,
                                                                    const uint16_t* __restrict__ gain, float eps,
                                                                    float* __restrict__ Y, int ldy, int add, RopeOut ro) {
-    constexpr bool QKV = MODE == FEW_QKV;
+    constexpr bool QKV = MODE == FEW_QKV, NORM = MODE >= FEW_NORM, SWIGLU = MODE == FEW_SWIGLU || MODE == FEW_SWIGLU_NORM;
     constexpr int D = 8;        // k-steps in flight per wave (CT KiB of weights each)
     constexpr int WS = 72;      // float4 units between the 16x16 tiles in LDS, 18 between a tile's row groups: no two
     constexpr int QS = 18;      // threads of the final sum that read at once share a bank
     __shared__ float4 s_acc[kFewWaves * CT * WS];
     __shared__ float s_ss[kFewWaves][16];
-    static_assert(!QKV || CT == 2, "a rotary pair sits in the two halves of a 32-column tile");
+    static_assert(CT == 2 || (!QKV && !SWIGLU), "a rotary pair, and gate and up of a column, sit in one 32-column tile");
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int row = lane & 15, kq = lane >> 4;
@@ -69,7 +72,7 @@ __global__ __launch_bounds__(64 * kFewWaves) void linear_few_kernel(const uint16
 
     const int n_out = ct0 * 16 + oc;
     float y_old = 0.f;
-    if (!QKV && add && live && n_out < N && tid < 256 * CT) y_old = Y[(size_t)om * ldy + n_out];
+    if (!QKV && !SWIGLU && add && live && n_out < N && tid < 256 * CT) y_old = Y[(size_t)om * ldy + n_out];
 
     const int S = Kpad / (32 * kFewWaves);  // k-steps of this wave (the packed weights are zero past K)
     const int st0 = wave * S;
@@ -87,7 +90,7 @@ __global__ __launch_bounds__(64 * kFewWaves) void linear_few_kernel(const uint16
 #pragma unroll
     for (int t = 0; t < CT; ++t) acc[t] = floatx4{0.f, 0.f, 0.f, 0.f};
     float ss = 0.f;
-    uint4 w[D][CT], g[QKV ? D : 1];
+    uint4 w[D][CT], g[NORM ? D : 1];
     float4 a[D][2];                           // fp32 rows
     uint4 p[MODE == FEW_PACKED ? D : 1][2];   // packed terms: hi, lo
 
@@ -104,7 +107,7 @@ __global__ __launch_bounds__(64 * kFewWaves) void linear_few_kernel(const uint16
         const int k = min(st * 32 + kq * 8, K - 8);
         a[s][0] = *reinterpret_cast<const float4*>(arow + k);
         a[s][1] = *reinterpret_cast<const float4*>(arow + k + 4);
-        if (QKV) g[s] = *reinterpret_cast<const uint4*>(gain + k);
+        if (NORM) g[s] = *reinterpret_cast<const uint4*>(gain + k);
     };
     auto compute = [&](int step, int s) {
         const int k0 = k_step(step) * 32;
@@ -120,7 +123,7 @@ __global__ __launch_bounds__(64 * kFewWaves) void linear_few_kernel(const uint16
 #pragma unroll
                 for (int e = 0; e < 8; ++e) v[e] = ok ? v[e] : 0.f;
             }
-            if (QKV) {
+            if (NORM) {
                 const uint32_t gw[4] = {g[s].x, g[s].y, g[s].z, g[s].w};
 #pragma unroll
                 for (int e = 0; e < 8; ++e) {
@@ -174,7 +177,7 @@ __global__ __launch_bounds__(64 * kFewWaves) void linear_few_kernel(const uint16
 #pragma unroll
     for (int t = 0; t < CT; ++t)
         s_acc[(wave * CT + t) * WS + row + kq * QS] = make_float4(acc[t][0], acc[t][1], acc[t][2], acc[t][3]);
-    if (QKV) {
+    if (NORM) {
         ss += __shfl_xor(ss, 16);
         ss += __shfl_xor(ss, 32);
         if (lane < 16) s_ss[wave][lane] = ss;
@@ -185,7 +188,7 @@ __global__ __launch_bounds__(64 * kFewWaves) void linear_few_kernel(const uint16
     float v = 0.f;
 #pragma unroll
     for (int k = 0; k < kFewWaves; ++k) v += sp[k * CT * WS * 4];
-    if (QKV) {
+    if (NORM) {
         float tot = 0.f;
 #pragma unroll
         for (int k = 0; k < kFewWaves; ++k) tot += s_ss[k][om];
@@ -204,6 +207,18 @@ __global__ __launch_bounds__(64 * kFewWaves) void linear_few_kernel(const uint16
             uint16_t* tile = ro.pool.base + tile_base(ro.pool, ro.layer, block, is_v ? kv - ro.pool.n_kv : kv);
             tile[is_v ? 32 * half + v_off(slot, e) : k_off(slot, e)] = f32_to_bf16_rne(v);
         }
+    } else if (SWIGLU) {
+        // column oc of the tile is gate (oc / 4 even) or up of column 4 * (oc / 8) + oc % 4 of its 16 (gate_up_packed_row in linear.hip)
+        const float up = __shfl_xor(v, 4);
+        const float act = v / (1.0f + __expf(-v)) * up;  // (in the lanes of gate columns)
+        const float next = __shfl_xor(act, 1);
+        if (!live || (oc & 5) != 0 || n_out >= N) return;  // a lane of an even gate column writes its own and the next one
+        uint32_t hi, lo;
+        split2(act, next, hi, lo);
+        const int col = (int)blockIdx.x * 16 + oc / 8 * 4 + (oc & 3);
+        uint32_t* dst = reinterpret_cast<uint32_t*>(Y) + ((size_t)(col / 8) * M + om) * 4 + (col & 7) / 2;
+        dst[0] = hi;
+        dst[(size_t)ldy * 4] = lo;
     } else {
         if (live && n_out < N) Y[(size_t)om * ldy + n_out] = y_old + v;
     }
@@ -215,45 +230,72 @@ bool linear_few_rows(int M) {
     return M <= 16 && !t.linear_mt && !t.linear_nf && !t.linear_ksplit && !t.linear_ks && !t.linear_big_all;
 }
 
-// 16-column tiles per workgroup.  Two (half as many loads of the same activations) where that still gives every CU a workgroup:
-// 8192 outputs of 28672 inputs 68 against 75 us at one row, 72 against 89 us at 8; 4096 outputs of 14336 inputs 25 against 20 us
-static int few_col_tiles(const Linear& L) { return (L.N + 31) / 32 >= kNumCU ? 2 : 1; }
+// 16-column tiles per workgroup.  Two (half as many loads of the same activations) where that takes a round of the chip less: 8192
+// outputs of 28672 inputs 68 against 75 us at one row, 72 against 89 us at 8; 5120 outputs of 8192 inputs 16.1 against 21.1 and
+// 19.3 against 25.6; 4096 outputs of 14336 inputs 25 against 20.  Two rounds of them against three of one (9216 columns) are
+// as fast at 8 rows and faster above.
+static int few_col_tiles(const Linear& L, int M) {
+    const int tiles = (L.N + 15) / 16;
+    return tiles > kNumCU && (tiles <= 2 * kNumCU || tiles > 3 * kNumCU || M > 8) ? 2 : 1;
+}
 
 // Time of the kernel above at M rows, in microseconds: a launch's start and end, and the longest of
 //   the weight stream at 7.2 TB/s;
 //   what one CU takes in, weights and activations of its workgroups: 50 GB/s (fp32 rows; 45 with the rotation behind them,
-//     70 for packed terms), and 27 (one column tile) or 31 GB/s of weights for workgroups that share a CU while others idle;
+//     70 for packed terms), and 27 (one column tile) or 31 GB/s of weights for workgroups that share a CU while others idle; of two
+//     column tiles in one round 42 GB/s of weights and then 95 of packed terms or 57 of fp32 rows (5120 outputs of 14336 inputs:
+//     packed 26.8 us at one row, 36.5 at 16);
 //   what all CUs together take in: 12 TB/s, of fp32 rows less the longer K is (10.4 at 28672), and a sixth less with two
 //     column tiles if K is no multiple of 256 (16384 x 5808 and 14000 x 5008 at 16 rows: 10.0 and 9.4, 16384 x 6144: 11.5).
 // The rates are fitted to single projections of 256 .. 16384 columns, K = 1024 .. 32768, and to the layers of 15 decoders of
 // 256 .. 16384 hidden columns, at 1 .. 16 rows; it is within 10 % of most of them (8B widths at 16 rows: 61 against 60 us for
 // QKV, O and down; 5120 wide with 40 KV heads: 119 against 126).
-static double few_us(const Linear& L, int M, FewMode mode) {
-    const int ct = mode == FEW_QKV ? 2 : few_col_tiles(L);
+static double few_us(const Linear& L, int M, FewMode mode, int ct) {
     const int wgs = (L.N + 16 * ct - 1) / (16 * ct), rounds = (wgs + kNumCU - 1) / kNumCU;
     const double w = 32e-6 * ct * L.K, a = 4e-6 * M * L.K;  // MB of weights and activations per workgroup
-    const double cu = mode == FEW_QKV ? 0.045 : (mode == FEW_PACKED ? 0.070 : 0.050);  // MB/us
+    const double cu = mode >= FEW_NORM ? 0.045 : (mode == FEW_PACKED ? 0.070 : 0.050);  // MB/us
     const double chip = mode == FEW_PACKED ? 12.0 : (12.2 - L.K / 16000.0) * (ct == 2 && L.K % 256 ? 0.84 : 1.0);
     double t = wgs * w / 7.2;
     const auto at_least = [&](double v) { t = v > t ? v : t; };
     at_least(rounds * (w + a) / cu);
     at_least((rounds > 1 ? rounds * kNumCU : wgs) * (w + a) / chip);
     if (rounds > 1) at_least(rounds * w / (ct == 1 ? 0.027 : 0.031));
+    else if (ct == 2 && mode <= FEW_PACKED) at_least(w / 0.042 + a / (mode == FEW_PACKED ? 0.095 : 0.057));
     return 4.0 + t;
 }
 // the tiled kernel's, whose K-slices fill the chip evenly; it hardly depends on the rows there
 static double tiled_us(const Linear& L) { return 3.5 + 2e-6 * L.N * L.K / 6.6; }
+
+// Products that the tiled kernel does not slice, with or without the norm in the operand load: gate/up and the head.  There a
+// workgroup walks the whole of K in one chain of chunks (5.8 ns per k), which with fewer than a column tile per wave and CU nothing
+// hides.  Up to one round of 32 columns a workgroup the few-row kernel is faster at any K (28.6 -> 10.6 us for 2816 columns
+// of K = 4096 at one row, 29.9 -> 15.3 for 8192 at 16; 5.9 -> 3.1 for 512 of K = 256), in two rounds from K = 2048 and up to 8
+// rows (16384 columns: 17.6 -> 14.7 at 8 rows; at K = 1024 11.2 against 11.4; inside a step at K = 3072 and 13 rows 1 us a layer
+// lost); beyond that the weight stream decides.  Whole steps of two layers, 1024 wide: 92 -> 81 us at 4 rows, 102 -> 94 at 16.
+static double unsliced_us(const Linear& L) {
+    const double chain = 3.3 + 0.0058 * L.K;
+    return chain > tiled_us(L) ? chain : tiled_us(L);
+}
+bool norm_few_pays(const Linear& L, int M) { return linear_few_rows(M) && (L.N <= 32 * kNumCU || (L.N <= 64 * kNumCU && L.K >= 2048 && M <= 8)); }
 
 // A whole layer: what the few-row QKV, O and down projections take longer than the tiled ones must stay below the two norms and
 // the rotation that become part of them (13.6 us up to 4096 columns, 20 at 8192, 25 at 16384, less what the norm costs where it
 // goes).  Measured end to end, us per layer gained by this path at 1 / 8 / 12 / 16 rows: 8B widths 9 / 6 / 1 / -4, 70B widths
 // 8 / 7 / 2 / -9, 6144 wide (384 workgroups) 0 / -9 / -22 / -36, 12288 wide 6 / -12 / -23 / -51, 5120 wide with 40 KV heads (320 and
 // 480 workgroups) -8 / -17 / -31 / -43.  On one set of weights, whole steps by this rule are within 1 % of the better path.
-bool step_few_rows(const Linear& qkv, const Linear& o, const Linear& down, int M) {
+bool step_few_rows(const Linear& qkv, const Linear& o, const Linear& gu, const Linear& down, int M) {
     if (!linear_few_rows(M)) return false;
     const double saved = 5.9 + 1.3 / 1024 * qkv.K;
-    return few_us(qkv, M, FEW_QKV) + few_us(o, M, FEW_ROWS) + few_us(down, M, FEW_PACKED) <=
-           tiled_us(qkv) + tiled_us(o) + tiled_us(down) + (saved > 13.0 ? saved : 13.0);
+    double pays = tiled_us(qkv) + tiled_us(o) + tiled_us(down) + (saved > 13.0 ? saved : 13.0);
+    int ct_o = (o.N + 31) / 32 >= kNumCU ? 2 : 1, ct_down = (down.N + 31) / 32 >= kNumCU ? 2 : 1;
+    if (qkv.N <= 32 * kNumCU) {  // (a QKV of two rounds was measured with these column tiles and without a gate/up of its own)
+        ct_o = few_col_tiles(o, M);
+        ct_down = few_col_tiles(down, M);
+        const double gu_saved = norm_few_pays(gu, M) ? unsliced_us(gu) - few_us(gu, M, FEW_SWIGLU_NORM, 2) : 0.0;
+        pays += gu_saved > 0.0 ? gu_saved : 0.0;
+        if (ct_o == 2) pays -= 2.0;  // (5120 hidden columns at 11 rows: 1.5 us a layer more than estimated)
+    }
+    return few_us(qkv, M, FEW_QKV, 2) + few_us(o, M, FEW_ROWS, ct_o) + few_us(down, M, FEW_PACKED, ct_down) <= pays;
 }
 
 // A projection by itself: against the tiled kernel, the sum of its slices (5 us), and no less than the 25 us that the host takes to
@@ -263,12 +305,12 @@ bool step_few_rows(const Linear& qkv, const Linear& o, const Linear& down, int M
 bool linear_few_pays(const Linear& L, int M) {
     if (!linear_few_rows(M) || L.N > 16384 || (L.K > 16384 && L.N < 4096)) return false;
     const double tiled = 5.0 + tiled_us(L);
-    return few_us(L, M, FEW_ROWS) <= (tiled > 25.5 ? tiled : 25.5);
+    return few_us(L, M, FEW_ROWS, few_col_tiles(L, M)) <= (tiled > 25.5 ? tiled : 25.5);
 }
 
 // the same for the down projection of a feed-forward block, whose scratch memory is there anyway
 bool linear_few_pays_packed(const Linear& L, int M) {
-    return linear_few_rows(M) && L.N <= 16384 && few_us(L, M, FEW_PACKED) <= 5.0 + tiled_us(L);
+    return linear_few_rows(M) && L.N <= 16384 && few_us(L, M, FEW_PACKED, few_col_tiles(L, M)) <= 5.0 + tiled_us(L);
 }
 
 int32_t launch_linear_few(const Linear& L, const float* A, int64_t lda, int M, int packed, float* y, int ldy, int add, hipStream_t st) {
@@ -276,7 +318,7 @@ int32_t launch_linear_few(const Linear& L, const float* A, int64_t lda, int M, i
     if (M > 16) return fail(CHIRON_ERR_INVALID_ARG, "linear: %d rows on the few-row path", M);
     if (L.K % 16 != 0 || L.K < 16) return fail(CHIRON_ERR_SHAPE, "linear: K=%d must be a positive multiple of 16", L.K);
     if ((!packed && lda % 4 != 0) || ((uintptr_t)A & 15)) return fail(CHIRON_ERR_INVALID_ARG, "linear: input rows must be 16-byte aligned");
-    const int ct = few_col_tiles(L);
+    const int ct = few_col_tiles(L, M);
     const dim3 grid((L.N + 16 * ct - 1) / (16 * ct)), block(64 * kFewWaves);
 #define CHIRON_FEW(CT_, MODE_) \
     launch(linear_few_kernel<CT_, MODE_>, grid, block, st, L.w, L.tstride, L.N, L.K, L.Kpad, A, lda, M, (const uint16_t*)nullptr, 0.f, y, ldy, add, RopeOut())
@@ -284,6 +326,28 @@ int32_t launch_linear_few(const Linear& L, const float* A, int64_t lda, int M, i
     else if (ct == 1) CHIRON_FEW(1, FEW_ROWS);
     else if (packed) CHIRON_FEW(2, FEW_PACKED);
     else CHIRON_FEW(2, FEW_ROWS);
+#undef CHIRON_FEW
+    CHIRON_HIP(hipGetLastError());
+    return CHIRON_OK;
+}
+
+// A fused gate/up matrix (ldy: the padded K of its consumer), with the norm in its operand load or without, or a plain projection with it
+int32_t launch_norm_few(const Linear& L, const float* h, int lda, int M, const NormIn* norm, int swiglu, float* y, int ldy, hipStream_t st) {
+    if (M == 0) return CHIRON_OK;
+    if (M > 16) return fail(CHIRON_ERR_INVALID_ARG, "linear: %d rows on the few-row path", M);
+    if (L.K % 16 != 0 || L.K < 16) return fail(CHIRON_ERR_SHAPE, "linear: K=%d must be a positive multiple of 16", L.K);
+    if (lda % 4 != 0 || ((uintptr_t)h & 15)) return fail(CHIRON_ERR_INVALID_ARG, "linear: input rows must be 16-byte aligned");
+    if (swiglu && (L.N % 32 != 0 || ldy % 8 != 0 || ((uintptr_t)y & 15))) return fail(CHIRON_ERR_INVALID_ARG, "linear: SwiGLU needs whole gate/up tiles and 16-byte aligned output");
+    if (!swiglu && !norm) return fail(CHIRON_ERR_INVALID_ARG, "linear: no norm");
+    const int ct = swiglu ? 2 : few_col_tiles(L, M);
+    const NormIn nm = norm ? *norm : NormIn();
+    const dim3 grid((L.N + 16 * ct - 1) / (16 * ct)), block(64 * kFewWaves);
+#define CHIRON_FEW(CT_, MODE_, LDY_) \
+    launch(linear_few_kernel<CT_, MODE_>, grid, block, st, L.w, L.tstride, L.N, L.K, L.Kpad, h, (int64_t)lda, M, nm.gain, nm.eps, y, LDY_, 0, RopeOut())
+    if (swiglu && norm) CHIRON_FEW(2, FEW_SWIGLU_NORM, M * (ldy / 8));
+    else if (swiglu) CHIRON_FEW(2, FEW_SWIGLU, M * (ldy / 8));
+    else if (ct == 1) CHIRON_FEW(1, FEW_NORM, ldy);
+    else CHIRON_FEW(2, FEW_NORM, ldy);
 #undef CHIRON_FEW
     CHIRON_HIP(hipGetLastError());
     return CHIRON_OK;

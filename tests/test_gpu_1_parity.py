@@ -1146,3 +1146,27 @@ def test_linear_shapes_by_estimate(M, N, K):
     gu, down = B().GateUp(Wg.cuda(), Wu.cuda()), B().Linear(Wd.cuda())
     assert rel_err(gu.ffn(down, torch.from_numpy(xs).cuda()).cpu().numpy(), want) <= KERNEL_TOL
     gu.close(); down.close()
+
+
+@pytest.mark.parametrize("M,K,F,N", [(1, 16, 16, 16), (16, 272, 4096, 4112), (3, 2064, 8192, 8192), (9, 1040, 4112, 100), (16, 2048, 8208, 9216), (12, 2320, 48, 5120)])
+def test_few_rows_gate_up_and_two_column_tiles(M, K, F, N):
+    """gate/up by the few-row kernel with SwiGLU in its epilogue (up to one round of 32-column tiles, 4096 columns, two at K >= 2048,
+    and what lies past either), and outputs of 4097 .. 8192 columns, whose workgroups take two column tiles"""
+    x, Wg, Wu, Wd, _, want = ffn_case(M, K, F, N, M + K + F)
+    b = B()
+    gu, down = b.GateUp(Wg.cuda(), Wu.cuda()), b.Linear(Wd.cuda())
+    print("few gate/up", M, K, F, N, flush=True)
+    assert rel_err(gu.ffn(down, torch.from_numpy(x).cuda()).cpu().numpy(), want) <= KERNEL_TOL
+    gu.close(); down.close()
+
+
+@pytest.mark.parametrize("over,batch", [(dict(vocab=8192), 16), (dict(vocab=8208), 3), (dict(hidden=2064, ffn=4112, vocab=16384), 9), (dict(hidden=4624, ffn=32, vocab=96), 2)])
+def test_step_of_few_rows_with_narrow_gate_up_and_head(over, batch):
+    """steps whose gate/up and head are products of the few-row kernel too (one round of 32-column tiles, two at K >= 2048), and the
+    widths behind them, against the oracle"""
+    c = make_case(m=dict(I.TINY, n_layers=1, **over), batch=batch, kind="tiny", seed=47, storage="bf16", gain_jitter=0.2)
+    print("few head", over, batch, flush=True)
+    g = gpu_setup(c)
+    (_, got, want, _), norms = norm_launches(g, lambda: run_both(c, g))
+    assert norms == 0  # the few-row path
+    check_logits(got, want, min_agree=1.0 - 1.0 / batch)
