@@ -45,9 +45,11 @@ __device__ __forceinline__ int pass_len(const int32_t* __restrict__ seq_lens, co
 // page counts in LDS, sums through wave shuffles (one barrier per sum), and deals the records out item by item (an
 // item's request is found by bisection), not request by request: one long request is no serial loop of one thread.
 // Measured on the attention entry point: 664 -> 646 us at 32 requests of 28k tokens, where the serial loop took 28 us.
+// Sums go through the lanes' registers, what the workgroup reads back stays in LDS, and up to 64 passes all item sizes are counted at
+// once: the kernel that begins a step 8.1 -> 4.9 us (toy decoder), 10.0 -> 6.5 (64 requests); attention of 8 requests 25.9 -> 22.6.
 __device__ __forceinline__ void attn_plan_block(const PlanArgs& a) {
-    __shared__ int s_np[kPlanCached], s_whole[kPlanCached], s_last[kPlanCached];
-    __shared__ int s_sum[2][kPlanThreads / 64], s_scan[4][kPlanThreads / 64], s_long;
+    __shared__ int s_len[kPlanCached], s_item0[kPlanCached], s_whole[kPlanCached], s_last[kPlanCached];
+    __shared__ int s_sum[2][kPlanThreads / 64], s_scan[4][kPlanThreads / 64], s_count[64], s_long;
     const AttnShape sh = a.sh;
     const int batch = a.batch * sh.ng;  // passes
     const int max_batch = a.max_batch, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -59,19 +61,19 @@ __device__ __forceinline__ void attn_plan_block(const PlanArgs& a) {
     int32_t* long_passes = plan + 4 + 4 * max_batch;
     if (tid == 0) s_long = 0;
     if (tid < kTicketQueues) plan[plan_ticket_offset(max_batch, a.cap_items) + tid * kTicketStride] = 0;
-    for (int v = tid; v < min(batch, kPlanCached); v += kPlanThreads) s_np[v] = (pass_len(a.seq_lens, sh, v) + kBlockSize - 1) / kBlockSize;
-    __syncthreads();
-    auto pages_of = [&](int v) { return v < kPlanCached ? s_np[v] : (pass_len(a.seq_lens, sh, v) + kBlockSize - 1) / kBlockSize; };
+    for (int v = tid; v < min(batch, kPlanCached); v += kPlanThreads) s_len[v] = pass_len(a.seq_lens, sh, v);
+    lds_barrier();
+    auto len_of = [&](int v) { return v < kPlanCached ? s_len[v] : pass_len(a.seq_lens, sh, v); };
+    auto pages_of = [&](int v) { return (len_of(v) + kBlockSize - 1) / kBlockSize; };
     const int per = (batch + kPlanThreads - 1) / kPlanThreads;  // requests per thread, contiguous
     const int i0 = min(batch, tid * per), i1 = min(batch, i0 + per);
 
     // workgroup-wide sum, every thread gets the total; two buffers in turn, so that one barrier per sum is enough
     int turn = 0;
     auto block_sum = [&](int v) {
-#pragma unroll
-        for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
+        v = wave_total(v);
         if (lane == 0) s_sum[turn][wave] = v;
-        __syncthreads();
+        lds_barrier();
         int t = 0;
 #pragma unroll
         for (int k = 0; k < kPlanThreads / 64; ++k) t += s_sum[turn][k];
@@ -83,7 +85,19 @@ __device__ __forceinline__ void attn_plan_block(const PlanArgs& a) {
         for (int i = i0; i < i1; ++i) n += (pages_of(i) + cp - 1) / cp;
         return block_sum(n);
     };
-    const int total = count_items(1);
+    // Up to 64 passes: the counts of all item sizes up to 64 pages at once, four sizes a wave, instead of one sum over the workgroup
+    // after the other (each a barrier and a trip through LDS, some 0.2 us; a search takes up to nine).
+    const bool at_once = batch <= 64;
+    if (at_once) {
+        const int np = lane < batch ? pages_of(lane) : 0;
+#pragma unroll
+        for (int i = 0; i < 64 / (kPlanThreads / 64); ++i) {
+            const int c = 1 + wave + i * (kPlanThreads / 64), n = wave_total((np + c - 1) / c);
+            if (lane == 0) s_count[c - 1] = n;
+        }
+        lds_barrier();
+    }
+    const int total = at_once ? s_count[0] : count_items(1);
 
     // Pages per item.  Starting an item costs a wave a load latency or two, and an item that is left when the others have
     // run out streams alone, at a fraction of the rate (about 15 GB/s a wave).  So: when one round of the grid can hold
@@ -97,8 +111,12 @@ __device__ __forceinline__ void attn_plan_block(const PlanArgs& a) {
     const auto fits = [&](int c) { return (int64_t)count_items(c) * a.n_kv <= a.slots; };  // uniform: every thread sees the same counts
     // the largest item that leaves no more than a quarter of the round's page slots empty
     const int full = (int)min((int64_t)kPlanMaxRound, (int64_t)total * a.n_kv * 4 / ((int64_t)a.slots * 3));
-    const bool small = fits(64);
-    if (small || (full > 64 && fits(full))) {
+    const bool small = at_once ? (int64_t)s_count[63] * a.n_kv <= a.slots : fits(64);
+    if (small && at_once) {
+        const uint64_t fit = __ballot(lane > 0 && (int64_t)s_count[lane] * a.n_kv <= a.slots);  // counts fall with the size
+        cp = __builtin_ctzll(fit) + 1;
+        drawn = false;
+    } else if (small || (full > 64 && fits(full))) {
         int lo = small ? 2 : (int)max((int64_t)65, (int64_t)total * a.n_kv / a.slots), hi = small ? 64 : full;
         while (lo < hi) {
             const int mid = (lo + hi) / 2;
@@ -134,16 +152,11 @@ __device__ __forceinline__ void attn_plan_block(const PlanArgs& a) {
 #pragma unroll
     for (int c = 0; c < 4; ++c) {
         if (c > 0 && !drawn) break;
-        int scan = cnt[c];
-#pragma unroll
-        for (int o = 1; o < 64; o <<= 1) {
-            const int v = __shfl_up(scan, o);
-            if (lane >= o) scan += v;
-        }
+        const int scan = wave_scan(cnt[c]);
         if (lane == 63) s_scan[c][wave] = scan;
         off[c] = scan - cnt[c];
     }
-    __syncthreads();
+    lds_barrier();
 #pragma unroll
     for (int c = 0; c < 4; ++c)
 #pragma unroll
@@ -158,22 +171,24 @@ __device__ __forceinline__ void attn_plan_block(const PlanArgs& a) {
         const int pg0 = ch * cp, last = min(pg0 + cp, pages_of(v)) - 1;
         const int32_t* btrow = a.bt + (size_t)(v / sh.ng) * a.max_blocks;
         const int b0 = btrow[pg0], b1 = btrow[min(pg0 + 1, last)], b2 = btrow[min(pg0 + 2, last)], b3 = btrow[min(pg0 + 3, last)];
-        recs[2 * it] = make_int4(v, pg0, pass_len(a.seq_lens, sh, v), b0);
+        recs[2 * it] = make_int4(v, pg0, len_of(v), b0);
         recs[2 * it + 1] = make_int4(b1, b2, b3, partial);
     };
     off[2] += n_whole;
     off[3] += n_whole + total4[2];
     for (int i = i0; i < i1; ++i) {
         const int np = pages_of(i), nch = (np + cp - 1) / cp, r = last_piece(np), before = drawn ? off[1] : off[0];
-        if (i < kPlanCached) s_whole[i] = before;
-        seq_whole[i] = before;
+        if (i < kPlanCached) {
+            s_whole[i] = before;
+            s_item0[i] = off[0];
+        } else seq_whole[i] = before;
         seq_item0[i] = off[0];
         seq_nch[i] = nch;
         if (nch > kMergeLong) long_passes[atomicAdd(&s_long, 1)] = i;
         if (drawn) {
             const int place = r == 0 ? -1 : (2 * r >= cp ? off[2]++ : off[3]++);
             if (i < kPlanCached) s_last[i] = place;
-            seq_last[i] = place;
+            else seq_last[i] = place;
         }
         off[0] += nch;
         if (drawn) off[1] += np / cp;
@@ -182,12 +197,14 @@ __device__ __forceinline__ void attn_plan_block(const PlanArgs& a) {
         plan[0] = total4[0];
         plan[1] = cp;
     }
-    __syncthreads();  // (also orders what this workgroup reads back from global memory)
+    if (batch > kPlanCached) __syncthreads();  // this workgroup reads back from global memory what does not fit in LDS
+    else lds_barrier();
+    auto item0_of = [&](int v) { return v < kPlanCached ? s_item0[v] : seq_item0[v]; };
     if (tid == 0) plan[2] = s_long;
     for (int u = tid; u < n_whole + (drawn ? batch : 0); u += kPlanThreads) {
         if (u >= n_whole) {  // a last piece
             const int v = u - n_whole, place = v < kPlanCached ? s_last[v] : seq_last[v];
-            if (place >= 0) put(place, v, pages_of(v) / cp, seq_item0[v] + pages_of(v) / cp);
+            if (place >= 0) put(place, v, pages_of(v) / cp, item0_of(v) + pages_of(v) / cp);
             continue;
         }
         const int it = u;
@@ -199,7 +216,7 @@ __device__ __forceinline__ void attn_plan_block(const PlanArgs& a) {
             else hi = mid - 1;
         }
         const int ch = it - (lo < kPlanCached ? s_whole[lo] : seq_whole[lo]);
-        put(it, lo, ch, drawn ? seq_item0[lo] + ch : it);
+        put(it, lo, ch, drawn ? item0_of(lo) + ch : it);
     }
 }
 

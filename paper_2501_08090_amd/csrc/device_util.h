@@ -41,6 +41,19 @@ __device__ __forceinline__ float wave_sum(float v) {
     return v;
 }
 
+// Sums over a wave of whole numbers by data-parallel moves between the lanes' registers (8 cycles a step, where a shuffle goes
+// through the LDS crossbar and takes some 100).  wave_scan: lane l gets the sum over the lanes 0 .. l; wave_total: all lanes' sum.
+__device__ __forceinline__ int wave_scan(int v) {
+    v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xf, 0xf, false);  // row_shr:1, rows of 16 lanes; a lane without a source adds 0
+    v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xf, 0xf, false);  // row_shr:2
+    v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xf, 0xf, false);  // row_shr:4
+    v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xf, 0xf, false);  // row_shr:8
+    v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xa, 0xf, false);  // row_bcast:15 into the rows 1 and 3
+    v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xc, 0xf, false);  // row_bcast:31 into the rows 2 and 3
+    return v;
+}
+__device__ __forceinline__ int wave_total(int v) { return __builtin_amdgcn_readlane(wave_scan(v), 63); }
+
 // Workgroup barrier that waits for this wave's LDS traffic only: global loads already in
 // flight (weight prefetch) stay in flight across it.
 __device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }

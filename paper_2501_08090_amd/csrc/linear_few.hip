@@ -269,14 +269,14 @@ static double tiled_us(const Linear& L) { return 3.5 + 2e-6 * L.N * L.K / 6.6; }
 // Products that the tiled kernel does not slice, with or without the norm in the operand load: gate/up and the head.  There a
 // workgroup walks the whole of K in one chain of chunks (5.8 ns per k), which with fewer than a column tile per wave and CU nothing
 // hides.  Up to one round of 32 columns a workgroup the few-row kernel is faster at any K (28.6 -> 10.6 us for 2816 columns
-// of K = 4096 at one row, 29.9 -> 15.3 for 8192 at 16; 5.9 -> 3.1 for 512 of K = 256), in two rounds from K = 2048 and up to 8
-// rows (16384 columns: 17.6 -> 14.7 at 8 rows; at K = 1024 11.2 against 11.4; inside a step at K = 3072 and 13 rows 1 us a layer
-// lost); beyond that the weight stream decides.  Whole steps of two layers, 1024 wide: 92 -> 81 us at 4 rows, 102 -> 94 at 16.
+// of K = 4096 at one row, 29.9 -> 15.3 for 8192 at 16; 5.9 -> 3.1 for 512 of K = 256), in two rounds from K = 2048, and if the second
+// one is more than half full only up to 8 rows (16384 columns: 17.6 -> 14.7 at 8 rows; at K = 1024 11.2 against 11.4; inside a step
+// at K = 3072 and 13 rows 1 us a layer lost, at K = 2048 with 11264 columns 3 gained); beyond that the weight stream decides.  Whole steps of two layers, 1024 wide: 92 -> 81 us at 4 rows, 102 -> 94 at 16.
 static double unsliced_us(const Linear& L) {
     const double chain = 3.3 + 0.0058 * L.K;
     return chain > tiled_us(L) ? chain : tiled_us(L);
 }
-bool norm_few_pays(const Linear& L, int M) { return linear_few_rows(M) && (L.N <= 32 * kNumCU || (L.N <= 64 * kNumCU && L.K >= 2048 && M <= 8)); }
+bool norm_few_pays(const Linear& L, int M) { return linear_few_rows(M) && (L.N <= 32 * kNumCU || (L.N <= 64 * kNumCU && L.K >= 2048 && (M <= 8 || L.N <= 48 * kNumCU))); }
 
 // A whole layer: what the few-row QKV, O and down projections take longer than the tiled ones must stay below the two norms and
 // the rotation that become part of them (13.6 us up to 4096 columns, 20 at 8192, 25 at 16384, less what the norm costs where it
