@@ -393,8 +393,13 @@ static int32_t step_rows(chiron_model* m, chiron_kvpool* p, const int32_t* block
             STEP(CHIRON_K_DOWN, launch_linear_few(m->down[l], m->gub, (int64_t)B * (m->down[l].Kpad / 8), B, 1, m->h, H, 1, st));
         }
         const NormIn ln{m->final_norm, c.rms_eps};
-        if (norm_few_pays(m->lm, B)) STEP(CHIRON_K_LMHEAD, launch_norm_few(m->lm, m->h, H, B, &ln, 0, logits, c.vocab, st));
-        else STEP(CHIRON_K_LMHEAD, launch_linear(m->lm, m->h, H, B, logits, c.vocab, EPI_STORE, PRO_NONE, nullptr, 1, nullptr, nullptr, st, &ln));
+        if (B <= 16 && norm_few_pays(m->lm, B)) STEP(CHIRON_K_LMHEAD, launch_norm_few(m->lm, m->h, H, B, &ln, 0, logits, c.vocab, st));
+        else {
+            // the tiled kernel takes the norm for up to 16 rows; with more, the head (one product a step) stays with it and a norm of its own
+            if (B > 16) STEP(CHIRON_K_RMSNORM, launch_rmsnorm(m->h, m->part, 0, ln.gain, B, H, c.rms_eps, m->x, st));
+            STEP(CHIRON_K_LMHEAD, launch_linear(m->lm, B > 16 ? m->x : m->h, H, B, logits, c.vocab, EPI_STORE, PRO_NONE, nullptr, 1, nullptr, nullptr, st,
+                                                B > 16 ? nullptr : &ln));
+        }
         return CHIRON_OK;
     }
     for (int l = 0; l < c.n_layers; ++l) {
@@ -710,7 +715,7 @@ struct OpScratch {
 static OpScratch op_linear_scratch(const Linear& L, int M, int prologue, SliceCost slices, bool in_place = false) {
     OpScratch sc;
     sc.slices = slices;
-    if (prologue == PRO_NONE && !in_place && linear_few_pays(L, M)) return sc;  // the few-row path needs none
+    if (prologue == PRO_NONE && !in_place && linear_few_pays(L, M, slices)) return sc;  // the few-row path needs none
     const bool split = prologue == PRO_NONE && tuning().linear_big_all && M >= linear_big_min_rows(L);
     if (split) sc.split_bytes = 2 * linear_big_split_elems(M, L.Kpad) * 2;
     // wide outputs (LM head, gate/up) have enough column tiles on their own and are never sliced in the step
@@ -727,7 +732,7 @@ static OpScratch op_linear_scratch(const Linear& L, int M, int prologue, SliceCo
 // product goes to the scratch memory whole, sliced or not, and the sum of the slices brings it to y.
 static int32_t op_linear_common(const Linear& L, const float* x, int lda, int M, float* y, int accumulate, int prologue,
                                 const OpScratch& sc, void* scratch, hipStream_t st, bool in_place = false) {
-    if (prologue == PRO_NONE && !in_place && linear_few_pays(L, M)) return launch_linear_few(L, x, lda, M, 0, y, L.N, accumulate, st);
+    if (prologue == PRO_NONE && !in_place && linear_few_pays(L, M, sc.slices)) return launch_linear_few(L, x, lda, M, 0, y, L.N, accumulate, st);
     float* part = sc.part_bytes ? (float*)scratch : nullptr;
     uint16_t* asplit = sc.split_bytes ? (uint16_t*)((char*)scratch + sc.part_bytes) : nullptr;
     int ks = 1;
@@ -776,7 +781,7 @@ int32_t chiron_op_swiglu_ffn(const chiron_linear* gate_up, const chiron_linear* 
     if (D.K != F) return fail(CHIRON_ERR_SHAPE, "swiglu_ffn: gate/up has %d columns, the down projection %d inputs", F, D.K);
     hipStream_t st = (hipStream_t)stream;
     // the intermediate in the form the decode step gives it at this row count
-    const bool few = linear_few_pays_packed(D, M);
+    const bool few = ffn_few_pays(G, D, M);
     const bool packed = !few && M >= linear_big_min_rows(D);
     const size_t bytes = ((packed ? 2 * linear_big_split_elems(M, D.Kpad) * 2 : (size_t)M * D.Kpad * 4) + 255) / 256 * 256;
     const OpScratch sc = few ? OpScratch() : op_linear_scratch(D, M, packed ? PRO_PACKED : PRO_NONE, SLICES_BLOCK);
@@ -785,8 +790,8 @@ int32_t chiron_op_swiglu_ffn(const chiron_linear* gate_up, const chiron_linear* 
     if (rc) return rc;
     void* scratch = (char*)act + bytes;
     if (few) {
-        rc = norm_few_pays(G, M) ? launch_norm_few(G, x, G.K, M, nullptr, 1, (float*)act, D.Kpad, st)
-                                 : launch_linear(G, x, G.K, M, (float*)act, D.Kpad, EPI_SWIGLU_FEW, PRO_NONE, nullptr, 1, nullptr, nullptr, st);
+        rc = norm_few_pays(G, M, false) ? launch_norm_few(G, x, G.K, M, nullptr, 1, (float*)act, D.Kpad, st)
+                                        : launch_linear(G, x, G.K, M, (float*)act, D.Kpad, EPI_SWIGLU_FEW, PRO_NONE, nullptr, 1, nullptr, nullptr, st);
         if (!rc) rc = launch_linear_few(D, (const float*)act, (int64_t)M * (D.Kpad / 8), M, 1, y, D.N, accumulate, st);
     } else if (packed) {
         // the epilogue writes the columns below F only: the padding of K must not hold NaN bits when the down projection reads it

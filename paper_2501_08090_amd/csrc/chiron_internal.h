@@ -135,14 +135,15 @@ int32_t launch_reduce_partials(const float* part, int ks, int64_t n, float* y, i
 int32_t launch_pack_rows(const uint16_t* src, int rows, int K, size_t tstride, uint16_t* dst_packed, int row_offset,
                          hipStream_t st, int interleave = 0);
 
-// ---- projections of up to 16 rows (linear_few.hip) -----------------------------------------------
+// ---- projections of a few rows (linear_few.hip) --------------------------------------------------
 // whether M rows can take that path (a forced launch shape keeps the tiled kernels)
 bool linear_few_rows(int M);
-// whether they should: the layers of a decode step, a projection by itself, the down projection of a feed-forward block
+// whether they should: the layers of a decode step, a gate/up or a head (norm: with a norm before it), a projection by itself,
+// a feed-forward block
 bool step_few_rows(const Linear& qkv, const Linear& o, const Linear& gu, const Linear& down, int M);
-bool norm_few_pays(const Linear& L, int M);
-bool linear_few_pays(const Linear& L, int M);
-bool linear_few_pays_packed(const Linear& L, int M);
+bool norm_few_pays(const Linear& L, int M, bool norm = true);
+bool linear_few_pays(const Linear& L, int M, SliceCost slices);
+bool ffn_few_pays(const Linear& gu, const Linear& down, int M);
 // y (+)= A * W^T; one launch, no workspace.  A: fp32 rows of stride lda, or (packed) the two bf16 terms that
 // EPI_SWIGLU_FEW writes, with lda = distance from the hi to the lo terms in 16-byte units
 int32_t launch_linear_few(const Linear& L, const float* A, int64_t lda, int M, int packed, float* y, int ldy, int add, hipStream_t st);

@@ -806,7 +806,7 @@ int32_t launch_linear(const Linear& L, const float* A, int lda, int M, float* y,
                       float* part, int max_split, int* ksplit_out, uint16_t* asplit, hipStream_t st, const NormIn* norm, SliceCost slices) {
     if (ksplit_out) *ksplit_out = 1;
     if (M == 0) return CHIRON_OK;
-    if (norm && (max_split > 1 || prologue != PRO_NONE || !linear_few_rows(M)))
+    if (norm && (max_split > 1 || prologue != PRO_NONE || M > 16 || !linear_few_rows(M)))
         return fail(CHIRON_ERR_INVALID_ARG, "linear: a norm in the operand load needs an unsliced launch of few rows");
     if (epilogue != EPI_STORE && epilogue != EPI_ADD && epilogue != EPI_SWIGLU && epilogue != EPI_SWIGLU_PACKED && epilogue != EPI_SWIGLU_FEW)
         return fail(CHIRON_ERR_INVALID_ARG, "linear: unknown epilogue %d", epilogue);

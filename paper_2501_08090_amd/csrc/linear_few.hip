@@ -1,4 +1,4 @@
-// Projections of a few rows (up to 16).  There the weight stream is everything, and what the tiled kernel of linear.hip
+// Projections of a few rows (up to 16, narrow ones up to 32).  There the weight stream is everything, and what the tiled kernel of linear.hip
 // spends around it is launches: K-slices that a kernel of their own has to add up, the norm before, the rotary embedding
 // behind.  Here a workgroup owns 16 or 32 output columns over the WHOLE of K: its 8 waves take an eighth of K each, add
 // their accumulators through LDS, and the result is final.  So the residual stream is complete when the kernel ends, the
@@ -34,17 +34,18 @@ constexpr int kFewWaves = 8;
 // FEW_NORM: a plain projection of it.  FEW_SWIGLU_NORM: FEW_SWIGLU of it.
 // FEW_QKV: the fused QKV projection of a decode step, which ends in the rotary embedding and the append to the cache.
 enum FewMode { FEW_ROWS, FEW_PACKED, FEW_SWIGLU, FEW_NORM, FEW_SWIGLU_NORM, FEW_QKV };
-template <int CT, int MODE>
+// RT: 16-row tiles; two of them (17 .. 32 rows) leave registers for half the k-steps in flight.
+template <int CT, int MODE, int RT = 1>
 __global__ __launch_bounds__(64 * kFewWaves) void linear_few_kernel(const uint16_t* __restrict__ Wp, size_t tstride, int N, int K, int Kpad,
                                                                    const float* __restrict__ A, int64_t lda, int M,
                                                                    const uint16_t* __restrict__ gain, float eps,
                                                                    float* __restrict__ Y, int ldy, int add, RopeOut ro) {
     constexpr bool QKV = MODE == FEW_QKV, NORM = MODE >= FEW_NORM, SWIGLU = MODE == FEW_SWIGLU || MODE == FEW_SWIGLU_NORM;
-    constexpr int D = 8;        // k-steps in flight per wave (CT KiB of weights each)
+    constexpr int D = RT == 1 ? 8 : 4;  // k-steps in flight per wave (CT KiB of weights each)
     constexpr int WS = 72;      // float4 units between the 16x16 tiles in LDS, 18 between a tile's row groups: no two
     constexpr int QS = 18;      // threads of the final sum that read at once share a bank
-    __shared__ float4 s_acc[kFewWaves * CT * WS];
-    __shared__ float s_ss[kFewWaves][16];
+    __shared__ float4 s_acc[RT][kFewWaves * CT * WS];
+    __shared__ float s_ss[RT][kFewWaves][16];
     static_assert(CT == 2 || (!QKV && !SWIGLU), "a rotary pair, and gate and up of a column, sit in one 32-column tile");
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -54,25 +55,30 @@ __global__ __launch_bounds__(64 * kFewWaves) void linear_few_kernel(const uint16
     // this thread's output: row om, column oc of the workgroup's columns.  What the epilogue needs for it (the old value of
     // the residual stream, or a chain of dependent loads for the rotation and the slot) is fetched first and is there long
     // before the weights are.
+    // With two row tiles: rows om and om + 16.
     const int om = tid / (16 * CT), oc = tid % (16 * CT);
-    const bool live = om < M;
-    float cs = 0.f, sn = 0.f;
-    int block = 0, slot = 0;
+    float cs[RT], sn[RT];
+    int block[RT], slot[RT];
     const int half = QKV ? ro.pool.d / 2 : 1;
     const int hd = QKV ? (int)blockIdx.x / (ro.pool.d / 32) : 0;                          // head
     const int j = QKV ? ((int)blockIdx.x % (ro.pool.d / 32)) * 16 + (oc & 15) : 0;        // first dim of this thread's pair
-    if (QKV && live) {
-        const int req = om / ro.q_len;
-        const int ps = ro.seq_lens[req] + om % ro.q_len;
-        cs = ro.cos_t[(size_t)om * half + j];
-        sn = ro.sin_t[(size_t)om * half + j];
-        block = ro.bt[(size_t)req * ro.max_blocks + ps / kBlockSize];
-        slot = ps % kBlockSize;
-    }
-
     const int n_out = ct0 * 16 + oc;
-    float y_old = 0.f;
-    if (!QKV && !SWIGLU && add && live && n_out < N && tid < 256 * CT) y_old = Y[(size_t)om * ldy + n_out];
+    float y_old[RT];
+#pragma unroll
+    for (int r = 0; r < RT; ++r) {
+        const int m = om + 16 * r;
+        cs[r] = sn[r] = y_old[r] = 0.f;
+        block[r] = slot[r] = 0;
+        if (QKV && m < M) {
+            const int req = m / ro.q_len;
+            const int ps = ro.seq_lens[req] + m % ro.q_len;
+            cs[r] = ro.cos_t[(size_t)m * half + j];
+            sn[r] = ro.sin_t[(size_t)m * half + j];
+            block[r] = ro.bt[(size_t)req * ro.max_blocks + ps / kBlockSize];
+            slot[r] = ps % kBlockSize;
+        }
+        if (!QKV && !SWIGLU && add && m < M && n_out < N && tid < 256 * CT) y_old[r] = Y[(size_t)m * ldy + n_out];
+    }
 
     const int S = Kpad / (32 * kFewWaves);  // k-steps of this wave (the packed weights are zero past K)
     const int st0 = wave * S;
@@ -84,15 +90,21 @@ __global__ __launch_bounds__(64 * kFewWaves) void linear_few_kernel(const uint16
         return st0 + (sr >= S ? sr - S : sr);
     };
     const uint16_t* wp = Wp + (size_t)(ct0 / 2) * tstride + (size_t)((ct0 & 1) * 128) + kq * 256 + row * 8;
-    const float* arow = A + (size_t)min(row, M - 1) * lda;                    // fp32 rows
-    const uint4* apack = reinterpret_cast<const uint4*>(A) + kq * M + min(row, M - 1);  // packed terms
-    floatx4 acc[CT];
+    const float* arow[RT];   // fp32 rows
+    const uint4* apack[RT];  // packed terms
+    floatx4 acc[RT][CT];
+    float ss[RT];
 #pragma unroll
-    for (int t = 0; t < CT; ++t) acc[t] = floatx4{0.f, 0.f, 0.f, 0.f};
-    float ss = 0.f;
+    for (int r = 0; r < RT; ++r) {
+        arow[r] = A + (size_t)min(row + 16 * r, M - 1) * lda;
+        apack[r] = reinterpret_cast<const uint4*>(A) + kq * M + min(row + 16 * r, M - 1);
+#pragma unroll
+        for (int t = 0; t < CT; ++t) acc[r][t] = floatx4{0.f, 0.f, 0.f, 0.f};
+        ss[r] = 0.f;
+    }
     uint4 w[D][CT], g[NORM ? D : 1];
-    float4 a[D][2];                           // fp32 rows
-    uint4 p[MODE == FEW_PACKED ? D : 1][2];   // packed terms: hi, lo
+    float4 a[D][RT][2];                           // fp32 rows
+    uint4 p[MODE == FEW_PACKED ? D : 1][RT][2];   // packed terms: hi, lo
 
     auto load = [&](int step, int s) {
         const int st = k_step(min(step, S - 1));
@@ -100,24 +112,34 @@ __global__ __launch_bounds__(64 * kFewWaves) void linear_few_kernel(const uint16
 #pragma unroll
         for (int t = 0; t < CT; ++t) w[s][t] = load_stream_16(wk + t * 128);
         if (MODE == FEW_PACKED) {
-            p[s][0] = apack[(size_t)st * (4 * M)];
-            p[s][1] = apack[(size_t)st * (4 * M) + lda];
+#pragma unroll
+            for (int r = 0; r < RT; ++r) {
+                p[s][r][0] = apack[r][(size_t)st * (4 * M)];
+                p[s][r][1] = apack[r][(size_t)st * (4 * M) + lda];
+            }
             return;
         }
         const int k = min(st * 32 + kq * 8, K - 8);
-        a[s][0] = *reinterpret_cast<const float4*>(arow + k);
-        a[s][1] = *reinterpret_cast<const float4*>(arow + k + 4);
+#pragma unroll
+        for (int r = 0; r < RT; ++r) {
+            a[s][r][0] = *reinterpret_cast<const float4*>(arow[r] + k);
+            a[s][r][1] = *reinterpret_cast<const float4*>(arow[r] + k + 4);
+        }
         if (NORM) g[s] = *reinterpret_cast<const uint4*>(gain + k);
     };
     auto compute = [&](int step, int s) {
         const int k0 = k_step(step) * 32;
-        uint4 hi, lo;
-        if (MODE == FEW_PACKED) {
-            hi = p[s][0];
-            lo = p[s][1];
-            if (k0 + 32 > K && k0 + kq * 8 >= K) hi = lo = make_uint4(0, 0, 0, 0);  // the padding of K may hold any bits
-        } else {
-            float v[8] = {a[s][0].x, a[s][0].y, a[s][0].z, a[s][0].w, a[s][1].x, a[s][1].y, a[s][1].z, a[s][1].w};
+        uint4 hi[RT], lo[RT];
+#pragma unroll
+        for (int r = 0; r < RT; ++r) {
+            if (MODE == FEW_PACKED) {
+                hi[r] = p[s][r][0];
+                lo[r] = p[s][r][1];
+                if (k0 + 32 > K && k0 + kq * 8 >= K) hi[r] = lo[r] = make_uint4(0, 0, 0, 0);  // the padding of K may hold any bits
+                continue;
+            }
+            const float4 &a0 = a[s][r][0], &a1 = a[s][r][1];
+            float v[8] = {a0.x, a0.y, a0.z, a0.w, a1.x, a1.y, a1.z, a1.w};
             if (k0 + 32 > K) {  // uniform: a step that reaches past K
                 const bool ok = k0 + kq * 8 < K;
 #pragma unroll
@@ -127,21 +149,25 @@ __global__ __launch_bounds__(64 * kFewWaves) void linear_few_kernel(const uint16
                 const uint32_t gw[4] = {g[s].x, g[s].y, g[s].z, g[s].w};
 #pragma unroll
                 for (int e = 0; e < 8; ++e) {
-                    ss = fmaf(v[e], v[e], ss);
+                    ss[r] = fmaf(v[e], v[e], ss[r]);
                     v[e] *= (e & 1) ? bf16_hi(gw[e / 2]) : bf16_lo(gw[e / 2]);
                 }
             }
-            split2(v[0], v[1], hi.x, lo.x);
-            split2(v[2], v[3], hi.y, lo.y);
-            split2(v[4], v[5], hi.z, lo.z);
-            split2(v[6], v[7], hi.w, lo.w);
+            split2(v[0], v[1], hi[r].x, lo[r].x);
+            split2(v[2], v[3], hi[r].y, lo[r].y);
+            split2(v[4], v[5], hi[r].z, lo[r].z);
+            split2(v[6], v[7], hi[r].w, lo[r].w);
         }
 #pragma unroll
-        for (int t = 0; t < CT; ++t)
-            acc[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(*reinterpret_cast<bf16x8*>(&w[s][t]), *reinterpret_cast<bf16x8*>(&hi), acc[t], 0, 0, 0);
+        for (int r = 0; r < RT; ++r)
 #pragma unroll
-        for (int t = 0; t < CT; ++t)
-            acc[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(*reinterpret_cast<bf16x8*>(&w[s][t]), *reinterpret_cast<bf16x8*>(&lo), acc[t], 0, 0, 0);
+            for (int t = 0; t < CT; ++t)
+                acc[r][t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(*reinterpret_cast<bf16x8*>(&w[s][t]), *reinterpret_cast<bf16x8*>(&hi[r]), acc[r][t], 0, 0, 0);
+#pragma unroll
+        for (int r = 0; r < RT; ++r)
+#pragma unroll
+            for (int t = 0; t < CT; ++t)
+                acc[r][t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(*reinterpret_cast<bf16x8*>(&w[s][t]), *reinterpret_cast<bf16x8*>(&lo[r]), acc[r][t], 0, 0, 0);
     };
 
     if (S >= D) {
@@ -175,59 +201,67 @@ __global__ __launch_bounds__(64 * kFewWaves) void linear_few_kernel(const uint16
 
     // D[i][j]: lane holds column j = lane % 16 (an activation row) and rows i = 4 * (lane / 16) + r (output columns)
 #pragma unroll
-    for (int t = 0; t < CT; ++t)
-        s_acc[(wave * CT + t) * WS + row + kq * QS] = make_float4(acc[t][0], acc[t][1], acc[t][2], acc[t][3]);
-    if (NORM) {
-        ss += __shfl_xor(ss, 16);
-        ss += __shfl_xor(ss, 32);
-        if (lane < 16) s_ss[wave][lane] = ss;
+    for (int r = 0; r < RT; ++r) {
+#pragma unroll
+        for (int t = 0; t < CT; ++t)
+            s_acc[r][(wave * CT + t) * WS + row + kq * QS] = make_float4(acc[r][t][0], acc[r][t][1], acc[r][t][2], acc[r][t][3]);
+        if (NORM) {
+            ss[r] += __shfl_xor(ss[r], 16);
+            ss[r] += __shfl_xor(ss[r], 32);
+            if (lane < 16) s_ss[r][wave][lane] = ss[r];
+        }
     }
     __syncthreads();
     if (CT == 1 && tid >= 256) return;
-    const float* sp = reinterpret_cast<const float*>(s_acc) + (size_t)((oc / 16) * WS + om + ((oc & 15) / 4) * QS) * 4 + (oc & 3);
-    float v = 0.f;
 #pragma unroll
-    for (int k = 0; k < kFewWaves; ++k) v += sp[k * CT * WS * 4];
-    if (NORM) {
-        float tot = 0.f;
+    for (int r = 0; r < RT; ++r) {
+        const int m = om + 16 * r;
+        const bool live = m < M;
+        const float* sp = reinterpret_cast<const float*>(s_acc[r]) + (size_t)((oc / 16) * WS + om + ((oc & 15) / 4) * QS) * 4 + (oc & 3);
+        float v = 0.f;
 #pragma unroll
-        for (int k = 0; k < kFewWaves; ++k) tot += s_ss[k][om];
-        v *= 1.0f / sqrtf(tot / (float)K + eps);
-    }
-    if (QKV) {
-        const float other = __shfl_xor(v, 16);  // the other half of the rotary pair (dims j and j + d/2)
-        if (!live) return;
-        const int hi = oc / 16, e = j + hi * half;
-        if (hd < ro.n_q + ro.pool.n_kv) v = hi ? v * cs + other * sn : v * cs - other * sn;
-        if (hd < ro.n_q) {
-            ro.q_out[(size_t)om * ro.n_q * 2 * half + (size_t)hd * 2 * half + e] = v;
-        } else {
-            const int kv = hd - ro.n_q;  // K heads, then V heads
-            const bool is_v = kv >= ro.pool.n_kv;
-            uint16_t* tile = ro.pool.base + tile_base(ro.pool, ro.layer, block, is_v ? kv - ro.pool.n_kv : kv);
-            tile[is_v ? 32 * half + v_off(slot, e) : k_off(slot, e)] = f32_to_bf16_rne(v);
+        for (int k = 0; k < kFewWaves; ++k) v += sp[k * CT * WS * 4];
+        if (NORM) {
+            float tot = 0.f;
+#pragma unroll
+            for (int k = 0; k < kFewWaves; ++k) tot += s_ss[r][k][om];
+            v *= 1.0f / sqrtf(tot / (float)K + eps);
         }
-    } else if (SWIGLU) {
-        // column oc of the tile is gate (oc / 4 even) or up of column 4 * (oc / 8) + oc % 4 of its 16 (gate_up_packed_row in linear.hip)
-        const float up = __shfl_xor(v, 4);
-        const float act = v / (1.0f + __expf(-v)) * up;  // (in the lanes of gate columns)
-        const float next = __shfl_xor(act, 1);
-        if (!live || (oc & 5) != 0 || n_out >= N) return;  // a lane of an even gate column writes its own and the next one
-        uint32_t hi, lo;
-        split2(act, next, hi, lo);
-        const int col = (int)blockIdx.x * 16 + oc / 8 * 4 + (oc & 3);
-        uint32_t* dst = reinterpret_cast<uint32_t*>(Y) + ((size_t)(col / 8) * M + om) * 4 + (col & 7) / 2;
-        dst[0] = hi;
-        dst[(size_t)ldy * 4] = lo;
-    } else {
-        if (live && n_out < N) Y[(size_t)om * ldy + n_out] = y_old + v;
+        if (QKV) {
+            const float other = __shfl_xor(v, 16);  // the other half of the rotary pair (dims j and j + d/2)
+            if (!live) return;
+            const int hi = oc / 16, e = j + hi * half;
+            if (hd < ro.n_q + ro.pool.n_kv) v = hi ? v * cs[r] + other * sn[r] : v * cs[r] - other * sn[r];
+            if (hd < ro.n_q) {
+                ro.q_out[(size_t)m * ro.n_q * 2 * half + (size_t)hd * 2 * half + e] = v;
+            } else {
+                const int kv = hd - ro.n_q;  // K heads, then V heads
+                const bool is_v = kv >= ro.pool.n_kv;
+                uint16_t* tile = ro.pool.base + tile_base(ro.pool, ro.layer, block[r], is_v ? kv - ro.pool.n_kv : kv);
+                tile[is_v ? 32 * half + v_off(slot[r], e) : k_off(slot[r], e)] = f32_to_bf16_rne(v);
+            }
+        } else if (SWIGLU) {
+            // column oc of the tile is gate (oc / 4 even) or up of column 4 * (oc / 8) + oc % 4 of its 16 (gate_up_packed_row in linear.hip)
+            const float up = __shfl_xor(v, 4);
+            const float act = v / (1.0f + __expf(-v)) * up;  // (in the lanes of gate columns)
+            const float next = __shfl_xor(act, 1);
+            if (!live || (oc & 5) != 0 || n_out >= N) continue;  // a lane of an even gate column writes its own and the next one
+            uint32_t hi, lo;
+            split2(act, next, hi, lo);
+            const int col = (int)blockIdx.x * 16 + oc / 8 * 4 + (oc & 3);
+            uint32_t* dst = reinterpret_cast<uint32_t*>(Y) + ((size_t)(col / 8) * M + m) * 4 + (col & 7) / 2;
+            dst[0] = hi;
+            dst[(size_t)ldy * 4] = lo;
+        } else {
+            if (live && n_out < N) Y[(size_t)m * ldy + n_out] = y_old[r] + v;
+        }
     }
 }
 
 // ---- which rows take this path -------------------------------------------------------------------------------
 bool linear_few_rows(int M) {
     const Tuning& t = tuning();
-    return M <= 16 && !t.linear_mt && !t.linear_nf && !t.linear_ksplit && !t.linear_ks && !t.linear_big_all;
+    return M <= 32 && !t.linear_mt && !t.linear_nf && !t.linear_ksplit && !t.linear_ks && !t.linear_big_all;
 }
 
 // 16-column tiles per workgroup.  Two (half as many loads of the same activations) where that takes a round of the chip less: 8192
@@ -276,52 +310,78 @@ static double unsliced_us(const Linear& L) {
     const double chain = 3.3 + 0.0058 * L.K;
     return chain > tiled_us(L) ? chain : tiled_us(L);
 }
-bool norm_few_pays(const Linear& L, int M) { return linear_few_rows(M) && (L.N <= 32 * kNumCU || (L.N <= 64 * kNumCU && L.K >= 2048 && (M <= 8 || L.N <= 48 * kNumCU))); }
+// From 17 rows on the activations weigh twice as much and the estimate decides, in the same range of widths (32 rows: gate/up of a
+// block of 4096 x 4096 27 -> 15 us; 11264 columns of K = 2048 15 against 18).
+constexpr double kNormUs = 4.5;  // an RMSNorm of its own
+static bool gate_up_few(const Linear& L, int M, bool norm, double* us) {
+    *us = few_us(L, M, norm ? FEW_SWIGLU_NORM : FEW_SWIGLU, 2);
+    return L.N <= 64 * kNumCU && *us <= unsliced_us(L) + (norm ? kNormUs : 0.0);
+}
+bool norm_few_pays(const Linear& L, int M, bool norm) {
+    double us;
+    if (M > 16) return linear_few_rows(M) && gate_up_few(L, M, norm, &us);
+    return linear_few_rows(M) && (L.N <= 32 * kNumCU || (L.N <= 64 * kNumCU && L.K >= 2048 && (M <= 8 || L.N <= 48 * kNumCU)));
+}
 
 // A whole layer: what the few-row QKV, O and down projections take longer than the tiled ones must stay below the two norms and
 // the rotation that become part of them (13.6 us up to 4096 columns, 20 at 8192, 25 at 16384, less what the norm costs where it
 // goes).  Measured end to end, us per layer gained by this path at 1 / 8 / 12 / 16 rows: 8B widths 9 / 6 / 1 / -4, 70B widths
 // 8 / 7 / 2 / -9, 6144 wide (384 workgroups) 0 / -9 / -22 / -36, 12288 wide 6 / -12 / -23 / -51, 5120 wide with 40 KV heads (320 and
 // 480 workgroups) -8 / -17 / -31 / -43.  On one set of weights, whole steps by this rule are within 1 % of the better path.
+// From 17 rows on the few-row kernel must take gate/up too (the tiled one has the norm for 16 rows), and 1 us must be left: gained at 17 / 24 / 32 rows 9 / 8 / 7 us a layer at 256 hidden columns, 6 / 4 / 2 at 1024; it would
+// be -1 / -5 / -11 at 2048 and -11 / -19 / -25 at the 8B widths.
 bool step_few_rows(const Linear& qkv, const Linear& o, const Linear& gu, const Linear& down, int M) {
-    if (!linear_few_rows(M)) return false;
+    if (!linear_few_rows(M) || (M > 16 && qkv.N > 32 * kNumCU)) return false;
     const double saved = 5.9 + 1.3 / 1024 * qkv.K;
     double pays = tiled_us(qkv) + tiled_us(o) + tiled_us(down) + (saved > 13.0 ? saved : 13.0);
     int ct_o = (o.N + 31) / 32 >= kNumCU ? 2 : 1, ct_down = (down.N + 31) / 32 >= kNumCU ? 2 : 1;
     if (qkv.N <= 32 * kNumCU) {  // (a QKV of two rounds was measured with these column tiles and without a gate/up of its own)
         ct_o = few_col_tiles(o, M);
         ct_down = few_col_tiles(down, M);
-        const double gu_saved = norm_few_pays(gu, M) ? unsliced_us(gu) - few_us(gu, M, FEW_SWIGLU_NORM, 2) : 0.0;
-        pays += gu_saved > 0.0 ? gu_saved : 0.0;
+        if (norm_few_pays(gu, M)) {
+            const double gu_saved = unsliced_us(gu) - few_us(gu, M, FEW_SWIGLU_NORM, 2);
+            if (M > 16) pays += gu_saved - 1.0;
+            else if (gu_saved > 0.0) pays += gu_saved;
+        } else if (M > 16) {
+            return false;
+        }
         if (ct_o == 2) pays -= 2.0;  // (5120 hidden columns at 11 rows: 1.5 us a layer more than estimated)
     }
     return few_us(qkv, M, FEW_QKV, 2) + few_us(o, M, FEW_ROWS, ct_o) + few_us(down, M, FEW_PACKED, ct_down) <= pays;
 }
 
 // A projection by itself: against the tiled kernel, the sum of its slices (5 us), and no less than the 25 us that the host takes to
-// enqueue the two with their scratch memory.  A long K without a workgroup for every CU is a serial chain that nothing hides
+// enqueue the two with their scratch memory (18 where the few-row kernel has two row tiles: 21 .. 28 us a call through the tiled
+// kernel, 6.7 at 20 rows of 1024 x 1024, 9.0 at 2048 x 8192 and 12 at 32 rows of 1024 x 16384 through this one; behind a gate/up the host is
+// ahead: 2048 x 5632 at 20 rows would take 39 us with it against 31).  A long K without a workgroup for every CU is a serial chain that nothing hides
 // (2048 x 28672, one row: 33 against 29 us).  4096 x 14336: 24 against 28 us at 8 rows, 33 against 30 at 16; 10240 x 28672 (320
 // workgroups): 112 against 98 at one row.  Very wide outputs have enough column tiles for the tiled kernel unsliced.
-bool linear_few_pays(const Linear& L, int M) {
+bool linear_few_pays(const Linear& L, int M, SliceCost slices) {
     if (!linear_few_rows(M) || L.N > 16384 || (L.K > 16384 && L.N < 4096)) return false;
     const double tiled = 5.0 + tiled_us(L);
-    return few_us(L, M, FEW_ROWS, few_col_tiles(L, M)) <= (tiled > 25.5 ? tiled : 25.5);
+    const double host = M <= 16 ? 25.5 : slices == SLICES_ALONE ? 18.0 : 0.0;
+    return few_us(L, M, FEW_ROWS, few_col_tiles(L, M)) <= (tiled > host ? tiled : host);
 }
 
-// the same for the down projection of a feed-forward block, whose scratch memory is there anyway
-bool linear_few_pays_packed(const Linear& L, int M) {
-    return linear_few_rows(M) && L.N <= 16384 && few_us(L, M, FEW_PACKED, few_col_tiles(L, M)) <= 5.0 + tiled_us(L);
+// the same for the down projection of a feed-forward block, whose scratch memory is there anyway; from 17 rows on with what the
+// few-row kernel saves at gate/up (4096 x 4096: 45 -> 30 us at 20 rows, 47 -> 35 at 32; 2048 x 5632 would go from 31 to 33 and from 32 to 38)
+bool ffn_few_pays(const Linear& gu, const Linear& down, int M) {
+    if (!linear_few_rows(M) || down.N > 16384) return false;
+    double us, pays = 5.0 + tiled_us(down);
+    if (M > 16 && gate_up_few(gu, M, false, &us)) pays += unsliced_us(gu) - us;
+    return few_us(down, M, FEW_PACKED, few_col_tiles(down, M)) <= pays;
 }
 
 int32_t launch_linear_few(const Linear& L, const float* A, int64_t lda, int M, int packed, float* y, int ldy, int add, hipStream_t st) {
     if (M == 0) return CHIRON_OK;
-    if (M > 16) return fail(CHIRON_ERR_INVALID_ARG, "linear: %d rows on the few-row path", M);
+    if (M > 32) return fail(CHIRON_ERR_INVALID_ARG, "linear: %d rows on the few-row path", M);
     if (L.K % 16 != 0 || L.K < 16) return fail(CHIRON_ERR_SHAPE, "linear: K=%d must be a positive multiple of 16", L.K);
     if ((!packed && lda % 4 != 0) || ((uintptr_t)A & 15)) return fail(CHIRON_ERR_INVALID_ARG, "linear: input rows must be 16-byte aligned");
     const int ct = few_col_tiles(L, M);
     const dim3 grid((L.N + 16 * ct - 1) / (16 * ct)), block(64 * kFewWaves);
 #define CHIRON_FEW(CT_, MODE_) \
-    launch(linear_few_kernel<CT_, MODE_>, grid, block, st, L.w, L.tstride, L.N, L.K, L.Kpad, A, lda, M, (const uint16_t*)nullptr, 0.f, y, ldy, add, RopeOut())
+    launch(M > 16 ? linear_few_kernel<CT_, MODE_, 2> : linear_few_kernel<CT_, MODE_, 1>, grid, block, st, L.w, L.tstride, L.N, L.K, L.Kpad, A, lda, M, \
+           (const uint16_t*)nullptr, 0.f, y, ldy, add, RopeOut())
     if (ct == 1 && packed) CHIRON_FEW(1, FEW_PACKED);
     else if (ct == 1) CHIRON_FEW(1, FEW_ROWS);
     else if (packed) CHIRON_FEW(2, FEW_PACKED);
@@ -334,7 +394,7 @@ int32_t launch_linear_few(const Linear& L, const float* A, int64_t lda, int M, i
 // A fused gate/up matrix (ldy: the padded K of its consumer), with the norm in its operand load or without, or a plain projection with it
 int32_t launch_norm_few(const Linear& L, const float* h, int lda, int M, const NormIn* norm, int swiglu, float* y, int ldy, hipStream_t st) {
     if (M == 0) return CHIRON_OK;
-    if (M > 16) return fail(CHIRON_ERR_INVALID_ARG, "linear: %d rows on the few-row path", M);
+    if (M > 32) return fail(CHIRON_ERR_INVALID_ARG, "linear: %d rows on the few-row path", M);
     if (L.K % 16 != 0 || L.K < 16) return fail(CHIRON_ERR_SHAPE, "linear: K=%d must be a positive multiple of 16", L.K);
     if (lda % 4 != 0 || ((uintptr_t)h & 15)) return fail(CHIRON_ERR_INVALID_ARG, "linear: input rows must be 16-byte aligned");
     if (swiglu && (L.N % 32 != 0 || ldy % 8 != 0 || ((uintptr_t)y & 15))) return fail(CHIRON_ERR_INVALID_ARG, "linear: SwiGLU needs whole gate/up tiles and 16-byte aligned output");
@@ -343,7 +403,8 @@ int32_t launch_norm_few(const Linear& L, const float* h, int lda, int M, const N
     const NormIn nm = norm ? *norm : NormIn();
     const dim3 grid((L.N + 16 * ct - 1) / (16 * ct)), block(64 * kFewWaves);
 #define CHIRON_FEW(CT_, MODE_, LDY_) \
-    launch(linear_few_kernel<CT_, MODE_>, grid, block, st, L.w, L.tstride, L.N, L.K, L.Kpad, h, (int64_t)lda, M, nm.gain, nm.eps, y, LDY_, 0, RopeOut())
+    launch(M > 16 ? linear_few_kernel<CT_, MODE_, 2> : linear_few_kernel<CT_, MODE_, 1>, grid, block, st, L.w, L.tstride, L.N, L.K, L.Kpad, h, \
+           (int64_t)lda, M, nm.gain, nm.eps, y, LDY_, 0, RopeOut())
     if (swiglu && norm) CHIRON_FEW(2, FEW_SWIGLU_NORM, M * (ldy / 8));
     else if (swiglu) CHIRON_FEW(2, FEW_SWIGLU, M * (ldy / 8));
     else if (ct == 1) CHIRON_FEW(1, FEW_NORM, ldy);
@@ -355,10 +416,10 @@ int32_t launch_norm_few(const Linear& L, const float* h, int lda, int M, const N
 
 int32_t launch_qkv_few(const Linear& L, const float* h, int lda, int M, const NormIn& norm, const RopeOut& ro, hipStream_t st) {
     if (M == 0) return CHIRON_OK;
-    if (M > 16) return fail(CHIRON_ERR_INVALID_ARG, "linear: %d rows on the few-row path", M);
+    if (M > 32) return fail(CHIRON_ERR_INVALID_ARG, "linear: %d rows on the few-row path", M);
     if (L.N != (ro.n_q + 2 * ro.pool.n_kv) * ro.pool.d || ro.pool.d % 32 != 0)
         return fail(CHIRON_ERR_SHAPE, "linear: %d columns are not the heads of a fused QKV projection", L.N);
-    launch(linear_few_kernel<2, FEW_QKV>, dim3(L.N / 32), dim3(64 * kFewWaves), st, L.w, L.tstride, L.N, L.K, L.Kpad, h, (int64_t)lda, M, norm.gain,
+    launch(M > 16 ? linear_few_kernel<2, FEW_QKV, 2> : linear_few_kernel<2, FEW_QKV, 1>, dim3(L.N / 32), dim3(64 * kFewWaves), st, L.w, L.tstride, L.N, L.K, L.Kpad, h, (int64_t)lda, M, norm.gain,
            norm.eps, (float*)nullptr, 0, 0, ro);
     CHIRON_HIP(hipGetLastError());
     return CHIRON_OK;

@@ -1160,6 +1160,45 @@ def test_few_rows_gate_up_and_two_column_tiles(M, K, F, N):
     gu.close(); down.close()
 
 
+@pytest.mark.parametrize("M,K,F,N", [(17, 16, 16, 17), (32, 272, 688, 4096), (31, 1040, 48, 4112), (17, 2064, 4096, 2048), (32, 4096, 16, 96), (24, 5008, 16, 48)])
+def test_few_rows_two_row_tiles(M, K, F, N):
+    """17 .. 32 rows of a projection and a feed-forward block: one and two column tiles, whole rings of k-steps, a remainder, a last
+    step past K, and widths past the range, against the oracle"""
+    x, Wg, Wu, Wd, _, want = ffn_case(M, K, F, N, M + K + F)
+    b = B()
+    gu, down, lin = b.GateUp(Wg.cuda(), Wu.cuda()), b.Linear(Wd.cuda()), b.Linear(Wg.cuda())
+    print("two row tiles", M, K, F, N, flush=True)
+    assert rel_err(gu.ffn(down, torch.from_numpy(x).cuda()).cpu().numpy(), want) <= KERNEL_TOL
+    y0 = np.random.default_rng(M).standard_normal((M, F)).astype(np.float32)
+    wg = orc.linear(x, I.to_numpy_storage(Wg))
+    assert rel_err(lin(torch.from_numpy(x).cuda()).cpu().numpy(), wg) <= KERNEL_TOL
+    assert rel_err(lin(torch.from_numpy(x).cuda(), torch.from_numpy(y0).cuda(), accumulate=True).cpu().numpy(), wg + y0) <= KERNEL_TOL
+    gu.close(); down.close(); lin.close()
+
+
+@pytest.mark.parametrize("over,batch,T,norms", [({}, 17, 1, 1), (dict(hidden=1040, ffn=2832, vocab=16416), 16, 2, 1),
+                                                (dict(hidden=272, n_kv_heads=4), 31, 1, 1), (dict(hidden=2048, ffn=5632), 32, 1, 3)])
+def test_step_of_two_row_tiles(over, batch, T, norms):
+    """steps of 17 .. 32 rows: layers by the few-row kernel and a head behind a norm of its own, and a width past that range, each
+    against the general path"""
+    c = make_case(m=dict(I.TINY, n_layers=1, **over), batch=batch, kind="tiny", seed=53, storage="bf16", gain_jitter=0.2)
+    g = gpu_setup(c, max_batch=batch * T)
+    b = B()
+    sl = torch.from_numpy((c.seq_lens - T).astype(np.int32)).cuda()
+    tok = torch.from_numpy(np.random.default_rng(3).integers(0, c.m["vocab"], (batch, T)).astype(np.int32)).cuda()
+    out = []
+    for mt in (0, 1):
+        print("two row tiles", over, batch, T, "mt", mt, flush=True)
+        b.set_tuning("linear_mt", mt)
+        try:
+            lg, n = norm_launches(g, lambda: b.decode_step_multi(g.model, g.pool, g.block_table, sl, tok))
+        finally:
+            b.set_tuning("linear_mt", 0)
+        assert n == (3 if mt else norms)
+        out.append(lg.cpu().numpy().reshape(batch * T, -1))
+    assert np.abs(out[0] - out[1]).max() <= 2e-3 * out[1].std()
+
+
 @pytest.mark.parametrize("over,batch", [(dict(vocab=8192), 16), (dict(vocab=8208), 3), (dict(hidden=2064, ffn=4112, vocab=16384), 9), (dict(hidden=4624, ffn=32, vocab=96), 2)])
 def test_step_of_few_rows_with_narrow_gate_up_and_head(over, batch):
     """steps whose gate/up and head are products of the few-row kernel too (one round of 32-column tiles, two at K >= 2048), and the
