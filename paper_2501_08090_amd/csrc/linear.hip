@@ -319,6 +319,9 @@ __device__ __forceinline__ void linear_tile(const uint16_t* __restrict__ Wp, siz
                 for (int i = 0; i < TPT; ++i) stage_task(c_begin, i, 0, a0[i], g0);
                 lds_barrier();
                 int buf = 0, c = c_begin;
+                // The loop of eight waves of 128 rows runs at a rate that depends on where in a 64-byte line it starts (the LM head
+                // at 500 rows 838 us at byte 0, 832 at 48, 825 at 20): it is put there whatever the code before it.
+                if constexpr (NW == 8 && MT == 4) asm volatile(".p2align 6\n\ts_nop 0\n\ts_nop 0\n\ts_nop 0\n\ts_nop 0\n\ts_nop 0");
                 do {
 #pragma unroll
                     for (int s = 0; s < KS; ++s) {
@@ -479,7 +482,10 @@ __device__ __forceinline__ void linear_tile(const uint16_t* __restrict__ Wp, siz
 // Workgroups are dealt to the 8 XCDs round-robin.  The 1-D grid (of a multiple of 8) is re-read so that consecutive logical ids
 // sit on ONE XCD, and the M-tile index varies fastest: the workgroups that stream the same weight tiles for
 // different rows then share that XCD's L2 instead of each pulling the tile from HBM.
-__device__ __forceinline__ int logical_block(int block, int total, int remap) { return remap ? (block % 8) * ((total + 7) / 8) + block / 8 : block; }
+__device__ __forceinline__ int logical_block(unsigned block, int total, int remap) {
+    const int per_xcd = (total + 7) / 8;
+    return remap ? (block % 8) * per_xcd + block / 8 : block;
+}
 
 template <int MT, int NF, int KS, int PRO, bool WNT = true, bool NORM = false, int NW = 4>
 __global__ __launch_bounds__(64 * NW, (NW == 8 || (MT * NF <= 8 && !(MT == 4 && PRO != PRO_NONE)) ? 2 : 1)) void linear_kernel(const uint16_t* __restrict__ Wp, size_t tstride, int Npad, int Nreal, int K, int Kpad,
@@ -487,10 +493,12 @@ __global__ __launch_bounds__(64 * NW, (NW == 8 || (MT * NF <= 8 && !(MT == 4 && 
                                                      float* __restrict__ Y, int ldy, int chunks_per_split,
                                                      int mode, size_t part_stride, int gx, int gy, int gz, int remap,
                                                      const uint16_t* __restrict__ gain, float eps) {
-    const int logical = logical_block(blockIdx.x, gx * gy * gz, remap);
-    if (logical >= gx * gy * gz) return;  // uniform over the workgroup
-    linear_tile<MT, NF, KS, PRO, WNT, NORM, NW>(Wp, tstride, Npad, Nreal, K, Kpad, A, lda, M, Y, ldy, chunks_per_split, mode, part_stride,
-                                                (logical / gz) % gx, logical / (gz * gx), logical % gz, gain, eps);
+    const int total = gx * gy * gz;
+    const int logical = logical_block(blockIdx.x, total, remap);
+    if (logical >= total) return;  // uniform over the workgroup
+    const int bz = logical % gz, bx = (logical / gz) % gx, by = logical / (gz * gx);
+    linear_tile<MT, NF, KS, PRO, WNT, NORM, NW>(Wp, tstride, Npad, Nreal, K, Kpad, A, lda, M, Y, ldy, chunks_per_split, mode, part_stride, bx, by, bz,
+                                                gain, eps);
 }
 
 // 128 rows x 512 columns by eight waves, K whole.  The tiles of whole rounds of the chip as they are (`whole` of them, a multiple of
