@@ -305,7 +305,8 @@ static double tiled_us(const Linear& L) { return 3.5 + 2e-6 * L.N * L.K / 6.6; }
 // hides.  Up to one round of 32 columns a workgroup the few-row kernel is faster at any K (28.6 -> 10.6 us for 2816 columns
 // of K = 4096 at one row, 29.9 -> 15.3 for 8192 at 16; 5.9 -> 3.1 for 512 of K = 256), in two rounds from K = 2048, and if the second
 // one is more than half full only up to 8 rows (16384 columns: 17.6 -> 14.7 at 8 rows; at K = 1024 11.2 against 11.4; inside a step
-// at K = 3072 and 13 rows 1 us a layer lost, at K = 2048 with 11264 columns 3 gained); beyond that the weight stream decides.  Whole steps of two layers, 1024 wide: 92 -> 81 us at 4 rows, 102 -> 94 at 16.
+// at K = 3072 and 13 rows 1 us a layer lost, at K = 2048 with 11264 columns 3 gained); beyond that the weight stream decides.
+// Whole steps of two layers, 1024 wide: 92 -> 81 us at 4 rows, 102 -> 94 at 16.
 static double unsliced_us(const Linear& L) {
     const double chain = 3.3 + 0.0058 * L.K;
     return chain > tiled_us(L) ? chain : tiled_us(L);
@@ -328,8 +329,9 @@ bool norm_few_pays(const Linear& L, int M, bool norm) {
 // goes).  Measured end to end, us per layer gained by this path at 1 / 8 / 12 / 16 rows: 8B widths 9 / 6 / 1 / -4, 70B widths
 // 8 / 7 / 2 / -9, 6144 wide (384 workgroups) 0 / -9 / -22 / -36, 12288 wide 6 / -12 / -23 / -51, 5120 wide with 40 KV heads (320 and
 // 480 workgroups) -8 / -17 / -31 / -43.  On one set of weights, whole steps by this rule are within 1 % of the better path.
-// From 17 rows on the few-row kernel must take gate/up too (the tiled one has the norm for 16 rows), and 1 us must be left: gained at 17 / 24 / 32 rows 9 / 8 / 7 us a layer at 256 hidden columns, 6 / 4 / 2 at 1024; it would
-// be -1 / -5 / -11 at 2048 and -11 / -19 / -25 at the 8B widths.
+// From 17 rows on the few-row kernel must take gate/up too (the tiled one has the norm for 16 rows), and 1 us must be left: gained
+// at 17 / 24 / 32 rows 9 / 8 / 7 us a layer at 256 hidden columns, 6 / 4 / 2 at 1024; it would be -1 / -5 / -11 at 2048 and
+// -11 / -19 / -25 at the 8B widths.
 bool step_few_rows(const Linear& qkv, const Linear& o, const Linear& gu, const Linear& down, int M) {
     if (!linear_few_rows(M) || (M > 16 && qkv.N > 32 * kNumCU)) return false;
     const double saved = 5.9 + 1.3 / 1024 * qkv.K;
@@ -394,7 +396,7 @@ int32_t launch_linear_few(const Linear& L, const float* A, int64_t lda, int M, i
 // A fused gate/up matrix (ldy: the padded K of its consumer), with the norm in its operand load or without, or a plain projection with it
 int32_t launch_norm_few(const Linear& L, const float* h, int lda, int M, const NormIn* norm, int swiglu, float* y, int ldy, hipStream_t st) {
     if (M == 0) return CHIRON_OK;
-    if (M > 32) return fail(CHIRON_ERR_INVALID_ARG, "linear: %d rows on the few-row path", M);
+    if (M > (swiglu ? 32 : 16)) return fail(CHIRON_ERR_INVALID_ARG, "linear: %d rows on the few-row path", M);
     if (L.K % 16 != 0 || L.K < 16) return fail(CHIRON_ERR_SHAPE, "linear: K=%d must be a positive multiple of 16", L.K);
     if (lda % 4 != 0 || ((uintptr_t)h & 15)) return fail(CHIRON_ERR_INVALID_ARG, "linear: input rows must be 16-byte aligned");
     if (swiglu && (L.N % 32 != 0 || ldy % 8 != 0 || ((uintptr_t)y & 15))) return fail(CHIRON_ERR_INVALID_ARG, "linear: SwiGLU needs whole gate/up tiles and 16-byte aligned output");
@@ -402,13 +404,14 @@ int32_t launch_norm_few(const Linear& L, const float* h, int lda, int M, const N
     const int ct = swiglu ? 2 : few_col_tiles(L, M);
     const NormIn nm = norm ? *norm : NormIn();
     const dim3 grid((L.N + 16 * ct - 1) / (16 * ct)), block(64 * kFewWaves);
-#define CHIRON_FEW(CT_, MODE_, LDY_) \
-    launch(M > 16 ? linear_few_kernel<CT_, MODE_, 2> : linear_few_kernel<CT_, MODE_, 1>, grid, block, st, L.w, L.tstride, L.N, L.K, L.Kpad, h, \
-           (int64_t)lda, M, nm.gain, nm.eps, y, LDY_, 0, RopeOut())
-    if (swiglu && norm) CHIRON_FEW(2, FEW_SWIGLU_NORM, M * (ldy / 8));
-    else if (swiglu) CHIRON_FEW(2, FEW_SWIGLU, M * (ldy / 8));
-    else if (ct == 1) CHIRON_FEW(1, FEW_NORM, ldy);
-    else CHIRON_FEW(2, FEW_NORM, ldy);
+#define CHIRON_FEW(CT_, MODE_, RT_, LDY_) \
+    launch(linear_few_kernel<CT_, MODE_, RT_>, grid, block, st, L.w, L.tstride, L.N, L.K, L.Kpad, h, (int64_t)lda, M, nm.gain, nm.eps, y, LDY_, 0, RopeOut())
+    if (swiglu && norm && M > 16) CHIRON_FEW(2, FEW_SWIGLU_NORM, 2, M * (ldy / 8));
+    else if (swiglu && norm) CHIRON_FEW(2, FEW_SWIGLU_NORM, 1, M * (ldy / 8));
+    else if (swiglu && M > 16) CHIRON_FEW(2, FEW_SWIGLU, 2, M * (ldy / 8));
+    else if (swiglu) CHIRON_FEW(2, FEW_SWIGLU, 1, M * (ldy / 8));
+    else if (ct == 1) CHIRON_FEW(1, FEW_NORM, 1, ldy);
+    else CHIRON_FEW(2, FEW_NORM, 1, ldy);
 #undef CHIRON_FEW
     CHIRON_HIP(hipGetLastError());
     return CHIRON_OK;
