@@ -28,11 +28,11 @@ MFMA_BF16_PEAK_TFLOPS = 2500.0
 # `sha` is source_hash() of the kernel's file at that time; with any other source the figure is reported null.
 TRAFFIC = {
     # (workload, kernel class): (source file, source_hash, fetch bytes, write bytes)
-    ("llama8b-b64-lognormal800", "attn"): ("attention.hip", "1c0e4644f4c54475cf59316009738234d2c27603c27ad556ae580eb81f239f23", 275681758, 4259901),
-    ("llama8b-b64-lognormal800", "gateup"): ("linear.hip", "f70f49659a0166fa4db558e6975177f24afa34fcbcdfe65f1249f77f7474f6f7", 243437734, 3670016),
-    ("llama8b-b64-lognormal800", "down"): ("linear.hip", "f70f49659a0166fa4db558e6975177f24afa34fcbcdfe65f1249f77f7474f6f7", 121337938, 16777226),
-    ("llama8b-mixed-sweep512", "attn"): ("attention.hip", "1c0e4644f4c54475cf59316009738234d2c27603c27ad556ae580eb81f239f23", 4196770145, 21763276),
-    ("llama8b-b32-long32k", "attn"): ("attention.hip", "1c0e4644f4c54475cf59316009738234d2c27603c27ad556ae580eb81f239f23", 3721447830, 4260188),
+    ("llama8b-b64-lognormal800", "attn"): ("attention.hip", "944820f5463cfa0c75c2f0af53386ff28ffbbc5d36fa719d237443a06ee400f8", 275722902, 4259906),
+    ("llama8b-b64-lognormal800", "gateup"): ("linear.hip", "5727ed657fe743b30ee62e5b1830a919d83022803174b775763e2f9c6f0c78f1", 243439785, 3670016),
+    ("llama8b-b64-lognormal800", "down"): ("linear.hip", "5727ed657fe743b30ee62e5b1830a919d83022803174b775763e2f9c6f0c78f1", 121347169, 16777219),
+    ("llama8b-mixed-sweep512", "attn"): ("attention.hip", "944820f5463cfa0c75c2f0af53386ff28ffbbc5d36fa719d237443a06ee400f8", 4196868943, 21763141),
+    ("llama8b-b32-long32k", "attn"): ("attention.hip", "944820f5463cfa0c75c2f0af53386ff28ffbbc5d36fa719d237443a06ee400f8", 3721444296, 4260192),
 }
 
 
