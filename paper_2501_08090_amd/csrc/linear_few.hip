@@ -231,7 +231,8 @@ __global__ __launch_bounds__(64 * kFewWaves) void linear_few_kernel(const uint16
             const float other = __shfl_xor(v, 16);  // the other half of the rotary pair (dims j and j + d/2)
             if (!live) return;
             const int hi = oc / 16, e = j + hi * half;
-            if (hd < ro.n_q + ro.pool.n_kv) v = hi ? v * cs[r] + other * sn[r] : v * cs[r] - other * sn[r];
+            // (one rounding less than two products and a sum; written out, as the compiler contracts it in some forms of this loop only)
+            if (hd < ro.n_q + ro.pool.n_kv) v = fmaf(v, cs[r], hi ? other * sn[r] : -(other * sn[r]));
             if (hd < ro.n_q) {
                 ro.q_out[(size_t)m * ro.n_q * 2 * half + (size_t)hd * 2 * half + e] = v;
             } else {

@@ -1209,3 +1209,46 @@ def test_step_of_few_rows_with_narrow_gate_up_and_head(over, batch):
     (_, got, want, _), norms = norm_launches(g, lambda: run_both(c, g))
     assert norms == 0  # the few-row path
     check_logits(got, want, min_agree=1.0 - 1.0 / batch)
+
+
+@pytest.mark.parametrize("m,batch", [(I.TINY, 1), (I.TINY, 16), (I.TINY, 32), (G4_D128, 5)])
+def test_few_row_rotation_rounds_one_product(m, batch):
+    """The QKV projection of few rows rotates with one product rounded and the other inside a fused multiply-add.  Every rotary pair
+    is an exact number of 24 bits (three bf16 weights against inputs of one) that its angle all but cancels, so what is left is the
+    rounding itself: the new K has to be the bf16 value of fma(x, cos, -+round(y sin))."""
+    m = dict(m, n_layers=1, rms_eps=1e-12)
+    H, d, nkv = m["hidden"], m["head_dim"], m["n_kv_heads"]
+    half, pos = d // 2, 77
+    rng = np.random.default_rng(5)
+    ang = pos * float(m["rope_base"]) ** (-2.0 * np.arange(half) / d)
+    cs, sn = np.cos(ang).astype(np.float32), np.sin(ang).astype(np.float32)
+    x = rng.uniform(1, 2, (nkv, half)).astype(np.float32)
+    y = np.empty_like(x)
+    y[::2] = x[::2].astype(np.float64) * cs / sn   # x cos - y sin is next to nothing (the pair's first half)
+    y[1::2] = -x[1::2].astype(np.float64) * sn / cs  # y cos + x sin is (its second half)
+    want_k = np.concatenate([x, y], 1)  # [nkv, d], before the rotation
+    c = make_case(m=m, kind="tiny", seed=3, storage="bf16", seq_lens=[pos] * batch)
+    wk = torch.zeros((nkv * d, H))
+    rest = torch.from_numpy(want_k.reshape(-1).copy())
+    for t in range(3):
+        wk[:, t] = rest.to(torch.bfloat16).float()
+        rest = rest - wk[:, t]
+    assert not rest.any()
+    c.w_t["wk"] = [wk.to(torch.bfloat16)]
+    for n in ("embed", "final_norm"):
+        c.w_t[n] = torch.ones_like(c.w_t[n])
+    c.w_t["attn_norm"] = [torch.ones_like(c.w_t["attn_norm"][0])]
+    g = gpu_setup(c)
+    print("rotation of few rows", batch, flush=True)
+    _, norms = norm_launches(g, lambda: B().decode_step(g.model, g.pool, g.block_table, g.seq_lens, g.tokens))
+    assert norms == (batch > 16)  # the few-row path
+
+    def fma(a, cos, prod):  # exact products of 48 bits, a sum of 64
+        return (a.astype(np.longdouble) * cos + prod.astype(np.longdouble)).astype(np.float32)
+    want = np.concatenate([fma(x, cs, -(y * sn)), fma(y, cs, x * sn)], 1)
+    want = torch.from_numpy(want).to(torch.bfloat16)
+    split = torch.from_numpy(np.concatenate([x * cs - y * sn, y * cs + x * sn], 1)).to(torch.bfloat16)
+    assert float((split != want).float().mean()) > 0.2  # (two rounded products would show)
+    for i in range(batch):
+        k, _ = g.pool.gather(0, g.block_table[i].contiguous(), pos + 1)
+        assert np.array_equal(bits(k[pos]), bits(want)), i
