@@ -126,6 +126,14 @@ size_t linear_big_split_elems(int M, int Kpad);
 int32_t launch_clear_k_padding(uint16_t* asplit, int M, int K, int Kpad, hipStream_t st);
 int linear_big_min_rows(const Linear& L);
 int linear_max_split();
+// the launch shape of a tiled projection: rows / 32 and column tiles per wave, waves per workgroup, k-steps per chunk,
+// workgroups along N and M, K-slices and chunks per slice
+struct LinearShape {
+    int mt, nf, nw, ks, gx, gz, ksplit, cps;
+};
+LinearShape linear_shape(const Linear& L, int M, bool sliceable, int prologue, int max_split, SliceCost slices);
+// how often this thread had to search for one so far (and did not find it among its last answers)
+int64_t& linear_shape_searches();
 // number of K-slices launch_linear takes for M rows when it is given a workspace of max_split slices
 int linear_slices(const Linear& L, int M, int prologue, int max_split, SliceCost slices);
 int32_t launch_reduce_partials(const float* part, int ks, int64_t n, float* y, int accumulate, hipStream_t st);

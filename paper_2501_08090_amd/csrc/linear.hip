@@ -240,12 +240,12 @@ static void by_estimate(const Linear& L, int M, int kc, int most, SliceCost slic
         }
 }
 
-// the launch shape of a tiled projection: rows / 32 and column tiles per wave, waves per workgroup, k-steps per chunk,
-// workgroups along N and M, K-slices and chunks per slice
-struct LinearShape {
-    int mt, nf, nw, ks, gx, gz, ksplit, cps;
-};
-static LinearShape linear_shape(const Linear& L, int M, bool sliceable, int prologue, int max_split, SliceCost slices) {
+int64_t& linear_shape_searches() {
+    static thread_local int64_t n = 0;
+    return n;
+}
+
+LinearShape linear_shape(const Linear& L, int M, bool sliceable, int prologue, int max_split, SliceCost slices) {
     const Tuning& tn = tuning();
     // Tile shape.  Up to 64 rows the kernel is HBM-bound: 32- or 64-row tiles; one column tile per wave when K can
     // be sliced (twice the workgroups along N, so half the K-slices for the consumer to add up) or when that is
@@ -359,17 +359,28 @@ static LinearShape linear_shape(const Linear& L, int M, bool sliceable, int prol
     //   sliced, with the sum of the slices: 8192 x 512, 512 rows 36 -> 14; 6144 x 4096, 384 rows 58 -> 53; 2048 x 2048, 100 rows
     //   16 -> 12; 462 shapes 0.88, none over 1.04.  (Up to 32 rows their choice is within 3 % of the best everywhere.)
     if (prologue == PRO_NONE && M > 32 && !tn.linear_mt && !tn.linear_nf && !tn.linear_ksplit && !tn.linear_ks && tn.linear_target_blocks == kNumCU) {
-        // (a pure function of these sizes, about 3 us of the host's time: its last answers are kept, per thread)
+        // A pure function of these sizes, 1 .. 3 us of the host's time: a thread keeps its last 32 answers, which are looked through one by
+        // one (some 20 ns).  A step of many layers asks for five products again and again, so all five have to stay, whatever their widths.
         struct Answer {
             int N, K, M, most, slices, mt, nf, ksplit, cps;
         };
-        static thread_local Answer answers[64];
+        static thread_local Answer answers[32];
+        static thread_local unsigned next = 0;
         const int most = sliceable ? max_split : 1;
-        Answer& a = answers[((unsigned)L.N * 31u + (unsigned)L.K * 17u + (unsigned)M * 5u + (unsigned)most + (unsigned)slices) % 64u];
-        if (a.M != M || a.N != L.N || a.K != L.K || a.most != most || a.slices != slices) {
-            a = Answer{L.N, L.K, M, most, slices, mt, nf, ksplit, cps};
-            by_estimate(L, M, KC, most, slices, a.mt, a.nf, a.ksplit, a.cps);
+        const Answer* known = nullptr;
+        for (const Answer& e : answers)
+            if (e.N == L.N && e.K == L.K && e.M == M && e.most == most && e.slices == slices) {
+                known = &e;
+                break;
+            }
+        if (!known) {
+            Answer& e = answers[next++ % 32];
+            e = Answer{L.N, L.K, M, most, slices, mt, nf, ksplit, cps};
+            by_estimate(L, M, KC, most, slices, e.mt, e.nf, e.ksplit, e.cps);
+            ++linear_shape_searches();
+            known = &e;
         }
+        const Answer& a = *known;
         mt = a.mt;
         nf = a.nf;
         ksplit = a.ksplit;

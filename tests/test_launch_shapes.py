@@ -1,0 +1,59 @@
+"""Launch shapes of the projections, asked of the library's own functions on the host: needs no GPU."""
+import ctypes as C
+
+import pytest
+
+from paper_2501_08090_amd import binding as B
+
+STEP, BLOCK, ALONE = range(3)  # SliceCost
+MOST = 16                      # linear_max_split()
+
+
+class Linear(C.Structure):
+    _fields_ = [("w", C.c_void_p), ("N", C.c_int), ("K", C.c_int), ("Npad", C.c_int), ("Kpad", C.c_int), ("tstride", C.c_size_t), ("owned", C.c_bool)]
+
+
+class Shape(C.Structure):
+    _fields_ = [(n, C.c_int) for n in ("mt", "nf", "nw", "ks", "gx", "gz", "ksplit", "cps")]
+
+    def key(self):
+        """tile, K-slices and chunks per slice (eight waves of half the columns are four of whole ones)"""
+        return self.mt, self.nf * self.nw // 4, self.ksplit, self.cps
+
+
+def linear(N, K):
+    return Linear(None, N, K, (N + 31) // 32 * 32, (K + 255) // 256 * 256, 0, False)
+
+
+def shape(N, K, M, sliceable=True, slices=STEP):
+    f = B.load()._ZN6chiron12linear_shapeERKNS_6LinearEibiiNS_9SliceCostE
+    f.restype = Shape
+    return f(C.byref(linear(N, K)), C.c_int(M), C.c_bool(sliceable), C.c_int(0), C.c_int(MOST if sliceable else 1), C.c_int(slices))
+
+
+def searches():
+    f = B.load()._ZN6chiron21linear_shape_searchesEv
+    f.restype = C.POINTER(C.c_int64)
+    return f()[0]
+
+
+# QKV, O, gate/up, down and head: (N, K, sliceable)
+def products(H, qkv, qn, F, vocab):
+    return (qkv, H, True), (H, qn, True), (2 * F, H, False), (H, F, True), (vocab, H, False)
+
+
+WIDTHS = {"8b": products(4096, 6144, 4096, 14336, 128256), "70b": products(8192, 10240, 8192, 28672, 128256)}
+
+
+@pytest.mark.parametrize("widths", [WIDTHS["8b"], WIDTHS["70b"], products(5120, 7168, 5120, 13824, 32000), products(1024, 1536, 1024, 2816, 32768),
+                                    products(256, 512, 256, 688, 1024)])
+def test_a_step_searches_for_each_product_once(widths):
+    """the five products of a step are asked for layer after layer: only the first layer, the head and another row count search"""
+    for M in (64, 128, 500, 437):
+        before = searches()
+        for _ in range(3):
+            for _ in range(32):
+                for N, K, sliceable in widths[:4]:
+                    shape(N, K, M, sliceable)
+            shape(*widths[4][:2], M, widths[4][2])
+        assert searches() - before <= 5
