@@ -177,7 +177,8 @@ static void launch_cfg(int nblocks, hipStream_t st, const Linear& L, const float
                                                            part_stride, gx, gy, gz, tuning().linear_xcd_remap, norm.gain, norm.eps);
 }
 
-int linear_max_split() { return 16; }
+constexpr int kMaxSplit = 16;
+int linear_max_split() { return kMaxSplit; }
 
 // Rows from which the down projection is faster on the tiled two-term form of its input (128-row tiles, copied straight
 // into LDS) than on fp32 rows (64- and 96-row tiles, split on the way into LDS); the gate/up epilogue writes whichever
@@ -203,41 +204,66 @@ struct TileCost {
 static constexpr TileCost kTileCost[] = {{1, 1, 6.5, 1.2, 6.7},    {1, 2, 9.9, 1.8, 11.3},   {2, 1, 8.8, 2.5, 9.5},   {2, 2, 13.4, 2.9, 15.4}, {2, 4, 22.5, 6.0, 27.4},
                                          {3, 1, 12.3, 2.8, 15.0},  {3, 2, 20.0, 3.9, 21.5},  {4, 1, 19.2, 2.6, 17.5}, {4, 2, 25.2, 4.8, 26.5}, {4, 4, 37.3, 11.8, 48.7}};
 // A launch, its slowest CU or the weights at 6.4 TB/s, the result at 4.5 TB/s; K-slices (of M x N fp32) are written and read again by
-// whoever adds them: 0.4 us per MB, and 4 us for a launch of its own.  The host takes about as long for a call as for 15 us of a
-// block's second half or, where it has to allocate the slices, 26 us: a shape that is faster than that gains nothing by slicing.
+// whoever adds them: 0.4 us per MB, and 4 us for a launch of its own.
 // (128 x 512 tiles: a last round that is at most half full is taken as tiles of 256 columns, see linear_wide_kernel)
 static bool halved_last_round(int64_t wgs) { return wgs > kNumCU && wgs % kNumCU != 0 && wgs % kNumCU <= kNumCU / 2; }
-static double shape_us(const Linear& L, int M, const TileCost& t, int ksplit, int64_t k_per_slice, SliceCost slices) {
-    const int64_t wgs = (int64_t)((L.Npad / 32 + 4 * t.nf - 1) / (4 * t.nf)) * ((M + 32 * t.mt - 1) / (32 * t.mt)) * ksplit;
+static double shape_us(const Linear& L, int M, const TileCost& t, int64_t tiles, int ksplit, int64_t k_per_slice, SliceCost slices) {
+    const int64_t wgs = tiles * ksplit;
     double per_k = wgs <= kNumCU ? t.one + t.fill * wgs / kNumCU : t.many * ((wgs + kNumCU - 1) / kNumCU);
     if (t.mt * t.nf == 16 && ksplit == 1 && halved_last_round(wgs)) per_k = t.many * (wgs / kNumCU) + 28.0;
     const double run = 1e-3 * k_per_slice * per_k, stream = 2e-6 * L.N * L.K / 6.4;
-    double us = 4.0 + (run > stream ? run : stream);
+    const double us = 4.0 + (run > stream ? run : stream);
     if (ksplit == 1) return us + 4e-6 * M * L.N / 4.5;
-    us += 0.4e-6 * 4.0 * ksplit * M * L.N + (slices == SLICES_STEP ? 1.0 : 4.0);
-    const double host = slices == SLICES_ALONE ? 26.0 : slices == SLICES_BLOCK ? 15.0 : 0.0;
-    return us > host ? us : host;
+    return us + 0.4e-6 * 4.0 * ksplit * M * L.N + (slices == SLICES_STEP ? 1.0 : 4.0);
 }
+// A call with slices takes this long however fast its kernels are, so a sliced shape is no better than that against an unsliced one.
+// A projection by itself: it allocates the slices, and the allocation waits until the stream has nothing left to do (18 .. 26 us a call
+// behind other work as well as alone); in a captured graph its memory nodes take as long (22 .. 24 us a call, where one launch
+// takes what its kernel does: 8 .. 17 us for 20 to 30 rows of 100 .. 400 columns at K = 2000 .. 4000).  The second half of a block:
+// what the host needs for it.
+static double sliced_call_us(SliceCost slices) { return slices == SLICES_ALONE ? 26.0 : slices == SLICES_BLOCK ? 15.0 : 0.0; }
 
 // Puts the shape with the least estimate in the place of the one given (tile, slices and chunks of kc per slice) if it is 5 % below
-// that one's; `most` slices at most.
+// that one's; `most` slices at most.  Sliced shapes are compared among each other by their kernels, also where the call
+// takes longer than those (182 rows of 4254 x 3056: 39 us with the shape of the rules, 35 with the best; 128 rows of 2048 x 2048
+// from a graph 26 and 22).
 static void by_estimate(const Linear& L, int M, int kc, int most, SliceCost slices, int& mt, int& nf, int& ksplit, int& cps) {
-    double best = 1e30;
+    struct Candidate {
+        double us;
+        int mt, nf, ksplit, cps;
+    };
+    const auto tiles = [&](const TileCost& t) { return (int64_t)((L.Npad / 32 + 4 * t.nf - 1) / (4 * t.nf)) * ((M + 32 * t.mt - 1) / (32 * t.mt)); };
+    Candidate best[2] = {{1e30, 0, 0, 0, 0}, {1e30, 0, 0, 0, 0}};  // unsliced, sliced
+    const int given = ksplit > 1;
+    double floor_us = sliced_call_us(slices);
     for (const TileCost& t : kTileCost)
-        if (t.mt == mt && t.nf == nf) best = 0.95 * shape_us(L, M, t, ksplit, (int64_t)cps * kc, slices);
-    const int chunks = (L.K + 63) / 64, rule_cps = cps;
-    for (const TileCost& t : kTileCost)
-        for (int want = 1; want <= most && (want == 1 || want <= chunks / 2); ++want) {
-            const int c = (chunks + want - 1) / want;
-            if ((chunks + c - 1) / c != want || (most > 1 && c > 16 && c > rule_cps)) continue;  // an empty slice; too long a one
-            const double us = shape_us(L, M, t, want, (int64_t)c * 64, slices);
-            if (us >= best) continue;
-            best = us;
-            mt = t.mt;
-            nf = t.nf;
-            ksplit = want;
-            cps = c;
+        if (t.mt == mt && t.nf == nf) best[given] = Candidate{0.95 * shape_us(L, M, t, tiles(t), ksplit, (int64_t)cps * kc, slices), mt, nf, ksplit, cps};
+    const int chunks = (L.K + 63) / 64;
+    int per_slice[kMaxSplit + 1] = {0};  // chunks, for each number of slices (0: not to be tried)
+    for (int want = 1; want <= most && want <= kMaxSplit && (want == 1 || want <= chunks / 2); ++want) {
+        const int c = (chunks + want - 1) / want;
+        if ((chunks + c - 1) / c != want || (most > 1 && c > 16 && c > cps)) continue;  // an empty slice; too long a one
+        per_slice[want] = c;
+    }
+    bool stays = true;
+    for (const TileCost& t : kTileCost) {
+        const int64_t n = tiles(t);
+        for (int want = 1; want <= kMaxSplit; ++want) {
+            if (!per_slice[want]) continue;
+            const double us = shape_us(L, M, t, n, want, (int64_t)per_slice[want] * 64, slices);
+            Candidate& b = best[want > 1];
+            if (us >= b.us) continue;
+            b = Candidate{us, t.mt, t.nf, want, per_slice[want]};
+            if ((want > 1) == given) stays = false;
         }
+    }
+    if (given && stays) floor_us *= 0.95;
+    const double sliced = best[1].us > floor_us ? best[1].us : floor_us;
+    const Candidate& b = best[given ? sliced <= best[0].us : sliced < best[0].us];
+    mt = b.mt;
+    nf = b.nf;
+    ksplit = b.ksplit;
+    cps = b.cps;
 }
 
 int64_t& linear_shape_searches() {

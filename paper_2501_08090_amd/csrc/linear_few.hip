@@ -353,17 +353,20 @@ bool step_few_rows(const Linear& qkv, const Linear& o, const Linear& gu, const L
     return few_us(qkv, M, FEW_QKV, 2) + few_us(o, M, FEW_ROWS, ct_o) + few_us(down, M, FEW_PACKED, ct_down) <= pays;
 }
 
-// A projection by itself: against the tiled kernel, the sum of its slices (5 us), and no less than the 25 us that the host takes to
-// enqueue the two with their scratch memory (18 where the few-row kernel has two row tiles: 21 .. 28 us a call through the tiled
-// kernel, 6.7 at 20 rows of 1024 x 1024, 9.0 at 2048 x 8192 and 12 at 32 rows of 1024 x 16384 through this one; behind a gate/up the host is
-// ahead: 2048 x 5632 at 20 rows would take 39 us with it against 31).  A long K without a workgroup for every CU is a serial chain that nothing hides
+// A projection by itself: against the tiled kernel, the sum of its slices (5 us), and no less than 25.5 us, which a call with slices takes
+// however fast its kernels are (18 where the few-row kernel has two row tiles; 18 .. 24 measured).  That is their scratch memory: its
+// allocation waits until the stream has nothing left to do, so a call behind other work takes as long as one on an idle stream,
+// and in a captured graph the memory nodes take it (10 rows of 357 x 4256: 10.4 us behind other work, 10.7 in a graph, against 20
+// and 22 with slices; 17 rows of 128 x 6912 18.7 and 18.9 against 24 and 22; 20 rows: 1024 x 1024 6.7, 2048 x 8192 9.0; 32 rows of
+// 1024 x 16384 12).  Behind a gate/up, whose block allocates for both, there is no such floor (2048 x 5632 at 20 rows would take 39 us with it
+// against 31).  A long K without a workgroup for every CU is a serial chain that nothing hides
 // (2048 x 28672, one row: 33 against 29 us).  4096 x 14336: 24 against 28 us at 8 rows, 33 against 30 at 16; 10240 x 28672 (320
 // workgroups): 112 against 98 at one row.  Very wide outputs have enough column tiles for the tiled kernel unsliced.
 bool linear_few_pays(const Linear& L, int M, SliceCost slices) {
     if (!linear_few_rows(M) || L.N > 16384 || (L.K > 16384 && L.N < 4096)) return false;
     const double tiled = 5.0 + tiled_us(L);
-    const double host = M <= 16 ? 25.5 : slices == SLICES_ALONE ? 18.0 : 0.0;
-    return few_us(L, M, FEW_ROWS, few_col_tiles(L, M)) <= (tiled > host ? tiled : host);
+    const double call = M <= 16 ? 25.5 : slices == SLICES_ALONE ? 18.0 : 0.0;
+    return few_us(L, M, FEW_ROWS, few_col_tiles(L, M)) <= (tiled > call ? tiled : call);
 }
 
 // the same for the down projection of a feed-forward block, whose scratch memory is there anyway; from 17 rows on with what the

@@ -57,3 +57,12 @@ def test_a_step_searches_for_each_product_once(widths):
                     shape(N, K, M, sliceable)
             shape(*widths[4][:2], M, widths[4][2])
         assert searches() - before <= 5
+
+
+@pytest.mark.parametrize("M,N,K", [(128, 2048, 2048), (182, 4254, 3056), (157, 517, 7648), (325, 941, 1488), (163, 2091, 1968)])
+@pytest.mark.parametrize("slices", [BLOCK, ALONE])
+def test_sliced_shapes_are_compared_by_their_kernels(M, N, K, slices):
+    """what a call with slices takes at least is no reason to take a slower sliced shape: the shape is the one inside a step, where
+    there is no such floor"""
+    assert shape(N, K, M, slices=STEP).ksplit > 1
+    assert shape(N, K, M, slices=slices).key() == shape(N, K, M, slices=STEP).key()
