@@ -131,7 +131,8 @@ int linear_max_split();
 struct LinearShape {
     int mt, nf, nw, ks, gx, gz, ksplit, cps;
 };
-LinearShape linear_shape(const Linear& L, int M, bool sliceable, int prologue, int max_split, SliceCost slices);
+// (swept: by the rules from the sweeps at the 8B and 70B widths alone, without the estimate)
+LinearShape linear_shape(const Linear& L, int M, bool sliceable, int prologue, int max_split, SliceCost slices, bool swept = false);
 // how often this thread had to search for one so far (and did not find it among its last answers)
 int64_t& linear_shape_searches();
 // number of K-slices launch_linear takes for M rows when it is given a workspace of max_split slices

@@ -271,7 +271,7 @@ int64_t& linear_shape_searches() {
     return n;
 }
 
-LinearShape linear_shape(const Linear& L, int M, bool sliceable, int prologue, int max_split, SliceCost slices) {
+LinearShape linear_shape(const Linear& L, int M, bool sliceable, int prologue, int max_split, SliceCost slices, bool swept) {
     const Tuning& tn = tuning();
     // Tile shape.  Up to 64 rows the kernel is HBM-bound: 32- or 64-row tiles; one column tile per wave when K can
     // be sliced (twice the workgroups along N, so half the K-slices for the consumer to add up) or when that is
@@ -378,13 +378,20 @@ LinearShape linear_shape(const Linear& L, int M, bool sliceable, int prologue, i
     ksplit = (chunks + cps - 1) / cps;  // no empty slices
     // The rules above come from sweeps at the 8B and 70B widths.  Elsewhere they can leave most of the chip idle (128-row tiles of 512
     // columns from 384 rows on: 48 workgroups for a gate/up of 4096 columns) or double the rounds of the grid, and a short K is
-    // sliced into ramps.  So any other shape whose estimate is 5 % below theirs takes their place; at their own widths up to 256
-    // rows none does.  Slices stay at most 1024 long (or as long as theirs): longer sums would round a little more.
+    // sliced into ramps.  So any other shape whose estimate is 5 % below theirs takes their place.  Slices stay at most 1024 long
+    // (or as long as theirs): longer sums would round a little more.
     //   gate/up, us: 4096 columns, K = 4096, 384 rows 162 -> 63; 5632, K = 2048, 512 rows 85 -> 56; 1376, K = 4096, 160 rows 55 -> 33;
     //   512 shapes of the sweep 0.88 of the time on average, none over 1.01.
     //   sliced, with the sum of the slices: 8192 x 512, 512 rows 36 -> 14; 6144 x 4096, 384 rows 58 -> 53; 2048 x 2048, 100 rows
     //   16 -> 12; 462 shapes 0.88, none over 1.04.  (Up to 32 rows their choice is within 3 % of the best everywhere.)
-    if (prologue == PRO_NONE && M > 32 && !tn.linear_mt && !tn.linear_nf && !tn.linear_ksplit && !tn.linear_ks && tn.linear_target_blocks == kNumCU) {
+    // At the widths of the sweeps and up to 256 rows it replaces, inside a step, us a launch by the rules -> now:
+    //   8B QKV at 65 .. 96 rows 20.6 -> 18.9 (96-row tiles of 256 columns in 10 slices -> of 128 in 5) and O 17.0 -> 15.6, with less for
+    //   the rotation (6.1 -> 4.8) and the norms (12.9 -> 11.7 a layer) to add up; O at 129 .. 192 rows 20.0 -> 17.5 (8 slices of 96-row
+    //   tiles -> 5 of 64-row ones); 70B QKV at 129 .. 192 rows 72.8 -> 64.9 (3 slices -> 4), down at 129 .. 152 rows 173.6 -> 175.6 and at
+    //   193 .. 223 187.4 -> 187.5 (4 -> 8); the head of 128256 columns at 96 rows 238 -> 226, at K = 8192 473 -> 444.
+    //   Error of a product against 64 bits, in 1e-6 of it: 8B QKV 2.456 -> 2.461 (slices of 448 and 832 inputs), O 2.451 -> 2.454 and
+    //   2.463 -> 2.468, 70B QKV 2.498 -> 2.488, down 2.573 -> 2.513.
+    if (!swept && prologue == PRO_NONE && M > 32 && !tn.linear_mt && !tn.linear_nf && !tn.linear_ksplit && !tn.linear_ks && tn.linear_target_blocks == kNumCU) {
         // A pure function of these sizes, 1 .. 3 us of the host's time: a thread keeps its last 32 answers, which are looked through one by
         // one (some 20 ns).  A step of many layers asks for five products again and again, so all five have to stay, whatever their widths.
         struct Answer {

@@ -25,10 +25,10 @@ def linear(N, K):
     return Linear(None, N, K, (N + 31) // 32 * 32, (K + 255) // 256 * 256, 0, False)
 
 
-def shape(N, K, M, sliceable=True, slices=STEP):
-    f = B.load()._ZN6chiron12linear_shapeERKNS_6LinearEibiiNS_9SliceCostE
+def shape(N, K, M, sliceable=True, slices=STEP, swept=False):
+    f = B.load()._ZN6chiron12linear_shapeERKNS_6LinearEibiiNS_9SliceCostEb
     f.restype = Shape
-    return f(C.byref(linear(N, K)), C.c_int(M), C.c_bool(sliceable), C.c_int(0), C.c_int(MOST if sliceable else 1), C.c_int(slices))
+    return f(C.byref(linear(N, K)), C.c_int(M), C.c_bool(sliceable), C.c_int(0), C.c_int(MOST if sliceable else 1), C.c_int(slices), C.c_bool(swept))
 
 
 def searches():
@@ -66,3 +66,19 @@ def test_sliced_shapes_are_compared_by_their_kernels(M, N, K, slices):
     there is no such floor"""
     assert shape(N, K, M, slices=STEP).ksplit > 1
     assert shape(N, K, M, slices=slices).key() == shape(N, K, M, slices=STEP).key()
+
+
+# where the estimate replaces the shape of the rules at the widths that those were swept at, up to 256 rows (the comment at the
+# estimate has the times of both): {(widths, product of `products`): rows}
+REPLACED = {("8b", 0): [*range(65, 97)], ("8b", 1): [*range(65, 97), *range(129, 193)], ("8b", 4): [96],
+            ("70b", 0): [*range(129, 193)], ("70b", 3): [*range(129, 153), *range(193, 224)], ("70b", 4): [96]}
+
+
+@pytest.mark.parametrize("widths", WIDTHS)
+def test_the_swept_widths_keep_the_shapes_that_were_swept(widths):
+    """up to 256 rows every launch at the 8B and 70B widths has the shape of the rules, but for those that were timed with the other;
+    no slice gets longer than 1024 inputs, or the rules' own, by it"""
+    for i, (N, K, sliceable) in enumerate(WIDTHS[widths]):
+        other = [M for M in range(1, 257) if shape(N, K, M, sliceable).key() != shape(N, K, M, sliceable, swept=True).key()]
+        assert other == REPLACED.get((widths, i), []), (N, K)
+        assert all(shape(N, K, M).cps <= max(16, shape(N, K, M, swept=True).cps) for M in other if sliceable)
