@@ -262,6 +262,7 @@ __global__ __launch_bounds__(64 * kFewWaves) void linear_few_kernel(const uint16
 // ---- which rows take this path -------------------------------------------------------------------------------
 bool linear_few_rows(int M) {
     const Tuning& t = tuning();
+    if (M > 16 && t.linear_big_min_m > 0 && M >= t.linear_big_min_m) return false;  // as from there on the tiled two-term form is asked for
     return M <= 32 && !t.linear_mt && !t.linear_nf && !t.linear_ksplit && !t.linear_ks && !t.linear_big_all;
 }
 

@@ -1199,6 +1199,28 @@ def test_step_of_two_row_tiles(over, batch, T, norms):
     assert np.abs(out[0] - out[1]).max() <= 2e-3 * out[1].std()
 
 
+def test_the_two_term_form_can_be_asked_for_at_few_rows():
+    """linear_big_min_m within 17 .. 32 rows: from there on a feed-forward block takes the tiled two-term form, and a step the path that may
+    (a model made for so few rows has no workspace for it), not the few-row kernel"""
+    c = make_case(m=dict(I.TINY, n_layers=1), batch=20, kind="tiny", seed=59, storage="bf16", gain_jitter=0.2)
+    g = gpu_setup(c)
+    x, Wg, Wu, Wd, _, want_ffn = ffn_case(20, 272, 688, 256, 5)
+    b = B()
+    gu, down = b.GateUp(Wg.cuda(), Wu.cuda()), b.Linear(Wd.cuda())
+    for start, norms in ((0, 1), (21, 1), (20, 3)):
+        print("two-term form from", start, flush=True)
+        b.set_tuning("linear_big_min_m", start)
+        try:
+            (_, got, want, _), n = norm_launches(g, lambda: run_both(c, g))
+            y = gu.ffn(down, torch.from_numpy(x).cuda()).cpu().numpy()
+        finally:
+            b.set_tuning("linear_big_min_m", 0)
+        assert n == norms
+        check_logits(got, want, min_agree=0.95)
+        assert rel_err(y, want_ffn) <= KERNEL_TOL
+    gu.close(); down.close()
+
+
 @pytest.mark.parametrize("over,batch", [(dict(vocab=8192), 16), (dict(vocab=8208), 3), (dict(hidden=2064, ffn=4112, vocab=16384), 9), (dict(hidden=4624, ffn=32, vocab=96), 2)])
 def test_step_of_few_rows_with_narrow_gate_up_and_head(over, batch):
     """steps whose gate/up and head are products of the few-row kernel too (one round of 32-column tiles, two at K >= 2048), and the

@@ -82,3 +82,17 @@ def test_the_swept_widths_keep_the_shapes_that_were_swept(widths):
         other = [M for M in range(1, 257) if shape(N, K, M, sliceable).key() != shape(N, K, M, sliceable, swept=True).key()]
         assert other == REPLACED.get((widths, i), []), (N, K)
         assert all(shape(N, K, M).cps <= max(16, shape(N, K, M, swept=True).cps) for M in other if sliceable)
+
+
+def test_a_forced_start_of_the_two_term_form_ends_the_few_rows():
+    """linear_big_min_m at 17 .. 32 rows takes effect where the few-row kernel would pay; up to 16 rows that kernel comes first, as ever"""
+    f = B.load()._ZN6chiron15linear_few_rowsEi
+    f.restype = C.c_bool
+    few = lambda M: f(C.c_int(M))
+    assert [few(M) for M in (1, 16, 17, 32, 33)] == [True, True, True, True, False]
+    try:
+        for start, want in ((1, [True, False, False, False]), (20, [True, True, False, False]), (33, [True] * 4), (-1, [True] * 4)):
+            B.set_tuning("linear_big_min_m", start)
+            assert [few(M) for M in (16, 19, 20, 32)] == want, start
+    finally:
+        B.set_tuning("linear_big_min_m", 0)
