@@ -23,6 +23,7 @@
 namespace chiron {
 
 constexpr int kFewWaves = 8;
+constexpr int kFewRing = 8;  // k-steps of 32 in flight per wave with one row tile
 
 // CT: 16-column tiles per workgroup.
 // FEW_ROWS: A is fp32 rows.
@@ -41,7 +42,7 @@ __global__ __launch_bounds__(64 * kFewWaves) void linear_few_kernel(const uint16
                                                                    const uint16_t* __restrict__ gain, float eps,
                                                                    float* __restrict__ Y, int ldy, int add, RopeOut ro) {
     constexpr bool QKV = MODE == FEW_QKV, NORM = MODE >= FEW_NORM, SWIGLU = MODE == FEW_SWIGLU || MODE == FEW_SWIGLU_NORM;
-    constexpr int D = RT == 1 ? 8 : 4;  // k-steps in flight per wave (CT KiB of weights each)
+    constexpr int D = RT == 1 ? kFewRing : kFewRing / 2;  // k-steps in flight per wave (CT KiB of weights each)
     constexpr int WS = 72;      // float4 units between the 16x16 tiles in LDS, 18 between a tile's row groups: no two
     constexpr int QS = 18;      // threads of the final sum that read at once share a bank
     __shared__ float4 s_acc[RT][kFewWaves * CT * WS];
@@ -328,9 +329,14 @@ bool norm_few_pays(const Linear& L, int M, bool norm) {
 
 // A whole layer: what the few-row QKV, O and down projections take longer than the tiled ones must stay below the two norms and
 // the rotation that become part of them (13.6 us up to 4096 columns, 20 at 8192, 25 at 16384, less what the norm costs where it
-// goes).  Measured end to end, us per layer gained by this path at 1 / 8 / 12 / 16 rows: 8B widths 9 / 6 / 1 / -4, 70B widths
-// 8 / 7 / 2 / -9, 6144 wide (384 workgroups) 0 / -9 / -22 / -36, 12288 wide 6 / -12 / -23 / -51, 5120 wide with 40 KV heads (320 and
-// 480 workgroups) -8 / -17 / -31 / -43.  On one set of weights, whole steps by this rule are within 1 % of the better path.
+// goes).  A QKV of two rounds over a K that is no whole number of rings per wave (8 k-steps of 32, 8 waves) takes some 1.5 us per 1024 of
+// K longer than estimated, as the last ring is loaded in full, again in either round.  Measured end to end, us per layer gained by this path:
+//   8B widths 9 / 6 / 1 / -4 at 1 / 8 / 12 / 16 rows, 70B widths 6 / 6 / 5 / 2 / 0 at 1 / 9 / 10 / 11 / 12, 12288 wide 6 / -12 / -23 / -51 at 1 / 8 / 12 / 16;
+//   hidden columns, QKV columns: 4096, 12288 6 / 5 / 2 / -4 at 1 / 8 / 11 / 16; 2048, 10240 5 / 4 / 1 at 1 / 4 / 8;
+//   two rounds and part of a ring: 5120, 15360 5 / 3 / 0 / -4 at 1 / 4 / 5 / 8; 5120, 12288 2 / 0 / -6 and 4608, 13824 2 / 0 / -6 at 1 / 4 / 8;
+//   7168, 10240 5 / 4 / 3 / -1 at 1 / 4 / 7 / 8; 3584, 10240 5 / 4 / 1 / -1 and 3072, 10240 5 / 4 / 0 / -4 at 1 / 4 / 8 / 10; 2560, 10240 1 / 0 / -2 / -6
+//   at 1 / 4 / 6 / 8; three rounds: 6144, 18432 10 / 6 / 2 / -4 at 1 / 8 / 10 / 11.
+// On one set of weights, whole steps by this rule are within 1 % of the better path.
 // From 17 rows on the few-row kernel must take gate/up too (the tiled one has the norm for 16 rows), and 1 us must be left: gained
 // at 17 / 24 / 32 rows 9 / 8 / 7 us a layer at 256 hidden columns, 6 / 4 / 2 at 1024; it would be -1 / -5 / -11 at 2048 and
 // -11 / -19 / -25 at the 8B widths.
@@ -338,10 +344,8 @@ bool step_few_rows(const Linear& qkv, const Linear& o, const Linear& gu, const L
     if (!linear_few_rows(M) || (M > 16 && qkv.N > 32 * kNumCU)) return false;
     const double saved = 5.9 + 1.3 / 1024 * qkv.K;
     double pays = tiled_us(qkv) + tiled_us(o) + tiled_us(down) + (saved > 13.0 ? saved : 13.0);
-    int ct_o = (o.N + 31) / 32 >= kNumCU ? 2 : 1, ct_down = (down.N + 31) / 32 >= kNumCU ? 2 : 1;
-    if (qkv.N <= 32 * kNumCU) {  // (a QKV of two rounds was measured with these column tiles and without a gate/up of its own)
-        ct_o = few_col_tiles(o, M);
-        ct_down = few_col_tiles(down, M);
+    const int ct_o = few_col_tiles(o, M), ct_down = few_col_tiles(down, M);
+    if (qkv.N <= 32 * kNumCU) {
         if (norm_few_pays(gu, M)) {
             const double gu_saved = unsliced_us(gu) - few_us(gu, M, FEW_SWIGLU_NORM, 2);
             if (M > 16) pays += gu_saved - 1.0;
@@ -349,7 +353,8 @@ bool step_few_rows(const Linear& qkv, const Linear& o, const Linear& gu, const L
         } else if (M > 16) {
             return false;
         }
-        if (ct_o == 2) pays -= 2.0;  // (5120 hidden columns at 11 rows: 1.5 us a layer more than estimated)
+    } else if (qkv.N <= 64 * kNumCU && qkv.Kpad % (32 * kFewWaves * kFewRing) != 0) {
+        pays -= 0.0015 * qkv.K;
     }
     return few_us(qkv, M, FEW_QKV, 2) + few_us(o, M, FEW_ROWS, ct_o) + few_us(down, M, FEW_PACKED, ct_down) <= pays;
 }

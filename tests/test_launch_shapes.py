@@ -96,3 +96,22 @@ def test_a_forced_start_of_the_two_term_form_ends_the_few_rows():
             assert [few(M) for M in (16, 19, 20, 32)] == want, start
     finally:
         B.set_tuning("linear_big_min_m", 0)
+
+
+# hidden, QKV, O's inputs, ffn: {rows: us per layer that a step gains by the few-row kernels, measured end to end}
+GAINED = {(4096, 6144, 4096, 14336): {1: 9, 8: 6, 12: 1, 16: -4}, (8192, 10240, 8192, 28672): {1: 6, 9: 6, 10: 5, 11: 2, 16: -9},
+          (4096, 12288, 4096, 11008): {1: 6, 8: 5, 11: 2, 16: -4}, (2048, 10240, 8192, 8192): {1: 5, 4: 4, 8: 1},
+          (5120, 15360, 5120, 13824): {1: 5, 4: 3, 8: -4, 11: -10}, (5120, 12288, 8192, 13824): {8: -6, 11: -12}, (4608, 13824, 4608, 12288): {8: -6, 11: -9},
+          (7168, 10240, 8192, 20480): {1: 5, 4: 4, 7: 3, 11: -8}, (3584, 10240, 8192, 9728): {1: 5, 4: 4, 6: 4}, (3072, 10240, 8192, 8192): {1: 5, 4: 4, 10: -4},
+          (2560, 10240, 8192, 8192): {8: -6, 10: -7}, (6144, 18432, 6144, 16384): {1: 10, 8: 6, 11: -4}, (5120, 6144, 4096, 13824): {1: 8, 10: 2, 16: -8},
+          (6144, 6144, 4096, 16384): {1: 16, 14: 6}, (4608, 6144, 4096, 8192): {1: 17, 11: 6}}
+
+
+@pytest.mark.parametrize("widths", GAINED)
+def test_a_step_takes_the_few_row_kernels_where_they_gained(widths):
+    H, qkv, qn, F = widths
+    f = B.load()._ZN6chiron13step_few_rowsERKNS_6LinearES2_S2_S2_i
+    f.restype = C.c_bool
+    ops = [linear(qkv, H), linear(H, qn), linear(2 * F, H), linear(H, F)]
+    for M, gain in GAINED[widths].items():
+        assert f(*(C.byref(o) for o in ops), C.c_int(M)) == (gain > 0), (widths, M)
