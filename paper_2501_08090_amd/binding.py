@@ -7,6 +7,7 @@ fallback: if the library has not been built, loading raises.
 """
 import ctypes as C
 import os
+from operator import index
 
 import torch
 
@@ -53,7 +54,8 @@ class ProfilePoint(C.Structure):
 _lib = None
 
 # Entry points that a serving loop calls again and again, with their argument types (p: pointer or stream, i: int32, l: int64): their
-# arguments go in as plain numbers, without a ctypes object for each (5.2 -> 2.6 us of Python a call).
+# arguments go in as plain numbers, without a ctypes object for each (5.2 -> 2.6 us of Python a call).  What a caller hands in as a number
+# goes through index() first: no whole number is a TypeError, where ctypes would raise an ArgumentError, which is none.
 _HOT = {"chiron_decode_step": "pppppipp", "chiron_decode_step_multi": "pppppiipp", "chiron_append_kv": "pipppipplp",
         "chiron_gather_kv": "pipippp", "chiron_kv_swap_out": "ppipp", "chiron_kv_swap_in": "ppipp", "chiron_op_linear": "ppipip",
         "chiron_op_gate_up_swiglu": "ppipp", "chiron_op_swiglu_ffn": "pppipip", "chiron_op_paged_attention": "ppipppipp"}
@@ -175,7 +177,7 @@ class KVPool:
 
     def append(self, layer, k, v, block_table, seq_idx, pos):
         n = seq_idx.numel()
-        _check(load().chiron_append_kv(self._h, layer, _address(k, torch.bfloat16), _address(v, torch.bfloat16),
+        _check(load().chiron_append_kv(self._h, index(layer), _address(k, torch.bfloat16), _address(v, torch.bfloat16),
                                        _address(block_table, torch.int32), block_table.shape[1],
                                        _address(seq_idx, torch.int32), _address(pos, torch.int32), n, _stream_number()))
 
@@ -183,7 +185,7 @@ class KVPool:
         cfg = self.model.cfg
         k = torch.empty((length, cfg.n_kv_heads, cfg.head_dim), dtype=torch.bfloat16, device="cuda")
         v = torch.empty_like(k)
-        _check(load().chiron_gather_kv(self._h, layer, _address(block_table_row, torch.int32), length, k.data_ptr(), v.data_ptr(),
+        _check(load().chiron_gather_kv(self._h, index(layer), _address(block_table_row, torch.int32), index(length), k.data_ptr(), v.data_ptr(),
                                        _stream_number()))
         return k, v
 
@@ -402,6 +404,6 @@ def op_paged_attention(model, pool, layer, q, block_table, ctx_lens):
     B = ctx_lens.numel()
     _check_table(model, block_table, B)
     out = torch.empty_like(q)
-    _check(load().chiron_op_paged_attention(model._h, pool._h, layer, _address(q, torch.float32), _address(block_table, torch.int32),
+    _check(load().chiron_op_paged_attention(model._h, pool._h, index(layer), _address(q, torch.float32), _address(block_table, torch.int32),
                                             _address(ctx_lens, torch.int32), B, _address(out), _stream_number()))
     return out

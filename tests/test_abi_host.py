@@ -6,6 +6,7 @@ import re
 
 import numpy as np
 import pytest
+import torch
 
 from paper_2501_08090_amd import binding as B
 from paper_2501_08090_amd import inputs as I
@@ -118,3 +119,15 @@ def test_host_validation_of_multi_token_inputs():
     assert chk(lens=np.array([5, 14, 62], np.int32)) == -4        # 62 + 3 positions need 5 pages, rows hold 4
     assert B.check_step_inputs_host(cfg, 6, np.zeros((5, 4), np.int32), np.zeros(5, np.int32), np.zeros((5, 3), np.int32)) == -3
 
+
+def test_a_layer_that_is_no_whole_number_is_a_type_error():
+    B.load()
+    pool = B.KVPool.__new__(B.KVPool)
+    pool._h, t = C.c_void_p(), torch.zeros((1, 1), dtype=torch.int32)
+    for layer in (0.5, None, "0"):
+        with pytest.raises(TypeError, match="interpreted as an integer"):
+            pool.append(layer, None, None, t, t, t)
+    for layer in (0, np.int32(0), True):  # these get as far as the table, which is no GPU tensor
+        with pytest.raises(TypeError, match="GPU tensor"):
+            pool.append(layer, None, None, t, t, t)
+    pool._h = None
