@@ -10,6 +10,7 @@ import torch
 
 import chiron_oracle as orc
 from helpers import as_f64, bf16_to_f32, bits, fresh_pool, gpu_setup, make_case
+from test_launch_shapes import ALONE, STEP, shape
 from paper_2501_08090_amd import inputs as I
 
 pytestmark = pytest.mark.gpu
@@ -246,7 +247,7 @@ def ffn_case(M, K, F, N, seed, scale=2.0):
 
 @pytest.mark.parametrize("M,K,F", [(4, 256, 688), (1, 64, 16), (33, 1040, 48), (64, 512, 1408), (40, 64, 96), (96, 256, 2064),
                                    (130, 512, 704), (390, 256, 1376), (17, 2048, 14336), (300, 256, 14336),
-                                   (400, 64, 14336)])  # the 128-row x 4-tile wave shape
+                                   (400, 64, 14336)])
 def test_gate_up_swiglu(M, K, F):
     """SwiGLU in the gate/up projection's epilogue: every column of silu(gate) * up against the oracle (a slip in the
     interleaved packing would pair a gate column with the wrong up column); widths of one 16-column group, of ragged
@@ -264,11 +265,12 @@ def test_gate_up_swiglu(M, K, F):
 
 @pytest.mark.parametrize("M,K,F,N", [(4, 256, 688, 256), (64, 256, 1408, 512), (40, 64, 64, 96), (390, 128, 704, 512), (80, 512, 704, 512),
                                      (96, 64, 64, 96), (97, 64, 688, 96), (200, 256, 2048, 1024), (513, 128, 688, 512),
-                                     (600, 64, 2048, 256), (520, 64, 4096, 64)])  # last: tiled output from the widest wave shape
+                                     (600, 64, 2048, 256), (520, 64, 4096, 64)])
 def test_swiglu_ffn(M, K, F, N):
     """The feed-forward block as the step runs it: gate/up with the SwiGLU epilogue, then the down projection, the
     intermediate as fp32 rows (up to 512 rows at these widths) or as tiled bf16 terms (from 513 rows on; F = 688 leaves
-    K padding in the down projection's operand).  test_linear_large_batch_kernel forces the tiled form at other sizes."""
+    K padding in the down projection's operand).  test_linear_large_batch_kernel forces the tiled form at other sizes,
+    test_linear_of_every_tile from every tile."""
     x, Wg, Wu, Wd, _, want = ffn_case(M, K, F, N, M + K + F + N)
     print("swiglu_ffn", M, K, F, N, flush=True)
     gu, down = B().GateUp(Wg.cuda(), Wu.cuda()), B().Linear(Wd.cuda())
@@ -323,23 +325,103 @@ def test_swiglu_ffn_records_no_memset_into_a_graph(M, F):
     gu.close(); down.close()
 
 
-@pytest.mark.parametrize("M,N,K", [(97, 8200, 2064), (128, 4096, 1024), (100, 2080, 512), (129, 2080, 272), (250, 2144, 528), (384, 8224, 64),
-                                   (500, 8192, 192), (387, 16400, 48), (97, 16352, 3088), (127, 8200, 6160), (100, 4096, 12304),
-                                   (97, 65600, 64), (96, 65600, 64), (128, 65536, 48)])
-def test_linear_eight_waves(M, N, K):
-    """the eight-wave shapes: 128 x 512 (from 384 rows, wide outputs; 97 of 65600 columns) and 64 x 256 with several M-tiles; ragged rows, columns past
-    the last tile, K below and past whole chunks.  Beside them the four-wave ones they border on: one 96-row tile of 129 rows,
-    and 64 x 512 for 97..128 rows where slices of at least twelve chunks fill the chip, or 65536 columns one round of it unsliced."""
+def pinned(mt=0, nf=0, ksplit=0, **more):
+    """context in which projections take this tile (and none is chosen by estimate)"""
+    import contextlib
+
+    @contextlib.contextmanager
+    def on():
+        knobs = dict(linear_mt=mt, linear_nf=nf, linear_ksplit=ksplit, **more)
+        try:
+            for k, v in knobs.items():
+                B().set_tuning(k, v)
+            yield
+        finally:
+            for k in knobs:
+                B().set_tuning(k, 0)
+    return on()
+
+
+@pytest.mark.parametrize("M,N,K,tile", [(97, 8200, 2064, (2, 2, 8)), (128, 4096, 1024, (2, 2, 8)), (100, 2080, 512, (2, 2, 8)), (129, 2080, 272, (3, 2, 4)),
+                                        (250, 2144, 528, (2, 2, 8)), (384, 8224, 64, (4, 4, 8)), (384, 8224, 336, (4, 4, 8)), (500, 8192, 192, (4, 4, 8)),
+                                        (387, 16400, 48, (4, 4, 8)), (387, 16400, 464, (4, 4, 8)), (97, 16352, 3088, (2, 4, 4)), (127, 8200, 6160, (2, 4, 4)),
+                                        (100, 4096, 12304, (2, 4, 4)), (97, 65600, 64, (4, 4, 8)), (96, 65600, 64, (3, 2, 4)), (128, 65536, 48, (2, 4, 4))])
+def test_linear_eight_waves(M, N, K, tile):
+    """the eight-wave kernels, by name: 128 x 512 and 64 x 256 with several M-tiles; ragged rows, columns past
+    the last tile, K below, at and past whole chunks, one chunk and several.  Beside them four-wave ones: a 96-row tile of 129 rows,
+    and 64 x 512.  `tile` is what the rules from the sweeps take; the product is taken with it and with whatever shape the estimate puts in
+    its place."""
     rng = np.random.default_rng(M + 3 * N + 5 * K)
     x = rng.standard_normal((M, K)).astype(np.float32)
     W = I.normal((N, K), 0.05, 6, "w8", N, K)
-    print("linear eight waves", M, N, K, flush=True)
     lin = B().Linear(W.cuda())
     want = orc.linear(x, I.to_numpy_storage(W))
     y0 = rng.standard_normal((M, N)).astype(np.float32)
-    assert rel_err(lin(torch.from_numpy(x).cuda()).cpu().numpy(), want) <= KERNEL_TOL
-    assert rel_err(lin(torch.from_numpy(x).cuda(), torch.from_numpy(y0).cuda(), accumulate=True).cpu().numpy(), want + y0) <= KERNEL_TOL
+    for mt, nf in (tile[:2], (0, 0)):
+        with pinned(mt, nf):
+            s = shape(N, K, M, N <= 16384, ALONE)
+            print("linear eight waves", M, N, K, s.key(), flush=True)
+            assert not mt or (s.mt, s.nf * s.nw // 4, s.nw) == tile
+            assert rel_err(lin(torch.from_numpy(x).cuda()).cpu().numpy(), want) <= KERNEL_TOL
+            assert rel_err(lin(torch.from_numpy(x).cuda(), torch.from_numpy(y0).cuda(), accumulate=True).cpu().numpy(), want + y0) <= KERNEL_TOL
     lin.close()
+
+
+@pytest.mark.parametrize("mt,nf", [(1, 1), (1, 2), (2, 1), (2, 2), (2, 4), (3, 1), (3, 2), (4, 1), (4, 2), (4, 4)])
+@pytest.mark.parametrize("tiles", [1, 3])
+def test_linear_of_every_tile(mt, nf, tiles):
+    """every tile that is built, by name: with one row tile and with several (weights with and without the streaming hint), ragged rows and columns, K of
+    several chunks and a remainder, whole and in slices; alone, added to y, as gate/up (rings of 8 and 16 k-steps) and with the tiled two-term
+    form written and, by the 128-row tiles, read"""
+    M, K, N = 32 * mt * tiles - 7, 656, 128 * nf * 2 + 72
+    x, Wg, Wu, Wd, act, y = ffn_case(M, 336, 656, N, 10 * mt + nf + tiles)
+    rng = np.random.default_rng(M + N)
+    b = B()
+    lin, gu, xa = b.Linear(Wd.cuda()), b.GateUp(Wg.cuda(), Wu.cuda()), torch.from_numpy(act).cuda()
+    y0 = rng.standard_normal((M, N)).astype(np.float32)
+    for ksplit in (1, 3):
+        with pinned(mt, nf, ksplit):
+            s = shape(N, K, M, True, ALONE)
+            assert (s.mt, s.nf * s.nw // 4, s.ksplit, s.gz) == (mt, nf, ksplit, tiles)
+            assert s.nw == (8 if (mt, nf) == (4, 4) or ((mt, nf) == (2, 2) and tiles > 1) else 4)
+            print("every tile", mt, nf, tiles, ksplit, flush=True)
+            assert rel_err(lin(xa).cpu().numpy(), y) <= KERNEL_TOL
+            assert rel_err(lin(xa, torch.from_numpy(y0).cuda(), accumulate=True).cpu().numpy(), y + y0) <= KERNEL_TOL
+            assert rel_err(gu.swiglu(torch.from_numpy(x).cuda()).cpu().numpy(), act) <= KERNEL_TOL
+        with pinned(mt, nf, ksplit, linear_big_min_m=1):
+            assert rel_err(gu.ffn(lin, torch.from_numpy(x).cuda()).cpu().numpy(), y) <= KERNEL_TOL
+    gu.close(); lin.close()
+
+
+@pytest.mark.parametrize("M,N,K", [(600, 28640, 336), (300, 44000, 208), (129, 65792, 192), (1290, 12320, 656)])
+def test_wide_products_with_a_halved_last_round(M, N, K):
+    """128 x 512 tiles of which the last round of the chip is at most half full and taken as tiles of 256 columns: K of three chunks and more, so that
+    both loops turn over their buffers; ragged rows, a last column tile that is half there (44000) and not at all for one half (65792); stored, added to
+    y, and SwiGLU as fp32 rows and as tiled terms (from 513 rows on)"""
+    x, Wg, Wu, Wd, act, y = ffn_case(M, K, N // 2, 96, M + N + K, scale=1.0)
+    b = B()
+    gu, down = b.GateUp(Wg.cuda(), Wu.cuda()), b.Linear(Wd.cuda())
+    rng = np.random.default_rng(M + N)
+    W = torch.cat([Wg, Wu])
+    xg = torch.from_numpy(x).cuda()
+    y0 = torch.from_numpy(rng.standard_normal((M, N)).astype(np.float32)).cuda()
+    lin = b.Linear(W.cuda())
+    want = orc.linear(x, I.to_numpy_storage(W))
+    with pinned(4, 4, 1):
+        s = shape(N, K, M, False, STEP)
+        assert (s.mt, s.nf, s.nw, s.ksplit) == (4, 2, 8, 1) and s.cps >= 3
+        assert s.gx * s.gz > 256 and 0 < s.gx * s.gz % 256 <= 128
+        print("halved last round", M, N, K, s.gx, s.gz, flush=True)
+        assert rel_err(lin(xg).cpu().numpy(), want) <= KERNEL_TOL
+        assert rel_err(lin(xg, y0.clone(), accumulate=True).cpu().numpy(), want + y0.cpu().numpy()) <= KERNEL_TOL
+        # silu(g) u of up to 8 million values: |d| <= 1.1 |u| |dg| + |g| |du|, as silu' <= 1.1 and |silu(g)| <= |g|, and dg and du are within
+        # KERNEL_TOL of the scale of their own products, g and u (a single large u shows the error of its g in full)
+        g, u = want[:, :N // 2], want[:, N // 2:]
+        bound = KERNEL_TOL * want.std() * (1.1 * np.abs(u) + np.abs(g))
+        assert np.all(np.abs(gu.swiglu(xg).cpu().numpy() - act) <= bound + 1e-30)
+    with pinned(4, 4):
+        assert rel_err(gu.ffn(down, xg).cpu().numpy(), y) <= KERNEL_TOL
+    gu.close(); down.close(); lin.close()
 
 
 @pytest.mark.parametrize("M,F", [(129, 16400), (200, 24576), (256, 8192)])
@@ -1128,9 +1210,9 @@ def test_error_paths_on_device():
                                    (640, 8224, 1040), (1025, 3072, 2064), (512, 8192, 48), (40, 2048, 2048), (686, 1955, 1136), (2000, 96, 6160),
                                    (600, 28640, 80), (1290, 12300, 48)])  # 128 x 512 tiles with the last round in halves
 def test_linear_shapes_by_estimate(M, N, K):
-    """widths and row counts between those that the launch shapes were swept at, where the estimated time decides: every tile that is
-    built (32 to 128 rows, 128 to 512 columns), slices or none, ragged rows and columns; alone, added to y, and as the two halves of
-    a feed-forward block (K of which is the narrow side)"""
+    """widths and row counts between those that the launch shapes were swept at, where the estimated time decides: slices or none, ragged
+    rows and columns; alone, added to y, and as the two halves of a feed-forward block (K of which is the narrow side).  Which tile it
+    takes is its own affair: test_linear_of_every_tile has every one by name."""
     rng = np.random.default_rng(M + 3 * N + 7 * K)
     x = rng.standard_normal((M, K)).astype(np.float32)
     W = I.normal((N, K), 0.05, 12, "wse", N, K)
@@ -1179,23 +1261,26 @@ def test_few_rows_two_row_tiles(M, K, F, N):
 @pytest.mark.parametrize("over,batch,T,norms", [({}, 17, 1, 1), (dict(hidden=1040, ffn=2832, vocab=16416), 16, 2, 1),
                                                 (dict(hidden=272, n_kv_heads=4), 31, 1, 1), (dict(hidden=2048, ffn=5632), 32, 1, 3)])
 def test_step_of_two_row_tiles(over, batch, T, norms):
-    """steps of 17 .. 32 rows: layers by the few-row kernel and a head behind a norm of its own, and a width past that range, each
-    against the general path"""
+    """steps of 17 .. 32 rows against the oracle: layers by the few-row kernel and a head behind a norm of its own, a width past that range,
+    and each by the general path, to which the distance is that of fp32 rounding"""
     c = make_case(m=dict(I.TINY, n_layers=1, **over), batch=batch, kind="tiny", seed=53, storage="bf16", gain_jitter=0.2)
+    lens = (c.seq_lens - T).astype(np.int32)
+    c.seq_lens = lens  # room for T new tokens in the pages that are there
+    c.seq_idx, c.pos = I.prefill_index(lens)
+    c.kv_t = [I.make_kv_layer(c.m, int(lens.sum()), 0, seed=53, dtype=torch.bfloat16)]
+    c.kv = [(I.to_numpy_storage(k), I.to_numpy_storage(v)) for k, v in c.kv_t]
     g = gpu_setup(c, max_batch=batch * T)
     b = B()
-    sl = torch.from_numpy((c.seq_lens - T).astype(np.int32)).cuda()
-    tok = torch.from_numpy(np.random.default_rng(3).integers(0, c.m["vocab"], (batch, T)).astype(np.int32)).cuda()
+    toks = np.random.default_rng(3).integers(0, c.m["vocab"], (batch, T)).astype(np.int32)
+    want = orc.decode_step_multi(c.cfg, c.w, fresh_pool(c), c.block_table, lens, toks).reshape(batch * T, -1)
     out = []
     for mt in (0, 1):
         print("two row tiles", over, batch, T, "mt", mt, flush=True)
-        b.set_tuning("linear_mt", mt)
-        try:
-            lg, n = norm_launches(g, lambda: b.decode_step_multi(g.model, g.pool, g.block_table, sl, tok))
-        finally:
-            b.set_tuning("linear_mt", 0)
+        with pinned(mt):
+            lg, n = norm_launches(g, lambda: b.decode_step_multi(g.model, g.pool, g.block_table, g.seq_lens, torch.from_numpy(toks).cuda()))
         assert n == (3 if mt else norms)
         out.append(lg.cpu().numpy().reshape(batch * T, -1))
+        check_logits(out[-1], want, min_agree=1.0 - 1.0 / batch)
     assert np.abs(out[0] - out[1]).max() <= 2e-3 * out[1].std()
 
 
