@@ -9,8 +9,9 @@ namespace chiron {
 
 // plan buffer layout (int32): [0] n_items, [1] chunk_pages, [2] number of long passes (more than kMergeLong items), [3] unused,
 // [4, 4+max_batch) first partial result of pass v, [.., +max_batch) number of partial results of pass v (one per item, in
-// page order), [.., +max_batch) items placed before v's first, [.., +max_batch) place of v's last piece in the list if
-// that is no whole item, [.., +max_batch) the long passes in any order.  A pass v = request * ng + token group (AttnShape).
+// page order), [.., +max_batch) and [.., +max_batch) scratch of the workgroup that builds the list: items placed before v's first and
+// place of v's last piece if that is no whole item, of passes from kPlanCached on only (those before are in LDS, their words
+// hold anything), [.., +max_batch) the long passes in any order.  A pass v = request * ng + token group (AttnShape).
 // Then, 32-byte aligned, one record of 8 ints per item, in the order in which items are taken: {pass, first
 // page, attended length, the ids of the item's first four pages (past its end: its last page), partial result}: everything a
 // wave needs before its first tile load, in one scalar load instead of a chain of four dependent ones (the block table does
@@ -25,7 +26,7 @@ __host__ __device__ inline int64_t plan_ticket_offset(int max_batch, int cap_ite
 constexpr int kPlanThreads = 1024;  // threads of the workgroup that runs attn_plan_block
 constexpr int kPlanMaxRound = 4096; // largest item, in pages, of a list that one round of the grid holds
 constexpr int kMergeLong = 16;      // a pass of more items is long for the merge
-constexpr int kPlanCached = 2048;   // passes whose page counts and offsets are kept in LDS
+constexpr int kPlanCached = 2048;   // passes whose lengths and places are kept in LDS
 
 struct PlanArgs {
     int32_t* plan;
@@ -42,7 +43,7 @@ __device__ __forceinline__ int pass_len(const int32_t* __restrict__ seq_lens, co
 }
 
 // One workgroup of kPlanThreads threads.  It is a chain of workgroup-wide sums and of dependent loads, so it keeps the
-// page counts in LDS, sums through wave shuffles (one barrier per sum), and deals the records out item by item (an
+// page counts in LDS, takes one barrier per sum, and deals the records out item by item (an
 // item's request is found by bisection), not request by request: one long request is no serial loop of one thread.
 // Measured on the attention entry point: 664 -> 646 us at 32 requests of 28k tokens, where the serial loop took 28 us.
 // Sums go through the lanes' registers, what the workgroup reads back stays in LDS, and up to 64 passes all item sizes are counted at
