@@ -61,6 +61,26 @@ int32_t launch_pack_rows(const uint16_t* src, int rows, int K, size_t tstride, u
     return CHIRON_OK;
 }
 
+// Byte of a 64-byte line at which a kernel's loop over the chunks of K starts (-1: wherever it falls).  With the same instructions in it a
+// loop takes up to 6 % longer at some places than at others.  us a launch on the same weights, every place in turn (K = 4096):
+//   96 x 256     gate/up of 160 rows (8B widths)   94.1 at 28 and 60, 95.3 .. 96.5 at 12, 24, 44 and 56, 98.9 .. 100.4 elsewhere
+//   64 x 512     gate/up of 200 rows               112.0 at 28, 112.3 .. 113.2 at 24, 56 and 60, 113.8 .. 117.4 elsewhere
+//   128 x 512    gate/up of 500 rows               199.4 .. 200.9 at 8 .. 20 and 40 .. 52, 202 .. 209 elsewhere
+//   64 x 256, eight waves, 150 rows of 20000 columns    70.8 at 16 and 48, 71.3 at 20 and 52, up to 73.2 elsewhere
+//   96 x 128, gate/up of 80 rows, 65.1 at 20 and 66.2 at 60; 128 x 512 of two-term input 0.3 to 1.3 % of a block of 400 rows (8192 -> 28672 -> 8192)
+//   less at 12 than at 24.  The other kernels showed no difference beyond the runs' own.
+constexpr int loop_byte(int mt, int nf, int ks, int pro, int nw) {
+    if (pro == PRO_PACKED) return mt == 4 && nf == 4 ? 12 : -1;
+    if (nw == 8) return mt == 4 ? 20 : 16;
+    if (mt == 3) return nf == 2 ? 28 : (ks == 8 ? 20 : -1);
+    return mt == 2 && nf == 4 ? 28 : -1;
+}
+// What follows starts there as long as the compiler puts nothing in between: a test reads the places out of the built library.
+template <int BYTE>
+__device__ __forceinline__ void place_loop() {
+    if constexpr (BYTE >= 0) asm volatile(".p2align 6\n\t.rept %0\n\ts_nop 0\n\t.endr" ::"n"(BYTE / 4));
+}
+
 // ---- the kernel ------------------------------------------------------------------------------------------
 // Pipeline per workgroup: weights sit in a ring of KS*NF register fragments per wave; as soon as the MFMAs of
 // k-step s have been issued, slot s is reloaded with the same k-step of the NEXT chunk, so about one chunk of
@@ -72,22 +92,434 @@ int32_t launch_pack_rows(const uint16_t* src, int rows, int K, size_t tstride, u
 // 8B gate/up shape at 2048 rows: the weight stream alone 268 us with the hint, 194 us without).
 // NORM: the input is rmsnorm(A) * gain.  A workgroup of an unsliced projection reads whole rows anyway: the gain is applied
 // while a chunk is staged, the sum of squares is taken from the same values, and the row's 1/rms multiplies the accumulators.
+// The workgroup's columns, K-slice and M-tile are bx, by, bz.
+template <int MT, int NF, int KS, int PRO, bool WNT = true, bool NORM = false, int NW = 4>
+__device__ __forceinline__ void linear_tile(const uint16_t* __restrict__ Wp, size_t tstride, int Npad, int Nreal, int K, int Kpad,
+                                            const float* __restrict__ A, int lda, int M, float* __restrict__ Y, int ldy, int chunks_per_split,
+                                            int mode, size_t part_stride, int bx, int by, int bz, const uint16_t* __restrict__ gain, float eps) {
+    constexpr int MROWS = 32 * MT;
+    constexpr int RS = MROWS + 1;      // LDS row stride in 16-byte units (+1 breaks the power-of-two stride)
+    constexpr int KG = 2 * KS;         // 8-wide k-groups per chunk
+    constexpr int KC = 16 * KS;        // k per chunk
+    // (with NORM there are at most 16 rows: the upper half of the tile is not staged where that saves whole passes, and the
+    // columns of the product that it would give are never stored)
+    constexpr int T = 64 * NW;  // threads
+    constexpr int SROWS = NORM && MT == 1 && 16 * KG % T == 0 ? 16 : MROWS;
+    constexpr int TASKS = SROWS * KG;  // 8-float staging tasks per chunk
+    static_assert(TASKS % T == 0, "staging assumes whole passes of the workgroup");
+    constexpr int TPT = TASKS / T;
+    // activation loads and staging spread over the k-steps of a chunk (see below; measured on one device against the
+    // bunched form: gate/up at 64 rows 50.3 against 53.6 us, at 192 rows 101 against 109 us).  The widest tile keeps
+    // them bunched: it has no registers left for the first chunk's separate staging set.
+    constexpr bool SPREAD = PRO != PRO_PACKED && MT * NF <= 8 && TPT <= KS;
+    static_assert(!NORM || SPREAD, "the norm is built into the spread staging only");
+
+    __shared__ uint4 lds_hi[2][KG * RS];
+    __shared__ uint4 lds_lo[2][KG * RS];
+
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int m0 = bz * MROWS;
+    const int tile0 = (bx * NW + wave) * NF;  // first 32-column tile of this wave
+    const int chunks_total = (K + KC - 1) / KC;
+    const int c_begin = by * chunks_per_split;
+    int c_end = c_begin + chunks_per_split;
+    if (c_end > chunks_total) c_end = chunks_total;
+
+    floatx16 acc[NF][MT];
+#pragma unroll
+    for (int f = 0; f < NF; ++f)
+#pragma unroll
+        for (int t = 0; t < MT; ++t)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) acc[f][t][r] = 0.f;
+
+    uint4 w[KS][NF];
+    float4 areg[TPT][2];  // fp32 staging registers (unused with PRO_PACKED, whose input goes straight into LDS)
+    // PRO_PACKED: A points at the hi terms in 32-row x 8-k tile order, the lo terms follow them
+    const int mtiles_all = (M + 31) / 32;
+    const float4* Ahi = reinterpret_cast<const float4*>(A);
+    const float4* Alo = Ahi + (size_t)mtiles_all * 32 * (Kpad / 8);
+
+    // The loop body holds no divergent branch: every load is unconditional on a clamped address (the packed
+    // weights are zero-padded in K to a whole chunk, out-of-range activation rows/columns are zeroed by a
+    // select), so the compiler can count outstanding loads exactly and never drains the queue.
+    const int kgroups = Kpad / 8;
+    const uint16_t* wp[NF];
+#pragma unroll
+    for (int f = 0; f < NF; ++f) {
+        int tile = min(tile0 + f, Npad / 32 - 1);  // a wave past the last tile recomputes it; its stores are masked
+        wp[f] = Wp + (size_t)tile * tstride + (lane >> 5) * 256 + (lane & 31) * 8;
+    }
+    auto load_w = [&](int c, int s) {
+        size_t off = (size_t)(c * KC + s * 16) * 32;
+#pragma unroll
+        // non-temporal: a step reads every weight once, and what the weights do not displace stays cached for the
+        // activations and the K/V pages (same-device A/B on the whole step: -7 % at 1 request, -1.5 % at 64..2048)
+        for (int f = 0; f < NF; ++f)
+            w[s][f] = WNT ? load_stream_16(wp[f] + off) : *reinterpret_cast<const uint4*>(wp[f] + off);
+    };
+    // staging task i of a chunk: 8 consecutive k of one row, thread tid + T*i.  A thread's tasks share their k, so the
+    // gains of a chunk are one load, with the last task: by then the previous chunk's gains have been used.
+    uint4 g0 = make_uint4(0, 0, 0, 0), greg = g0;  // gains of the first chunk and of the one being staged
+    float ss[TPT];                                 // this thread's part of its rows' sums of squares
+#pragma unroll
+    for (int i = 0; i < TPT; ++i) ss[i] = 0.f;
+    auto load_task = [&](int c, int i, float4 (&ar)[2], uint4& gr) {
+        int task = tid + i * T;
+        int kg = task % KG, m = task / KG;
+        int k = c * KC + kg * 8;
+        const float* p = A + (size_t)min(m0 + m, M - 1) * lda + min(k, K - 8);
+        ar[0] = *reinterpret_cast<const float4*>(p);
+        ar[1] = *reinterpret_cast<const float4*>(p + 4);
+        if (NORM && i == TPT - 1) gr = *reinterpret_cast<const uint4*>(gain + min(k, K - 8));
+    };
+    auto stage_task = [&](int c, int i, int buf, const float4 (&ar)[2], const uint4& gr) {
+        int task = tid + i * T;
+        int kg = task % KG, m = task / KG;
+        const bool ok = (m0 + m < M) && (c * KC + kg * 8 < K);
+        float v[8] = {ar[0].x, ar[0].y, ar[0].z, ar[0].w, ar[1].x, ar[1].y, ar[1].z, ar[1].w};
+#pragma unroll
+        for (int e = 0; e < 8; ++e) v[e] = ok ? v[e] : 0.f;
+        if (NORM) {
+            const uint32_t gw[4] = {gr.x, gr.y, gr.z, gr.w};
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+                ss[i] = fmaf(v[e], v[e], ss[i]);
+                v[e] *= (e & 1) ? bf16_hi(gw[e / 2]) : bf16_lo(gw[e / 2]);
+            }
+        }
+        uint4 hi, lo;
+        split2(v[0], v[1], hi.x, lo.x);
+        split2(v[2], v[3], hi.y, lo.y);
+        split2(v[4], v[5], hi.z, lo.z);
+        split2(v[6], v[7], hi.w, lo.w);
+        lds_hi[buf][kg * RS + m] = hi;
+        lds_lo[buf][kg * RS + m] = lo;
+    };
+    auto load_a = [&](int c) {
+#pragma unroll
+        for (int i = 0; i < TPT; ++i) load_task(c, i, areg[i], greg);
+    };
+    auto stage_a = [&](int c, int buf) {
+#pragma unroll
+        for (int i = 0; i < TPT; ++i) stage_task(c, i, buf, areg[i], greg);
+    };
+    // PRO_PACKED: chunk c of the pre-split activations goes HBM/L2 -> LDS directly (16 bytes per lane, a wave
+    // fills 64 consecutive rows of one k-group), no registers and no LDS store instructions in between
+    constexpr int JOBS = KG * (MROWS / 64) * 2;  // (k-group, 64-row half, hi|lo) per chunk, dealt to the waves
+    static_assert(PRO != PRO_PACKED || (MROWS % 64 == 0 && JOBS % NW == 0), "packed input needs 64-row halves");
+    constexpr int WJOBS = PRO == PRO_PACKED ? JOBS / NW : 1;
+    // per job: this lane's source at chunk 0 (it advances by one chunk of k-groups per chunk) and the wave-uniform
+    // LDS byte address of the job's destination in either buffer
+    const float4* dma_src[WJOBS];
+    uint32_t dma_dst[WJOBS];  // in buffer 0; buffer 1 lies KG*RS pieces further in both arrays
+    if (PRO == PRO_PACKED) {
+#pragma unroll
+        for (int j = 0; j < WJOBS; ++j) {
+            const int job = wave + NW * j;
+            const int lo = job & 1, half = (job >> 1) % (MROWS / 64), kg = (job >> 1) / (MROWS / 64);
+            const int m = half * 64 + lane;
+            const size_t idx = ((size_t)min(bz * MT + m / 32, mtiles_all - 1) * kgroups + kg) * 32 + (m & 31);
+            dma_src[j] = (lo ? Alo : Ahi) + idx;
+            dma_dst[j] = __builtin_amdgcn_readfirstlane(lds_address((lo ? lds_lo[0] : lds_hi[0]) + kg * RS + half * 64));
+        }
+    }
+    auto dma_a = [&](int c, int buf) {
+#pragma unroll
+        for (int j = 0; j < WJOBS; ++j)
+            global_to_lds_16(dma_src[j] + (size_t)c * (KG * 32), dma_dst[j] + (uint32_t)buf * (uint32_t)(KG * RS * sizeof(uint4)));
+    };
+    // LDS fragments of one k-step: hi and lo terms of the MT row tiles
+    struct Frags {
+        bf16x8 h[MT], l[MT];
+    };
+    auto read_frags = [&](int buf, int s, Frags& fr) {
+#pragma unroll
+        for (int t = 0; t < MT; ++t) {
+            int idx = (s * 2 + (lane >> 5)) * RS + t * 32 + (lane & 31);
+            uint4 h = lds_hi[buf][idx], l = lds_lo[buf][idx];
+            fr.h[t] = *reinterpret_cast<bf16x8*>(&h);
+            fr.l[t] = *reinterpret_cast<bf16x8*>(&l);
+        }
+    };
+    auto mma_frags = [&](int s, const Frags& fr) {
+        // hi terms of every accumulator first, then the lo terms: consecutive MFMAs never chain on one accumulator
+#pragma unroll
+        for (int f = 0; f < NF; ++f)
+#pragma unroll
+            for (int t = 0; t < MT; ++t)
+                acc[f][t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(*reinterpret_cast<bf16x8*>(&w[s][f]), fr.h[t], acc[f][t], 0, 0, 0);
+#pragma unroll
+        for (int f = 0; f < NF; ++f)
+#pragma unroll
+            for (int t = 0; t < MT; ++t)
+                acc[f][t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(*reinterpret_cast<bf16x8*>(&w[s][f]), fr.l[t], acc[f][t], 0, 0, 0);
+    };
+    // Up to 96 rows a workgroup has one wave per SIMD and few MFMAs per k-step, so the chain "fragments arrive from
+    // LDS -> MFMAs -> reload the weight slot" paces the weight stream.  There the fragments of k-step s+1 are read while
+    // the MFMAs of k-step s run (two register sets); only a chunk's first k-step waits for LDS.  (Measured on the 8B
+    // gate/up shape at 64 rows with the LDS reads taken out: 5.5 of 55 us.)  The 128-row tiles have enough MFMAs per
+    // k-step to cover the reads and no registers to spare.
+    constexpr bool PIPE = MT < 4;
+    Frags fr[PIPE ? 2 : 1];
+    auto mma_step = [&](int buf, int s) {
+        if constexpr (PIPE) {
+            if (s == 0) read_frags(buf, 0, fr[0]);
+            if (s + 1 < KS) read_frags(buf, s + 1, fr[(s + 1) & 1]);
+            mma_frags(s, fr[s & 1]);
+        } else {
+            read_frags(buf, s, fr[0]);
+            mma_frags(s, fr[0]);
+        }
+    };
+
+    // Order of memory operations (kept in place by the scheduling fences): per iteration the KS weight reloads
+    // come first, the activation loads last, in the prologue likewise, so at every use the number of younger
+    // loads in flight is the same on the loop's entry edge and on its back edge.
+    if (PRO == PRO_PACKED) {
+        if (c_begin < c_end) {  // uniform over the workgroup
+            const int c_last = c_end - 1;
+#pragma unroll
+            for (int s = 0; s < KS; ++s) {
+                load_w(c_begin, s);
+                __builtin_amdgcn_sched_barrier(0);  // same issue order as in the loop: k-step 0 is the oldest
+            }
+            dma_a(c_begin, 0);
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+            lds_barrier();
+            int buf = 0, c = c_begin;
+            if (c < c_last) {
+                place_loop<loop_byte(MT, NF, KS, PRO, NW)>();
+                do {
+                    // start the copy of chunk c+1 into the idle buffer (last read before the barrier that ended the
+                    // previous round), multiply chunk c out of the other one while refilling the weight ring
+                    dma_a(c + 1, buf ^ 1);
+                    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                    for (int s = 0; s < KS; ++s) {
+                        mma_step(buf, s);
+                        load_w(c + 1, s);
+                        __builtin_amdgcn_sched_barrier(0);
+                    }
+                    // the KS*NF weight loads just issued are younger than the activation copy: let them fly
+                    asm volatile("s_waitcnt vmcnt(%0)" ::"n"(KS * NF) : "memory");
+                    lds_barrier();
+                    buf ^= 1;
+                } while (++c < c_last);
+            }
+#pragma unroll
+            for (int s = 0; s < KS; ++s) mma_step(buf, s);
+        }
+    } else if (SPREAD) {
+        // Activation traffic spread over the chunk: the loads of a task's next-but-one chunk are issued, and the task's
+        // next chunk is converted and written to LDS, right after one particular k-step's weight reload instead of all
+        // together before the barrier.  A burst of activation loads keeps the CU's address unit busy (1 KiB per load
+        // instruction at 64 bytes per cycle, four waves at once) exactly when the next chunk's weight reloads want to
+        // go out, and in a latency-bound weight stream every delayed request is lost time.
+        if (c_begin < c_end) {  // uniform over the workgroup
+            const int c_last = c_end - 1;
+            // first chunk through a register set of its own, issued before everything else; the ring and the second
+            // chunk's tasks follow in the loop's order, so that the wait counts of entry and back edge agree.  (Two
+            // chunks or more and a single chunk are separate paths: in one path the compiler moves the second chunk's
+            // loads, which only the loop uses, behind the barrier and out of that order.)
+            float4 a0[TPT][2];
+#pragma unroll
+            for (int i = 0; i < TPT; ++i) load_task(c_begin, i, a0[i], g0);
+            __builtin_amdgcn_sched_barrier(0);
+            if (c_begin < c_last) {
+#pragma unroll
+                for (int s = 0; s < KS; ++s) {
+                    load_w(c_begin, s);
+                    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                    for (int i = 0; i < TPT; ++i)
+                        if (i * KS / TPT == s) {
+                            load_task(c_begin + 1, i, areg[i], greg);
+                            __builtin_amdgcn_sched_barrier(0);
+                        }
+                }
+#pragma unroll
+                for (int i = 0; i < TPT; ++i) stage_task(c_begin, i, 0, a0[i], g0);
+                lds_barrier();
+                int buf = 0, c = c_begin;
+                place_loop<loop_byte(MT, NF, KS, PRO, NW)>();
+                do {
+#pragma unroll
+                    for (int s = 0; s < KS; ++s) {
+                        mma_step(buf, s);
+                        load_w(c + 1, s);
+                        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                        for (int i = 0; i < TPT; ++i)
+                            if (i * KS / TPT == s) {
+                                stage_task(c + 1, i, buf ^ 1, areg[i], greg);
+                                __builtin_amdgcn_sched_barrier(0);
+                                load_task(min(c + 2, c_last), i, areg[i], greg);
+                                __builtin_amdgcn_sched_barrier(0);
+                            }
+                    }
+                    lds_barrier();
+                    buf ^= 1;
+                } while (++c < c_last);
+#pragma unroll
+                for (int s = 0; s < KS; ++s) mma_step(buf, s);
+            } else {
+#pragma unroll
+                for (int s = 0; s < KS; ++s) load_w(c_begin, s);
+#pragma unroll
+                for (int i = 0; i < TPT; ++i) stage_task(c_begin, i, 0, a0[i], g0);
+                lds_barrier();
+#pragma unroll
+                for (int s = 0; s < KS; ++s) mma_step(0, s);
+            }
+        }
+    } else
+    if (c_begin < c_end) {   // uniform over the workgroup
+        const int c_last = c_end - 1;
+#pragma unroll
+        for (int s = 0; s < KS; ++s) {
+            load_w(c_begin, s);
+            __builtin_amdgcn_sched_barrier(0);  // same issue order as in the loop: k-step 0 is the oldest
+        }
+        load_a(c_begin);
+        stage_a(c_begin, 0);
+        load_a(min(c_begin + 1, c_last));
+        lds_barrier();
+        int buf = 0;
+        for (int c = c_begin; c < c_last; ++c) {
+#pragma unroll
+            for (int s = 0; s < KS; ++s) {
+                mma_step(buf, s);
+                load_w(c + 1, s);  // slot s is free again: fetch the same k-step of the next chunk
+                __builtin_amdgcn_sched_barrier(0);
+            }
+            stage_a(c + 1, buf ^ 1);
+            __builtin_amdgcn_sched_barrier(0);
+            load_a(min(c + 2, c_last));
+            __builtin_amdgcn_sched_barrier(0);
+            lds_barrier();
+            buf ^= 1;
+        }
+#pragma unroll
+        for (int s = 0; s < KS; ++s) mma_step(buf, s);
+    }
+
+    if constexpr (NORM) {
+        __shared__ float s_inv[MROWS];
+        // the KG threads that staged a row sit side by side in one wave
+#pragma unroll
+        for (int i = 0; i < TPT; ++i) {
+            float s = ss[i];
+#pragma unroll
+            for (int o = 1; o < KG; o <<= 1) s += __shfl_xor(s, o);
+            if (tid % KG == 0) s_inv[(tid + i * T) / KG] = 1.0f / sqrtf(s / (float)K + eps);
+        }
+        lds_barrier();
+#pragma unroll
+        for (int t = 0; t < MT; ++t) {
+            const float inv = s_inv[t * 32 + (lane & 31)];
+#pragma unroll
+            for (int f = 0; f < NF; ++f)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) acc[f][t][r] *= inv;
+        }
+    }
+
+    // D[i][j]: lane holds column j = lane%32 (an activation row m) and rows i = 8*(r/4) + 4*(lane/32) + r%4
+    // (output columns n) for r = 0..15.
+    if (mode >= EPI_SWIGLU) {
+        // Fused gate/up: in tile T the lanes of half 0 hold gate[m][16T + r], those of half 1 up[m][16T + r].  The halves
+        // swap eight values each, after which half h owns the columns 16T + 8h .. + 7 of row m.
+        const int half = lane >> 5;
+#pragma unroll
+        for (int f = 0; f < NF; ++f) {
+            const int tile = tile0 + f;
+#pragma unroll
+            for (int t = 0; t < MT; ++t) {
+                float v[8];
+#pragma unroll
+                for (int e = 0; e < 8; ++e) {
+                    const float mine_g = acc[f][t][e], mine_u = acc[f][t][8 + e];  // half 0: gate e, (gate 8+e); half 1: (up e), up 8+e
+                    const float got = __shfl_xor(half ? mine_g : mine_u, 32);       // half 0 receives up e, half 1 gate 8+e
+                    const float g = half ? got : mine_g, u = half ? mine_u : got;
+                    v[e] = g / (1.0f + __expf(-g)) * u;
+                }
+                const int m = m0 + t * 32 + (lane & 31);
+                if (m >= M || tile >= Npad / 32) continue;
+                if (mode == EPI_SWIGLU) {
+                    float* dst = Y + (size_t)m * ldy + tile * 16 + half * 8;
+                    *reinterpret_cast<float4*>(dst) = make_float4(v[0], v[1], v[2], v[3]);
+                    *reinterpret_cast<float4*>(dst + 4) = make_float4(v[4], v[5], v[6], v[7]);
+                } else {
+                    // the two bf16 terms in 32-row x 8-k tile order (ldy = k-groups of the consumer, part_stride = distance
+                    // from the hi to the lo terms in 16-byte units), or with the M rows of a k-group side by side
+                    uint4 hi, lo;
+                    split2(v[0], v[1], hi.x, lo.x);
+                    split2(v[2], v[3], hi.y, lo.y);
+                    split2(v[4], v[5], hi.z, lo.z);
+                    split2(v[6], v[7], hi.w, lo.w);
+                    uint4* dst = reinterpret_cast<uint4*>(Y) + (mode == EPI_SWIGLU_FEW ? (size_t)(2 * tile + half) * M + m
+                                     : ((size_t)(m / 32) * ldy + (size_t)(2 * tile + half)) * 32 + (m & 31));
+                    dst[0] = hi;
+                    dst[part_stride] = lo;
+                }
+            }
+        }
+        return;
+    }
+#pragma unroll
+    for (int f = 0; f < NF; ++f) {
+        int nb = (tile0 + f) * 32 + (lane >> 5) * 4;
+#pragma unroll
+        for (int t = 0; t < MT; ++t) {
+            int m = m0 + t * 32 + (lane & 31);
+            if (m >= M) continue;
+            // EPI_STORE: y = acc;  EPI_ADD: y += acc (this workgroup is the only writer);  EPI_SLICES: slice `by` of the workspace
+            float* yrow = Y + (mode == EPI_SLICES ? (size_t)by * part_stride : (size_t)0) + (size_t)m * ldy;
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                int n = nb + q * 8;
+                if (n + 3 < Nreal && (ldy & 3) == 0) {
+                    float4 v = make_float4(acc[f][t][q * 4], acc[f][t][q * 4 + 1], acc[f][t][q * 4 + 2], acc[f][t][q * 4 + 3]);
+                    float4* dst = reinterpret_cast<float4*>(yrow + n);
+                    if (mode == EPI_ADD) {
+                        float4 o = *dst;
+                        v.x += o.x; v.y += o.y; v.z += o.z; v.w += o.w;
+                    }
+                    *dst = v;
+                } else {
+#pragma unroll
+                    for (int e = 0; e < 4; ++e)
+                        if (n + e < Nreal) {
+                            float v = acc[f][t][q * 4 + e];
+                            yrow[n + e] = mode == EPI_ADD ? yrow[n + e] + v : v;
+                        }
+                }
+            }
+        }
+    }
+}
+
+// Workgroups are dealt to the 8 XCDs round-robin.  The 1-D grid (of a multiple of 8) is re-read so that consecutive logical ids
+// sit on ONE XCD, and the M-tile index varies fastest: the workgroups that stream the same weight tiles for
+// different rows then share that XCD's L2 instead of each pulling the tile from HBM.
+__device__ __forceinline__ int logical_block(unsigned block, int total, int remap) {
+    const int per_xcd = (total + 7) / 8;
+    return remap ? (block % 8) * per_xcd + block / 8 : block;
+}
+
 template <int MT, int NF, int KS, int PRO, bool WNT = true, bool NORM = false, int NW = 4>
 __global__ __launch_bounds__(64 * NW, (NW == 8 || (MT * NF <= 8 && !(MT == 4 && PRO != PRO_NONE)) ? 2 : 1)) void linear_kernel(const uint16_t* __restrict__ Wp, size_t tstride, int Npad, int Nreal, int K, int Kpad,
                                                      const float* __restrict__ A, int lda, int M,
                                                      float* __restrict__ Y, int ldy, int chunks_per_split,
                                                      int mode, size_t part_stride, int gx, int gy, int gz, int remap,
                                                      const uint16_t* __restrict__ gain, float eps) {
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    // Workgroups are dealt to the 8 XCDs round-robin.  The 1-D grid is re-read so that consecutive logical ids
-    // sit on ONE XCD, and the M-tile index varies fastest: the workgroups that stream the same weight tiles for
-    // different rows then share that XCD's L2 instead of each pulling the tile from HBM.
     const int total = gx * gy * gz;
-    const int per_xcd = (total + 7) / 8;
-    const int logical = remap ? (blockIdx.x % 8) * per_xcd + blockIdx.x / 8 : blockIdx.x;
-    if (logical >= total) return;  // grid is padded to a multiple of 8 (uniform over the workgroup)
+    const int logical = logical_block(blockIdx.x, total, remap);
+    if (logical >= total) return;  // uniform over the workgroup
     const int bz = logical % gz, bx = (logical / gz) % gx, by = logical / (gz * gx);
-#include "linear_tile.inc"
+    linear_tile<MT, NF, KS, PRO, WNT, NORM, NW>(Wp, tstride, Npad, Nreal, K, Kpad, A, lda, M, Y, ldy, chunks_per_split, mode, part_stride, bx, by, bz,
+                                                gain, eps);
 }
 
 // 128 rows x 512 columns by eight waves, K whole.  The tiles of whole rounds of the chip as they are (`whole` of them, a multiple of
@@ -98,25 +530,17 @@ __global__ __launch_bounds__(64 * NW, (NW == 8 || (MT * NF <= 8 && !(MT == 4 && 
 __global__ __launch_bounds__(512, 2) void linear_wide_kernel(const uint16_t* __restrict__ Wp, size_t tstride, int Npad, int Nreal, int K, int Kpad,
                                                              const float* __restrict__ A, int lda, int M, float* __restrict__ Y, int ldy, int mode,
                                                              size_t part_stride, int gx, int gz, int whole, int remap) {
-    constexpr int MT = 4, KS = 4, PRO = PRO_NONE, NW = 8, by = 0;
-    constexpr bool WNT = false, NORM = false;
-    constexpr const uint16_t* gain = nullptr;
-    constexpr float eps = 0.f;
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int chunks_per_split = (K + 63) / 64;
+    const int chunks = (K + 63) / 64;
     if ((int)blockIdx.x < whole) {
-        constexpr int NF = 2;
-        const int tile = remap ? (int)(blockIdx.x % 8) * (whole / 8) + (int)(blockIdx.x / 8) : (int)blockIdx.x;
-        const int bx = tile / gz, bz = tile % gz;
-#include "linear_tile.inc"
+        const int logical = logical_block(blockIdx.x, whole, remap);
+        linear_tile<4, 2, 4, PRO_NONE, false, false, 8>(Wp, tstride, Npad, Nreal, K, Kpad, A, lda, M, Y, ldy, chunks, mode, part_stride, logical / gz, 0,
+                                                        logical % gz, nullptr, 0.f);
     } else {
-        constexpr int NF = 1;
-        const int rest = gx * gz - whole, block = (int)blockIdx.x - whole, per_xcd = (2 * rest + 7) / 8;
-        const int half = remap ? block % 8 * per_xcd + block / 8 : block;
-        if (half >= 2 * rest) return;  // grid is padded to a multiple of 8 (uniform over the workgroup)
-        const int tile = whole + half % rest;
-        const int bx = 2 * (tile / gz) + half / rest, bz = tile % gz;
-#include "linear_tile.inc"
+        const int rest = gx * gz - whole, logical = logical_block(blockIdx.x - whole, 2 * rest, remap);
+        if (logical >= 2 * rest) return;  // uniform over the workgroup
+        const int tile = whole + logical % rest;
+        linear_tile<4, 1, 4, PRO_NONE, false, false, 8>(Wp, tstride, Npad, Nreal, K, Kpad, A, lda, M, Y, ldy, chunks, mode, part_stride,
+                                                        2 * (tile / gz) + logical / rest, 0, tile % gz, nullptr, 0.f);
     }
 }
 
