@@ -28,11 +28,11 @@ MFMA_BF16_PEAK_TFLOPS = 2500.0
 # `sha` is source_hash() of the kernel's file at that time; with any other source the figure is reported null.
 TRAFFIC = {
     # (workload, kernel class): (source file, source_hash, fetch bytes, write bytes)
-    ("llama8b-b64-lognormal800", "attn"): ("attention.hip", "944820f5463cfa0c75c2f0af53386ff28ffbbc5d36fa719d237443a06ee400f8", 275722902, 4259906),
-    ("llama8b-b64-lognormal800", "gateup"): ("linear.hip", "5727ed657fe743b30ee62e5b1830a919d83022803174b775763e2f9c6f0c78f1", 243439785, 3670016),
-    ("llama8b-b64-lognormal800", "down"): ("linear.hip", "5727ed657fe743b30ee62e5b1830a919d83022803174b775763e2f9c6f0c78f1", 121347169, 16777219),
-    ("llama8b-mixed-sweep512", "attn"): ("attention.hip", "944820f5463cfa0c75c2f0af53386ff28ffbbc5d36fa719d237443a06ee400f8", 4196868943, 21763141),
-    ("llama8b-b32-long32k", "attn"): ("attention.hip", "944820f5463cfa0c75c2f0af53386ff28ffbbc5d36fa719d237443a06ee400f8", 3721444296, 4260192),
+    ("llama8b-b64-lognormal800", "attn"): ("attention.hip", "f29be5e7e2a0ec94b8abdb919a5c840d3570340d7077b54416e633e343e05eb4", 275719179, 4259896),
+    ("llama8b-b64-lognormal800", "gateup"): ("linear.hip", "20926ed0a363a8f5ed45c82f17b1669b626433ef9c916c90ef534e7fa7be8671", 243439524, 3670016),
+    ("llama8b-b64-lognormal800", "down"): ("linear.hip", "20926ed0a363a8f5ed45c82f17b1669b626433ef9c916c90ef534e7fa7be8671", 121354181, 16777221),
+    ("llama8b-mixed-sweep512", "attn"): ("attention.hip", "f29be5e7e2a0ec94b8abdb919a5c840d3570340d7077b54416e633e343e05eb4", 4196899182, 21763220),
+    ("llama8b-b32-long32k", "attn"): ("attention.hip", "f29be5e7e2a0ec94b8abdb919a5c840d3570340d7077b54416e633e343e05eb4", 3721448773, 4260155),
 }
 
 
